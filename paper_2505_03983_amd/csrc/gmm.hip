@@ -415,7 +415,8 @@ struct LogitOp {
         mx = fmaxf(mx, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(mx), 0x141, 0xf, 0xf, true)));
         mx = fmaxf(mx, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(mx), 0x140, 0xf, 0xf, true)));
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        if (mok && fr.l32 == 0) pmax[(int64_t)m * np + Cfg::WGN * fr.tile_n + fr.wn] = mx;
+        // (a 256-wide last tile has groups behind the last one a row has room for)
+        if (mok && fr.l32 == 0 && Cfg::WGN * fr.tile_n + fr.wn < np) pmax[(int64_t)m * np + Cfg::WGN * fr.tile_n + fr.wn] = mx;
       }
     }
   }
@@ -620,9 +621,9 @@ struct CombineOp {
 // that (rows with more than two live groups are not candidates): onehot[row] = b or -1, and onehot_tile[row tile] =
 // 1 when all its rows qualify -- the second GEMM then skips the tile and gmm_onehot_kernel writes it.
 // The component b of a one-hot row, or -1: called by a whole wavefront with the row's partial maxima p[np] (np <= 64,
-// groups of 64 columns), its maximum mx and its logits.
+// groups of 64 columns, the last one short when C is no multiple), its maximum mx and its C logits.
 __device__ __forceinline__ int onehot_component(const float* __restrict__ p, int np, float mx,
-                                                const float* __restrict__ row_logits, int lane) {
+                                                const float* __restrict__ row_logits, int64_t C, int lane) {
   const float thr = mx - CombineOp::kZeroGap;
   unsigned long long groups = __ballot(lane < np && p[min(lane, np - 1)] >= thr);
   if (__popcll(groups) > 2) return -1;
@@ -630,7 +631,7 @@ __device__ __forceinline__ int onehot_component(const float* __restrict__ p, int
   while (groups) {
     const int g = __ffsll((long long)groups) - 1;
     groups &= groups - 1;
-    const float v = row_logits[g * 64 + lane];
+    const float v = g * 64 + lane < C ? row_logits[g * 64 + lane] : -INFINITY;
     count += __popcll(__ballot(v >= thr));
     const unsigned long long at_max = __ballot(v == mx);
     if (at_max) b = g * 64 + __ffsll((long long)at_max) - 1;
@@ -685,7 +686,7 @@ __global__ __launch_bounds__(256) void gmm_rowmax_kernel(const int* __restrict__
       for (int k = 0; k < RW; ++k) {
         const int row = m0 + r0 + k;
         if (row >= n) continue;   // the same for the whole wavefront
-        const int b = onehot_component(p[k], np, mx[k], logits + (int64_t)row * ldl, lane);
+        const int b = onehot_component(p[k], np, mx[k], logits + (int64_t)row * ldl, ldl, lane);
         if (lane == 0) {
           onehot[row] = b;
           if (b < 0) s_any[np] = 0;
@@ -723,7 +724,7 @@ __global__ __launch_bounds__(256) void gmm_rowmax_rows_kernel(const int* __restr
   mx = wave_max(mx);
   if (lane == 0) rmax[row] = mx;
   if (onehot) {
-    const int b = onehot_component(p, np, mx, logits + (int64_t)row * ldl, lane);
+    const int b = onehot_component(p, np, mx, logits + (int64_t)row * ldl, ldl, lane);
     if (lane == 0) {
       onehot[row] = b;
       if (chain && chain_comp) chain_comp[chain[row]] = b;

@@ -1,0 +1,39 @@
+"""GPU kernels at the edges of the ranges their dispatch rules give them, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_helpers as H
+from oracle_helpers import oracle_setup
+from paper_2505_03983_amd import runtime
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _denoise(cfg, n, seed=3):
+    T, p, model = oracle_setup(cfg)
+    rng = np.random.default_rng(seed)
+    if cfg["kind"] == "gmm":     # unequal weights
+        p["log_w"] = np.log(rng.dirichlet(np.ones(cfg["C"]))).astype(np.float32)
+        from oracle_helpers import gmm_model
+        model = gmm_model(T, p)
+    ctx = runtime.open_ctx(cfg, p, seed=0, chains=-(-n // cfg["L"]))
+    tau = rng.integers(1, cfg["K"] + 1, n).astype(np.int32)
+    ab = T["abar"][tau]
+    x0 = p["means"][rng.integers(0, cfg["C"], n)] + 0.5 * rng.standard_normal((n, cfg["d"]))
+    x = (np.sqrt(ab)[:, None] * x0 + np.sqrt(1 - ab)[:, None] * rng.standard_normal((n, cfg["d"]))).astype(np.float32)
+    out = torch.full((n, cfg["d"]), float("nan"), dtype=torch.float32, device=DEV)
+    ctx.denoise(torch.from_numpy(x).to(DEV), torch.from_numpy(tau).to(DEV), out)
+    torch.cuda.synchronize()
+    ctx.close()
+    return out.cpu().numpy(), model(cfg["K"] - tau, x.astype(np.float64))
+
+
+@pytest.mark.parametrize("d, C, n", [(96, 1056, 15000), (80, 1040, 19000), (500, 1000, 8100),
+                                     (96, 1056, 16400), (160, 640, 16400)])
+def test_mixture_calls_on_the_tiled_kernels(d, C, n):
+    """Two fp16 terms, three bf16 terms, fp32; then the least rows that go to 256-wide tiles, C ending inside one.
+    Logits of up to ~2^9 in fp32 move a weight by at most 2^9 2^-24 = 3e-5 of itself, and the mean by no more."""
+    got, want = _denoise(dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25), n)
+    assert H.rel_err(got, want) <= 3e-5
