@@ -9,10 +9,12 @@
 //   D       = (sqrt(ab) s2 / V) x + (1 - ab s2 / V) sum_k r_k mu_k
 // i.e. single-head attention with keys = values = the component means.
 //
-// Two paths:
-//  * row-wise kernel (one wavefront per row) for small or oddly shaped
-//    problems, where a launch is latency-bound anyway;
-//  * matrix-core path for large aligned problems: logits = X M^T (MFMA GEMM
+// Three paths:
+//  * row-wise kernel (one wavefront per row) for mixtures of a few numbers,
+//    where a launch is all there is;
+//  * fp32 matrix cores straight from global memory (gmm_few.h) for small calls
+//    and odd shapes;
+//  * tiled matrix-core path for large aligned problems: logits = X M^T (MFMA GEMM
 //    with the affine map fused in the epilogue) materialised in HBM
 //    [rows, C] -- at 288 GB of HBM the 1 GB of logits of the largest workload
 //    costs ~4% of the GEMM time to write and re-read, and keeps both GEMMs at
@@ -42,6 +44,7 @@
 #include "gemm_split2_big.h"
 #include "gmm_state.h"
 #include "gmm_cert.h"
+#include "gmm_few.h"
 
 namespace asd {
 
@@ -74,13 +77,15 @@ __device__ __forceinline__ float4 row_coef(const float4* coef_tau, const int32_t
 // ---------------------------------------------------------------------------
 // preparation kernels
 // ---------------------------------------------------------------------------
-__global__ void gmm_prep_kernel(int C, int d, const float* __restrict__ means, float* __restrict__ means_t,
-                                float* __restrict__ musq) {
+// means_t [d][cp] (zeroed by the caller where C is padded), means_p [C][dp] (NULL: d is not padded), musq [C]
+__global__ void gmm_prep_kernel(int C, int d, int cp, int dp, const float* __restrict__ means,
+                                float* __restrict__ means_t, float* __restrict__ means_p, float* __restrict__ musq) {
   const int k = blockIdx.x;
   float s = 0.f;
   for (int j = threadIdx.x; j < d; j += blockDim.x) {
     const float m = means[(int64_t)k * d + j];
-    means_t[(int64_t)j * C + k] = m;
+    means_t[(int64_t)j * cp + k] = m;
+    if (means_p) means_p[(int64_t)k * dp + j] = m;
     s = fmaf(m, m, s);
   }
   __shared__ float red[256];
@@ -152,6 +157,7 @@ __global__ __launch_bounds__(256) void gmm_row_scale_kernel(const int* __restric
 // row-wise path: 4 wavefronts per workgroup, one row per wavefront per pass
 // LDS per wavefront: x[d] then p[C]
 // ---------------------------------------------------------------------------
+constexpr int kRowwiseMixture = 256;   // largest C d of the mixtures it serves (gmm_eval)
 constexpr float kZeroGapNat = kCertZeroGap * 0.6931471805599453f;   // the zero gap in the natural-log units of these kernels
 __global__ __launch_bounds__(256) void gmm_rowwise_kernel(const int* __restrict__ n_dev, int nrows_max, int d, int C, const float* __restrict__ in_base,
                                                           const int64_t* __restrict__ in_off,
@@ -213,99 +219,6 @@ __global__ __launch_bounds__(256) void gmm_rowwise_kernel(const int* __restrict_
       }
     }
     __syncthreads();
-  }
-}
-
-// ---------------------------------------------------------------------------
-// row-wise path with the mixture in LDS (d % 4 == 0 and C*(d+4) floats fit): the workgroup copies
-// the means (rows padded by 4 floats, so that 16 lanes reading the same 16-byte column of 16
-// different rows hit 16 different bank groups), |mu|^2 and log w into LDS, then each wavefront
-// serves rows from it.  No cross-lane traffic inside the loops:
-//   pass 1: lane = component: <x, mu_k> over d from LDS (x is a broadcast read),
-//   pass 2: softmax over the C logits (two wavefront reductions),
-//   pass 3: lane = coordinate: sum_k p_k mu_k[j] (p is a broadcast read).
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void gmm_rowwise_lds_kernel(const int* __restrict__ n_dev, int nrows_max, int d,
-                                                              int C, int rows_per_wave,
-                                                              const float* __restrict__ in_base,
-                                                              const int64_t* __restrict__ in_off,
-                                                              float* __restrict__ out_base,
-                                                              const int64_t* __restrict__ out_off,
-                                                              const int32_t* __restrict__ tau,
-                                                              const float4* __restrict__ coef_tau,
-                                                              const float* __restrict__ means,
-                                                              const float* __restrict__ musq,
-                                                              const float* __restrict__ log_w) {
-  extern __shared__ __attribute__((aligned(16))) float lds[];
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int d4 = d >> 2, dp = d + 4, C4 = (C + 3) & ~3;
-  const int nrows = min(*n_dev, nrows_max);
-  if (blockIdx.x * 4 * rows_per_wave >= nrows) return;
-  float* m_l = lds;                          // [C][dp]
-  float* q_l = m_l + (size_t)C * dp;         // [C]
-  float* lw_l = q_l + C4;                    // [C]
-  float* ps = lw_l + C4 + (size_t)wave * C4; // [4][C4] logits, then softmax weights
-  float* xs = lw_l + C4 + 4 * (size_t)C4 + (size_t)wave * d;  // [4][d]
-  {
-    const float4* Mg = reinterpret_cast<const float4*>(means);
-    for (int t = threadIdx.x; t < C * d4; t += 256) {
-      const int k = t / d4, c = t - k * d4;
-      *reinterpret_cast<float4*>(&m_l[k * dp + 4 * c]) = Mg[t];
-    }
-    for (int t = threadIdx.x; t < C; t += 256) {
-      q_l[t] = musq[t];
-      lw_l[t] = log_w[t];
-    }
-  }
-  __syncthreads();
-  for (int it = 0; it < rows_per_wave; ++it) {
-    const int n = (blockIdx.x * rows_per_wave + it) * 4 + wave;
-    if (n >= nrows) break;  // uniform per wavefront; no workgroup barrier below
-    const float4 cf = coef_tau[tau[n]];
-    const float* x = in_base + in_off[n];
-    for (int j = lane; j < d; j += 64) xs[j] = x[j];
-    // (LDS operations of one wavefront complete in order: xs is visible to all its lanes below)
-    float mx = -INFINITY;
-    for (int k = lane; k < C; k += 64) {
-      const float* mk = m_l + k * dp;
-      float dot = 0.f;
-#pragma unroll 4
-      for (int c = 0; c < d4; ++c) {
-        const float4 xv = *reinterpret_cast<const float4*>(&xs[4 * c]);
-        const float4 mv = *reinterpret_cast<const float4*>(&mk[4 * c]);
-        dot = fmaf(xv.x, mv.x, fmaf(xv.y, mv.y, fmaf(xv.z, mv.z, fmaf(xv.w, mv.w, dot))));
-      }
-      const float lg = fmaf(cf.x, dot, fmaf(-cf.y, q_l[k], lw_l[k]));
-      ps[k] = lg;
-      mx = fmaxf(mx, lg);
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    float sum = 0.f;
-    for (int k = lane; k < C4; k += 64) {
-      const float p = (k < C && !(ps[k] - mx < -kZeroGapNat)) ? expf(ps[k] - mx) : 0.f;
-      ps[k] = p;
-      sum += p;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    const float sc = cf.w / sum;
-    float* out = out_base + out_off[n];
-    for (int j = lane; j < d; j += 64) {
-      float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-      const float* mj = m_l + j;
-#pragma unroll 2
-      for (int k = 0; k < C4; k += 4) {
-        const float4 p = *reinterpret_cast<const float4*>(&ps[k]);
-        // rows past C do not exist: their weights are 0 and the reads are clamped to the last row
-        a0 = fmaf(p.x, mj[min(k + 0, C - 1) * dp], a0);
-        a1 = fmaf(p.y, mj[min(k + 1, C - 1) * dp], a1);
-        a2 = fmaf(p.z, mj[min(k + 2, C - 1) * dp], a2);
-        a3 = fmaf(p.w, mj[min(k + 3, C - 1) * dp], a3);
-      }
-      out[j] = fmaf(cf.z, xs[j], sc * ((a0 + a1) + (a2 + a3)));
-    }
   }
 }
 
@@ -1324,7 +1237,13 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
   g->log_w = den.log_w;
   const int d = ctx->d, C = den.C;
   ctx->model_macs_per_row = 2.0 * C * d;
-  ASD_HIP(hipMalloc(&g->means_t, sizeof(float) * (size_t)d * C));
+  const int dp = (d + 3) & ~3, cp = (C + 3) & ~3;   // rows of whole float4 for the kernels that read the mixture as such
+  ASD_HIP(hipMalloc(&g->means_t, sizeof(float) * (size_t)d * cp));
+  if (cp != C) ASD_HIP(hipMemset(g->means_t, 0, sizeof(float) * (size_t)d * cp));
+  if (dp != d) {
+    ASD_HIP(hipMalloc(&g->means_p, sizeof(float) * (size_t)C * dp));
+    ASD_HIP(hipMemset(g->means_p, 0, sizeof(float) * (size_t)C * dp));
+  }
   ASD_HIP(hipMalloc(&g->musq, sizeof(float) * (size_t)C));
   ASD_HIP(hipMalloc(&g->coef_tau, sizeof(float4) * (size_t)ctx->n_tau));
   // per-time-index coefficients, in double on the host
@@ -1353,28 +1272,14 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
   hipError_t e = hipMemcpy(g->coef_tau, h, sizeof(float4) * (size_t)ctx->n_tau, hipMemcpyHostToDevice);
   delete[] h;
   ASD_HIP(e);
-  hipLaunchKernelGGL(gmm_prep_kernel, dim3(C), dim3(256), 0, 0, C, d, g->means, g->means_t, g->musq);
+  hipLaunchKernelGGL(gmm_prep_kernel, dim3(C), dim3(256), 0, 0, C, d, cp, dp, g->means, g->means_t,
+                     g->means_p, g->musq);
   ASD_HIP(hipGetLastError());
   ASD_HIP(hipDeviceSynchronize());
 
   g->rowwise_lds = sizeof(float) * 4 * (size_t)(d + C);
   const bool aligned = (d % 4 == 0) && (C % 4 == 0);
-  const bool big = (double)ctx->n_rows_max * C * d >= (double)(1 << 26);
-  const bool rowwise_ok = g->rowwise_lds <= 64 * 1024;
-  g->use_mfma = aligned && (big || !rowwise_ok);
-  if (!g->use_mfma && !rowwise_ok) {
-    set_error("GMM denoiser: C=%d, d=%d needs d %% 4 == 0 and C %% 4 == 0 at this size", C, d);
-    return ASD_EUNSUPPORTED;
-  }
-  if (!g->use_mfma && d % 4 == 0) {
-    const size_t C4 = ((size_t)C + 3) & ~(size_t)3;
-    const size_t bytes = sizeof(float) * ((size_t)C * (d + 4) + 2 * C4 + 4 * C4 + 4 * (size_t)d);
-    if (bytes <= 150 * 1024) {
-      g->lds_rowwise_bytes = bytes;
-      ASD_HIP(hipFuncSetAttribute((const void*)gmm_rowwise_lds_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  160 * 1024));
-    }
-  }
+  g->use_mfma = aligned && (double)ctx->n_rows_max * C * d >= (double)(1 << 26);
   if (g->use_mfma && d % 16 == 0 && C % 16 == 0) {
     if (d % GmmTile2::BK == 0 && C % GmmTile2::BK == 0) {
       // fp16 terms for both calls: the means times b_scale (a power of two that brings the largest |mu| into fp16's
@@ -1492,6 +1397,11 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
       }
     }
   }
+  if (!g->use_mfma) {
+    g->np = (int)ceil_div(C, 64);
+    ASD_HIP(hipMalloc(&g->logits, sizeof(float) * (size_t)ctx->n_rows_max * cp));
+    ASD_HIP(hipMalloc(&g->pmax, sizeof(float) * (size_t)ctx->n_rows_max * g->np));
+  }
   if (g->use_mfma) {
     g->np = 2 * (int)ceil_div(C, GmmTileSkinny::BN);  // room for the finest of the tilings
     // split K for the second GEMM of the draft call (one row per chain): few output tiles, long K
@@ -1545,6 +1455,7 @@ void gmm_destroy(asd_ctx* ctx) {
   GmmState* g = ctx->gmm;
   if (!g) return;
   (void)hipFree(g->means_t);
+  (void)hipFree(g->means_p);
   (void)hipFree(g->means_img);
   (void)hipFree(g->means_t_img);
   (void)hipFree(g->means_img_s);
@@ -1585,23 +1496,29 @@ void gmm_destroy(asd_ctx* ctx) {
 asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
   GmmState* g = ctx->gmm;
   const int d = ctx->d, C = g->C, n = rows.n;
-  if (!g->use_mfma && g->lds_rowwise_bytes) {
+  const double macs = (double)n * C * d;
+  // A mixture of a few numbers: one launch, a row per wavefront (7 x 5, 500 rows: 6.2 us, the kernels below 8.5; at
+  // 8 x 16 and 4096 rows 11.5 against 9.6, and a wavefront's serial walk over C grows from there).
+  if ((int64_t)C * d <= kRowwiseMixture) {
     ProfScope ps(ctx, ASD_PROF_GMM_ROWWISE, rows.call, st);
-    // one row per wavefront while that still gives fewer workgroups than CUs, else four
-    const int rpw = n > 4 * 256 ? 4 : 1;
-    hipLaunchKernelGGL(gmm_rowwise_lds_kernel, dim3((unsigned)ceil_div(n, 4 * rpw)), dim3(256),
-                       g->lds_rowwise_bytes, st, rows.n_dev, n, d, C, rpw, rows.in_base, rows.in_off, rows.out_base,
-                       rows.out_off, rows.tau, g->coef_tau, g->means, g->musq, g->log_w);
-    ASD_HIP(hipGetLastError());
-    return ASD_OK;
-  }
-  if (!g->use_mfma) {
-    ProfScope ps(ctx, ASD_PROF_GMM_ROWWISE, rows.call, st);
-    const int blocks = (int)std::min<int64_t>(ceil_div(n, 4), 4096);
+    const int blocks = (int)std::min<int64_t>(ceil_div(n, 4), 65536);
     hipLaunchKernelGGL(gmm_rowwise_kernel, dim3(blocks), dim3(256), g->rowwise_lds, st, rows.n_dev, n, d, C, rows.in_base,
                        rows.in_off, rows.out_base, rows.out_off, rows.tau, g->coef_tau, g->means, g->musq,
                        g->log_w);
     ASD_HIP(hipGetLastError());
+    return ASD_OK;
+  }
+  // Calls small enough that the tiled kernels below do not fill the chip (or that they do not take at all).  Measured,
+  // n rows, microseconds per call, these / the split-operand kernels: d = C = 512, n = 1024 35 / 118, n = 4096 83 / 130,
+  // n = 8192 (2.1e9 products) 146 / 140; d 96, C 4096, n 4096 (1.6e9) 145 / 195; against the fp32 tiles: d 100, C 1000,
+  // n 950 24 / 154; d 1000, C 4000, n 1000 (4e9) 240 / 485, n = 2000 532 / 525; d 500, C 1000, n 10000 (5e9) 332 / 303.
+  // A screened context keeps its own kernels at every size: the draft call's verdict and the certificate's candidates
+  // pass from call to call there.
+  if (!g->use_mfma || (!g->screen_ok && macs < (g->split_ok ? 1.5e9 : 4e9))) {
+    ProfScope ps(ctx, ASD_PROF_GMM_ROWWISE, rows.call, st);
+    ASD_HIP(launch_gmm_few(FewArgs{rows.n_dev, n, d, C, (d + 3) & ~3, (C + 3) & ~3, rows.in_base, rows.in_off, rows.out_base,
+                                   rows.out_off, rows.tau, g->coef_tau, g->means_p ? g->means_p : g->means, g->means_t,
+                                   g->musq, g->log_w, g->logits, g->pmax, 0}, st));
     return ASD_OK;
   }
   // partial row maxima per row: one per wavefront column of the tiling in use

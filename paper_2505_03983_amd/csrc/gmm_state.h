@@ -11,10 +11,11 @@ struct GmmState {
   float var = 0.f;
   const float* means = nullptr;  // caller's [C, d]
   const float* log_w = nullptr;  // caller's [C]
-  float* means_t = nullptr;      // [d, C]
+  float* means_t = nullptr;      // [d, C rounded up to 4]
+  float* means_p = nullptr;      // [C, d rounded up to 4] zero-padded copy; NULL when d % 4 == 0
   float* musq = nullptr;         // [C]
   float4* coef_tau = nullptr;    // [n_tau]: (kappa, gamma, cx, cm)
-  float* logits = nullptr;       // [rows_max, C] (matrix-core path only)
+  float* logits = nullptr;       // [rows_max, C] (C rounded up to 4 where only gmm_few.h's kernels use it)
   float* pmax = nullptr;         // [rows_max, np] partial row maxima of the logits
   int np = 0;
   float* rmax = nullptr;         // [rows_max] row maxima of the verify call's logits (split-operand path)
@@ -80,7 +81,6 @@ struct GmmState {
   int32_t* cert_cnt = nullptr;     // [row tiles]: rows of the tile that have finished / passed (zero between calls)
   int32_t* live_tiles = nullptr;   // [1 + row tiles]: number of row tiles that are not certified, then their indices
   size_t rowwise_lds = 0;
-  size_t lds_rowwise_bytes = 0;  // > 0: the mixture fits in LDS and d % 4 == 0 (gmm_rowwise_lds_kernel)
 };
 
 }  // namespace asd

@@ -30,10 +30,24 @@ def _denoise(cfg, n, seed=3):
     return out.cpu().numpy(), model(cfg["K"] - tau, x.astype(np.float64))
 
 
+@pytest.mark.parametrize("d, C, n", [
+    (1, 1, 1), (2, 128, 5), (16, 16, 17),                 # the row-wise kernel, up to C d = 256
+    (1, 257, 1), (257, 1, 3), (15, 18, 15), (17, 16, 16), # just past it: one partial tile in every direction
+    (100, 64, 33), (97, 65, 16), (256, 1024, 1), (260, 1028, 47), (301, 1003, 40),   # k shared by 1, 2, 4 wavefronts
+    (5, 33, 8200), (64, 1024, 1025), (130, 1027, 993),    # 32 x 32 tiles: last row, column and k step partial
+    (2000, 3000, 9),                                      # a mixture that no LDS holds, neither size a tile's multiple
+])
+def test_mixture_calls_of_few_rows(d, C, n):
+    """fp32 products and sums: logits of up to ~2^9 in fp32 move a weight by at most 2^9 2^-24 = 3e-5 of itself, and
+    the mean by no more."""
+    got, want = _denoise(dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25), n)
+    assert H.rel_err(got, want) <= 3e-5
+
+
 @pytest.mark.parametrize("d, C, n", [(96, 1056, 15000), (80, 1040, 19000), (500, 1000, 8100),
                                      (96, 1056, 16400), (160, 640, 16400)])
 def test_mixture_calls_on_the_tiled_kernels(d, C, n):
-    """Two fp16 terms, three bf16 terms, fp32; then the least rows that go to 256-wide tiles, C ending inside one.
-    Logits of up to ~2^9 in fp32 move a weight by at most 2^9 2^-24 = 3e-5 of itself, and the mean by no more."""
+    """The least products that go to the tiles: two fp16 terms, three bf16 terms, fp32; then the least rows that go to
+    256-wide tiles, C ending inside one (same bound)."""
     got, want = _denoise(dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25), n)
     assert H.rel_err(got, want) <= 3e-5
