@@ -1,5 +1,5 @@
 // Shared pieces of the bf16 x bf16 -> fp32 GEMMs on the gfx950 matrix cores (the kernels are in
-// gemm_bf16_pipe.h and gemm_split3.h): the MFMA operand / accumulator vector types, the fp32 -> bf16
+// gemm_bf16_slab.h and gemm_split3.h): the MFMA operand / accumulator vector types, the fp32 -> bf16
 // rounding, and the pointer types and wait of the direct-to-LDS loads.
 #pragma once
 #include <hip/hip_runtime.h>

@@ -17,7 +17,7 @@
 // multiple of the number of row tiles a workgroup keeps its rows of A -- they stay in the caches -- and walks along
 // the columns; the workgroups of one XCD (w mod 8) share row tiles modulo 8.
 //
-// Data movement, LDS layout, swizzle and the hand-over between slabs are those of gemm_bf16_pipe.h with two int8 in
+// Data movement and the hand-over between slabs follow gemm_bf16_slab.h on row-major operands (see PipeCfg16), with two int8 in
 // the place of one bf16: a row's slab is 128 bytes = 128 k, a lane's 16-byte chunk feeds one
 // v_mfma_i32_32x32x32_i8 (twice the multiply-adds of the bf16 instruction in the same time), and the sums are exact.
 // A and W are handed over as arrays of 16-bit units: K16, lda and ldw count pairs of int8.
@@ -29,9 +29,53 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "gemm_bf16_pipe.h"
+#include "gemm_bf16.h"
 
 namespace asd {
+
+// BM x BN workgroup tile, STAGES LDS stages, WGM x WGN wavefronts (each owns a (BM/WGM) x (BN/WGN) sub-tile).
+//
+// A stage: A rows then W rows, each row = one slab of 128 bytes = 8 chunks of 16 bytes, unpadded (a wave's direct load
+// writes 64 consecutive chunks = 8 rows).  LDS serves 256 bytes per clock (64 banks), i.e. 16 lanes of a 128-bit read at a
+// time; chunk c of row r is stored at chunk slot c ^ ((r >> 1) & 7): a row pair shares a key and differs in the 128-byte
+// half, so the 16 rows of a fragment read land in 16 different 16-byte slots of a 256-byte line.  The permutation is
+// applied on the global side (lane L of a wave-load fetches the chunk that belongs in slot L), which still reads whole
+// 128-byte row segments.  A direct-to-LDS load of 1 KB occupies the CU's single address path for ~16 cycles and the
+// issuing wavefront stalls until it is accepted: with two wavefronts per SIMD the neighbour's MFMAs run meanwhile.
+template <int BM_, int BN_, int STAGES_, int WGM_ = 2, int WGN_ = 4>
+struct PipeCfg16 {
+  static constexpr int BM = BM_, BN = BN_, STAGES = STAGES_, BK = 64, WGM = WGM_, WGN = WGN_;
+  static constexpr int NW = WGM * WGN, THREADS = 64 * NW;
+  static constexpr int WM = BM / WGM, WN = BN / WGN;          // wavefront sub-tile
+  static constexpr int MI = WM / 32, NJ = WN / 32;
+  static constexpr int AR = BM;
+  static constexpr int A_LOADS = AR / 8 / NW, W_LOADS = BN / 8 / NW;  // wave-loads (8 rows each) per wavefront per slab
+  static constexpr int LPS = A_LOADS + W_LOADS;
+  static constexpr int STAGE_BYTES = (AR + BN) * 128;
+  static constexpr size_t LDS_BYTES = (size_t)STAGES * STAGE_BYTES;
+  static_assert(WM % 32 == 0 && WN % 32 == 0 && STAGES >= 3 && STAGES <= 8, "tile shape");
+  static_assert(AR % (8 * NW) == 0 && BN % (8 * NW) == 0, "wave-loads must divide evenly among the wavefronts");
+  static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
+  static_assert(LPS * (STAGES - 1) <= 63, "vmcnt range");
+  // loads of the next slab issued inside MFMA group g (0..3), and those of group 3 issued after the hand-over
+  static constexpr int loads_in_group(int g) { return LPS / 4 + (g < LPS % 4 ? 1 : 0); }
+  static constexpr int loads_before_group(int g) { return g == 0 ? 0 : loads_before_group(g - 1) + loads_in_group(g - 1); }
+  static constexpr int LA = loads_in_group(3) > 0 ? 1 : 0;
+};
+
+// Wait until at most `slabs` * LPS + EXTRA of this wavefront's loads are outstanding (slabs in 0..6).
+template <int LPS, int EXTRA>
+__device__ __forceinline__ void wait_vmcnt_slabs(int slabs) {
+  switch (slabs) {
+    case 0: wait_vmcnt<EXTRA>(); break;
+    case 1: wait_vmcnt<(1 * LPS + EXTRA <= 63 ? 1 * LPS + EXTRA : 63)>(); break;
+    case 2: wait_vmcnt<(2 * LPS + EXTRA <= 63 ? 2 * LPS + EXTRA : 63)>(); break;
+    case 3: wait_vmcnt<(3 * LPS + EXTRA <= 63 ? 3 * LPS + EXTRA : 63)>(); break;
+    case 4: wait_vmcnt<(4 * LPS + EXTRA <= 63 ? 4 * LPS + EXTRA : 63)>(); break;
+    case 5: wait_vmcnt<(5 * LPS + EXTRA <= 63 ? 5 * LPS + EXTRA : 63)>(); break;
+    default: wait_vmcnt<(6 * LPS + EXTRA <= 63 ? 6 * LPS + EXTRA : 63)>(); break;
+  }
+}
 
 template <class Cfg>
 __global__ __launch_bounds__(Cfg::THREADS) void gemm_i8_colmax_stream_kernel(int Ma, const int* __restrict__ N_dev,
@@ -41,7 +85,6 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_i8_colmax_stream_kernel(int
                                                                              const int32_t* __restrict__ on,
                                                                              const int32_t* __restrict__ live_cols,
                                                                              int32_t* __restrict__ out, int nsub) {
-  static_assert(Cfg::PLANES == 1, "one plane");
   constexpr int BM = Cfg::BM, BN = Cfg::BN, STAGES = Cfg::STAGES, MI = Cfg::MI, NJ = Cfg::NJ, NW = Cfg::NW;
   constexpr int AR = Cfg::AR, WM = Cfg::WM, WN = Cfg::WN;
   constexpr int A_LOADS = Cfg::A_LOADS, W_LOADS = Cfg::W_LOADS, LPS = Cfg::LPS, STAGE_BYTES = Cfg::STAGE_BYTES;

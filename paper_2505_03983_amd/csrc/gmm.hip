@@ -37,7 +37,6 @@
 //  4. the second GEMM visits the live K slabs of the remaining row tiles.
 #include "common.h"
 #include "device_util.h"
-#include "gemm_bf16_pipe.h"
 #include "gemm_i8_stream.h"
 #include "gemm_f32.h"
 #include "gemm_split3.h"

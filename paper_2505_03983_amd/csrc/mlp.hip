@@ -17,23 +17,47 @@
 // with two terms the same figure is ~4e-6 of the output scale.
 #include "common.h"
 #include "gemm_bf16.h"
-#include "gemm_bf16_pipe.h"
+#include "gemm_bf16_slab.h"
 
 namespace asd {
 
-// Verify call, K % 64 == 0: the direct-to-LDS pipeline.  A CU moves about 30 bytes per clock from
-// L2 into LDS whatever the kernel does, so the tile is as large as the problem allows: 128 x 256
-// (MFMA-bound fraction of the loop ~60%) when that still gives every CU a tile, else 128 x 128.
-typedef PipeCfg16<128, 256, 3, 2, 4> MlpPipeWide;
-typedef PipeCfg16<128, 128, 4, 2, 4> MlpPipeSquare;
-// Draft call (one row per chain): the weights are streamed once for a handful of rows.  64 x 64 tiles
-// with 7 slabs (56 KB of weights) in flight each, and K split so that there are at least as many
-// workgroups as CUs: ~14 MB of the weight stream in flight, which is what HBM latency asks for.
-typedef PipeCfg16<64, 64, 8, 2, 2> MlpPipeSkinny;
-// The same three roles with a two-plane A operand (act_terms = 2).  A stage holds both planes of the A slab, so
-// 128 x 128 output tiles load as many bytes per MFMA as 128 x 256 tiles do with one plane.
-typedef PipeCfg16<128, 128, 3, 2, 4, 2> MlpPipe2;
-typedef PipeCfg16<64, 64, 6, 2, 2, 2> MlpPipeSkinny2;
+// Tile shapes: output rows x columns, slabs per stage, stages, wavefronts, planes of A.  With two planes a slab of the
+// largest tile is 32 KB, so its stages are single slabs.  The small ones read fragments a stage ahead.
+template <int PL>
+struct MlpTiles {
+  typedef SlabCfg<128, 256, 3 - PL, PL == 2 ? 4 : 3, 2, 4, PL> T128x256;
+  typedef SlabCfg<128, 128, 2, PL == 2 ? 3 : 4, 2, 4, PL> T128x128;
+  typedef SlabCfg<64, 128, 2, PL == 2 ? 4 : 5, 2, 2, PL> T64x128;
+  typedef SlabCfg<64, 64, 2, PL == 2 ? 6 : 8, 2, 2, PL, true> T64x64;
+  typedef SlabCfg<32, 64, 2, PL == 2 ? 6 : 8, 1, 2, PL, true> T32x64;
+};
+// Which one: the least ceil(tiles / CUs) x time of a tile, a tile taking f + k per 64 of K (a workgroup has its CU to
+// itself; microseconds, fitted to K = 1024 and 4096 with two planes, 960 and 1536 with one, from a single tile to eight
+// rounds of them).  Measured, two planes, 4096 x 4096 weights (start: 128 x 128 throughout, 160 us at 1984 rows and 63 at
+// 456): 1984 rows 128 / 148 / 157 / - / -, 456 rows 79 / 55 / 39 / 56 / -, 200 rows - / 51 / 38 / 28 / 42; 1024 x 1024:
+// 3840 rows 32 / 27 / 31 / - / -, 960 rows 26 / 18 / 12 / 11 / 16, 120 rows - / 17 / 13 / 9 / 8.
+struct TileCost {
+  int bm, bn;
+  float f, k;
+};
+constexpr TileCost kTileCost[2][5] = {
+    {{128, 256, 1.f, 1.05f}, {128, 128, 3.f, 0.75f}, {64, 128, 3.f, 0.45f}, {64, 64, 3.5f, 0.33f}, {32, 64, 4.f, 0.2f}},
+    {{128, 256, 0.f, 2.0f}, {128, 128, 3.f, 1.1f}, {64, 128, 3.5f, 0.55f}, {64, 64, 4.7f, 0.365f}, {32, 64, 4.5f, 0.26f}}};
+static int pick_tile(int planes, int n, int N, int K) {
+  int best = 0;
+  float best_t = INFINITY;
+  for (int i = 0; i < 5; ++i) {
+    const TileCost& c = kTileCost[planes - 1][i];
+    const int64_t rounds = ceil_div(ceil_div(n, c.bm) * ceil_div(N, c.bn), 256);
+    const float t = (float)rounds * (c.f + c.k * (float)K / 64.f);
+    if (t < best_t) {
+      best_t = t;
+      best = i;
+    }
+  }
+  return best;
+}
+
 constexpr int kMaxSplits = 8;
 
 struct SplitScratch {
@@ -41,57 +65,59 @@ struct SplitScratch {
   int rows = 0;            // rows the scratch was sized for (one per chain)
   bool small_verify = false;  // verify calls may be far below their row bound (windows from the controller)
 };
-// Verify calls of at most this many rows go to the 64 x 64 tiles of the draft call: a few row tiles
-// against a whole weight matrix is a weight stream again, not a 128 x 256-tile problem.
+// Verify calls of at most this many rows against a large weight matrix have a launch of their own when the controller
+// chooses the windows: both are queued, and the row count in device memory decides which one does the work.
 constexpr int kSmallVerifyRows = 256;
 
-// Both operands have row pitch ld = padded(K) (see pitch_of).  a_plane > 0: A has a second plane that many
-// elements behind the first (two-term activations).
-template <class Epi>
-static hipError_t mlp_gemm(int call, const int* n_dev, int n, int N, int K, int64_t ld, const uint16_t* A,
-                           int64_t a_plane, const uint16_t* Wt, Epi e, hipStream_t st, const SplitScratch& sc) {
-  // K is rounded up to the slab size: columns K .. ld-1 of both operands are zero (pitch_of leaves
-  // room for it), so the extra products vanish.
-  const int Kp = (int)(ceil_div(K, 64) * 64);
-  const bool two = a_plane > 0;
-  if (call == 0) {
-    const int64_t tiles = ceil_div(n, MlpPipeSkinny::BM) * ceil_div(N, MlpPipeSkinny::BN);
-    int splits = 1;
-    // only a weight matrix that takes several microseconds to stream repays the second launch
-    if (n <= sc.rows && (int64_t)N * Kp * 2 >= (8 << 20))
-      while (splits < kMaxSplits && tiles * splits < 256 && (Kp / 64) % (2 * splits) == 0) splits *= 2;
-    return two ? launch_gemm_bf16_nt_pipe<MlpPipeSkinny2, 0>(n_dev, n, N, Kp, A, ld, a_plane, Wt, ld, e, st, splits, sc.part)
-               : launch_gemm_bf16_nt_pipe<MlpPipeSkinny, 0>(n_dev, n, N, Kp, A, ld, 0, Wt, ld, e, st, splits, sc.part);
-  }
-  {
-    const int64_t wide_tiles = ceil_div(n, 128) * ceil_div(N, 256);
-    int m_lo = -1;
-    if (sc.small_verify && n > kSmallVerifyRows && (int64_t)N * Kp * 2 >= (8 << 20)) {
-      // both shapes are queued; the row count in device memory decides which one does the work
-      hipError_t e0 =
-          two ? launch_gemm_bf16_nt_pipe<MlpPipeSkinny2, 1>(n_dev, kSmallVerifyRows, N, Kp, A, ld, a_plane, Wt, ld, e, st, 1,
-                                                            nullptr, -1, kSmallVerifyRows)
-              : launch_gemm_bf16_nt_pipe<MlpPipeSkinny, 1>(n_dev, kSmallVerifyRows, N, Kp, A, ld, 0, Wt, ld, e, st, 1,
-                                                           nullptr, -1, kSmallVerifyRows);
-      if (e0 != hipSuccess) return e0;
-      m_lo = kSmallVerifyRows;
-    }
-    if (two) return launch_gemm_bf16_nt_pipe<MlpPipe2, 1>(n_dev, n, N, Kp, A, ld, a_plane, Wt, ld, e, st, 1, nullptr, m_lo);
-    return wide_tiles >= 192 ? launch_gemm_bf16_nt_pipe<MlpPipeWide, 1>(n_dev, n, N, Kp, A, ld, 0, Wt, ld, e, st, 1, nullptr, m_lo)
-                             : launch_gemm_bf16_nt_pipe<MlpPipeSquare, 1>(n_dev, n, N, Kp, A, ld, 0, Wt, ld, e, st, 1, nullptr,
-                                                                          m_lo);
+template <int PL, int CALL, class Epi>
+static hipError_t mlp_gemm_tile(int tile, const int* n_dev, int n, int N, int K, SlabMat A, SlabMat Wt, Epi e, hipStream_t st,
+                                int m_lo, int m_hi) {
+  typedef MlpTiles<PL> T;
+  switch (tile) {
+    case 0: return launch_gemm_bf16_slab<typename T::T128x256, CALL>(n_dev, n, N, K, A, Wt, e, st, 1, nullptr, m_lo, m_hi);
+    case 1: return launch_gemm_bf16_slab<typename T::T128x128, CALL>(n_dev, n, N, K, A, Wt, e, st, 1, nullptr, m_lo, m_hi);
+    case 2: return launch_gemm_bf16_slab<typename T::T64x128, CALL>(n_dev, n, N, K, A, Wt, e, st, 1, nullptr, m_lo, m_hi);
+    case 3: return launch_gemm_bf16_slab<typename T::T64x64, CALL>(n_dev, n, N, K, A, Wt, e, st, 1, nullptr, m_lo, m_hi);
+    default: return launch_gemm_bf16_slab<typename T::T32x64, CALL>(n_dev, n, N, K, A, Wt, e, st, 1, nullptr, m_lo, m_hi);
   }
 }
 
-// Row pitch (elements) of every bf16 matrix the GEMMs read: K plus 64 elements (128 bytes).
-// With the natural pitch (a power of two times 2 bytes for the widths used here) the rows a
-// workgroup streams in parallel all start on the same few HBM channels; the odd pitch spreads them.
-static inline int64_t pitch_of(int K) { return (int64_t)K + 64; }
+template <int PL, class Epi>
+static hipError_t mlp_gemm_planes(int call, const int* n_dev, int n, int N, int K, SlabMat A, SlabMat Wt, Epi e,
+                                  hipStream_t st, const SplitScratch& sc) {
+  const int Kp = slab_count(K) * 32;
+  const bool large = (int64_t)N * Kp * 2 >= (8 << 20);   // a weight matrix that takes several microseconds to stream
+  if (call == 0) {
+    // One row per chain: a stream of the weights.  64 x 64 tiles and a K split that gives every CU a workgroup keep ~14 MB
+    // of it in flight, which is what HBM latency asks for; only a large matrix repays the second launch.
+    typedef typename MlpTiles<PL>::T64x64 T;
+    const int64_t tiles = ceil_div(n, T::BM) * ceil_div(N, T::BN);
+    int splits = 1;
+    if (large && n <= sc.rows)
+      while (splits < kMaxSplits && tiles * splits < 256 && (Kp / 64) % (2 * splits) == 0) splits *= 2;
+    if (splits > 1) return launch_gemm_bf16_slab<T, 0>(n_dev, n, N, K, A, Wt, e, st, splits, sc.part);
+    return mlp_gemm_tile<PL, 0>(pick_tile(PL, n, N, Kp), n_dev, n, N, K, A, Wt, e, st, -1, 0x7fffffff);
+  }
+  int m_lo = -1;
+  if (sc.small_verify && n > kSmallVerifyRows && large) {
+    const hipError_t e0 = mlp_gemm_tile<PL, 1>(pick_tile(PL, kSmallVerifyRows, N, Kp), n_dev, kSmallVerifyRows, N, K, A, Wt, e,
+                                               st, -1, kSmallVerifyRows);
+    if (e0 != hipSuccess) return e0;
+    m_lo = kSmallVerifyRows;
+  }
+  return mlp_gemm_tile<PL, 1>(pick_tile(PL, n, N, Kp), n_dev, n, N, K, A, Wt, e, st, m_lo, 0x7fffffff);
+}
+
+template <class Epi>
+static hipError_t mlp_gemm(int call, const int* n_dev, int n, int N, int K, SlabMat A, SlabMat Wt, Epi e, hipStream_t st,
+                           const SplitScratch& sc) {
+  return A.plane > 0 ? mlp_gemm_planes<2>(call, n_dev, n, N, K, A, Wt, e, st, sc)
+                     : mlp_gemm_planes<1>(call, n_dev, n, N, K, A, Wt, e, st, sc);
+}
 
 struct MlpState {
   int width = 0, n_blocks = 0, E = 0, in_dim = 0;
-  int64_t ld_in = 0, ld_h = 0;   // padded pitches of [*, in_dim] and [*, width] bf16 matrices
-  uint16_t* wp_in = nullptr;     // padded copies of the caller's weights
+  uint16_t* wp_in = nullptr;     // copies of the caller's weights in slab layout (gemm_bf16_slab.h)
   uint16_t* wp_blk = nullptr;
   uint16_t* wp_out = nullptr;
   float out_clip = 0.f;
@@ -104,9 +130,11 @@ struct MlpState {
   const float* b_out = nullptr;
   const uint16_t* temb = nullptr;
   int act_terms = 1;          // bf16 terms an activation enters a product with (1 or 2)
-  uint16_t* in_bf = nullptr;  // [act_terms][rows_max, ld_in]: the planes of a matrix lie in_plane elements apart
+  // activations in slab layout, act_terms planes each, the planes of a matrix in_plane / h_plane elements apart
+  int64_t rows_pad = 0;       // rows they are laid out with
+  uint16_t* in_bf = nullptr;  // [act_terms][slabs of d + E][rows_pad][32]
   float* h = nullptr;         // [rows_max, width]
-  uint16_t* hb[2] = {nullptr, nullptr};   // [act_terms][rows_max, ld_h] each, planes h_plane apart
+  uint16_t* hb[2] = {nullptr, nullptr};   // [act_terms][slabs of width][rows_pad][32] each
   int64_t in_plane = 0, h_plane = 0;      // 0 when act_terms == 1
   SplitScratch split;
 };
@@ -119,7 +147,7 @@ __device__ __forceinline__ uint16_t bf16_lo(float v, uint16_t hi) { return f32_t
 // the time embedding, which is bf16 data) go to the second plane
 __global__ void mlp_pack_kernel(const int* __restrict__ n_dev, int n_rows, int d, int E, const float* __restrict__ in_base,
                                 const int64_t* __restrict__ in_off, const int32_t* __restrict__ tau,
-                                const uint16_t* __restrict__ temb, uint16_t* __restrict__ in_bf, int64_t ld_in,
+                                const uint16_t* __restrict__ temb, uint16_t* __restrict__ in_bf, int64_t in_slab,
                                 int64_t in_plane) {
   const int n = blockIdx.x;
   const int q = blockIdx.y * blockDim.x + threadIdx.x;  // group of 8 elements
@@ -144,8 +172,21 @@ __global__ void mlp_pack_kernel(const int* __restrict__ n_dev, int n_rows, int d
   } else {
     o = *reinterpret_cast<const uint4*>(temb + (int64_t)tau[n] * E + (q * 8 - d));
   }
-  *reinterpret_cast<uint4*>(in_bf + (int64_t)n * ld_in + q * 8) = o;
-  if (in_plane) *reinterpret_cast<uint4*>(in_bf + in_plane + (int64_t)n * ld_in + q * 8) = l;
+  uint16_t* dst = in_bf + (q >> 2) * in_slab + (int64_t)n * 32 + (q & 3) * 8;
+  *reinterpret_cast<uint4*>(dst) = o;
+  if (in_plane) *reinterpret_cast<uint4*>(dst + in_plane) = l;
+}
+
+// The caller's weights [rows, K] (row-major bf16) in slab layout: eight elements per thread, zeros in the padding
+__global__ __launch_bounds__(256) void mlp_pack_weights_kernel(int rows, int K, int64_t rows_pad, int nslabs,
+                                                               const uint16_t* __restrict__ w, uint16_t* __restrict__ out) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;   // chunk: slab, row, quarter
+  if (t >= rows_pad * nslabs * 4) return;
+  const int64_t row = (t >> 2) % rows_pad;
+  const int k = (int)((t >> 2) / rows_pad) * 32 + (int)(t & 3) * 8;
+  uint4 v = make_uint4(0u, 0u, 0u, 0u);
+  if (row < rows && k < K) v = *reinterpret_cast<const uint4*>(w + row * K + k);   // (K is a multiple of 8)
+  *reinterpret_cast<uint4*>(out + t * 8) = v;
 }
 
 // SiLU with the hardware exp2 and reciprocal: relative error ~1e-6, inside what the re-rounding of the
@@ -171,16 +212,16 @@ struct InEpi {  // h = acc + b; hb = bf16 terms of h
   float* h;
   uint16_t* hb;
   const float* bias;
-  int64_t ld, ldb;  // pitch of h (fp32) and of hb (bf16)
+  int64_t ld, slab;  // pitch of h (fp32), elements of a slab of hb (bf16)
   int64_t lo_plane; // > 0: offset of hb's second plane (two-term activations)
   static constexpr bool kLoads = false;
   // four consecutive columns n..n+3 (n % 4 == 0) of row m
   __device__ __forceinline__ float4 load4(int, int) const { return make_float4(0.f, 0.f, 0.f, 0.f); }
-  __device__ __forceinline__ void store4(int m, int n, float4 a, float4) const {
-    const float4 b = load_bias4(bias, n);
+  __device__ __forceinline__ float4 column4(int n) const { return load_bias4(bias, n); }
+  __device__ __forceinline__ void store4(int m, int n, float4 a, float4, float4 b) const {
     const float4 v = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
     *reinterpret_cast<float4*>(h + (int64_t)m * ld + n) = v;
-    store_act4(hb + (int64_t)m * ldb + n, lo_plane, v);
+    store_act4(hb + (n >> 5) * slab + (int64_t)m * 32 + (n & 31), lo_plane, v);
   }
 };
 
@@ -188,19 +229,19 @@ struct BlockEpi {  // h += SiLU(acc + b); hb_next = bf16 terms of h
   float* h;
   uint16_t* hb_next;
   const float* bias;
-  int64_t ld, ldb;
+  int64_t ld, slab;
   int64_t lo_plane;
   static constexpr bool kLoads = true;
   __device__ __forceinline__ float4 load4(int m, int n) const {
     return *reinterpret_cast<const float4*>(h + (int64_t)m * ld + n);
   }
-  __device__ __forceinline__ void store4(int m, int n, float4 a, float4 p) const {
-    const float4 b = load_bias4(bias, n);
+  __device__ __forceinline__ float4 column4(int n) const { return load_bias4(bias, n); }
+  __device__ __forceinline__ void store4(int m, int n, float4 a, float4 p, float4 b) const {
     float* hp = h + (int64_t)m * ld + n;
     const float4 v = make_float4(p.x + silu(a.x + b.x), p.y + silu(a.y + b.y), p.z + silu(a.z + b.z),
                                  p.w + silu(a.w + b.w));
     *reinterpret_cast<float4*>(hp) = v;
-    store_act4(hb_next + (int64_t)m * ldb + n, lo_plane, v);
+    store_act4(hb_next + (n >> 5) * slab + (int64_t)m * 32 + (n & 31), lo_plane, v);
   }
 };
 
@@ -216,8 +257,8 @@ struct OutEpi {  // out[out_off[m] + n] = acc + b, as x_0 (or converted from a n
   const int64_t* in_off;
   static constexpr bool kLoads = false;
   __device__ __forceinline__ float4 load4(int, int) const { return make_float4(0.f, 0.f, 0.f, 0.f); }
-  __device__ __forceinline__ void store4(int m, int n, float4 a, float4) const {
-    const float4 b = load_bias4(bias, n);
+  __device__ __forceinline__ float4 column4(int n) const { return load_bias4(bias, n); }
+  __device__ __forceinline__ void store4(int m, int n, float4 a, float4, float4 b) const {
     float4 v = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
     if (eps_coef) {
       const float2 ec = eps_coef[tau[m]];
@@ -266,36 +307,39 @@ asd_status mlp_create(asd_ctx* ctx, const asd_denoiser& den) {
   const size_t rows = (size_t)ctx->n_rows_max;
   ctx->model_macs_per_row = (double)s->in_dim * s->width + (double)s->n_blocks * s->width * s->width +
                             (double)s->width * ctx->d;
-  s->ld_in = pitch_of(s->in_dim);
-  s->ld_h = pitch_of(s->width);
-  const size_t Wd = (size_t)s->width, nb = (size_t)s->n_blocks, dd = (size_t)ctx->d;
+  const int64_t Wd = s->width, dd = ctx->d;
   const size_t planes = (size_t)s->act_terms;
+  s->rows_pad = slab_rows((int64_t)rows);
+  const size_t in_elems = slab_elems((int64_t)rows, s->in_dim), h_elems = slab_elems((int64_t)rows, s->width);
   if (planes > 1) {
-    s->in_plane = (int64_t)rows * s->ld_in;
-    s->h_plane = (int64_t)rows * s->ld_h;
+    s->in_plane = (int64_t)in_elems;
+    s->h_plane = (int64_t)h_elems;
   }
-  ASD_HIP(hipMalloc(&s->in_bf, sizeof(uint16_t) * planes * rows * s->ld_in));
+  ASD_HIP(hipMalloc(&s->in_bf, sizeof(uint16_t) * planes * in_elems));
   ASD_HIP(hipMalloc(&s->h, sizeof(float) * rows * s->width));
-  ASD_HIP(hipMalloc(&s->hb[0], sizeof(uint16_t) * planes * rows * s->ld_h));
-  ASD_HIP(hipMalloc(&s->hb[1], sizeof(uint16_t) * planes * rows * s->ld_h));
-  ASD_HIP(hipMemset(s->in_bf, 0, sizeof(uint16_t) * planes * rows * s->ld_in));
-  ASD_HIP(hipMemset(s->hb[0], 0, sizeof(uint16_t) * planes * rows * s->ld_h));
-  ASD_HIP(hipMemset(s->hb[1], 0, sizeof(uint16_t) * planes * rows * s->ld_h));
-  // padded copies of the weights (one-time; the caller's arrays are not read again)
-  ASD_HIP(hipMalloc(&s->wp_in, sizeof(uint16_t) * Wd * s->ld_in));
-  ASD_HIP(hipMalloc(&s->wp_out, sizeof(uint16_t) * dd * s->ld_h));
-  ASD_HIP(hipMemset(s->wp_in, 0, sizeof(uint16_t) * Wd * s->ld_in));
-  ASD_HIP(hipMemset(s->wp_out, 0, sizeof(uint16_t) * dd * s->ld_h));
-  ASD_HIP(hipMemcpy2D(s->wp_in, 2 * s->ld_in, s->w_in, 2 * (size_t)s->in_dim, 2 * (size_t)s->in_dim, Wd,
-                      hipMemcpyDeviceToDevice));
-  ASD_HIP(hipMemcpy2D(s->wp_out, 2 * s->ld_h, s->w_out, 2 * Wd, 2 * Wd, dd, hipMemcpyDeviceToDevice));
-  if (nb) {
-    ASD_HIP(hipMalloc(&s->wp_blk, sizeof(uint16_t) * nb * Wd * s->ld_h));
-    ASD_HIP(hipMemset(s->wp_blk, 0, sizeof(uint16_t) * nb * Wd * s->ld_h));
-    ASD_HIP(hipMemcpy2D(s->wp_blk, 2 * s->ld_h, s->w_blk, 2 * Wd, 2 * Wd, nb * Wd, hipMemcpyDeviceToDevice));
+  ASD_HIP(hipMalloc(&s->hb[0], sizeof(uint16_t) * planes * h_elems));
+  ASD_HIP(hipMalloc(&s->hb[1], sizeof(uint16_t) * planes * h_elems));
+  ASD_HIP(hipMemset(s->in_bf, 0, sizeof(uint16_t) * planes * in_elems));
+  ASD_HIP(hipMemset(s->hb[0], 0, sizeof(uint16_t) * planes * h_elems));
+  ASD_HIP(hipMemset(s->hb[1], 0, sizeof(uint16_t) * planes * h_elems));
+  // the weights in slab layout (one-time; the caller's arrays are not read again)
+  auto pack = [](uint16_t* dst, const uint16_t* src, int64_t n, int K) -> hipError_t {
+    const int64_t chunks = (int64_t)slab_elems(n, K) / 8;
+    hipLaunchKernelGGL(mlp_pack_weights_kernel, dim3((unsigned)ceil_div(chunks, 256)), dim3(256), 0, 0, (int)n, K,
+                       slab_rows(n), slab_count(K), src, dst);
+    return hipGetLastError();
+  };
+  ASD_HIP(hipMalloc(&s->wp_in, sizeof(uint16_t) * slab_elems(Wd, s->in_dim)));
+  ASD_HIP(hipMalloc(&s->wp_out, sizeof(uint16_t) * slab_elems(dd, s->width)));
+  ASD_HIP(pack(s->wp_in, s->w_in, Wd, s->in_dim));
+  ASD_HIP(pack(s->wp_out, s->w_out, dd, s->width));
+  if (s->n_blocks) {
+    const size_t blk = slab_elems(Wd, s->width);
+    ASD_HIP(hipMalloc(&s->wp_blk, sizeof(uint16_t) * s->n_blocks * blk));
+    for (int l = 0; l < s->n_blocks; ++l) ASD_HIP(pack(s->wp_blk + l * blk, s->w_blk + (size_t)l * Wd * Wd, Wd, s->width));
   }
   {
-    const size_t max_n = std::max(Wd, dd);
+    const size_t max_n = (size_t)std::max(Wd, dd);
     s->split.rows = ctx->B;
     ASD_HIP(hipMalloc(&s->split.part, sizeof(float) * kMaxSplits * (size_t)ctx->B * max_n));
   }
@@ -329,26 +373,29 @@ asd_status mlp_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
     const int threads = groups >= 256 ? 256 : 64;
     dim3 grid((unsigned)n, (unsigned)ceil_div(groups, threads));
     hipLaunchKernelGGL(mlp_pack_kernel, grid, dim3(threads), 0, st, rows.n_dev, n, d, s->E, rows.in_base, rows.in_off,
-                       rows.tau, s->temb, s->in_bf, s->ld_in, s->in_plane);
+                       rows.tau, s->temb, s->in_bf, s->rows_pad * 32, s->in_plane);
     ASD_HIP(hipGetLastError());
   }
+  const int64_t slab = s->rows_pad * 32, w_rows = slab_rows(W);
+  const SlabMat in{s->in_bf, s->rows_pad, s->in_plane};
+  SlabMat h[2] = {{s->hb[0], s->rows_pad, s->h_plane}, {s->hb[1], s->rows_pad, s->h_plane}};
   {
     ProfScope ps(ctx, ASD_PROF_MLP_GEMM_IN, rows.call, st);
-    ASD_HIP(mlp_gemm(rows.call, rows.n_dev, n, W, s->in_dim, s->ld_in, s->in_bf, s->in_plane, s->wp_in,
-                     InEpi{s->h, s->hb[0], s->b_in, W, s->ld_h, s->h_plane}, st, s->split));
+    ASD_HIP(mlp_gemm(rows.call, rows.n_dev, n, W, s->in_dim, in, SlabMat{s->wp_in, w_rows, 0},
+                     InEpi{s->h, s->hb[0], s->b_in, W, slab, s->h_plane}, st, s->split));
   }
   int cur = 0;
+  const size_t blk = slab_elems(W, W);
   for (int l = 0; l < s->n_blocks; ++l) {
     ProfScope ps(ctx, ASD_PROF_MLP_GEMM_BLK, rows.call, st);
-    const BlockEpi e{s->h, s->hb[cur ^ 1], s->b_blk ? s->b_blk + (size_t)l * W : nullptr, W, s->ld_h, s->h_plane};
-    ASD_HIP(mlp_gemm(rows.call, rows.n_dev, n, W, W, s->ld_h, s->hb[cur], s->h_plane,
-                     s->wp_blk + (size_t)l * W * s->ld_h, e, st, s->split));
+    const BlockEpi e{s->h, s->hb[cur ^ 1], s->b_blk ? s->b_blk + (size_t)l * W : nullptr, W, slab, s->h_plane};
+    ASD_HIP(mlp_gemm(rows.call, rows.n_dev, n, W, W, h[cur], SlabMat{s->wp_blk + l * blk, w_rows, 0}, e, st, s->split));
     cur ^= 1;
   }
   {
     ProfScope ps(ctx, ASD_PROF_MLP_GEMM_OUT, rows.call, st);
     const OutEpi e{rows.out_base, rows.out_off, s->b_out, s->out_clip, s->eps_coef, rows.tau, rows.in_base, rows.in_off};
-    ASD_HIP(mlp_gemm(rows.call, rows.n_dev, n, d, W, s->ld_h, s->hb[cur], s->h_plane, s->wp_out, e, st, s->split));
+    ASD_HIP(mlp_gemm(rows.call, rows.n_dev, n, d, W, h[cur], SlabMat{s->wp_out, slab_rows(d), 0}, e, st, s->split));
   }
   return ASD_OK;
 }

@@ -51,3 +51,37 @@ def test_mixture_calls_on_the_tiled_kernels(d, C, n):
     256-wide tiles, C ending inside one (same bound)."""
     got, want = _denoise(dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25), n)
     assert H.rel_err(got, want) <= 3e-5
+
+
+@pytest.mark.parametrize("terms", [1, 2])
+@pytest.mark.parametrize("d, E, width, blocks, rows", [
+    (8, 0, 8, 1, (1, 2)),                            # one slab of K, most of it padding
+    (40, 24, 72, 2, (31, 32, 33, 300)),              # ragged columns; rows around a tile of 32
+    (104, 16, 1000, 1, (15, 65, 520, 1000, 3000)),   # every tile shape of a 1000-wide layer, none of them full
+    (64, 64, 2056, 1, (127, 129, 300, 2000)),        # weights large enough for the taller ones
+])
+def test_mlp_rows_do_not_depend_on_the_tile_that_computes_them(d, E, width, blocks, rows, terms):
+    """The network on row counts that go to different tile shapes: every shape adds an element's products in the same
+    order, so the rows two calls share are equal bit for bit; the smallest and the largest call against the oracle
+    (two terms: products of fp32 sums of 2056 terms of 2^-17 accuracy, 1e-4; one term: 2^-9, amplified, 5e-3)."""
+    from oracle_helpers import mlp_model
+    cfg = dict(kind="mlp", d=d, E=E, width=width, n_blocks=blocks, K=20, L=16, act_terms=terms)
+    T, p, _ = oracle_setup(cfg)
+    p["out_clip"] = 0.0
+    ctx = runtime.open_ctx(cfg, p, seed=0, chains=-(-max(rows) // 16))
+    rng = np.random.default_rng(5)
+    x = rng.standard_normal((max(rows), d)).astype(np.float32)
+    tau = rng.integers(1, cfg["K"] + 1, max(rows)).astype(np.int32)
+    xd, td = torch.from_numpy(x).to(DEV), torch.from_numpy(tau).to(DEV)
+    outs = []
+    for n in rows:
+        out = torch.full((n, d), float("nan"), dtype=torch.float32, device=DEV)
+        ctx.denoise(xd[:n], td[:n], out)
+        outs.append(out)
+    torch.cuda.synchronize()
+    ctx.close()
+    for a, b in zip(outs, outs[1:]):
+        assert torch.equal(a, b[:len(a)])
+    n = min(len(x), 300)
+    want = mlp_model(T, p)(cfg["K"] - tau[:n], x[:n].astype(np.float64))
+    assert H.rel_err(outs[-1][:n].cpu().numpy(), want) <= (5e-3 if terms == 1 else 1e-4)
