@@ -224,6 +224,40 @@ asd_status launch_plan_verify(asd_ctx* ctx, const int32_t* a, hipStream_t st, co
 // walks the window; rows are written coalesced.  HBM-bound: reads 2 rows,
 // writes w rows per chain.
 // ----------------------------------------------------------------------------
+// What the draft kernel does for the rest of the round when the plans are folded in (PlanOut), by one wavefront per chain.
+__device__ __forceinline__ void draft_books(int c, int lane, int K, int Lwin, int d, int ac, int w, bool live,
+                                            const PlanOut& plan, int extra) {
+  // Bookkeeping of the round, once: the draft call has consumed its row count; the round index
+  // advances and this round's slot of the live-chain ring starts at zero (the accept kernel adds to it).
+  if (c == 0 && lane == 0) {
+    plan.n_rows[0] = 0;
+    if (plan.ring) {
+      const int r = plan.ring[0];
+      plan.ring[0] = r + 1;
+      plan.ring[1 + (r % kLiveRing)] = 0;
+      plan.ring[1 + kLiveRing + (r % kLiveRing)] = 0;
+    }
+  }
+  // This chain's rows of the verify call: the drafted samples of slots 1..w-1, read in place from the
+  // trajectory, results to x0hat[c][slot].  One atomic add reserves the range; the wavefront fills it.
+  const int cnt = w - 1 + ((extra && live && ac + w < K) ? 1 : 0);
+  if (cnt > 0) {
+    int base = 0;
+    if (lane == 0) {
+      base = atomicAdd(&plan.n_rows[1], cnt);
+      if (plan.row_counts) atomicAdd((unsigned long long*)&plan.row_counts[1], (unsigned long long)cnt);
+    }
+    base = __shfl(base, 0, 64);
+    for (int s = 1 + lane; s <= cnt; s += 64) {
+      const int i = ac + s;
+      plan.in_off[base + s - 1] = ((int64_t)c * (K + 1) + i) * d;
+      plan.out_off[base + s - 1] = ((int64_t)c * (Lwin + extra) + s) * d;
+      plan.row_tau[base + s - 1] = plan.tau[i];
+      plan.row_chain[base + s - 1] = c;
+    }
+  }
+}
+
 template <bool FOLD>  // FOLD: also list this chain's rows of the verify call and keep the round's books (see PlanOut)
 __global__ __launch_bounds__(256) void draft_kernel(int K, int Lwin, int d, const Key* __restrict__ key_p,
                                                     const int32_t* __restrict__ a,
@@ -242,37 +276,7 @@ __global__ __launch_bounds__(256) void draft_kernel(int K, int Lwin, int d, cons
   const int ac = a[c];
   const bool live = ac < K && ac >= 0 && !(pending && !pending[c]);
   const int w = live ? min(win ? win[c] : Lwin, K - ac) : 0;
-  if (FOLD && blockIdx.x == 0) {
-    // Bookkeeping of the round, once: the draft call has consumed its row count; the round index
-    // advances and this round's slot of the live-chain ring starts at zero (the accept kernel adds to it).
-    if (c == 0 && threadIdx.x == 0) {
-      plan.n_rows[0] = 0;
-      if (plan.ring) {
-        const int r = plan.ring[0];
-        plan.ring[0] = r + 1;
-        plan.ring[1 + (r % kLiveRing)] = 0;
-        plan.ring[1 + kLiveRing + (r % kLiveRing)] = 0;
-      }
-    }
-    // This chain's rows of the verify call: the drafted samples of slots 1..w-1, read in place from the
-    // trajectory, results to x0hat[c][slot].  One atomic add reserves the range; the first wavefront fills it.
-    const int cnt = w - 1 + ((extra && live && ac + w < K) ? 1 : 0);
-    if (threadIdx.x < 64 && cnt > 0) {
-      int base = 0;
-      if (threadIdx.x == 0) {
-        base = atomicAdd(&plan.n_rows[1], cnt);
-        if (plan.row_counts) atomicAdd((unsigned long long*)&plan.row_counts[1], (unsigned long long)cnt);
-      }
-      base = __shfl(base, 0, 64);
-      for (int s = 1 + (int)threadIdx.x; s <= cnt; s += 64) {
-        const int i = ac + s;
-        plan.in_off[base + s - 1] = ((int64_t)c * (K + 1) + i) * d;
-        plan.out_off[base + s - 1] = ((int64_t)c * (Lwin + extra) + s) * d;
-        plan.row_tau[base + s - 1] = plan.tau[i];
-        plan.row_chain[base + s - 1] = c;
-      }
-    }
-  }
+  if (FOLD && blockIdx.x == 0 && threadIdx.x < 64) draft_books(c, threadIdx.x, K, Lwin, d, ac, w, live, plan, extra);
   if (blk >= nblk || !live) return;
   const Key key = *key_p;
   const bool vec = (d & 3) == 0;
@@ -292,13 +296,99 @@ __global__ __launch_bounds__(256) void draft_kernel(int K, int Lwin, int d, cons
   }
 }
 
+// The same for batches too small to fill the chip with one wavefront per 64 coordinate blocks: the noise of a window
+// does not depend on the recurrence, so the wavefronts of a workgroup share its slots (Philox and Box-Muller are all but
+// two of a step's instructions) and the first one then walks the window, with noise and coefficients from LDS.  Same
+// expressions, same bits.  Measured, kernel of a sample's round on average: 200 chains, d 128, L 32 13.3 -> 8.2 us; 256, d 112,
+// L 16 10.0 -> 7.0; 24, d 3072, L 20 9.8 -> 7.0; one chain, d 112, L 16 6.5 -> 4.4.
+constexpr int kDraftChunk = 32;   // slots whose noise LDS holds at a time (32 KB)
+
+template <bool FOLD>
+__global__ __launch_bounds__(1024) void draft_split_kernel(int K, int Lwin, int d, const Key* __restrict__ key_p,
+                                                           const int32_t* __restrict__ a,
+                                                           const float* __restrict__ c_x,
+                                                           const float* __restrict__ c_0,
+                                                           const float* __restrict__ sigma,
+                                                           const float* __restrict__ x0a, float* __restrict__ traj,
+                                                           const int32_t* __restrict__ win, PlanOut plan, int extra,
+                                                           const int32_t* __restrict__ pending) {
+  __shared__ float4 s_xi[kDraftChunk][64];
+  const int c = blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int blk = blockIdx.x * 64 + lane;
+  const int nblk = (d + 3) >> 2;
+  const int ac = a[c];
+  const bool live = ac < K && ac >= 0 && !(pending && !pending[c]);
+  const int w = live ? min(win ? win[c] : Lwin, K - ac) : 0;
+  // (the last wavefront: the first has the walk to do)
+  if (FOLD && blockIdx.x == 0 && wave == nw - 1) draft_books(c, lane, K, Lwin, d, ac, w, live, plan, extra);
+  if (!live) return;
+  const Key key = *key_p;
+  const bool vec = (d & 3) == 0;
+  const bool mine = blk < nblk;
+  float* row = traj + ((int64_t)c * (K + 1) + ac) * d;
+  float4 y = make_float4(0.f, 0.f, 0.f, 0.f), g = y;
+  if (wave == 0 && mine) {
+    y = load4(row, blk, d, vec);
+    g = load4(x0a + (int64_t)c * d, blk, d, vec);
+  }
+  for (int base = 0; base < w; base += kDraftChunk) {
+    const int n = min(kDraftChunk, w - base);
+    // lane k holds the coefficients of the chunk's slot k
+    float cxv = 0.f, c0v = 0.f, sgv = 0.f;
+    if (wave == 0 && lane < n) {
+      cxv = c_x[ac + base + lane];
+      c0v = c_0[ac + base + lane];
+      sgv = sigma[ac + base + lane];
+    }
+    if (base > 0) __syncthreads();   // the walk is done with the last chunk
+    for (int k = wave; k < n; k += nw) s_xi[k][lane] = normal4(key, (uint32_t)c, (uint32_t)(ac + base + k + 1), (uint32_t)blk);
+    __syncthreads();
+    if (wave == 0 && mine) {
+      for (int k0 = 0; k0 < n; k0 += 4) {
+        float4 xi[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) xi[u] = s_xi[k0 + u][lane];   // (kDraftChunk is a multiple of 4)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (k0 + u >= n) break;
+          const float cx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cxv), k0 + u));
+          const float c0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c0v), k0 + u));
+          const float sg = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sgv), k0 + u));
+          y.x = fmaf(sg, xi[u].x, fmaf(cx, y.x, c0 * g.x));
+          y.y = fmaf(sg, xi[u].y, fmaf(cx, y.y, c0 * g.y));
+          y.z = fmaf(sg, xi[u].z, fmaf(cx, y.z, c0 * g.z));
+          y.w = fmaf(sg, xi[u].w, fmaf(cx, y.w, c0 * g.w));
+          row += d;
+          store4(row, blk, d, vec, y);
+        }
+      }
+    }
+  }
+}
+
+// Wavefronts (a power of two, at most `most`) that may share the work of one where `base` of them are in flight
+// without sharing: up to 4096 in all, half of what the 256 CUs hold -- from there on the noise is bound by the ALUs, and
+// sharing only adds the way through LDS (1024 chains of d 1024 are 4096 wavefronts: 28 us unshared).
+static int share_waves(int64_t base, int most) {
+  int t = 1;
+  while (2 * t <= most && base * 2 * t <= 4096) t *= 2;
+  return t;
+}
+
 asd_status launch_draft(asd_ctx* ctx, float* traj, const int32_t* a, hipStream_t st, int32_t* ring, const int32_t* pending) {
   const int nblk = (ctx->d + 3) / 4;
   const int threads = nblk >= 256 ? 256 : (int)(ceil_div(nblk, 64) * 64);
   dim3 grid((unsigned)ceil_div(nblk, threads), (unsigned)ctx->B);
   ProfScope ps(ctx, ASD_PROF_DRAFT, 0, st);
   const PlanOut plan = plan_out(ctx, ring);
-  if (plan.in_off)
+  const int share = share_waves(ctx->B * ceil_div(nblk, 64), std::min(16, ctx->L));
+  if (share > 1) {
+    const dim3 sgrid((unsigned)ceil_div(nblk, 64), (unsigned)ctx->B);
+    hipLaunchKernelGGL(plan.in_off ? draft_split_kernel<true> : draft_split_kernel<false>, sgrid, dim3(64 * share), 0, st,
+                       ctx->K, ctx->L, ctx->d, ctx->key_dev, a, ctx->c_x, ctx->c_0, ctx->sigma, ctx->x0a, traj, ctx->cur_win,
+                       plan, plan.in_off && ctx->reuse_now ? 1 : 0, plan.in_off ? (const int32_t*)nullptr : pending);
+  } else if (plan.in_off)
     hipLaunchKernelGGL(draft_kernel<true>, grid, dim3(threads), 0, st, ctx->K, ctx->L, ctx->d, ctx->key_dev, a, ctx->c_x,
                        ctx->c_0, ctx->sigma, ctx->x0a, traj, ctx->cur_win, plan, ctx->reuse_now ? 1 : 0, (const int32_t*)nullptr);
   else
@@ -350,7 +440,7 @@ asd_status launch_copy_slot0(asd_ctx* ctx, float* x0hat, hipStream_t st) {
 // Accept + scan + resample + advance.  One workgroup per chain; its size follows d
 // (one thread per four coordinates, 1 to 16 wavefronts).
 //
-// The window is examined kAcceptChunk slots at a time, in order, and the walk stops at the
+// The window is examined a chunk of slots (G S, see the template) at a time, in order, and the walk stops at the
 // chunk that holds the first rejection: Alg. 2 only needs the accepted prefix, and the slots
 // behind the first rejection (most of the window, typically) are never read.
 // Per chunk:
@@ -369,8 +459,16 @@ asd_status launch_copy_slot0(asd_ctx* ctx, float* x0hat, hipStream_t st) {
 // HBM-bound: reads x0a, the examined rows of x0hat and one trajectory row, writes one row.
 // ----------------------------------------------------------------------------
 constexpr int kAcceptChunk = 8;
+constexpr int kAcceptChunkMax = 16;   // with 16 groups of wavefronts
 
-template <bool FOLD>  // FOLD: also list this chain's row of the next round's draft call (see PlanOut)
+// FOLD: also list this chain's row of the next round's draft call (see PlanOut).
+// S: slots a group of wavefronts examines in a chunk.  A group is the wavefronts that hold one row (a thread per four
+// coordinates, at most 16 wavefronts); the workgroup has G = blockDim / group size of them, and slot k of a chunk goes to
+// group k % G.  One group of S = 8 where the chains alone fill the chip; where they don't, what a slot costs is the latency
+// of its noise and sums, and up to 16 groups take a slot each.  A slot's sums are added in the same order by every form.
+// Measured against one group throughout: 200 chains, d 128, L 32 16.2 -> 9.3 us; 256, d 112, L 16 12.1 -> 8.7; one chain
+// 7.8 -> 4.9; 24 chains of d 3072 (twelve wavefronts a row: one group either way) 22.7, 1024 of d 1024 36.7, as before.
+template <bool FOLD, int S>
 __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const Key* __restrict__ key_p,
                                                       int32_t* __restrict__ a,
                                                       const float* __restrict__ c_0,
@@ -384,7 +482,7 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
                                                       int64_t* __restrict__ prof_counts,
                                                       const int32_t* __restrict__ pending) {
   // pending (or NULL): chains with pending[c] == 0 have had their round already (accept_early_kernel)
-  __shared__ float s_part[kAcceptChunk][16][2];  // per slot of the chunk, per wavefront: partial <D,xi>, |D|^2
+  __shared__ float s_part[kAcceptChunkMax][16][2];  // per slot of the chunk, per wavefront: partial <D,xi>, |D|^2
   __shared__ float s_rej[2];                     // <D,xi>, |D|^2 of the first rejected slot
   __shared__ int s_first;                        // index inside the chunk of the first rejection, 64 if none
 
@@ -393,7 +491,6 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
   const int nthreads = blockDim.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int nwaves = nthreads >> 6;
   const int ac = a[c];
   // the verify call has consumed its row count: the draft kernel of the next round starts from zero
   if constexpr (FOLD) {
@@ -423,36 +520,51 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
     vv = fmaf(dz, dz, vv);
     vv = fmaf(dw, dw, vv);
   };
-  const bool single = nblk <= nthreads;  // one coordinate block per thread: x0a stays in registers
-  const float4 ga1 = (single && tid < nblk) ? load4(g_a, tid, d, vec) : make_float4(0.f, 0.f, 0.f, 0.f);
+  constexpr bool kOne = S == kAcceptChunk;        // a single group
+  const int nwaves = kOne ? nthreads >> 6 : min(16, (nblk + 63) >> 6);   // wavefronts of a group
+  const int group = kOne ? 0 : wave / nwaves, groups = kOne ? 1 : (nthreads >> 6) / nwaves, chunk = S * groups;
+  const int rt = tid - group * nwaves * 64;       // thread's place in its group
+  const bool single = nblk <= 1024;      // one coordinate block per thread: x0a stays in registers
+  const float4 ga1 = (single && rt < nblk) ? load4(g_a, rt, d, vec) : make_float4(0.f, 0.f, 0.f, 0.f);
 
   int n_acc = w;
   int examined = 0;   // slots whose x0hat row was read for the test
-  for (int base = 0; base < w; base += kAcceptChunk) {
-    examined = min(w, base + kAcceptChunk) - 1;
-    // every thread walks the chunk's slots over its own coordinate blocks; the loads of the slots are
+  for (int base = 0; base < w; base += chunk) {
+    examined = min(w, base + chunk) - 1;
+    // one lane per slot of the chunk, for the test below: what does not depend on the sums (where a slot's latency is what
+    // counts, ahead of them)
+    float logu = 0.f, sg_t = 0.f, c0_t = 0.f;
+    auto test_terms = [&]() {
+      if (tid < chunk && base + tid >= 1 && base + tid < w) {
+        sg_t = sigma[ac + base + tid];
+        c0_t = c_0[ac + base + tid];
+        logu = logf(uniform1(key, (uint32_t)c, (uint32_t)(ac + base + tid + 1)));
+      }
+    };
+    if constexpr (!kOne) test_terms();
+    // every thread walks its group's slots over its own coordinate blocks; the loads of the slots are
     // independent, so a whole chunk of rows is in flight per wavefront
-    float dot[kAcceptChunk], vv[kAcceptChunk];
+    float dot[S], vv[S];
 #pragma unroll
-    for (int kk = 0; kk < kAcceptChunk; ++kk) dot[kk] = vv[kk] = 0.f;
+    for (int kk = 0; kk < S; ++kk) dot[kk] = vv[kk] = 0.f;
     if (single) {
-      if (tid < nblk) {
+      if (rt < nblk) {
 #pragma unroll
-        for (int kk = 0; kk < kAcceptChunk; ++kk) {
-          const int k = base + kk;
+        for (int kk = 0; kk < S; ++kk) {
+          const int k = base + kk * groups + group;
           if (k >= 1 && k < w) {
-            const float4 gk = load4(g_w + (int64_t)k * d, tid, d, vec);
-            const float4 xi = normal4(key, (uint32_t)c, (uint32_t)(ac + k + 1), (uint32_t)tid);
+            const float4 gk = load4(g_w + (int64_t)k * d, rt, d, vec);
+            const float4 xi = normal4(key, (uint32_t)c, (uint32_t)(ac + k + 1), (uint32_t)rt);
             slot_terms(ga1, gk, xi, dot[kk], vv[kk]);
           }
         }
       }
-    } else {
-      for (int blk = tid; blk < nblk; blk += nthreads) {
+    } else {   // (a single group: it has 16 wavefronts)
+      for (int blk = rt; blk < nblk; blk += nthreads) {
         const float4 ga = load4(g_a, blk, d, vec);
 #pragma unroll
-        for (int kk = 0; kk < kAcceptChunk; ++kk) {
-          const int k = base + kk;
+        for (int kk = 0; kk < S; ++kk) {
+          const int k = base + kk * groups + group;
           if (k >= 1 && k < w) {
             const float4 gk = load4(g_w + (int64_t)k * d, blk, d, vec);
             const float4 xi = normal4(key, (uint32_t)c, (uint32_t)(ac + k + 1), (uint32_t)blk);
@@ -462,11 +574,11 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
       }
     }
 #pragma unroll
-    for (int kk = 0; kk < kAcceptChunk; ++kk) {
+    for (int kk = 0; kk < S; ++kk) {
       const float ds = wave_sum(dot[kk]), vs = wave_sum(vv[kk]);
       if (lane == 0) {
-        s_part[kk][wave][0] = ds;
-        s_part[kk][wave][1] = vs;
+        s_part[kk * groups + group][wave - group * nwaves][0] = ds;
+        s_part[kk * groups + group][wave - group * nwaves][1] = vs;
       }
     }
     __syncthreads();
@@ -474,22 +586,20 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
     // Alg. 3 accept test, one thread per slot of the chunk
     if (tid < 64) {
       const int k = base + lane;
-      const bool valid = lane < kAcceptChunk && k < w;
-      float sd = 0.f, sv = 0.f, rho = -INFINITY, logu = 0.f;
+      const bool valid = lane < chunk && k < w;
+      if constexpr (kOne) test_terms();
+      float sd = 0.f, sv = 0.f, rho = -INFINITY;
       int bit = 1;  // slot 0, and the lanes that stand for no slot
       if (valid && k >= 1) {
         for (int q = 0; q < nwaves; ++q) {
           sd += s_part[lane][q][0];
           sv += s_part[lane][q][1];
         }
-        const int i = ac + k;
-        const float sg = sigma[i], c0 = c_0[i];
         bit = 0;
-        if (sg > 0.f) {
-          const float vxi = c0 * sd;
-          const float v2 = c0 * c0 * sv;
-          rho = -(vxi / sg + v2 / (2.0f * sg * sg));
-          logu = logf(uniform1(key, (uint32_t)c, (uint32_t)(i + 1)));
+        if (sg_t > 0.f) {
+          const float vxi = c0_t * sd;
+          const float v2 = c0_t * c0_t * sv;
+          rho = -(vxi / sg_t + v2 / (2.0f * sg_t * sg_t));
           bit = (logu <= rho) ? 1 : 0;
         }
       }
@@ -497,7 +607,7 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
         float* sp = stats + ((int64_t)c * L + k) * 4;
         sp[0] = sd;
         sp[1] = sv;
-        sp[2] = (k == 0) ? 0.f : logu;
+        sp[2] = (k == 0 || !(sg_t > 0.f)) ? 0.f : logu;
         sp[3] = (k == 0) ? 0.f : rho;
       }
       // Alg. 2: accepted prefix = trailing ones of the ballot
@@ -888,18 +998,28 @@ asd_status launch_accept(asd_ctx* ctx, float* traj, int32_t* a, const float* x0h
                          float* stats, int32_t* rounds, int32_t* live, hipStream_t st, const int32_t* pending) {
   ProfScope ps(ctx, ASD_PROF_ACCEPT, 0, st);
   const int nblk = (ctx->d + 3) / 4;
-  const int threads = (int)std::min<int64_t>(1024, ceil_div(nblk, 64) * 64);
+  const int waves = (int)std::min<int64_t>(16, ceil_div(nblk, 64));   // of a group
+  // groups: as many as the window has slots for while the chains alone leave the chip idle
+  const int groups = share_waves((int64_t)ctx->B * waves, std::min(16 / waves, ctx->L));
   const PlanOut plan = plan_out(ctx, nullptr);
   int64_t* prof_counts = prof_counting(ctx) ? ctx->row_counts : nullptr;
   int32_t* carry = ctx->reuse_now ? ctx->carry : nullptr;
-  if (plan.in_off)
-    hipLaunchKernelGGL(accept_kernel<true>, dim3(ctx->B), dim3(threads), 0, st, ctx->K, ctx->L, ctx->d, ctx->key_dev, a,
-                       ctx->c_0, ctx->sigma, ctx->x0a, carry, x0hat, x0_slots, traj, accepted, stats, rounds, live,
-                       ctx->cur_win, plan, prof_counts, pending);
-  else
-    hipLaunchKernelGGL(accept_kernel<false>, dim3(ctx->B), dim3(threads), 0, st, ctx->K, ctx->L, ctx->d, ctx->key_dev, a,
-                       ctx->c_0, ctx->sigma, ctx->x0a, carry, x0hat, x0_slots, traj, accepted, stats, rounds, live,
-                       ctx->cur_win, plan, prof_counts, pending);
+  const auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(ctx->B), dim3(64 * waves * groups), 0, st, ctx->K, ctx->L, ctx->d, ctx->key_dev, a, ctx->c_0,
+                       ctx->sigma, ctx->x0a, carry, x0hat, x0_slots, traj, accepted, stats, rounds, live, ctx->cur_win, plan,
+                       prof_counts, pending);
+  };
+  if (plan.in_off) {
+    if (groups >= 8) go(accept_kernel<true, 1>);
+    else if (groups == 4) go(accept_kernel<true, 2>);
+    else if (groups == 2) go(accept_kernel<true, 4>);
+    else go(accept_kernel<true, 8>);
+  } else {
+    if (groups >= 8) go(accept_kernel<false, 1>);
+    else if (groups == 4) go(accept_kernel<false, 2>);
+    else if (groups == 2) go(accept_kernel<false, 4>);
+    else go(accept_kernel<false, 8>);
+  }
   ASD_HIP(hipGetLastError());
   return ASD_OK;
 }

@@ -85,3 +85,41 @@ def test_mlp_rows_do_not_depend_on_the_tile_that_computes_them(d, E, width, bloc
     n = min(len(x), 300)
     want = mlp_model(T, p)(cfg["K"] - tau[:n], x[:n].astype(np.float64))
     assert H.rel_err(outs[-1][:n].cpu().numpy(), want) <= (5e-3 if terms == 1 else 1e-4)
+
+
+@pytest.mark.parametrize("d, L, batches", [
+    (8, 37, (1, 3, 300, 600, 1100, 2100, 4100)),   # a wavefront a row: 16, 8, 4, 2, 1 of them share the slots
+    (264, 37, (2, 600, 1100, 2100)),               # two wavefronts a row, the second nearly empty
+    (1544, 9, (2, 300, 600)),                      # seven: two groups at most
+    (4104, 5, (1, 20)),                            # more than a workgroup's threads
+])
+def test_round_kernels_do_not_depend_on_how_many_wavefronts_share_a_chain(d, L, batches):
+    """Rounds through the stage calls in batches of sizes that share a chain's slots among more or fewer wavefronts: the
+    chains two batches have in common are equal bit for bit (the network's rows do not depend on the batch)."""
+    cfg = dict(kind="mlp", d=d, E=8, width=8, n_blocks=1, K=60, L=L, act_terms=2)
+    T, p, _ = oracle_setup(cfg)
+    runs = []
+    for B in batches:
+        ctx = runtime.open_ctx(cfg, p, seed=4, chains=B)
+        g = torch.Generator(device=DEV).manual_seed(1)
+        n = min(B, min(batches[1:]))
+        y0 = torch.zeros(B, d, device=DEV)
+        y0[:n] = torch.randn(n, d, generator=g, device=DEV)
+        traj = torch.zeros(B, cfg["K"] + 1, d, device=DEV)
+        traj[:, 0] = y0
+        a = torch.zeros(B, dtype=torch.int32, device=DEV)
+        x0hat = torch.zeros(B, L, d, device=DEV)
+        acc = torch.zeros(4, B, dtype=torch.int32, device=DEV)
+        for r in range(4):
+            ctx.draft(traj, a)
+            ctx.verify(traj, a, x0hat)
+            ctx.accept(traj, a, x0hat, acc[r])
+        torch.cuda.synchronize()
+        ctx.close()
+        runs.append((n, traj[:n].cpu(), a[:n].cpu(), acc[:, :n].cpu()))
+    assert (runs[-1][3] >= 1).all() and len(set(runs[-1][3].flatten().tolist())) > 1
+    for (n1, t1, a1, c1), (n2, t2, a2, c2) in zip(runs, runs[1:]):
+        n = min(n1, n2)
+        assert torch.equal(a1[:n], a2[:n]) and torch.equal(c1[:, :n], c2[:, :n])
+        for i in range(n):
+            assert torch.equal(t1[i, :int(a1[i]) + 1], t2[i, :int(a2[i]) + 1])
