@@ -17,6 +17,7 @@
 // with two terms the same figure is ~4e-6 of the output scale.
 #include "common.h"
 #include "gemm_bf16.h"
+#include "gemm_bf16_few.h"
 #include "gemm_bf16_slab.h"
 
 namespace asd {
@@ -82,19 +83,41 @@ static hipError_t mlp_gemm_tile(int tile, const int* n_dev, int n, int N, int K,
   }
 }
 
+// The kernel for few rows (gemm_bf16_few.h), where one of its tiles gives every workgroup a CU to itself: 0 is 16 x 32, 1 is
+// 32 x 32, -1 neither.  Measured, microseconds a layer, this / the tiles above, 1, 32, 64, 128, 256 rows: 1024 x 1024, two
+// planes, 5.1 5.2 5.7 6.0 7.9 / 7.3 8.0 8.6 8.9 9.2, one plane 4.0 4.2 4.3 4.6 5.9 / 6.5 7.2 7.4 7.6 8.0; 1536 x 1536, one
+// plane, 128 rows (192 workgroups) 7.1 / 9.6, 256 rows (384) 11.2 / 9.8.  A product that is split over K below reads each
+// weight once per 64 rows there and once per 32 here: 4096 x 4096, 24 rows 13.7 / 19.6, 64 rows 18.0 / 19.9 from the Infinity
+// Cache, but slower from HBM, where a network of that size lies; it takes the smaller tile only.
+static int pick_few_tile(int n, int N, int splits) {
+  if (ceil_div(n, 16) * ceil_div(N, 32) <= 256) return 0;
+  return splits == 1 && ceil_div(n, 32) * ceil_div(N, 32) <= 256 ? 1 : -1;
+}
+template <int PL, class Epi>
+static hipError_t mlp_gemm_few(int tile, const int* n_dev, int n, int N, int K, SlabMat A, SlabMat Wt, Epi e, hipStream_t st,
+                               int splits) {
+  return tile == 0 ? launch_gemm_bf16_few<FewRowsCfg<1, 2, 16, PL>>(n_dev, n, N, K, A, Wt, e, st, splits)
+                   : launch_gemm_bf16_few<FewRowsCfg<2, 2, 8, PL>>(n_dev, n, N, K, A, Wt, e, st, splits);
+}
+
 template <int PL, class Epi>
 static hipError_t mlp_gemm_planes(int call, const int* n_dev, int n, int N, int K, SlabMat A, SlabMat Wt, Epi e,
                                   hipStream_t st, const SplitScratch& sc) {
   const int Kp = slab_count(K) * 32;
   const bool large = (int64_t)N * Kp * 2 >= (8 << 20);   // a weight matrix that takes several microseconds to stream
-  if (call == 0) {
-    // One row per chain: a stream of the weights.  64 x 64 tiles and a K split that gives every CU a workgroup keep ~14 MB
-    // of it in flight, which is what HBM latency asks for; only a large matrix repays the second launch.
-    typedef typename MlpTiles<PL>::T64x64 T;
+  // One row per chain against a large matrix: a stream of the weights, K split over workgroups.  64 x 64 tiles and a K split
+  // that gives every CU a workgroup keep ~14 MB of it in flight, which is what HBM latency asks for; only a large matrix
+  // repays the second launch.  (The split is a matter of the sizes alone, and the kernel for few rows adds its parts up
+  // the same way: the bits do not depend on which of them runs.)
+  typedef typename MlpTiles<PL>::T64x64 T;
+  int splits = 1;
+  if (call == 0 && large && n <= sc.rows) {
     const int64_t tiles = ceil_div(n, T::BM) * ceil_div(N, T::BN);
-    int splits = 1;
-    if (large && n <= sc.rows)
-      while (splits < kMaxSplits && tiles * splits < 256 && (Kp / 64) % (2 * splits) == 0) splits *= 2;
+    while (splits < kMaxSplits && tiles * splits < 256 && (Kp / 64) % (2 * splits) == 0) splits *= 2;
+  }
+  const int few = pick_few_tile(n, N, splits);
+  if (few >= 0) return mlp_gemm_few<PL>(few, n_dev, n, N, K, A, Wt, e, st, splits);
+  if (call == 0) {
     if (splits > 1) return launch_gemm_bf16_slab<T, 0>(n_dev, n, N, K, A, Wt, e, st, splits, sc.part);
     return mlp_gemm_tile<PL, 0>(pick_tile(PL, n, N, Kp), n_dev, n, N, K, A, Wt, e, st, -1, 0x7fffffff);
   }

@@ -123,3 +123,27 @@ def test_round_kernels_do_not_depend_on_how_many_wavefronts_share_a_chain(d, L, 
         assert torch.equal(a1[:n], a2[:n]) and torch.equal(c1[:, :n], c2[:, :n])
         for i in range(n):
             assert torch.equal(t1[i, :int(a1[i]) + 1], t2[i, :int(a2[i]) + 1])
+
+
+@pytest.mark.parametrize("terms, width, chains", [(1, 2304, 5), (2, 2304, 5), (2, 2304, 33), (2, 2560, 24), (1, 2560, 64)])
+def test_mlp_draft_call_of_few_rows_with_a_large_matrix(terms, width, chains):
+    """The draft call of a few chains adds its sums over K in parts where the weights are large (parts of 18 and of 10
+    slabs here: inside and across the stages of the kernel): the model values against those of asd_denoise, which adds
+    in one part.  fp32 sums in another order, re-rounded to 2^-17 (2^-9 with one term) between layers: 1e-5, 2e-2."""
+    cfg = dict(kind="mlp", d=64, E=16, width=width, n_blocks=2, K=20, L=2, act_terms=terms)
+    T, p, _ = oracle_setup(cfg)
+    p["out_clip"] = 0.0
+    ctx = runtime.open_ctx(cfg, p, seed=0, chains=chains)
+    g = torch.Generator(device=DEV).manual_seed(2)
+    traj = torch.zeros(chains, cfg["K"] + 1, 64, device=DEV)
+    traj[:, 0] = torch.randn(chains, 64, generator=g, device=DEV)
+    a = torch.zeros(chains, dtype=torch.int32, device=DEV)
+    x0hat = torch.zeros(chains, 2, 64, device=DEV)
+    want = torch.zeros(chains, 64, device=DEV)
+    ctx.denoise(traj[:, 0].contiguous(), torch.full((chains,), cfg["K"], dtype=torch.int32, device=DEV), want)
+    ctx.draft(traj, a)
+    ctx.verify(traj, a, x0hat)
+    torch.cuda.synchronize()
+    ctx.close()
+    assert torch.isfinite(want).all()
+    assert H.rel_err(x0hat[:, 0].cpu().numpy(), want.cpu().numpy()) <= (2e-2 if terms == 1 else 1e-5)
