@@ -211,7 +211,8 @@ static void teardown(asd_ctx* ctx) {
 }
 
 static RowPlan draft_rows(asd_ctx* ctx, const float* traj) {
-  return RowPlan{ctx->B, ctx->n_rows_dev + 0, traj, ctx->x0a, ctx->in_off, ctx->out_off, ctx->row_tau, 0, ctx->row_chain};
+  return RowPlan{ctx->B, ctx->n_rows_dev + 0, traj, ctx->x0a, ctx->in_off, ctx->out_off, ctx->row_tau, 0, ctx->row_chain,
+                 ctx->fold_plans && ctx->kind == ASD_DEN_MLP};
 }
 
 static RowPlan verify_rows(asd_ctx* ctx, const float* traj, float* x0hat) {
@@ -219,7 +220,7 @@ static RowPlan verify_rows(asd_ctx* ctx, const float* traj, float* x0hat) {
   const int block = ctx->cur_win ? 0 : model_row_block(ctx);    // the planner's filling of each chain's block (launch_plan_verify)
   if (block > 0) per_chain = (per_chain + block - 1) / block * block;
   return RowPlan{ctx->B * per_chain, ctx->n_rows_dev + 1, traj, x0hat, ctx->in_off, ctx->out_off, ctx->row_tau, 1,
-                 ctx->row_chain};
+                 ctx->row_chain, ctx->fold_plans && draft_packs_rows(ctx)};
 }
 
 __global__ void set_key_kernel(Key* dst, Key key) { *dst = key; }
@@ -500,9 +501,13 @@ asd_status asd_sample_sequential(asd_ctx* ctx, const float* y0, float* traj, voi
   if (ctx->stage != 0) return fail(ASD_ESTATE, "asd_sample_sequential called between stage calls");
   hipStream_t st = (hipStream_t)stream;
   ASD_TRY(flush_key(ctx, st));
+  struct FoldScope {   // every kernel lists the rows of the next model call
+    asd_ctx* c;
+    explicit FoldScope(asd_ctx* x) : c(x) { c->fold_plans = true; }
+    ~FoldScope() { c->fold_plans = false; }
+  } fold_scope(ctx);
   ASD_TRY(launch_init_state(ctx, y0, traj, ctx->a, nullptr, st));
   for (int i = 0; i < ctx->K; ++i) {
-    ASD_TRY(launch_plan_seq(ctx, i, st));
     ASD_TRY(model_eval(ctx, draft_rows(ctx, traj), st));
     ASD_TRY(launch_seq_step(ctx, traj, i, st));
   }

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gemm_bf16.h"
+
 namespace asd {
 
 // ----------------------------------------------------------------------------

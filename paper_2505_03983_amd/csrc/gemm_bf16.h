@@ -42,4 +42,18 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   return (uint16_t)(u >> 16);
 }
 
+__device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
+// lo term of a two-term activation: bf16(v - float(hi)) (the difference is exact in fp32)
+__device__ __forceinline__ uint16_t bf16_lo(float v, uint16_t hi) { return f32_to_bf16_rne(v - bf16_to_f32(hi)); }
+
+// hi and (lo_plane > 0) lo terms of four activations, to p and p + lo_plane
+__device__ __forceinline__ void store_act4(uint16_t* p, int64_t lo_plane, float4 v) {
+  const uint16_t h0 = f32_to_bf16_rne(v.x), h1 = f32_to_bf16_rne(v.y), h2 = f32_to_bf16_rne(v.z), h3 = f32_to_bf16_rne(v.w);
+  *reinterpret_cast<uint2*>(p) = make_uint2((uint32_t)h0 | ((uint32_t)h1 << 16), (uint32_t)h2 | ((uint32_t)h3 << 16));
+  if (lo_plane)
+    *reinterpret_cast<uint2*>(p + lo_plane) =
+        make_uint2((uint32_t)bf16_lo(v.x, h0) | ((uint32_t)bf16_lo(v.y, h1) << 16),
+                   (uint32_t)bf16_lo(v.z, h2) | ((uint32_t)bf16_lo(v.w, h3) << 16));
+}
+
 }  // namespace asd

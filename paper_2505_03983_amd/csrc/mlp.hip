@@ -162,9 +162,6 @@ struct MlpState {
   SplitScratch split;
 };
 
-__device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-// lo term of a two-term activation: bf16(v - float(hi)) (the difference is exact in fp32)
-__device__ __forceinline__ uint16_t bf16_lo(float v, uint16_t hi) { return f32_to_bf16_rne(v - bf16_to_f32(hi)); }
 
 // in_bf[n] = [ bf16(x_n) ; temb[tau_n] ], eight elements per thread; in_plane > 0: the lo terms of x (zero for
 // the time embedding, which is bf16 data) go to the second plane
@@ -218,15 +215,6 @@ __device__ __forceinline__ float silu(float z) {
   return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
 }
 
-// hi and (lo_plane > 0) lo terms of four activations, to p and p + lo_plane
-__device__ __forceinline__ void store_act4(uint16_t* p, int64_t lo_plane, float4 v) {
-  const uint16_t h0 = f32_to_bf16_rne(v.x), h1 = f32_to_bf16_rne(v.y), h2 = f32_to_bf16_rne(v.z), h3 = f32_to_bf16_rne(v.w);
-  *reinterpret_cast<uint2*>(p) = make_uint2((uint32_t)h0 | ((uint32_t)h1 << 16), (uint32_t)h2 | ((uint32_t)h3 << 16));
-  if (lo_plane)
-    *reinterpret_cast<uint2*>(p + lo_plane) =
-        make_uint2((uint32_t)bf16_lo(v.x, h0) | ((uint32_t)bf16_lo(v.y, h1) << 16),
-                   (uint32_t)bf16_lo(v.z, h2) | ((uint32_t)bf16_lo(v.w, h3) << 16));
-}
 __device__ __forceinline__ float4 load_bias4(const float* bias, int n) {
   return bias ? *reinterpret_cast<const float4*>(bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
 }
@@ -386,11 +374,16 @@ void mlp_destroy(asd_ctx* ctx) {
   ctx->mlp = nullptr;
 }
 
+PackOut mlp_pack_out(const asd_ctx* ctx) {
+  const MlpState* s = ctx->mlp;
+  return PackOut{s->in_bf, s->rows_pad * 32, s->in_plane, s->temb, s->E, ctx->d};
+}
+
 asd_status mlp_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
   MlpState* s = ctx->mlp;
   const int n = rows.n, d = ctx->d, W = s->width;
   s->split.small_verify = ctx->cur_win != nullptr;
-  {
+  if (!rows.packed) {
     ProfScope ps(ctx, ASD_PROF_MLP_PACK, rows.call, st);
     const int groups = s->in_dim / 8;
     const int threads = groups >= 256 ? 256 : 64;

@@ -7,6 +7,19 @@
 
 namespace asd {
 
+// Coordinates 4 blk .. of listed row `row`, and (by n lanes of a wavefront) its time embedding, as mlp_pack_kernel stores them.
+__device__ __forceinline__ void pack_row4(const PackOut& p, int64_t row, int blk, float4 v) {
+  store_act4(p.in_bf + (blk >> 3) * p.slab + row * 32 + (blk & 7) * 4, p.plane, v);
+}
+__device__ __forceinline__ void pack_temb(const PackOut& p, int64_t row, int tau, int lane, int n) {
+  for (int e = lane; e * 8 < p.E; e += n) {
+    const int k = p.d + 8 * e;
+    uint16_t* dst = p.in_bf + (k >> 5) * p.slab + row * 32 + (k & 31);
+    *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(p.temb + (int64_t)tau * p.E + 8 * e);
+    if (p.plane) *reinterpret_cast<uint4*>(dst + p.plane) = make_uint4(0u, 0u, 0u, 0u);
+  }
+}
+
 // ----------------------------------------------------------------------------
 // y_0, a = 0, rounds = 0
 // ----------------------------------------------------------------------------
@@ -34,7 +47,9 @@ __global__ void init_state_kernel(int B, int K, int d, const Key* __restrict__ k
   for (int blk = threadIdx.x; blk < nblk; blk += blockDim.x) {
     float4 v = y0 ? load4(y0 + (int64_t)c * d, blk, d, vec) : normal4(key, (uint32_t)c, 0u, (uint32_t)blk);
     store4(row, blk, d, vec, v);
+    if (plan.pack.in_bf) pack_row4(plan.pack, c, blk, v);
   }
+  if (plan.pack.in_bf) pack_temb(plan.pack, c, plan.tau[0], threadIdx.x, blockDim.x);
   if (threadIdx.x == 0) {
     a[c] = 0;
     if (carry) carry[c] = 0;
@@ -57,6 +72,7 @@ static PlanOut plan_out(asd_ctx* ctx, int32_t* ring) {
   p.tau = ctx->tau;
   p.row_counts = prof_counting(ctx) ? ctx->row_counts : nullptr;
   p.ring = ring;
+  if (ctx->kind == ASD_DEN_MLP) p.pack = mlp_pack_out(ctx);
   return p;
 }
 
@@ -225,7 +241,8 @@ asd_status launch_plan_verify(asd_ctx* ctx, const int32_t* a, hipStream_t st, co
 // writes w rows per chain.
 // ----------------------------------------------------------------------------
 // What the draft kernel does for the rest of the round when the plans are folded in (PlanOut), by one wavefront per chain.
-__device__ __forceinline__ void draft_books(int c, int lane, int K, int Lwin, int d, int ac, int w, bool live,
+// Returns the place of the chain's first row in the list.
+__device__ __forceinline__ int draft_books(int c, int lane, int K, int Lwin, int d, int ac, int w, bool live,
                                             const PlanOut& plan, int extra) {
   // Bookkeeping of the round, once: the draft call has consumed its row count; the round index
   // advances and this round's slot of the live-chain ring starts at zero (the accept kernel adds to it).
@@ -241,8 +258,8 @@ __device__ __forceinline__ void draft_books(int c, int lane, int K, int Lwin, in
   // This chain's rows of the verify call: the drafted samples of slots 1..w-1, read in place from the
   // trajectory, results to x0hat[c][slot].  One atomic add reserves the range; the wavefront fills it.
   const int cnt = w - 1 + ((extra && live && ac + w < K) ? 1 : 0);
+  int base = 0;
   if (cnt > 0) {
-    int base = 0;
     if (lane == 0) {
       base = atomicAdd(&plan.n_rows[1], cnt);
       if (plan.row_counts) atomicAdd((unsigned long long*)&plan.row_counts[1], (unsigned long long)cnt);
@@ -256,6 +273,7 @@ __device__ __forceinline__ void draft_books(int c, int lane, int K, int Lwin, in
       plan.row_chain[base + s - 1] = c;
     }
   }
+  return base;
 }
 
 template <bool FOLD>  // FOLD: also list this chain's rows of the verify call and keep the round's books (see PlanOut)
@@ -276,7 +294,7 @@ __global__ __launch_bounds__(256) void draft_kernel(int K, int Lwin, int d, cons
   const int ac = a[c];
   const bool live = ac < K && ac >= 0 && !(pending && !pending[c]);
   const int w = live ? min(win ? win[c] : Lwin, K - ac) : 0;
-  if (FOLD && blockIdx.x == 0 && threadIdx.x < 64) draft_books(c, threadIdx.x, K, Lwin, d, ac, w, live, plan, extra);
+  if (FOLD && blockIdx.x == 0 && threadIdx.x < 64) (void)draft_books(c, threadIdx.x, K, Lwin, d, ac, w, live, plan, extra);
   if (blk >= nblk || !live) return;
   const Key key = *key_p;
   const bool vec = (d & 3) == 0;
@@ -312,7 +330,9 @@ __global__ __launch_bounds__(1024) void draft_split_kernel(int K, int Lwin, int 
                                                            const float* __restrict__ x0a, float* __restrict__ traj,
                                                            const int32_t* __restrict__ win, PlanOut plan, int extra,
                                                            const int32_t* __restrict__ pending) {
+  // (packs the rows it lists if the row is one wavefront wide: draft_packs_rows)
   __shared__ float4 s_xi[kDraftChunk][64];
+  __shared__ int s_base;
   const int c = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int blk = blockIdx.x * 64 + lane;
@@ -321,8 +341,13 @@ __global__ __launch_bounds__(1024) void draft_split_kernel(int K, int Lwin, int 
   const bool live = ac < K && ac >= 0 && !(pending && !pending[c]);
   const int w = live ? min(win ? win[c] : Lwin, K - ac) : 0;
   // (the last wavefront: the first has the walk to do)
-  if (FOLD && blockIdx.x == 0 && wave == nw - 1) draft_books(c, lane, K, Lwin, d, ac, w, live, plan, extra);
+  if (FOLD && blockIdx.x == 0 && wave == nw - 1) {
+    const int b = draft_books(c, lane, K, Lwin, d, ac, w, live, plan, extra);
+    if (lane == 0) s_base = b;
+  }
   if (!live) return;
+  const bool pack = FOLD && plan.pack.in_bf && gridDim.x == 1;
+  const int listed = w - 1 + ((extra && ac + w < K) ? 1 : 0);
   const Key key = *key_p;
   const bool vec = (d & 3) == 0;
   const bool mine = blk < nblk;
@@ -344,6 +369,9 @@ __global__ __launch_bounds__(1024) void draft_split_kernel(int K, int Lwin, int 
     if (base > 0) __syncthreads();   // the walk is done with the last chunk
     for (int k = wave; k < n; k += nw) s_xi[k][lane] = normal4(key, (uint32_t)c, (uint32_t)(ac + base + k + 1), (uint32_t)blk);
     __syncthreads();
+    if (pack && wave > 0)
+      for (int k = wave - 1; k < n; k += nw - 1)
+        if (base + k < listed) pack_temb(plan.pack, s_base + base + k, plan.tau[ac + base + k + 1], lane, 64);
     if (wave == 0 && mine) {
       for (int k0 = 0; k0 < n; k0 += 4) {
         float4 xi[4];
@@ -361,6 +389,7 @@ __global__ __launch_bounds__(1024) void draft_split_kernel(int K, int Lwin, int 
           y.w = fmaf(sg, xi[u].w, fmaf(cx, y.w, c0 * g.w));
           row += d;
           store4(row, blk, d, vec, y);
+          if (pack && base + k0 + u < listed) pack_row4(plan.pack, s_base + base + k0 + u, blk, y);
         }
       }
     }
@@ -376,13 +405,19 @@ static int share_waves(int64_t base, int most) {
   return t;
 }
 
+static int draft_share(const asd_ctx* ctx) {
+  return share_waves(ctx->B * ceil_div((ctx->d + 3) / 4, 64), std::min(16, ctx->L));
+}
+
+bool draft_packs_rows(const asd_ctx* ctx) { return ctx->kind == ASD_DEN_MLP && ctx->d <= 256 && draft_share(ctx) > 1; }
+
 asd_status launch_draft(asd_ctx* ctx, float* traj, const int32_t* a, hipStream_t st, int32_t* ring, const int32_t* pending) {
   const int nblk = (ctx->d + 3) / 4;
   const int threads = nblk >= 256 ? 256 : (int)(ceil_div(nblk, 64) * 64);
   dim3 grid((unsigned)ceil_div(nblk, threads), (unsigned)ctx->B);
   ProfScope ps(ctx, ASD_PROF_DRAFT, 0, st);
   const PlanOut plan = plan_out(ctx, ring);
-  const int share = share_waves(ctx->B * ceil_div(nblk, 64), std::min(16, ctx->L));
+  const int share = draft_share(ctx);
   if (share > 1) {
     const dim3 sgrid((unsigned)ceil_div(nblk, 64), (unsigned)ctx->B);
     hipLaunchKernelGGL(plan.in_off ? draft_split_kernel<true> : draft_split_kernel<false>, sgrid, dim3(64 * share), 0, st,
@@ -398,26 +433,46 @@ asd_status launch_draft(asd_ctx* ctx, float* traj, const int32_t* a, hipStream_t
   return ASD_OK;
 }
 
-// Sequential baseline: every chain takes step `step` (window of one).
-__global__ void fill_i32_kernel(int n, int32_t v, int32_t* p) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
-asd_status launch_plan_seq(asd_ctx* ctx, int32_t step, hipStream_t st) {
-  hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)ceil_div(ctx->B, 256)), dim3(256), 0, st, ctx->B, step,
-                     ctx->a);
-  ASD_HIP(hipGetLastError());
-  return launch_plan_draft(ctx, ctx->a, st);
+// Sequential baseline: every chain takes step i, and the next step's model row (row c: chain c) is listed, and packed, with
+// it.  (With a kernel each for the step index, the plan and the packing a step of 64 chains of d 112 was ten launches, and
+// the host's pace.)
+__global__ __launch_bounds__(256) void seq_step_kernel(int K, int d, int i, const Key* __restrict__ key_p,
+                                                       const float* __restrict__ c_x, const float* __restrict__ c_0,
+                                                       const float* __restrict__ sigma, const float* __restrict__ x0a,
+                                                       float* __restrict__ traj, PlanOut plan) {
+  const int c = blockIdx.y;
+  const int blk = blockIdx.x * blockDim.x + threadIdx.x;
+  const bool more = i + 1 < K;
+  if (more && blockIdx.x == 0) {
+    if (threadIdx.x == 0) {
+      plan.in_off[c] = ((int64_t)c * (K + 1) + i + 1) * d;
+      plan.row_tau[c] = plan.tau[i + 1];
+      if (c == 0 && plan.row_counts) atomicAdd((unsigned long long*)&plan.row_counts[0], (unsigned long long)gridDim.y);
+    }
+    if (plan.pack.in_bf) pack_temb(plan.pack, c, plan.tau[i + 1], threadIdx.x, blockDim.x);
+  }
+  if (blk >= (d + 3) >> 2) return;
+  const Key key = *key_p;
+  const bool vec = (d & 3) == 0;
+  float* row = traj + ((int64_t)c * (K + 1) + i) * d;
+  float4 y = load4(row, blk, d, vec);
+  const float4 g = load4(x0a + (int64_t)c * d, blk, d, vec);
+  const float cx = c_x[i], c0 = c_0[i], sg = sigma[i];
+  const float4 xi = normal4(key, (uint32_t)c, (uint32_t)(i + 1), (uint32_t)blk);
+  y.x = fmaf(sg, xi.x, fmaf(cx, y.x, c0 * g.x));
+  y.y = fmaf(sg, xi.y, fmaf(cx, y.y, c0 * g.y));
+  y.z = fmaf(sg, xi.z, fmaf(cx, y.z, c0 * g.z));
+  y.w = fmaf(sg, xi.w, fmaf(cx, y.w, c0 * g.w));
+  store4(row + d, blk, d, vec, y);
+  if (more && plan.pack.in_bf) pack_row4(plan.pack, c, blk, y);
 }
 
 asd_status launch_seq_step(asd_ctx* ctx, float* traj, int32_t step, hipStream_t st) {
-  (void)step;
   const int nblk = (ctx->d + 3) / 4;
   const int threads = nblk >= 256 ? 256 : (int)(ceil_div(nblk, 64) * 64);
   dim3 grid((unsigned)ceil_div(nblk, threads), (unsigned)ctx->B);
-  hipLaunchKernelGGL(draft_kernel<false>, grid, dim3(threads), 0, st, ctx->K, 1, ctx->d, ctx->key_dev, ctx->a, ctx->c_x,
-                     ctx->c_0, ctx->sigma, ctx->x0a, traj, (const int32_t*)nullptr, PlanOut(), 0, (const int32_t*)nullptr);
+  hipLaunchKernelGGL(seq_step_kernel, grid, dim3(threads), 0, st, ctx->K, ctx->d, step, ctx->key_dev, ctx->c_x, ctx->c_0,
+                     ctx->sigma, ctx->x0a, traj, plan_out(ctx, nullptr));
   ASD_HIP(hipGetLastError());
   return ASD_OK;
 }
@@ -485,6 +540,7 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
   __shared__ float s_part[kAcceptChunkMax][16][2];  // per slot of the chunk, per wavefront: partial <D,xi>, |D|^2
   __shared__ float s_rej[2];                     // <D,xi>, |D|^2 of the first rejected slot
   __shared__ int s_first;                        // index inside the chunk of the first rejection, 64 if none
+  __shared__ int s_row;                          // place of this chain's row in the next draft call's list
 
   const int c = blockIdx.x;
   const int tid = threadIdx.x;
@@ -626,7 +682,16 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
     }
   }
 
-  int a_next;
+  const int a_next = n_acc < w ? ac + n_acc + 1 : ac + w;
+  // whole window accepted, and the model value at yhat_b is there (see below)
+  const bool carried = carry && n_acc == w && a_next < K;
+  // this chain's row of the next round's draft call
+  [[maybe_unused]] const bool lists = FOLD && a_next < K && !carried;
+  [[maybe_unused]] int idx = 0;   // its place in the list (thread 0; asked for now, looked at behind the resampling)
+  if constexpr (FOLD) {
+    if (tid == 0 && lists) idx = atomicAdd(&plan.n_rows[0], 1);
+  }
+  float4 y_kept = make_float4(0.f, 0.f, 0.f, 0.f);   // the resampled row, where a thread holds one block of it
   if (n_acc < w) {
     const int k = n_acc;  // slot index of the first rejection (>= 1)
     const int i = ac + k;
@@ -644,15 +709,23 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
       y.z = fmaf(-(ga.z - gk.z), coef, y.z);
       y.w = fmaf(-(ga.w - gk.w), coef, y.w);
       store4(row, blk, d, vec, y);
+      y_kept = y;
     }
-    a_next = i + 1;
-  } else {
-    a_next = ac + w;
+  }
+  if constexpr (FOLD) {
+    if (plan.pack.in_bf && lists) {
+      if (tid == 0) s_row = idx;
+      __syncthreads();
+      const float* row = traj + ((int64_t)c * (K + 1) + a_next) * d;
+      const bool kept = n_acc < w && nblk <= nthreads;
+      for (int blk = tid; blk < nblk; blk += nthreads)   // (a thread reads back what it has written itself)
+        pack_row4(plan.pack, s_row, blk, kept ? y_kept : load4(row, blk, d, vec));
+      pack_temb(plan.pack, s_row, plan.tau[a_next], tid, nthreads);
+    }
   }
   // Model-call reuse: the whole window was accepted, so the next round starts at yhat_b, where the verify call
   // has already evaluated the model (slot w): that value becomes x0a and the chain skips the next draft call.
   // (Every read of x0a by this workgroup lies before the barrier that ended the last group of slots.)
-  const bool carried = carry && n_acc == w && a_next < K;
   if (carried) {
     const float* g_e = g_w + (int64_t)w * d;
     for (int blk = tid; blk < nblk; blk += nthreads) store4(x0a + (int64_t)c * d, blk, d, vec, load4(g_e, blk, d, vec));
@@ -674,8 +747,7 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
     }
     // the round index was advanced at the start of this round
     if (live && a_next < K) atomicAdd(&live[1 + ((live[0] - 1) % kLiveRing)], 1);
-    if constexpr (FOLD) if (a_next < K && !carried) {  // this chain's row of the next round's draft call
-      const int idx = atomicAdd(&plan.n_rows[0], 1);
+    if constexpr (FOLD) if (lists) {
       plan.in_off[idx] = ((int64_t)c * (K + 1) + a_next) * d;
       plan.out_off[idx] = (int64_t)c * d;
       plan.row_tau[idx] = plan.tau[a_next];
