@@ -614,42 +614,67 @@ __global__ __launch_bounds__(256) void gmm_rowmax_kernel(const int* __restrict__
   }
 }
 
+// (what this share is: the screening pass, below)
+constexpr float kScreenDense = 0.4f;
+
 // The same for a call of few rows (the draft call: one row per chain), where a workgroup per 128 rows would be eight
 // workgroups: one wavefront per row for the maxima and the one-hot components (no live groups: that call's second
-// GEMM does not skip slabs), then one small workgroup per row tile for the tile flags.
+// GEMM does not skip slabs); the tile flags are formed by gmm_onehot_kernel.
 __global__ __launch_bounds__(256) void gmm_rowmax_rows_kernel(const int* __restrict__ n_dev, int n_max, int np,
                                                               const float* __restrict__ pmax, float* __restrict__ rmax,
                                                               const float* __restrict__ logits, int64_t ldl,
                                                               int32_t* __restrict__ onehot,
                                                               const int32_t* __restrict__ chain,
                                                               int32_t* __restrict__ chain_comp,
-                                                              const uint8_t* __restrict__ cert_tile) {
+                                                              const uint8_t* __restrict__ cert_tile,
+                                                              int32_t* __restrict__ on,
+                                                              unsigned long long* __restrict__ acc) {
+  // (One launch for what were three -- the maxima, the verdict, the tile flags, now formed where gmm_onehot_kernel needs
+  // them; with the row scales in the certificate a draft call of 200 rows is three launches, 12 us of 123 a round, shorter.)
+  // on (or NULL): this round's screening verdict, from the share of column groups the call's rows keep alive (kScreenDense).
+  // acc: groups alive in the low word, workgroups that are done in the high one -- one addition carries both, so the last
+  // workgroup knows the total without a fence; it decides and clears.  (Rows of a certified tile have no logits and keep
+  // one group alive each.)
   // chain, chain_comp (or NULL): the component of a one-hot row (or -1) is also kept per chain, as the candidate of
   // the one-hot certificate (gmm_certify_kernel).  cert_tile (or NULL): row tiles it has certified in this call --
   // their rows have no logits, and their chains' candidates stand.
-  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= min(*n_dev, n_max)) return;
-  if (cert_tile && cert_tile[row / CombineOp::kRowmaxTile]) return;
-  const float* p = pmax + (int64_t)row * np;
-  float mx = -INFINITY;
-  for (int q = lane; q < np; q += 64) mx = fmaxf(mx, p[q]);
-  mx = wave_max(mx);
-  if (lane == 0) rmax[row] = mx;
-  if (onehot) {
-    const int b = onehot_component(p, np, mx, logits + (int64_t)row * ldl, ldl, lane);
-    if (lane == 0) {
-      onehot[row] = b;
-      if (chain && chain_comp) chain_comp[chain[row]] = b;
+  __shared__ int s_alive[4];
+  const int n = min(*n_dev, n_max);
+  if ((int)blockIdx.x * 4 >= n) return;   // (no rows at all: nothing is counted, the verdict stands)
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = blockIdx.x * 4 + wave;
+  int alive = 0;
+  if (row < n && cert_tile && cert_tile[row / CombineOp::kRowmaxTile]) {
+    alive = 1;
+  } else if (row < n) {
+    const float* p = pmax + (int64_t)row * np;
+    float mx = -INFINITY;
+    for (int q = lane; q < np; q += 64) mx = fmaxf(mx, p[q]);
+    mx = wave_max(mx);
+    if (lane == 0) rmax[row] = mx;
+    if (on) {
+      float c = 0.f;
+      for (int q = lane; q < np; q += 64) c += p[q] >= mx - CombineOp::kZeroGap ? 1.f : 0.f;
+      alive = (int)wave_sum(c);
+    }
+    if (onehot) {
+      const int b = onehot_component(p, np, mx, logits + (int64_t)row * ldl, ldl, lane);
+      if (lane == 0) {
+        onehot[row] = b;
+        if (chain && chain_comp) chain_comp[chain[row]] = b;
+      }
     }
   }
-}
-__global__ __launch_bounds__(CombineOp::kRowmaxTile) void gmm_onehot_tiles_kernel(const int* __restrict__ n_dev, int n_max,
-                                                                                 const int32_t* __restrict__ onehot,
-                                                                                 uint8_t* __restrict__ onehot_tile) {
-  const int n = min(*n_dev, n_max), m = blockIdx.x * CombineOp::kRowmaxTile + threadIdx.x;
-  if (blockIdx.x * CombineOp::kRowmaxTile >= n) return;
-  const int bad = __syncthreads_or(m < n && onehot[m] < 0);
-  if (threadIdx.x == 0) onehot_tile[blockIdx.x] = bad ? 0 : 1;
+  if (!on) return;
+  if (lane == 0) s_alive[wave] = alive;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned add = (unsigned)(s_alive[0] + s_alive[1] + s_alive[2] + s_alive[3]);
+    const unsigned long long tot = atomicAdd(acc, (1ull << 32) | add) + ((1ull << 32) | add);
+    if ((int)(tot >> 32) == (n + 3) / 4) {
+      on[0] = (float)(uint32_t)tot < kScreenDense * (float)n * (float)np ? 1 : 0;
+      *acc = 0ull;
+    }
+  }
 }
 
 // The rows of the one-hot tiles, in closed form (see gmm_rowmax_kernel): kOnehotRows rows per workgroup, four of them
@@ -659,7 +684,7 @@ constexpr int kOnehotRows = 8;
 static_assert(CombineOp::kRowmaxTile % kOnehotRows == 0, "a workgroup's rows lie in one row tile");
 __global__ __launch_bounds__(256) void gmm_onehot_kernel(const int* __restrict__ n_dev, int n_max, int d,
                                                          const int32_t* __restrict__ onehot,
-                                                         const uint8_t* __restrict__ onehot_tile,
+                                                         uint8_t* __restrict__ onehot_tile, int form_tile,
                                                          const float* __restrict__ means,
                                                          const float* __restrict__ in_base,
                                                          const int64_t* __restrict__ in_off,
@@ -671,8 +696,16 @@ __global__ __launch_bounds__(256) void gmm_onehot_kernel(const int* __restrict__
   // cert_tile (or NULL): one-hot row tiles whose rows gmm_certify_kernel has written already
   const int n = min(*n_dev, n_max), m0 = blockIdx.x * kOnehotRows;
   if (m0 >= n) return;
+  // form_tile: the tile flags are formed here (the draft call; every workgroup of a tile looks at its 128 rows)
   const int tile = m0 / CombineOp::kRowmaxTile;
-  if (!onehot_tile[tile]) return;
+  if (form_tile) {
+    const int m = tile * CombineOp::kRowmaxTile + (int)threadIdx.x;
+    const int bad = __syncthreads_or((int)threadIdx.x < CombineOp::kRowmaxTile && m < n && onehot[m] < 0);
+    if (m0 % CombineOp::kRowmaxTile == 0 && threadIdx.x == 0) onehot_tile[tile] = bad ? 0 : 1;
+    if (bad) return;
+  } else if (!onehot_tile[tile]) {
+    return;
+  }
   if (cert_tile && cert_tile[tile]) return;
   constexpr int U = 4;
   for (int r0 = 0; r0 < kOnehotRows && m0 + r0 < n; r0 += U) {
@@ -795,8 +828,10 @@ __global__ __launch_bounds__(256) void gmm_certify_kernel(const int* __restrict_
                                                           int32_t* __restrict__ onehot,
                                                           uint8_t* __restrict__ onehot_tile,
                                                           uint8_t* __restrict__ cert_tile,
-                                                          int32_t* __restrict__ tile_cnt,
+                                                          int32_t* __restrict__ tile_cnt, float* __restrict__ a_scale,
                                                           unsigned long long* __restrict__ counts) {
+  // a_scale (or NULL): also what gmm_row_scale_kernel leaves for every row -- the draft call, where both pass over the same
+  // few rows, a wavefront each, and a launch costs more than the pass
   static_assert(kCertTile % 4 == 0, "whole workgroups per row tile");
   __shared__ int s_pass[4];
   const int n = min(*n_dev, n_max), m0 = blockIdx.x * 4;
@@ -814,16 +849,28 @@ __global__ __launch_bounds__(256) void gmm_certify_kernel(const int* __restrict_
       am = a_min[b];
       if (!cert_worth_reading(cf, am, d)) b = -1;
     }
-    if (b >= 0) {
+    float4 xv[V];
+    if (b >= 0 || a_scale) {
       const float4* x = reinterpret_cast<const float4*>(in_base + in_off[m]);
+#pragma unroll
+      for (int i = 0; i < V; ++i) xv[i] = lane + 64 * i < d / 4 ? x[lane + 64 * i] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if (a_scale) {
+      float mx = 0.f;
+#pragma unroll
+      for (int i = 0; i < V; ++i)
+        mx = fmaxf(fmaxf(mx, fmaxf(fabsf(xv[i].x), fabsf(xv[i].y))), fmaxf(fabsf(xv[i].z), fabsf(xv[i].w)));
+      mx = wave_max(mx);
+      if (lane == 0) a_scale[m] = fp16_scale(mx);
+    }
+    if (b >= 0) {
       const float4* mu = reinterpret_cast<const float4*>(means + (int64_t)b * d);
-      float4 xv[V], mv[V];
+      float4 mv[V];
       float p = 0.f, xx = 0.f;
 #pragma unroll
       for (int i = 0; i < V; ++i) {
         const int j = lane + 64 * i;
         const bool in = j < d / 4;
-        xv[i] = in ? x[j] : make_float4(0.f, 0.f, 0.f, 0.f);
         mv[i] = in ? mu[j] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
       const float qb = musq[b], bias_b = LogitOp::kLog2e * log_w[b];
@@ -916,7 +963,6 @@ constexpr int kScreenWgs = 256;         // resident workgroups of the screening 
 constexpr int kResidentWgs = 512;       // workgroups of the list form of the exact GEMM: two per CU
 // screen when the draft rows keep less than this share of their groups alive (timed at workload 5, where an unscreened
 // call runs on the tall tiles: 0.25, 0.4, 0.6, 0.85 give 55.0, 54.4, 54.7, 55.8 ms per sample)
-constexpr float kScreenDense = 0.4f;
 
 __device__ __forceinline__ int quant8(float v, float inv_s) { return max(-127, min(127, (int)rintf(v * inv_s))); }
 
@@ -1150,45 +1196,6 @@ __global__ __launch_bounds__(256) void gmm_screen_decide_kernel(const int* __res
     if (threadIdx.x == 0) {
       atomicAdd(&counts[1], (unsigned long long)(2 * ntn));
       if (screened) atomicAdd(&counts[4], (unsigned long long)(2 * ntn));
-    }
-  }
-}
-
-// After the draft call's logits: the share of column groups its rows keep alive -> on[0].  One wavefront per row;
-// acc[0] collects the count, acc[1] the workgroups that are done: the last one decides and clears both.
-constexpr int kRegimeBlocks = 64;
-__global__ __launch_bounds__(256) void gmm_regime_kernel(const int* __restrict__ n_dev, int n_max, int np,
-                                                         const float* __restrict__ pmax, int32_t* __restrict__ on,
-                                                         int32_t* __restrict__ acc,
-                                                         const uint8_t* __restrict__ cert_tile) {
-  // cert_tile (or NULL): row tiles certified one-hot; their rows have no logits and keep one group alive each
-  const int n = min(*n_dev, n_max);
-  if (n <= 0) return;   // every workgroup alike: nothing is counted, the verdict stands
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float alive = 0.f;
-  for (int m = blockIdx.x * 4 + wave; m < n; m += 4 * gridDim.x) {
-    if (cert_tile && cert_tile[m / kCertTile]) {
-      alive += 1.f;
-      continue;
-    }
-    const float* p = pmax + (int64_t)m * np;
-    float mx = -INFINITY;
-    for (int q = lane; q < np; q += 64) mx = fmaxf(mx, p[q]);
-    mx = wave_max(mx) - CombineOp::kZeroGap;
-    float c = 0.f;
-    for (int q = lane; q < np; q += 64) c += p[q] >= mx ? 1.f : 0.f;
-    alive += wave_sum(c);
-  }
-  if (lane == 0 && alive > 0.f) atomicAdd(&acc[0], (int32_t)alive);
-  __syncthreads();   // the four additions above come before this workgroup's ticket
-  if (threadIdx.x == 0) {
-    __threadfence();
-    if (atomicAdd(&acc[1], 1) == (int32_t)gridDim.x - 1) {
-      __threadfence();
-      const int32_t tot = atomicAdd(&acc[0], 0);
-      on[0] = (float)tot < kScreenDense * (float)n * (float)np ? 1 : 0;
-      acc[0] = 0;
-      acc[1] = 0;
     }
   }
 }
@@ -1551,7 +1558,8 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
     hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(n, 4)), dim3(256), 0, st, rows.n_dev, n, d, C, rows.in_base,
                        rows.in_off, rows.out_base, rows.out_off, rows.tau, g->coef_tau, rows.chain, g->chain_comp,
                        g->means22, g->musq, g->log_w, g->cert_amin, g->cert_glob, g->cert_globw, g->onehot, g->onehot_tile,
-                       g->cert_tile, g->cert_cnt, (prof_counting(ctx) && rows.call == 1) ? g->work_counts : nullptr);
+                       g->cert_tile, g->cert_cnt, rows.call == 0 && g->two_ok ? g->a_scale : (float*)nullptr,
+                       (prof_counting(ctx) && rows.call == 1) ? g->work_counts : nullptr);
     ASD_HIP(hipGetLastError());
     op1.skip_tile = cert_tile;
   }
@@ -1580,8 +1588,8 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
   const bool two = split && g->two_ok;   // fp16 terms (both calls), else three bf16 terms (verify call only)
   {
     ProfScope ps(ctx, ASD_PROF_GMM_LOGITS, rows.call, st);
-    if (two) {   // every row has its scale first: from the screening pass's quantiser, else from a kernel of its own
-      if (!screen) {
+    if (two) {   // every row has its scale first: from the screening pass's quantiser, the draft call's certificate, else a kernel of its own
+      if (!screen && !(cert && rows.call == 0)) {
         hipLaunchKernelGGL(gmm_row_scale_kernel, dim3((unsigned)ceil_div(n, 4)), dim3(256), 0, st, rows.n_dev, n, d,
                            rows.in_base, rows.in_off, g->a_scale, cert_tile);
         ASD_HIP(hipGetLastError());
@@ -1607,11 +1615,6 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
                         : launch_gemm_f32_nt<GmmTileSkinny, 0>(rows.n_dev, n, C, d, X, g->means, d, op1, st));
     }
   }
-  if (rows.call == 0 && g->screen_ok && g->screen_mode == 1) {   // this round's verify call: screen or not
-    hipLaunchKernelGGL(gmm_regime_kernel, dim3(kRegimeBlocks), dim3(256), 0, st, rows.n_dev, n, np, g->pmax,
-                       g->screen_on, g->screen_on + 2, cert_tile);
-    ASD_HIP(hipGetLastError());
-  }
   RowSrc P{g->logits, nullptr, C};
   // columns behind one partial row maximum: the first GEMM's wavefront sub-tile width (the last group may be short)
   const int gcols = split ? GmmTileSplit::WN : (rows.call ? GmmTile::WN : GmmTileSkinny::WN);
@@ -1623,6 +1626,7 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
     ProfScope ps(ctx, ASD_PROF_GMM_SOFTMAX, rows.call, st);
     // one-hot rows in closed form: with the sparse second GEMM only (the same switch), whole float4 rows
     const bool onehot = g->sparse_combine && d % 4 == 0 && np <= 64 && gcols == 64;
+    const bool verdict = rows.call == 0 && g->screen_ok && g->screen_mode == 1;   // this round's verify call: screen or not
     if (rows.call == 1) {
       hipLaunchKernelGGL(gmm_rowmax_kernel, dim3((unsigned)ceil_div(n, CombineOp::kRowmaxTile)), dim3(256),
                          sizeof(int) * (np + 1), st, rows.n_dev, n, np, g->pmax, g->rmax, g->glive, g->logits, (int64_t)C,
@@ -1631,15 +1635,13 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
     } else {
       hipLaunchKernelGGL(gmm_rowmax_rows_kernel, dim3((unsigned)ceil_div(n, 4)), dim3(256), 0, st, rows.n_dev, n, np,
                          g->pmax, g->rmax, g->logits, (int64_t)C, onehot ? g->onehot : (int32_t*)nullptr, rows.chain,
-                         (onehot && g->cert_ok) ? g->chain_comp : (int32_t*)nullptr, cert_tile);
-      if (onehot)
-        hipLaunchKernelGGL(gmm_onehot_tiles_kernel, dim3((unsigned)ceil_div(n, CombineOp::kRowmaxTile)),
-                           dim3(CombineOp::kRowmaxTile), 0, st, rows.n_dev, n, g->onehot, g->onehot_tile);
+                         (onehot && g->cert_ok) ? g->chain_comp : (int32_t*)nullptr, cert_tile,
+                         verdict ? g->screen_on : (int32_t*)nullptr, reinterpret_cast<unsigned long long*>(g->screen_on + 2));
     }
     ASD_HIP(hipGetLastError());
     if (onehot) {
       hipLaunchKernelGGL(gmm_onehot_kernel, dim3((unsigned)ceil_div(n, kOnehotRows)), dim3(256), 0, st, rows.n_dev, n, d, g->onehot,
-                         g->onehot_tile, two ? g->means22 : g->means, rows.in_base, rows.in_off, rows.out_base,
+                         g->onehot_tile, rows.call == 0 ? 1 : 0, two ? g->means22 : g->means, rows.in_base, rows.in_off, rows.out_base,
                          rows.out_off, g->coef_tau, rows.tau, cert_tile);
       ASD_HIP(hipGetLastError());
       op2.onehot_tile = g->onehot_tile;
