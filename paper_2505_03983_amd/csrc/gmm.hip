@@ -50,6 +50,9 @@ namespace asd {
 // verify call: tens of thousands of rows.  Measured on workload 5 (share of the fp32 MFMA peak, logits /
 // combine GEMM): 128x128x16 74 / 76%, 128x128x32 71 / 71%, 256x128x16 60 / 56%, 256x128x32 61 / 42%.
 typedef GemmCfg<128, 128, 16> GmmTile;
+// ... and smaller ones with the same slabs (and, per element, the same sums) where those leave CUs idle: f32_tile_fill.
+typedef GemmCfg<64, 128, 16> GmmTileHalf;
+typedef GemmCfg<64, 64, 16> GmmTileQuarter;
 typedef GemmCfg<64, 64, 32> GmmTileSkinny;                    // draft call: one row per chain, fill the chip
 // verify call on the bf16 matrix pipe with three-way split operands (fp32 accuracy; shapes that are multiples of 16 only)
 typedef Split3Cfg<128, 128, 2, 2> GmmTileSplit;
@@ -67,6 +70,17 @@ static_assert(Split2BigCfg::WN == GmmTile2::WN && Split2BigCfg::BM % 128 == 0, "
 static_assert(GmmTile2::BN == GmmTileSplit::BN && GmmTile2::WGN == GmmTileSplit::WGN && GmmTile2::BM == GmmTileSplit::BM &&
               GmmTile2::B_STAGE == GmmTile2Skinny::B_STAGE && GmmTile2::BK == GmmTile2Skinny::BK,
               "the tilings lay rows, row maxima and images out alike");
+
+// Share of the CUs' time that 128 x 128 tiles of n x N results keep busy (two workgroups share a CU's matrix pipes, so
+// whole tiles per CU are what counts).  The smaller tiles run at about 0.86 of their rate, and fill any chip that calls
+// of this size see.  Measured, microseconds a call, 128 x 128 throughout / second product on 64 x 64: 5000 rows, d 1000,
+// C 4000 (320 tiles, 0.63 filled) 930 / 806; 9000, 500, 1000 (0.55) 305 / 242; 16000, 300, 2000 (0.73) 524 / 456; 8192,
+// 1000, 4000 (1.0) 1143 / 1224.  First product on 64 x 128: 5000 rows, d 1000, C 1000 (0.63) 348 / 299; 9000, 500, 1000
+// (0.74) 305 / 302; 5000, 1000, 4000 (1.0) 930 / 934.
+static double f32_tile_fill(int n, int N) {
+  const int64_t tiles = ceil_div(n, GmmTile::BM) * ceil_div(N, GmmTile::BN);
+  return (double)tiles / (256.0 * (double)ceil_div(tiles, 256));
+}
 
 // (kappa, gamma, cx, cm) of a row
 __device__ __forceinline__ float4 row_coef(const float4* coef_tau, const int32_t* tau, int n) {
@@ -1535,6 +1549,8 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
                        : 2 * (int)ceil_div(C, rows.call ? GmmTile::BN : GmmTileSkinny::BN);
   // K split of the draft call's second GEMM (few output tiles, long K); both of its tilings use slabs of 32
   static_assert(GmmTileSplitSkinny::BK == GmmTileSkinny::BK, "one split plan for both");
+  static_assert(GmmTileHalf::BN == GmmTile::BN && GmmTileHalf::BK == GmmTile::BK && GmmTileQuarter::BK == GmmTile::BK,
+                "the tilings lay the row maxima out alike and add in the same order");
   const int splits = (!rows.call && g->draft_splits > 1 && n <= ctx->B) ? g->draft_splits : 1;
   RowSrc X{rows.in_base, rows.in_off, 0};
   LogitOp op1{g->logits, C, g->pmax, np, g->coef_tau, rows.tau, g->musq, g->log_w};
@@ -1611,7 +1627,9 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
     } else if (split) {
       ASD_HIP(launch_gemm_split3_nt<GmmTileSplit, 1, false>(rows.n_dev, n, C, d, X, g->means_img, op1, st));
     } else {
-      ASD_HIP(rows.call ? launch_gemm_f32_nt<GmmTile, 1>(rows.n_dev, n, C, d, X, g->means, d, op1, st)
+      ASD_HIP(rows.call ? (f32_tile_fill(n, C) < 0.75
+                               ? launch_gemm_f32_nt<GmmTileHalf, 1>(rows.n_dev, n, C, d, X, g->means, d, op1, st)
+                               : launch_gemm_f32_nt<GmmTile, 1>(rows.n_dev, n, C, d, X, g->means, d, op1, st))
                         : launch_gemm_f32_nt<GmmTileSkinny, 0>(rows.n_dev, n, C, d, X, g->means, d, op1, st));
     }
   }
@@ -1670,7 +1688,9 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
       ASD_HIP(launch_gemm_split3_nt<GmmTileSplit, 1, true>(rows.n_dev, n, d, C, P, g->means_t_img, op2, st, 1, nullptr,
                                                            g->sparse_combine));
     else
-      ASD_HIP(rows.call ? launch_gemm_f32_nt<GmmTile, 1>(rows.n_dev, n, d, C, P, g->means_t, C, op2, st)
+      ASD_HIP(rows.call ? (f32_tile_fill(n, d) < 0.86
+                               ? launch_gemm_f32_nt<GmmTileQuarter, 1>(rows.n_dev, n, d, C, P, g->means_t, C, op2, st)
+                               : launch_gemm_f32_nt<GmmTile, 1>(rows.n_dev, n, d, C, P, g->means_t, C, op2, st))
                         : launch_gemm_f32_nt<GmmTileSkinny, 0>(rows.n_dev, n, d, C, P, g->means_t, C, op2, st, splits,
                                                                 g->part));
     if (splits > 1) {

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def _denoise(cfg, n, seed=3):
+def _denoise(cfg, n, seed=3, keep=None):
     T, p, model = oracle_setup(cfg)
     rng = np.random.default_rng(seed)
     if cfg["kind"] == "gmm":     # unequal weights
@@ -23,10 +23,14 @@ def _denoise(cfg, n, seed=3):
     ab = T["abar"][tau]
     x0 = p["means"][rng.integers(0, cfg["C"], n)] + 0.5 * rng.standard_normal((n, cfg["d"]))
     x = (np.sqrt(ab)[:, None] * x0 + np.sqrt(1 - ab)[:, None] * rng.standard_normal((n, cfg["d"]))).astype(np.float32)
+    if keep is not None:         # a call of the first rows only
+        n, x, tau = keep, x[:keep], tau[:keep]
     out = torch.full((n, cfg["d"]), float("nan"), dtype=torch.float32, device=DEV)
     ctx.denoise(torch.from_numpy(x).to(DEV), torch.from_numpy(tau).to(DEV), out)
     torch.cuda.synchronize()
     ctx.close()
+    if keep is not None:
+        return out.cpu().numpy(), None
     return out.cpu().numpy(), model(cfg["K"] - tau, x.astype(np.float64))
 
 
@@ -51,6 +55,22 @@ def test_mixture_calls_on_the_tiled_kernels(d, C, n):
     256-wide tiles, C ending inside one (same bound)."""
     got, want = _denoise(dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25), n)
     assert H.rel_err(got, want) <= 3e-5
+
+
+@pytest.mark.parametrize("d, C, n", [
+    (1000, 4000, 1001),     # 256 tiles of the first product, 64 of the second (64 x 64 instead)
+    (500, 1000, 9000),      # both products on smaller tiles, none full at the edges; 8127 of the rows: neither
+    (512, 2052, 8100),      # neither
+])
+def test_fp32_tiles_do_not_depend_on_their_size(d, C, n):
+    """Calls of the fp32 kernels on either side of the rule that picks smaller tiles, and parts of them, which go to others:
+    the sums of an element are the same in every tile, so shared rows are equal bit for bit; against the oracle as above."""
+    got, want = _denoise(dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25), n)
+    assert H.rel_err(got, want) <= 3e-5
+    m = n - 70 - (n - 70) * 9 // 100
+    if m * C * d >= 4e9:
+        part, _ = _denoise(dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25), n, keep=m)
+        assert np.array_equal(part, got[:m])
 
 
 @pytest.mark.parametrize("terms", [1, 2])
