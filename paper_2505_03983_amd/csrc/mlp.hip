@@ -197,7 +197,8 @@ __global__ void mlp_pack_kernel(const int* __restrict__ n_dev, int n_rows, int d
   if (in_plane) *reinterpret_cast<uint4*>(dst + in_plane) = l;
 }
 
-// The caller's weights [rows, K] (row-major bf16) in slab layout: eight elements per thread, zeros in the padding
+// The caller's weights [rows, K] (row-major bf16) in slab layout: eight elements per thread, zeros in the padding.  (K is a
+// multiple of 8; the array itself may start at any element of a larger one.)
 __global__ __launch_bounds__(256) void mlp_pack_weights_kernel(int rows, int K, int64_t rows_pad, int nslabs,
                                                                const uint16_t* __restrict__ w, uint16_t* __restrict__ out) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;   // chunk: slab, row, quarter
@@ -205,7 +206,17 @@ __global__ __launch_bounds__(256) void mlp_pack_weights_kernel(int rows, int K, 
   const int64_t row = (t >> 2) % rows_pad;
   const int k = (int)((t >> 2) / rows_pad) * 32 + (int)(t & 3) * 8;
   uint4 v = make_uint4(0u, 0u, 0u, 0u);
-  if (row < rows && k < K) v = *reinterpret_cast<const uint4*>(w + row * K + k);   // (K is a multiple of 8)
+  if (row < rows && k < K) {
+    const uint16_t* p = w + row * K + k;
+    if (((uintptr_t)w & 15) == 0) {
+      v = *reinterpret_cast<const uint4*>(p);
+    } else {
+      v.x = p[0] | (uint32_t)p[1] << 16;
+      v.y = p[2] | (uint32_t)p[3] << 16;
+      v.z = p[4] | (uint32_t)p[5] << 16;
+      v.w = p[6] | (uint32_t)p[7] << 16;
+    }
+  }
   *reinterpret_cast<uint4*>(out + t * 8) = v;
 }
 

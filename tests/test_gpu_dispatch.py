@@ -167,3 +167,27 @@ def test_mlp_draft_call_of_few_rows_with_a_large_matrix(terms, width, chains):
     ctx.close()
     assert torch.isfinite(want).all()
     assert H.rel_err(x0hat[:, 0].cpu().numpy(), want.cpu().numpy()) <= (2e-2 if terms == 1 else 1e-5)
+
+
+def test_mlp_weights_may_start_anywhere():
+    """Weight matrices that are parts of a larger array, at an odd element: the same bits as from arrays of their own."""
+    from paper_2505_03983_amd import binding
+    cfg = dict(kind="mlp", d=24, E=8, width=72, n_blocks=2, K=20, L=4, act_terms=2)
+    T, p, _ = oracle_setup(cfg)
+    x = torch.randn(37, 24, generator=torch.Generator(device=DEV).manual_seed(3), device=DEV)
+    tau = torch.full((37,), 9, dtype=torch.int32, device=DEV)
+    outs = []
+    for shift in (0, 1):
+        den = runtime.device_params(cfg, p)
+        den["n_tau"] = cfg["K"] + 1
+        for k in ("w_in", "w_blk", "w_out"):
+            flat = torch.zeros(den[k].numel() + 8, dtype=den[k].dtype, device=DEV)
+            flat[shift:shift + den[k].numel()] = den[k].flatten()
+            den[k] = flat[shift:shift + den[k].numel()].view(den[k].shape)
+        ctx = binding.Ctx(binding.asd_schedule_ddpm_linear(cfg["K"]), den, cfg["L"], 10)
+        out = torch.zeros_like(x)
+        ctx.denoise(x, tau, out)
+        torch.cuda.synchronize()
+        ctx.close()
+        outs.append(out)
+    assert bool(torch.isfinite(outs[0]).all()) and torch.equal(outs[0], outs[1])
