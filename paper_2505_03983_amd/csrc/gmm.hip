@@ -1362,7 +1362,7 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
       ASD_HIP(hipMalloc(&g->tile_count, kTicketInts * sizeof(int32_t)));
       ASD_HIP(hipMemset(g->tile_count, 0, kTicketInts * sizeof(int32_t)));
       ASD_HIP(hipMalloc(&g->screen_on, 4 * sizeof(int32_t)));
-      const int32_t on[4] = {1, 1, 0, 0};   // verdict, the constant 1, the regime kernel's two accumulators
+      const int32_t on[4] = {1, 1, 0, 0};   // verdict, the constant 1, the verdict's accumulator (one 64-bit word, zero between calls)
       ASD_HIP(hipMemcpy(g->screen_on, on, sizeof(on), hipMemcpyHostToDevice));
       hipLaunchKernelGGL(gmm_screen_quant_means_kernel, dim3((unsigned)g->nps), dim3(256), 0, 0, C, d, g->means, g->musq,
                          g->log_w, g->means_q, g->means_grp);

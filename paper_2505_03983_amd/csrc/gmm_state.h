@@ -67,7 +67,7 @@ struct GmmState {
   uint32_t* tile_list = nullptr;   // [8][list_cap] tiles of logits to compute, by column tile modulo 8
   int32_t* tile_count = nullptr;   // the lists' lengths and the tickets drawn from each (layout: gemm_split3.h)
   int list_cap = 0;
-  int32_t* screen_on = nullptr;    // DEV [4]: the draft call's verdict for this round; the constant 1; two accumulators
+  int32_t* screen_on = nullptr;    // DEV [4]: the draft call's verdict for this round; the constant 1; its accumulator (64 bits)
   // One-hot certificate (gmm.hip): rows proven one-hot from the distance of a mean to its nearest neighbour and the
   // component the chain's last draft-call row sat on, written in closed form at once; row tiles of such rows skip the
   // rest of the call.
