@@ -20,6 +20,11 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Barrier of a workgroup whose LDS stages are refilled by direct loads: this wavefront's reads of LDS are over (its data is
+// in registers) before it says so.  (A bare s_barrier doesn't wait for them, and the compiler moves the products that would
+// have to behind it; __syncthreads() would also wait for the loads in flight.)
+__device__ __forceinline__ void lds_handover() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Scheduling hints for an MFMA loop.
 // `pairs` times {one MFMA, then `per` instructions of class `mask`}
 template <int MASK, int PAIRS, int PER>

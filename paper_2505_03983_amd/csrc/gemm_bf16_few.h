@@ -107,9 +107,7 @@ __global__ __launch_bounds__(64 * Cfg::NW) void gemm_bf16_few_kernel(const int* 
   constexpr int H = PL, U = 4 / PL;   // instructions per slab; slabs per batch of fragment reads
   for (int st = 0; st < nst; ++st) {
     wait_stages<LPW, STAGES - 1>(min(nst - 1 - st, STAGES - 1));
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    lds_handover();
     if (fin) {
       const uint8_t* sb = ldsb + (st % STAGES) * (Cfg::STAGE_BLOCKS * 1024);
       const int ns = min(SS, nslabs - st * SS);   // even
@@ -154,9 +152,7 @@ __global__ __launch_bounds__(64 * Cfg::NW) void gemm_bf16_few_kernel(const int* 
       }
     }
     if (st + STAGES < nst) {   // the stage's memory is refilled once nobody reads it
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
+      lds_handover();
       issue(st + STAGES);
     }
   }

@@ -182,12 +182,12 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_bf16_slab_kernel(const int*
     if (STAGES - 1 < nk) issue(STAGES - 1, ldsb + (STAGES - 1) * Cfg::STAGE_BYTES, 0, LPS);
     auto hand_over = [&](int behind) {   // stage after `behind` stages still in flight has landed, for every wavefront
       wait_stages<LPS, STAGES - 1>(behind);
-      if constexpr (NW > 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      if constexpr (NW > 1) lds_handover();
       else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     };
     auto hand_over_steady = [&]() {
       wait_vmcnt<LPS * (STAGES - 2)>();
-      if constexpr (NW > 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      if constexpr (NW > 1) lds_handover();
       else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     };
     auto read_stage = [&](const uint8_t* sb, int buf) {
@@ -234,17 +234,15 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_bf16_slab_kernel(const int*
   //              (two behind each of the first MFMAs) and its share of the direct loads of stage
   //              kt+STAGES-1 (one behind each following MFMA; that stage's memory was released by the
   //              barrier of the previous iteration) slotted in.
-  //              Half-way through the last group the wavefront waits for its loads of stage kt+1, meets
-  //              the others at the barrier (after which nobody reads stage kt's memory again: the last
-  //              group's fragments are already in registers) and reads the first fragments of stage kt+1
-  //              -- while the rest of the group executes.
+  //              Half-way through the last group the wavefront waits for its loads of stage kt+1 and for its
+  //              own reads of stage kt, meets the others at the barrier (after which nobody reads stage kt's
+  //              memory again) and reads the first fragments of stage kt+1 -- while the rest of the group
+  //              executes.
   constexpr int H1 = (G + 1) / 2, H2 = G - H1;       // MFMAs of the last group before / after the hand-over
   constexpr int RD = AI + NJ, SLOTS = (RD + 1) / 2, RLAST = RD - 2 * (SLOTS - 1);
   constexpr int REM = G > SLOTS ? G - SLOTS : 0;     // MFMAs of a group left after the read slots
   wait_stages<LPS, STAGES - 2>(nk - 1);   // stage 0 landed; the other prologue stages may be in flight
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+  lds_handover();
   read_frags(ldsb, 0, 0);
 
   int cur = 0, nst = STAGES - 1;          // LDS stages of kt and of kt + STAGES - 1
@@ -280,10 +278,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_bf16_slab_kernel(const int*
       // This wavefront's loads of stage kt+1 must have landed; those of the stages behind it may stay in flight.
       if (more) wait_vmcnt<LPS * (STAGES - 2)>();
       else wait_stages<LPS, STAGES - 2>(nk - 2 - kt);
-      // A bare barrier: __syncthreads() would add a fence that waits for *all* outstanding loads.
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
+      lds_handover();
       read_frags(ldsb + cur * Cfg::STAGE_BYTES, 0, 0);
     }
     mma((NG - 1) & 1, H1, H2);
@@ -297,7 +292,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_bf16_slab_kernel(const int*
   // Epilogue through LDS (the pipeline stages are free now): each wavefront parks its WM x WN fp32
   // sub-tile in its own LDS region, then walks it row by row with 16-byte accesses, so global traffic
   // is row-contiguous and the code is a short loop rather than 16*MI*NJ unrolled scalar stores.
-  __builtin_amdgcn_s_barrier();  // every wavefront is done reading the last stage
+  lds_handover();  // every wavefront is done reading the last stage
   float* stage = reinterpret_cast<float*>(ldsb) + wave * (WM * WN);
 #pragma unroll
   for (int i = 0; i < MI; ++i)

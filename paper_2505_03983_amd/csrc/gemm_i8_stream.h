@@ -189,9 +189,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_i8_colmax_stream_kernel(int
   };
 
   wait_vmcnt_slabs<LPS, 0>(min(STAGES - 2, F - 1));   // slab 0 landed
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+  lds_handover();
   read_frags(ldsb, 0, 0);
 
   int kt_c = 0, ti_c = 0;   // of the slab being multiplied: its index within its tile, the tile's number
@@ -219,9 +217,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_i8_colmax_stream_kernel(int
       // this wavefront's loads of slab f+1 must have landed; younger ones may stay in flight
       if (more) wait_vmcnt_slabs<LPS, LPS - LA>(STAGES - 3);
       else wait_vmcnt_slabs<LPS, 0>(F - 2 - f);
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();   // after it nobody reads slab f's stage again: the last group's fragments are in registers
-      asm volatile("" ::: "memory");
+      lds_handover();   // after it nobody reads slab f's stage again
       read_frags(ldsb + ((f + 1) % STAGES) * STAGE_BYTES, 0, 0);
     }
     if (more) issue(kt_n, nst, Cfg::loads_before_group(3) + LB, LA);
