@@ -1417,10 +1417,11 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
       }
     }
   }
-  if (!g->use_mfma) {
+  if (!g->use_mfma && (int64_t)C * d > kRowwiseMixture) {   // what gmm_few.h's kernels need (the row-wise one needs nothing)
     g->np = (int)ceil_div(C, 64);
-    ASD_HIP(hipMalloc(&g->logits, sizeof(float) * (size_t)ctx->n_rows_max * cp));
-    ASD_HIP(hipMalloc(&g->pmax, sizeof(float) * (size_t)ctx->n_rows_max * g->np));
+    g->few_rows = few_scratch_rows(ctx->n_rows_max, C);
+    ASD_HIP(hipMalloc(&g->logits, sizeof(float) * (size_t)g->few_rows * cp));
+    ASD_HIP(hipMalloc(&g->pmax, sizeof(float) * (size_t)g->few_rows * g->np));
   }
   if (g->use_mfma) {
     g->np = 2 * (int)ceil_div(C, GmmTileSkinny::BN);  // room for the finest of the tilings
@@ -1436,6 +1437,7 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
     }
     if (g->draft_splits > 1)
       ASD_HIP(hipMalloc(&g->part, sizeof(float) * gemm_f32_splitk_floats(g->draft_splits, ctx->B, d)));
+    g->few_rows = (int)ctx->n_rows_max;
     ASD_HIP(hipMalloc(&g->logits, sizeof(float) * (size_t)ctx->n_rows_max * C));
     ASD_HIP(hipMalloc(&g->pmax, sizeof(float) * (size_t)ctx->n_rows_max * g->np));
   }
@@ -1536,9 +1538,9 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
   // pass from call to call there.
   if (!g->use_mfma || (!g->screen_ok && macs < (g->split_ok ? 1.5e9 : 4e9))) {
     ProfScope ps(ctx, ASD_PROF_GMM_ROWWISE, rows.call, st);
-    ASD_HIP(launch_gmm_few(FewArgs{rows.n_dev, n, d, C, (d + 3) & ~3, (C + 3) & ~3, rows.in_base, rows.in_off, rows.out_base,
-                                   rows.out_off, rows.tau, g->coef_tau, g->means_p ? g->means_p : g->means, g->means_t,
-                                   g->musq, g->log_w, g->logits, g->pmax, 0}, st));
+    ASD_HIP(launch_gmm_few(FewArgs{rows.n_dev, 0, n, d, C, (d + 3) & ~3, (C + 3) & ~3, rows.in_base, rows.in_off,
+                                   rows.out_base, rows.out_off, rows.tau, g->coef_tau, g->means_p ? g->means_p : g->means,
+                                   g->means_t, g->musq, g->log_w, g->logits, g->pmax, 0}, g->few_rows, st));
     return ASD_OK;
   }
   // partial row maxima per row: one per wavefront column of the tiling in use

@@ -21,8 +21,9 @@ namespace asd {
 typedef float v4f_m __attribute__((ext_vector_type(4)));   // accumulator of v_mfma_f32_16x16x4_f32
 
 struct FewArgs {
-  const int32_t* n_dev;
-  int n_max, d, C, dp, cp;      // dp, cp: d and C rounded up to 4, the pitches of means_p and of means_t and logits
+  const int32_t* n_dev;         // rows of the whole call
+  int base, n_max;              // this launch's first row of them, and how many it takes at most; the row pointers start there
+  int d, C, dp, cp;             // dp, cp: d and C rounded up to 4, the pitches of means_p and of means_t and logits
   const float* in_base;
   const int64_t* in_off;
   float* out_base;
@@ -33,8 +34,8 @@ struct FewArgs {
   const float* means_t;         // [d][cp], zero-padded
   const float* musq;
   const float* log_w;
-  float* logits;                // [rows][cp], base-2 units; -inf behind C
-  float* pmax;                  // [rows][np]
+  float* logits;                // [n_max][cp], base-2 units; -inf behind C
+  float* pmax;                  // [n_max][np]
   int np;
 };
 
@@ -58,7 +59,7 @@ struct FewTile {
 template <class T, int KS, bool VX>
 __global__ __launch_bounds__(256 * KS) void gmm_few_logits_kernel(FewArgs p) {
   constexpr int MI = T::MI, NJ = T::NJ;
-  const int n = min(*p.n_dev, p.n_max);
+  const int n = min(*p.n_dev - p.base, p.n_max);
   const int row0 = blockIdx.x * T::ROWS;
   if (row0 >= n) return;
   const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(256 * KS) void gmm_few_logits_kernel(FewArgs p) {
 template <class T, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void gmm_few_combine_kernel(FewArgs p) {
   constexpr int MI = T::MI, NJ = T::NJ;
-  const int n = min(*p.n_dev, p.n_max);
+  const int n = min(*p.n_dev - p.base, p.n_max);
   const int row0 = blockIdx.x * T::ROWS;
   if (row0 >= n) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, g = lane >> 4;
@@ -253,26 +254,41 @@ inline void launch_few_combine(const FewArgs& p, hipStream_t st) {
   hipLaunchKernelGGL((gmm_few_combine_kernel<T, WAVES>), grid, dim3(64 * WAVES), lds, st, p);
 }
 
+// Rows whose logits the scratch holds at a time: 256 MB of them.  A call of more rows goes through it in parts, each of which
+// leaves the chip half idle at its end (d 2, C 1000, 60000 rows: 162 us in one part, 230 in four).
+inline int few_scratch_rows(int64_t rows, int C) {
+  const int64_t cap = ((int64_t)256 << 20) / ((int64_t)sizeof(float) * (((C + 3) & ~3) + (C + 63) / 64));
+  return (int)(rows < cap ? rows : cap / 32 * 32 > 32 ? cap / 32 * 32 : 32);
+}
+
 // Tile: 32 x 32 per wavefront (twice the products per byte) once that still gives every CU a workgroup -- d 128, C 1024:
 // 1000 rows 25 us against 32 with 16 x 16, 200 rows 27 against 16 -- else 16 x 16.  Wavefronts that share a k loop: as
-// many as leave each about four steps of 16 k.
-inline hipError_t launch_gmm_few(FewArgs p, hipStream_t st) {
+// many as leave each about four steps of 16 k.  (The rows of the whole call decide: all its parts add in one order.)
+// scratch_rows: rows that logits and pmax have room for.
+inline hipError_t launch_gmm_few(FewArgs p, int scratch_rows, hipStream_t st) {
   typedef FewTile<1, 1, 4> Small;
   typedef FewTile<2, 2, 2> Large;
-  const int64_t row_tiles = (p.n_max + Large::ROWS - 1) / Large::ROWS;
-  if (row_tiles * ((p.C + Large::GROUP - 1) / Large::GROUP) >= 256) {
-    p.np = (p.C + Large::GROUP - 1) / Large::GROUP;
-    launch_few_logits<Large, 1>(p, st);
-    if (p.C <= 1024) launch_few_combine<Large, 4>(p, st);
-    else launch_few_combine<Large, 8>(p, st);
-  } else {
-    p.np = (p.C + Small::GROUP - 1) / Small::GROUP;
-    if (p.d > 256) launch_few_logits<Small, 4>(p, st);
-    else if (p.d > 96) launch_few_logits<Small, 2>(p, st);
-    else launch_few_logits<Small, 1>(p, st);
-    if (p.C <= 128) launch_few_combine<Small, 4>(p, st);
-    else if (p.C <= 512) launch_few_combine<Small, 8>(p, st);
-    else launch_few_combine<Small, 16>(p, st);
+  const int rows = p.n_max;
+  const int64_t row_tiles = (rows + Large::ROWS - 1) / Large::ROWS;
+  const bool large = row_tiles * ((p.C + Large::GROUP - 1) / Large::GROUP) >= 256;
+  p.np = large ? (p.C + Large::GROUP - 1) / Large::GROUP : (p.C + Small::GROUP - 1) / Small::GROUP;
+  for (p.base = 0; p.base < rows; p.base += scratch_rows) {
+    p.n_max = rows - p.base < scratch_rows ? rows - p.base : scratch_rows;
+    if (large) {
+      launch_few_logits<Large, 1>(p, st);
+      if (p.C <= 1024) launch_few_combine<Large, 4>(p, st);
+      else launch_few_combine<Large, 8>(p, st);
+    } else {
+      if (p.d > 256) launch_few_logits<Small, 4>(p, st);
+      else if (p.d > 96) launch_few_logits<Small, 2>(p, st);
+      else launch_few_logits<Small, 1>(p, st);
+      if (p.C <= 128) launch_few_combine<Small, 4>(p, st);
+      else if (p.C <= 512) launch_few_combine<Small, 8>(p, st);
+      else launch_few_combine<Small, 16>(p, st);
+    }
+    p.in_off += scratch_rows;
+    p.out_off += scratch_rows;
+    p.tau += scratch_rows;
   }
   return hipGetLastError();
 }

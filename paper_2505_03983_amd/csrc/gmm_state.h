@@ -15,8 +15,9 @@ struct GmmState {
   float* means_p = nullptr;      // [C, d rounded up to 4] zero-padded copy; NULL when d % 4 == 0
   float* musq = nullptr;         // [C]
   float4* coef_tau = nullptr;    // [n_tau]: (kappa, gamma, cx, cm)
-  float* logits = nullptr;       // [rows_max, C] (C rounded up to 4 where only gmm_few.h's kernels use it)
-  float* pmax = nullptr;         // [rows_max, np] partial row maxima of the logits
+  float* logits = nullptr;       // [few_rows, C] (C rounded up to 4 where only gmm_few.h's kernels use it)
+  float* pmax = nullptr;         // [few_rows, np] partial row maxima of the logits
+  int few_rows = 0;              // rows these hold: rows_max with the tiled kernels, else few_scratch_rows (gmm_few.h)
   int np = 0;
   float* rmax = nullptr;         // [rows_max] row maxima of the verify call's logits (split-operand path)
   uint8_t* glive = nullptr;      // [row tiles][np] column groups that are live for a row of the tile

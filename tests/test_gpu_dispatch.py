@@ -48,6 +48,31 @@ def test_mixture_calls_of_few_rows(d, C, n):
     assert H.rel_err(got, want) <= 3e-5
 
 
+def test_mixture_calls_larger_than_their_scratch():
+    """66048 rows of logits fit the scratch of this mixture: two whole parts and 76 rows.  Same bound as above; a call of
+    fewer rows on the same tiles gives the same bits."""
+    cfg = dict(kind="gmm", d=3, C=999, K=50, L=16, var=0.25)
+    n = 2 * 66048 + 76
+    got, want = _denoise(cfg, n)
+    assert H.rel_err(got, want) <= 3e-5
+    part, _ = _denoise(cfg, n, keep=67000)
+    assert np.array_equal(part, got[:67000])
+
+
+@pytest.mark.parametrize("d, C", [(1, 256), (1, 300)])     # the row-wise kernel; the kernels for few rows
+def test_mixture_scratch_is_bounded(d, C):
+    """A context of a million rows takes some tens of bytes a row and at most 256 MiB of logits (a gigabyte if every row
+    had its own)."""
+    cfg = dict(kind="gmm", d=d, C=C, K=4, L=64, var=0.25)
+    T, p, _ = oracle_setup(cfg)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    ctx = runtime.open_ctx(cfg, p, chains=16384)
+    taken = free - torch.cuda.mem_get_info()[0]
+    ctx.close()
+    assert taken <= 64 * 16384 * 64 + (384 << 20), taken
+
+
 @pytest.mark.parametrize("d, C, n", [(96, 1056, 15000), (80, 1040, 19000), (500, 1000, 8100),
                                      (96, 1056, 16400), (160, 640, 16400)])
 def test_mixture_calls_on_the_tiled_kernels(d, C, n):
