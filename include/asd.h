@@ -86,6 +86,7 @@ typedef enum { ASD_DEN_GMM = 1, ASD_DEN_MLP = 2 } asd_den_kind;
  *   Eq. sl-defn; the schedule is then the Euler chain of Eq. euler-sde
  *   (c_x = 1, c_0 = eta_i, sigma = sqrt(eta_i)).  Exactly one of abar and
  *   sl_time is given.
+ *   d + C above 4096: d and C must be multiples of 4 (ASD_EUNSUPPORTED).
  * MLP: in = [bf16(x) ; temb[tau]] (d + temb_dim), h = W_in in + b_in,
  *   n_blocks times h += SiLU(W_l bf16(h) + b_l), out = W_out bf16(h) + b_out,
  *   D = clamp(out, -out_clip, out_clip) if out_clip > 0 (the usual clipping of

@@ -76,6 +76,8 @@ static asd_status validate(const asd_config* cfg) {
         if (!(tt >= 0.f) || !isfinite(tt)) return fail(ASD_EINVAL, "sl_time[%d] must be finite and >= 0", t);
       }
     }
+    if ((m.d % 4 || m.C % 4) && (int64_t)m.d + m.C > 4096)
+      return fail(ASD_EUNSUPPORTED, "GMM denoiser: C=%d, d=%d needs d %% 4 == 0 and C %% 4 == 0 at this size", m.C, m.d);
   } else if (m.kind == ASD_DEN_MLP) {
     if (m.width < 1 || m.n_blocks < 0 || m.temb_dim < 0) return fail(ASD_EINVAL, "bad MLP shape");
     if (!m.w_in || !m.w_out || (m.n_blocks > 0 && !m.w_blk) || (m.temb_dim > 0 && !m.temb))

@@ -7,6 +7,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import schedule
 from paper_2505_03983_amd import binding, probe
@@ -122,6 +123,21 @@ def test_init_rejects_bad_configs_on_the_host(over, status):
     with pytest.raises(binding.AsdError) as ei:
         binding.Ctx(s, den, kw["L"], kw["chains"])
     assert ei.value.status == status
+
+
+def test_mixture_shape_rule():
+    """d + C above 4096: both multiples of 4."""
+    def status(d, C):
+        s, den, kw = _cfg(d=d, C=C)
+        with pytest.raises(binding.AsdError) as ei:
+            binding.Ctx(s, den, kw["L"], kw["chains"])
+        return ei.value.status
+
+    for d, C in ((95, 4002), (96, 4001), (4093, 4), (4096, 1), (1501, 3003), (2**31 - 1, 2**31 - 1)):
+        assert status(d, C) == binding.ASD_EUNSUPPORTED, (d, C)
+    if not torch.cuda.is_available():      # (the parameters of these are no addresses)
+        for d, C in ((95, 4001), (4095, 1), (96, 4004), (4096, 4096)):
+            assert status(d, C) == binding.ASD_EDEVICE, (d, C)
 
 
 def test_mlp_shape_rules():
