@@ -9,9 +9,10 @@
 //   D       = (sqrt(ab) s2 / V) x + (1 - ab s2 / V) sum_k r_k mu_k
 // i.e. single-head attention with keys = values = the component means.
 //
-// Three paths:
-//  * row-wise kernel (one wavefront per row) for mixtures of a few numbers,
-//    where a launch is all there is;
+// Four paths:
+//  * two row-wise kernels (one wavefront per row; one of them keeps the mixture
+//    in LDS) for mixtures of a few numbers, where a launch is all there is, and
+//    for many rows against a few components;
 //  * fp32 matrix cores straight from global memory (gmm_few.h) for small calls
 //    and odd shapes;
 //  * tiled matrix-core path for large aligned problems: logits = X M^T (MFMA GEMM
@@ -170,7 +171,6 @@ __global__ __launch_bounds__(256) void gmm_row_scale_kernel(const int* __restric
 // row-wise path: 4 wavefronts per workgroup, one row per wavefront per pass
 // LDS per wavefront: x[d] then p[C]
 // ---------------------------------------------------------------------------
-constexpr int kRowwiseMixture = 256;   // largest C d of the mixtures it serves (gmm_eval)
 constexpr float kZeroGapNat = kCertZeroGap * 0.6931471805599453f;   // the zero gap in the natural-log units of these kernels
 __global__ __launch_bounds__(256) void gmm_rowwise_kernel(const int* __restrict__ n_dev, int nrows_max, int d, int C, const float* __restrict__ in_base,
                                                           const int64_t* __restrict__ in_off,
@@ -232,6 +232,99 @@ __global__ __launch_bounds__(256) void gmm_rowwise_kernel(const int* __restrict_
       }
     }
     __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// row-wise path with the mixture in LDS (d % 4 == 0 and C*(d+4) floats fit): the workgroup copies
+// the means (rows padded by 4 floats, so that 16 lanes reading the same 16-byte column of 16
+// different rows hit 16 different bank groups), |mu|^2 and log w into LDS, then each wavefront
+// serves rows from it.  No cross-lane traffic inside the loops:
+//   pass 1: lane = component: <x, mu_k> over d from LDS (x is a broadcast read),
+//   pass 2: softmax over the C logits (two wavefront reductions),
+//   pass 3: lane = coordinate: sum_k p_k mu_k[j] (p is a broadcast read).
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void gmm_rowwise_lds_kernel(const int* __restrict__ n_dev, int nrows_max, int d,
+                                                              int C, int rows_per_wave,
+                                                              const float* __restrict__ in_base,
+                                                              const int64_t* __restrict__ in_off,
+                                                              float* __restrict__ out_base,
+                                                              const int64_t* __restrict__ out_off,
+                                                              const int32_t* __restrict__ tau,
+                                                              const float4* __restrict__ coef_tau,
+                                                              const float* __restrict__ means,
+                                                              const float* __restrict__ musq,
+                                                              const float* __restrict__ log_w) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int d4 = d >> 2, dp = d + 4, C4 = (C + 3) & ~3;
+  const int nrows = min(*n_dev, nrows_max);
+  if (blockIdx.x * 4 * rows_per_wave >= nrows) return;
+  float* m_l = lds;                          // [C][dp]
+  float* q_l = m_l + (size_t)C * dp;         // [C]
+  float* lw_l = q_l + C4;                    // [C]
+  float* ps = lw_l + C4 + (size_t)wave * C4; // [4][C4] logits, then softmax weights
+  float* xs = lw_l + C4 + 4 * (size_t)C4 + (size_t)wave * d;  // [4][d]
+  {
+    const float4* Mg = reinterpret_cast<const float4*>(means);
+    for (int t = threadIdx.x; t < C * d4; t += 256) {
+      const int k = t / d4, c = t - k * d4;
+      *reinterpret_cast<float4*>(&m_l[k * dp + 4 * c]) = Mg[t];
+    }
+    for (int t = threadIdx.x; t < C; t += 256) {
+      q_l[t] = musq[t];
+      lw_l[t] = log_w[t];
+    }
+  }
+  __syncthreads();
+  for (int it = 0; it < rows_per_wave; ++it) {
+    const int n = (blockIdx.x * rows_per_wave + it) * 4 + wave;
+    if (n >= nrows) break;  // uniform per wavefront; no workgroup barrier below
+    const float4 cf = coef_tau[tau[n]];
+    const float* x = in_base + in_off[n];
+    for (int j = lane; j < d; j += 64) xs[j] = x[j];
+    // (LDS operations of one wavefront complete in order: xs is visible to all its lanes below)
+    float mx = -INFINITY;
+    for (int k = lane; k < C; k += 64) {
+      const float* mk = m_l + k * dp;
+      float dot = 0.f;
+#pragma unroll 4
+      for (int c = 0; c < d4; ++c) {
+        const float4 xv = *reinterpret_cast<const float4*>(&xs[4 * c]);
+        const float4 mv = *reinterpret_cast<const float4*>(&mk[4 * c]);
+        dot = fmaf(xv.x, mv.x, fmaf(xv.y, mv.y, fmaf(xv.z, mv.z, fmaf(xv.w, mv.w, dot))));
+      }
+      const float lg = fmaf(cf.x, dot, fmaf(-cf.y, q_l[k], lw_l[k]));
+      ps[k] = lg;
+      mx = fmaxf(mx, lg);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    float sum = 0.f;
+    for (int k = lane; k < C4; k += 64) {
+      const float p = (k < C && !(ps[k] - mx < -kZeroGapNat)) ? expf(ps[k] - mx) : 0.f;
+      ps[k] = p;
+      sum += p;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    const float sc = cf.w / sum;
+    float* out = out_base + out_off[n];
+    for (int j = lane; j < d; j += 64) {
+      float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+      const float* mj = m_l + j;
+#pragma unroll 2
+      for (int k = 0; k < C4; k += 4) {
+        const float4 p = *reinterpret_cast<const float4*>(&ps[k]);
+        // rows past C do not exist: their weights are 0 and the reads are clamped to the last row
+        a0 = fmaf(p.x, mj[min(k + 0, C - 1) * dp], a0);
+        a1 = fmaf(p.y, mj[min(k + 1, C - 1) * dp], a1);
+        a2 = fmaf(p.z, mj[min(k + 2, C - 1) * dp], a2);
+        a3 = fmaf(p.w, mj[min(k + 3, C - 1) * dp], a3);
+      }
+      out[j] = fmaf(cf.z, xs[j], sc * ((a0 + a1) + (a2 + a3)));
+    }
   }
 }
 
@@ -1247,6 +1340,66 @@ __global__ __launch_bounds__(256) void combine_finish_kernel(const int* __restri
 // ---------------------------------------------------------------------------
 // host
 // ---------------------------------------------------------------------------
+// LDS of gmm_rowwise_lds_kernel, 0 for mixtures it does not take.
+static size_t lds_rowwise_bytes(int d, int C) {
+  const size_t C4 = ((size_t)C + 3) & ~(size_t)3;
+  const size_t bytes = sizeof(float) * ((size_t)C * (d + 4) + 2 * C4 + 4 * C4 + 4 * (size_t)d);
+  return d % 4 == 0 && bytes <= 150 * 1024 ? bytes : 0;
+}
+
+// Which calls go to the row-wise kernels.  Measured, microseconds a call in a graph, LDS / global memory / the two launches of
+// gmm_few.h, (d, C):
+//   1024 rows: (4, 16) 6.4 / 6.8 / 9.4, (3, 80) - / 10.7 / 9.7 (and a launch more for the host), (64, 64) 7.8 / - / 10.1, (64, 128)
+//     9.9 / - / 10.2, (512, 16) 13.8 / - / 15.6, (1000, 8) 20.4 / - / 22.4; 256 rows of (1000, 8) 20.9 / - / 17.7; 442 of (4, 1392)
+//     45 / - / 19;
+//   4096 rows: (4, 16) 11.1 / 7.5 / 9.6, (7, 5) - / 7.1 / 10.5, (64, 4) 11.8 / 10.9 / 10.2, (128, 2) 14.7 / 15.9 / 11.9, (1, 256)
+//     - / 22.8 / 14.9;
+//   16384 rows: (2, 2) - / 11.0 / 14.3, (4, 16) 12.6 / 13.7 / 14.1, (2, 64) - / 19.2 / 15.8, (64, 16) 16.7 / 45 / 17.3, (256, 16)
+//     38.0 / - / 38.7, (512, 16) 85 / - / 68, (1000, 8) 140 / - / 118;
+//   60000 rows: (4, 16) 27.1 / 40 / 27.2, (64, 4) 34.5 / 81 / 44.1, (128, 16) 61 / - / 72, (128, 60) 111 / - / 84, (1000, 8) 444 / - /
+//     545, (2000, 4) 1102 / - / 1048;
+//   262144 rows: (16, 16) 101 / 264 / 83, (64, 16) 135 / 655 / 142.
+// Contexts that have the tiled kernels (tiled) weigh those against gmm_few.h from there on: few_rows_pays.
+// A wavefront per row is one launch, but walks C and d by itself; the LDS form also pays for its copy of the mixture, by
+// workgroup, and gmm_few.h for 32 components and a pass over the logits however few there are.
+enum RowwiseKernel { kRowwiseNone, kRowwiseGlobal, kRowwiseLds };
+static RowwiseKernel pick_rowwise(int n, int d, int C, bool tiled) {
+  const int64_t size = (int64_t)C * d;
+  const bool lds = lds_rowwise_bytes(d, C) > 0;
+  if (lds && n <= 1024 && size <= 10240 && C <= 128 && (d <= 512 || n > 512)) return kRowwiseLds;
+  if (size <= 256 && C <= (n <= 1024 ? 96 : 64) && d <= 64 && n <= (size <= 64 && !lds ? 32768 : 16383)) return kRowwiseGlobal;
+  if (!tiled && lds && n >= 8192 && C <= 16 && size <= (n >= 32768 ? 8000 : 4096) && (d >= 64 || n < 131072)) return kRowwiseLds;
+  return kRowwiseNone;
+}
+
+// Whether a call is faster through gmm_few.h than through the tiled kernels.  Both are two products, one over d and one
+// over C, and a sum of tiles times what a tile costs; what differs is how they fail to fill the chip.  The tiles of the tiled
+// kernels are large, so few rows leave CUs idle and the time is that of a tile however few there are; those of gmm_few.h
+// fill it with any call, at a lower rate, and pad C to 128 and d to 32.  Neither the rows nor the products alone tell which:
+// with 4e9 products, 3200 rows of (300, 4000) take 287 / 480 us this way / tiled, 650000 of (300, 20) 2011 / 1202, and of the
+// draft calls on fp16 terms 705 rows of (1568, 960) 156 / 55.
+// The figures (microseconds; d and C stand for the lengths of the two sums) are fitted to 880 calls of d 4..2048, C 4..4096,
+// 16..1.2 million rows and 7e7..9e9 products, whose times they give to 9% (gmm_few.h) and 12% (tiled) rms; the faster form
+// is taken but for a few calls in a hundred, at most 1.4 times slower.
+struct TiledCost {
+  int bm, bn, slots;      // tile; how many the chip runs in the time of one
+  double launch, d1, o1, c2, o2;
+};
+constexpr TiledCost kTiledF32 = {128, 128, 256, 0., .078, 6.5, .055, 7.8}, kTiledBf16 = {128, 128, 256, 36., .0365, 7.3, .048, 11.5},
+                    kTiledFp16 = {128, 128, 256, 34., .0151, 13.8, .0259, 18.3}, kDraftF32 = {64, 64, 512, 0., .0395, 3.3, .0438, 8.5},
+                    kDraftFp16 = {64, 128, 256, 2., .0109, 6.3, .003, 9.9};
+static bool few_rows_pays(const TiledCost& k, int splits, int64_t n, int64_t d, int64_t C) {
+  const bool large = few_large_tiles(n, (int)C);
+  const int b = large ? 32 : 16, group = large ? 128 : 64;
+  const double f1 = (double)(ceil_div(n, b) * ceil_div(C, group)) / 256., f2 = (double)(ceil_div(n, b) * ceil_div(d, b)) / 256.;
+  const double few = large ? 5. + .0127 * d + .0057 * C + (.0241 * d + 1.06) * f1 + (.009 * C + 1.06) * f2
+                           : .0085 * d + .0031 * C + .49 * f1 + (.0066 * C + .49) * f2;
+  const double r1 = (double)(ceil_div(n, k.bm) * ceil_div(C, k.bn)) / k.slots;
+  const double r2 = (double)(ceil_div(n, k.bm) * ceil_div(d, k.bn) * splits) / k.slots;
+  const double tiled = k.launch + (k.d1 * d + k.o1) * std::max(1., r1) + (k.c2 * C / splits + k.o2) * std::max(1., r2);
+  return few < tiled;
+}
+
 asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
   GmmState* g = new (std::nothrow) GmmState();
   if (!g) return ASD_ENOMEM;
@@ -1417,7 +1570,9 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
       }
     }
   }
-  if (!g->use_mfma && (int64_t)C * d > kRowwiseMixture) {   // what gmm_few.h's kernels need (the row-wise one needs nothing)
+  if (lds_rowwise_bytes(d, C) > 0)
+    ASD_HIP(hipFuncSetAttribute((const void*)gmm_rowwise_lds_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+  if (!g->use_mfma) {   // what gmm_few.h's kernels need
     g->np = (int)ceil_div(C, 64);
     g->few_rows = few_scratch_rows(ctx->n_rows_max, C);
     ASD_HIP(hipMalloc(&g->logits, sizeof(float) * (size_t)g->few_rows * cp));
@@ -1518,25 +1673,33 @@ void gmm_destroy(asd_ctx* ctx) {
 asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
   GmmState* g = ctx->gmm;
   const int d = ctx->d, C = g->C, n = rows.n;
-  const double macs = (double)n * C * d;
-  // A mixture of a few numbers: one launch, a row per wavefront (7 x 5, 500 rows: 6.2 us, the kernels below 8.5; at
-  // 8 x 16 and 4096 rows 11.5 against 9.6, and a wavefront's serial walk over C grows from there).
-  if ((int64_t)C * d <= kRowwiseMixture) {
+  const RowwiseKernel small = pick_rowwise(n, d, C, g->use_mfma);
+  if (small == kRowwiseLds) {
     ProfScope ps(ctx, ASD_PROF_GMM_ROWWISE, rows.call, st);
-    const int blocks = (int)std::min<int64_t>(ceil_div(n, 4), 65536);
-    hipLaunchKernelGGL(gmm_rowwise_kernel, dim3(blocks), dim3(256), g->rowwise_lds, st, rows.n_dev, n, d, C, rows.in_base,
-                       rows.in_off, rows.out_base, rows.out_off, rows.tau, g->coef_tau, g->means, g->musq,
+    // one row per wavefront while that still gives fewer workgroups than CUs, else four
+    const int rpw = n > 4 * 256 ? 4 : 1;
+    hipLaunchKernelGGL(gmm_rowwise_lds_kernel, dim3((unsigned)ceil_div(n, 4 * rpw)), dim3(256), lds_rowwise_bytes(d, C), st,
+                       rows.n_dev, n, d, C, rpw, rows.in_base, rows.in_off, rows.out_base, rows.out_off, rows.tau,
+                       g->coef_tau, g->means, g->musq, g->log_w);
+    ASD_HIP(hipGetLastError());
+    return ASD_OK;
+  }
+  if (small == kRowwiseGlobal) {
+    ProfScope ps(ctx, ASD_PROF_GMM_ROWWISE, rows.call, st);
+    hipLaunchKernelGGL(gmm_rowwise_kernel, dim3((unsigned)ceil_div(n, 4)), dim3(256), g->rowwise_lds, st, rows.n_dev, n, d, C,
+                       rows.in_base, rows.in_off, rows.out_base, rows.out_off, rows.tau, g->coef_tau, g->means, g->musq,
                        g->log_w);
     ASD_HIP(hipGetLastError());
     return ASD_OK;
   }
-  // Calls small enough that the tiled kernels below do not fill the chip (or that they do not take at all).  Measured,
-  // n rows, microseconds per call, these / the split-operand kernels: d = C = 512, n = 1024 35 / 118, n = 4096 83 / 130,
-  // n = 8192 (2.1e9 products) 146 / 140; d 96, C 4096, n 4096 (1.6e9) 145 / 195; against the fp32 tiles: d 100, C 1000,
-  // n 950 24 / 154; d 1000, C 4000, n 1000 (4e9) 240 / 485, n = 2000 532 / 525; d 500, C 1000, n 10000 (5e9) 332 / 303.
-  // A screened context keeps its own kernels at every size: the draft call's verdict and the certificate's candidates
-  // pass from call to call there.
-  if (!g->use_mfma || (!g->screen_ok && macs < (g->split_ok ? 1.5e9 : 4e9))) {
+  const bool split = g->use_split && (rows.call == 1 || g->split_draft_ok);
+  // K split of the draft call's second GEMM (few output tiles, long K); both of its tilings use slabs of 32
+  static_assert(GmmTileSplitSkinny::BK == GmmTileSkinny::BK, "one split plan for both");
+  const int splits = (!rows.call && g->draft_splits > 1 && n <= ctx->B) ? g->draft_splits : 1;
+  // (A screened context keeps its own kernels at every size: the draft call's verdict and the certificate's candidates
+  // pass from call to call there.)
+  const TiledCost& tiled = rows.call ? (!split ? kTiledF32 : g->two_ok ? kTiledFp16 : kTiledBf16) : (split ? kDraftFp16 : kDraftF32);
+  if (!g->use_mfma || (!g->screen_ok && few_rows_pays(tiled, splits, n, d, C))) {
     ProfScope ps(ctx, ASD_PROF_GMM_ROWWISE, rows.call, st);
     ASD_HIP(launch_gmm_few(FewArgs{rows.n_dev, 0, n, d, C, (d + 3) & ~3, (C + 3) & ~3, rows.in_base, rows.in_off,
                                    rows.out_base, rows.out_off, rows.tau, g->coef_tau, g->means_p ? g->means_p : g->means,
@@ -1544,16 +1707,12 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
     return ASD_OK;
   }
   // partial row maxima per row: one per wavefront column of the tiling in use
-  const bool split = g->use_split && (rows.call == 1 || g->split_draft_ok);
   static_assert(GmmTileSplit::BN == GmmTileSplitSkinny::BN && GmmTileSplit::WGN == GmmTileSplitSkinny::WGN,
                 "the two split tilings lay the row maxima out alike");
   const int np = split ? GmmTileSplit::WGN * (int)ceil_div(C, GmmTileSplit::BN)
                        : 2 * (int)ceil_div(C, rows.call ? GmmTile::BN : GmmTileSkinny::BN);
-  // K split of the draft call's second GEMM (few output tiles, long K); both of its tilings use slabs of 32
-  static_assert(GmmTileSplitSkinny::BK == GmmTileSkinny::BK, "one split plan for both");
   static_assert(GmmTileHalf::BN == GmmTile::BN && GmmTileHalf::BK == GmmTile::BK && GmmTileQuarter::BK == GmmTile::BK,
                 "the tilings lay the row maxima out alike and add in the same order");
-  const int splits = (!rows.call && g->draft_splits > 1 && n <= ctx->B) ? g->draft_splits : 1;
   RowSrc X{rows.in_base, rows.in_off, 0};
   LogitOp op1{g->logits, C, g->pmax, np, g->coef_tau, rows.tau, g->musq, g->log_w};
   // the verify call of the split path may be screened; only when the second GEMM skips what the first leaves out

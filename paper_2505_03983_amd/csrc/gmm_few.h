@@ -264,13 +264,17 @@ inline int few_scratch_rows(int64_t rows, int C) {
 // Tile: 32 x 32 per wavefront (twice the products per byte) once that still gives every CU a workgroup -- d 128, C 1024:
 // 1000 rows 25 us against 32 with 16 x 16, 200 rows 27 against 16 -- else 16 x 16.  Wavefronts that share a k loop: as
 // many as leave each about four steps of 16 k.  (The rows of the whole call decide: all its parts add in one order.)
+typedef FewTile<1, 1, 4> FewSmall;
+typedef FewTile<2, 2, 2> FewLarge;
+inline bool few_large_tiles(int64_t rows, int C) {
+  return (rows + FewLarge::ROWS - 1) / FewLarge::ROWS * ((C + FewLarge::GROUP - 1) / FewLarge::GROUP) >= 256;
+}
 // scratch_rows: rows that logits and pmax have room for.
 inline hipError_t launch_gmm_few(FewArgs p, int scratch_rows, hipStream_t st) {
-  typedef FewTile<1, 1, 4> Small;
-  typedef FewTile<2, 2, 2> Large;
+  typedef FewSmall Small;
+  typedef FewLarge Large;
   const int rows = p.n_max;
-  const int64_t row_tiles = (rows + Large::ROWS - 1) / Large::ROWS;
-  const bool large = row_tiles * ((p.C + Large::GROUP - 1) / Large::GROUP) >= 256;
+  const bool large = few_large_tiles(rows, p.C);
   p.np = large ? (p.C + Large::GROUP - 1) / Large::GROUP : (p.C + Small::GROUP - 1) / Small::GROUP;
   for (p.base = 0; p.base < rows; p.base += scratch_rows) {
     p.n_max = rows - p.base < scratch_rows ? rows - p.base : scratch_rows;

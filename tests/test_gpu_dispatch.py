@@ -35,8 +35,11 @@ def _denoise(cfg, n, seed=3, keep=None):
 
 
 @pytest.mark.parametrize("d, C, n", [
-    (1, 1, 1), (2, 128, 5), (16, 16, 17),                 # the row-wise kernel, up to C d = 256
-    (1, 257, 1), (257, 1, 3), (15, 18, 15), (17, 16, 16), # just past it: one partial tile in every direction
+    (1, 1, 1), (2, 64, 5), (15, 17, 1030), (64, 4, 16383),      # the row-wise kernel
+    (4, 1, 1), (16, 16, 17), (4, 150, 77), (512, 16, 1024),     # the one with the mixture in LDS: a row per wavefront
+    (16, 16, 16384), (256, 16, 8195), (1000, 8, 32771),         # four rows per wavefront, the last ones missing
+    (8, 32, 16384), (516, 4, 1000), (4, 16, 131072),            # just past them
+    (1, 257, 1), (257, 1, 3), (15, 18, 15), (17, 16, 16),       # one partial tile in every direction
     (100, 64, 33), (97, 65, 16), (256, 1024, 1), (260, 1028, 47), (301, 1003, 40),   # k shared by 1, 2, 4 wavefronts
     (5, 33, 8200), (64, 1024, 1025), (130, 1027, 993),    # 32 x 32 tiles: last row, column and k step partial
     (2000, 3000, 9),                                      # a mixture that no LDS holds, neither size a tile's multiple
