@@ -687,9 +687,12 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
   const bool carried = carry && n_acc == w && a_next < K;
   // this chain's row of the next round's draft call
   [[maybe_unused]] const bool lists = FOLD && a_next < K && !carried;
-  [[maybe_unused]] int idx = 0;   // its place in the list (thread 0; asked for now, looked at behind the resampling)
+  // its place in the list (thread 0).  A row that is packed needs it behind the resampling, so it is asked for now; else
+  // last: all chains add to one word, and thousands of them that end together queue there while holding their CU (2048
+  // chains, d 64, L 4: accept 72 us asked for here, 65 below).
+  [[maybe_unused]] int idx = 0;
   if constexpr (FOLD) {
-    if (tid == 0 && lists) idx = atomicAdd(&plan.n_rows[0], 1);
+    if (tid == 0 && lists && plan.pack.in_bf) idx = atomicAdd(&plan.n_rows[0], 1);
   }
   float4 y_kept = make_float4(0.f, 0.f, 0.f, 0.f);   // the resampled row, where a thread holds one block of it
   if (n_acc < w) {
@@ -748,6 +751,7 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
     // the round index was advanced at the start of this round
     if (live && a_next < K) atomicAdd(&live[1 + ((live[0] - 1) % kLiveRing)], 1);
     if constexpr (FOLD) if (lists) {
+      if (!plan.pack.in_bf) idx = atomicAdd(&plan.n_rows[0], 1);
       plan.in_off[idx] = ((int64_t)c * (K + 1) + a_next) * d;
       plan.out_off[idx] = (int64_t)c * d;
       plan.row_tau[idx] = plan.tau[a_next];
