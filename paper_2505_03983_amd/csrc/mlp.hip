@@ -32,25 +32,32 @@ struct MlpTiles {
   typedef SlabCfg<64, 64, 2, PL == 2 ? 6 : 8, 2, 2, PL, true> T64x64;
   typedef SlabCfg<32, 64, 2, PL == 2 ? 6 : 8, 1, 2, PL, true> T32x64;
 };
-// Which one: the least ceil(tiles / CUs) x time of a tile, a tile taking f + k per 64 of K (a workgroup has its CU to
-// itself; microseconds, fitted to K = 1024 and 4096 with two planes, 960 and 1536 with one, from a single tile to eight
-// rounds of them).  Measured, two planes, 4096 x 4096 weights (start: 128 x 128 throughout, 160 us at 1984 rows and 63 at
-// 456): 1984 rows 128 / 148 / 157 / - / -, 456 rows 79 / 55 / 39 / 56 / -, 200 rows - / 51 / 38 / 28 / 42; 1024 x 1024:
-// 3840 rows 32 / 27 / 31 / - / -, 960 rows 26 / 18 / 12 / 11 / 16, 120 rows - / 17 / 13 / 9 / 8.
+// Which one: the least rounds x time of a tile, a tile taking f + k per 64 of K (a workgroup has its CU to itself;
+// microseconds, fitted to K = 1024 and 4096 with two planes, 960 and 1536 with one, from a single tile to eight rounds of
+// them).  rounds is ceil(tiles / CUs) up to two; past that the CUs no longer finish together, and a started round costs
+// less than a whole one.  Measured, two planes, 4096 x 4096 weights (128 x 128 tiles throughout, before the slab layout: 160 us
+// at 1984 rows and 63 at 456): 1984 rows 128 / 148 / 157 / - / -, 456 rows 79 / 55 / 39 / 56 / -, 200 rows - / 51 / 38 / 28 / 42;
+// 2632 x 2632, 6746 rows 190 / 205 / 255 / 295 / -; 1024 x 1024: 3840 rows 32 / 27 / 31 / - / -, 960 rows 26 / 18 / 12 / 11 / 16, 120
+// rows - / 17 / 13 / 9 / 8.  Of 300 networks of 16..3072 inputs and widths of 64..4096 on 1..8192 rows, six run more than 7%
+// longer than on the one tile that suits them best, one more than 5% longer than on 128 x 128 tiles throughout.
 struct TileCost {
   int bm, bn;
   float f, k;
+  float least;   // of the widest tile, whose 128 KB of results alone take this long: K up to 450 (64-wide layers, 5659 rows, one
+                 // plane: 9.0 a layer, 6.7 on 128 x 128, 6.1 on 64 x 128)
 };
 constexpr TileCost kTileCost[2][5] = {
-    {{128, 256, 1.f, 1.05f}, {128, 128, 3.f, 0.75f}, {64, 128, 3.f, 0.45f}, {64, 64, 3.5f, 0.33f}, {32, 64, 4.f, 0.2f}},
-    {{128, 256, 0.f, 2.0f}, {128, 128, 3.f, 1.1f}, {64, 128, 3.5f, 0.55f}, {64, 64, 4.7f, 0.365f}, {32, 64, 4.5f, 0.26f}}};
+    {{128, 256, 1.f, 1.05f, 9.f}, {128, 128, 3.f, 0.75f, 0.f}, {64, 128, 3.f, 0.45f, 0.f}, {64, 64, 3.5f, 0.33f, 0.f}, {32, 64, 4.f, 0.2f, 0.f}},
+    {{128, 256, 0.f, 2.0f, 10.5f}, {128, 128, 3.f, 1.1f, 0.f}, {64, 128, 3.5f, 0.6f, 0.f}, {64, 64, 4.7f, 0.365f, 0.f}, {32, 64, 4.5f, 0.26f, 0.f}}};
 static int pick_tile(int planes, int n, int N, int K) {
   int best = 0;
   float best_t = INFINITY;
   for (int i = 0; i < 5; ++i) {
     const TileCost& c = kTileCost[planes - 1][i];
-    const int64_t rounds = ceil_div(ceil_div(n, c.bm) * ceil_div(N, c.bn), 256);
-    const float t = (float)rounds * (c.f + c.k * (float)K / 64.f);
+    const int64_t tiles = ceil_div(n, c.bm) * ceil_div(N, c.bn);
+    float rounds = (float)ceil_div(tiles, 256);
+    if (rounds > 2.f) rounds = 0.4f * rounds + 0.6f * (float)tiles / 256.f;
+    const float t = rounds * std::max(c.least, c.f + c.k * (float)K / 64.f);
     if (t < best_t) {
       best_t = t;
       best = i;
