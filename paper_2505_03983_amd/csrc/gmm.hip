@@ -91,7 +91,7 @@ __device__ __forceinline__ float4 row_coef(const float4* coef_tau, const int32_t
 // ---------------------------------------------------------------------------
 // preparation kernels
 // ---------------------------------------------------------------------------
-// means_t [d][cp] (zeroed by the caller where C is padded), means_p [C][dp] (NULL: d is not padded), musq [C]
+// means_t [d][cp] (zeroed by the caller where C is padded), means_p [C][dp] (NULL: not wanted), musq [C]
 __global__ void gmm_prep_kernel(int C, int d, int cp, int dp, const float* __restrict__ means,
                                 float* __restrict__ means_t, float* __restrict__ means_p, float* __restrict__ musq) {
   const int k = blockIdx.x;
@@ -1413,7 +1413,7 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
   const int dp = (d + 3) & ~3, cp = (C + 3) & ~3;   // rows of whole float4 for the kernels that read the mixture as such
   ASD_HIP(hipMalloc(&g->means_t, sizeof(float) * (size_t)d * cp));
   if (cp != C) ASD_HIP(hipMemset(g->means_t, 0, sizeof(float) * (size_t)d * cp));
-  if (dp != d) {
+  if (dp != d || ((uintptr_t)g->means & 15) != 0) {   // (the caller's means may start at any element of a larger array)
     ASD_HIP(hipMalloc(&g->means_p, sizeof(float) * (size_t)C * dp));
     ASD_HIP(hipMemset(g->means_p, 0, sizeof(float) * (size_t)C * dp));
   }
@@ -1448,6 +1448,7 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
   hipLaunchKernelGGL(gmm_prep_kernel, dim3(C), dim3(256), 0, 0, C, d, cp, dp, g->means, g->means_t,
                      g->means_p, g->musq);
   ASD_HIP(hipGetLastError());
+  if (g->means_p && dp == d) g->means = g->means_p;
   ASD_HIP(hipDeviceSynchronize());
 
   g->rowwise_lds = sizeof(float) * 4 * (size_t)(d + C);

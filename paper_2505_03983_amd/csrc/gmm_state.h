@@ -9,10 +9,10 @@ namespace asd {
 struct GmmState {
   int C = 0;
   float var = 0.f;
-  const float* means = nullptr;  // caller's [C, d]
+  const float* means = nullptr;  // caller's [C, d] (the copy below where that is not 16-byte aligned and d % 4 == 0)
   const float* log_w = nullptr;  // caller's [C]
   float* means_t = nullptr;      // [d, C rounded up to 4]
-  float* means_p = nullptr;      // [C, d rounded up to 4] zero-padded copy; NULL when d % 4 == 0
+  float* means_p = nullptr;      // [C, d rounded up to 4] zero-padded copy; NULL when the caller's serves as it is
   float* musq = nullptr;         // [C]
   float4* coef_tau = nullptr;    // [n_tau]: (kappa, gamma, cx, cm)
   float* logits = nullptr;       // [few_rows, C] (C rounded up to 4 where only gmm_few.h's kernels use it)

@@ -219,3 +219,28 @@ def test_mlp_weights_may_start_anywhere():
         ctx.close()
         outs.append(out)
     assert bool(torch.isfinite(outs[0]).all()) and torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("d, C", [(64, 60), (128, 130), (96, 1056)])     # mixture in LDS; few rows; operands packed once
+def test_mixture_means_may_start_anywhere(d, C):
+    """Means that are part of a larger array, at an odd element: the same bits as from an array of their own."""
+    from paper_2505_03983_amd import binding
+    cfg = dict(kind="gmm", d=d, C=C, K=20, L=64, var=0.25)
+    T, p, _ = oracle_setup(cfg)
+    n = 15000 if C == 1056 else 200
+    x = torch.randn(n, d, generator=torch.Generator(device=DEV).manual_seed(3), device=DEV)
+    tau = torch.full((n,), 9, dtype=torch.int32, device=DEV)
+    sched = binding.asd_schedule_ddpm_linear(cfg["K"])
+    outs = []
+    for shift in (0, 1):
+        den = runtime.device_params(cfg, p)
+        flat = torch.zeros(C * d + 8, device=DEV)
+        flat[shift:shift + C * d] = den["means"].flatten()
+        den.update(n_tau=cfg["K"] + 1, abar=sched["abar"], means=flat[shift:shift + C * d].view(C, d))
+        ctx = binding.Ctx(sched, den, cfg["L"], 240)
+        out = torch.zeros_like(x)
+        ctx.denoise(x, tau, out)
+        torch.cuda.synchronize()
+        ctx.close()
+        outs.append(out)
+    assert bool(torch.isfinite(outs[0]).all()) and torch.equal(outs[0], outs[1])
