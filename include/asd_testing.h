@@ -16,10 +16,18 @@ extern "C" {
 /* 1 if the next asd_sample on this context runs whole chains inside one workgroup (shape fits, switch on,
  * profiling off). */
 ASD_API int32_t asd_resident_active(const asd_ctx* ctx);
-/* Non-zero if the verify call of this context runs the split-operand kernels of the Gaussian-mixture denoiser: the
- * number of 16-bit matrix-core products they spend on one fp32 product -- 3 (two fp16 terms per operand: d and C
- * multiples of 32, both model calls) or 6 (three bf16 terms: multiples of 16, the verify call only). */
+/* Non-zero if the tiled kernels of this context's mixture verify calls work on split operands: the number of 16-bit
+ * matrix-core products they spend on one fp32 product -- 3 (two fp16 terms per operand: d and C multiples of 32, both
+ * model calls) or 6 (three bf16 terms: multiples of 16, the verify call only).  Calls that take the kernels for few rows
+ * (asd_use_few_rows) are fp32 throughout. */
 ASD_API int32_t asd_split_gemm_active(const asd_ctx* ctx);
+
+/* Mixture contexts large enough for the tiled kernels (d and C multiples of 4, chains * L * C * d >= 2^26) still send a
+ * call to the kernels for few rows, or to a row-wise one, where that is the faster way: by the call's rows, d and C, and
+ * never in a context that has the logit screen, on or off (asd_use_logit_screen).  on = 0: every call takes the tiled kernels (for tests
+ * and timing comparisons; results agree to fp32 rounding).  Default: on.  A call on the tiled kernels is timed in
+ * ASD_PROF_GMM_LOGITS, any other in ASD_PROF_GMM_ROWWISE.  Other contexts ignore the switch. */
+ASD_API asd_status asd_use_few_rows(asd_ctx* ctx, int32_t on);
 
 /* The second GEMM of the split-operand mixture denoiser (softmax weights times means) skips the stretches of
  * components whose weights are exactly 0.0f for every row of a tile (the denoiser takes a weight below 2^-40 of its
@@ -109,7 +117,7 @@ ASD_API asd_status asd_debug_randoms(uint64_t seed, uint32_t chain, uint32_t ste
 typedef enum {
   ASD_PROF_MODEL = 0,        /* a whole model call (all its kernels)          */
   ASD_PROF_PLAN = 1,         /* row planning                                  */
-  ASD_PROF_GMM_ROWWISE = 2,  /* GMM denoiser, one wavefront per row           */
+  ASD_PROF_GMM_ROWWISE = 2,  /* GMM denoiser outside the tiled kernels: a row-wise one, or the two for few rows */
   ASD_PROF_GMM_LOGITS = 3,   /* GMM logits GEMM  X M^T (+ the rows' fp16 scales) */
   ASD_PROF_GMM_SOFTMAX = 4,  /* GMM, between the two GEMMs: row maxima, one-hot rows */
   ASD_PROF_GMM_COMBINE = 5,  /* GMM  P M  GEMM + affine combination           */

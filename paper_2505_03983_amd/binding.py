@@ -74,6 +74,7 @@ def lib():
             "asd_logit_screen_active": (i32, [vp]),
             "asd_profile_model_work": (i32, [vp, vp, vp, vp, vp, vp, vp, vp]),
             "asd_use_tall_tiles": (i32, [vp, i32]),
+            "asd_use_few_rows": (i32, [vp, i32]),
             "asd_tall_tiles_active": (i32, [vp]),
             "asd_use_early_accept": (i32, [vp, i32]),
             "asd_early_accept_active": (i32, [vp]),
@@ -263,6 +264,9 @@ class Ctx:
 
     def logit_screen_active(self):
         return int(lib().asd_logit_screen_active(self.h))
+
+    def use_few_rows(self, on=True):
+        _check(lib().asd_use_few_rows(self.h, int(bool(on))))
 
     def use_tall_tiles(self, on=True):
         _check(lib().asd_use_tall_tiles(self.h, int(bool(on))))

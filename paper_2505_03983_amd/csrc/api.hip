@@ -550,6 +550,15 @@ asd_status asd_use_split_gemm(asd_ctx* ctx, int32_t on) {
   return ASD_OK;
 }
 
+asd_status asd_use_few_rows(asd_ctx* ctx, int32_t on) {
+  if (!ctx) return fail(ASD_EINVAL, "ctx is NULL");
+  if (ctx->gmm && ctx->gmm->few_on != (on != 0)) {
+    ctx->gmm->few_on = on != 0;
+    drop_round_graphs(ctx);   // the captured round holds the other kernels
+  }
+  return ASD_OK;
+}
+
 asd_status asd_use_sparse_combine(asd_ctx* ctx, int32_t on) {
   if (!ctx) return fail(ASD_EINVAL, "ctx is NULL");
   if (ctx->gmm && ctx->gmm->sparse_combine != (on != 0)) {

@@ -1674,7 +1674,7 @@ void gmm_destroy(asd_ctx* ctx) {
 asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
   GmmState* g = ctx->gmm;
   const int d = ctx->d, C = g->C, n = rows.n;
-  const RowwiseKernel small = pick_rowwise(n, d, C, g->use_mfma);
+  const RowwiseKernel small = g->use_mfma && !g->few_on ? kRowwiseNone : pick_rowwise(n, d, C, g->use_mfma);
   if (small == kRowwiseLds) {
     ProfScope ps(ctx, ASD_PROF_GMM_ROWWISE, rows.call, st);
     // one row per wavefront while that still gives fewer workgroups than CUs, else four
@@ -1700,7 +1700,7 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
   // (A screened context keeps its own kernels at every size: the draft call's verdict and the certificate's candidates
   // pass from call to call there.)
   const TiledCost& tiled = rows.call ? (!split ? kTiledF32 : g->two_ok ? kTiledFp16 : kTiledBf16) : (split ? kDraftFp16 : kDraftF32);
-  if (!g->use_mfma || (!g->screen_ok && few_rows_pays(tiled, splits, n, d, C))) {
+  if (!g->use_mfma || (g->few_on && !g->screen_ok && few_rows_pays(tiled, splits, n, d, C))) {
     ProfScope ps(ctx, ASD_PROF_GMM_ROWWISE, rows.call, st);
     ASD_HIP(launch_gmm_few(FewArgs{rows.n_dev, 0, n, d, C, (d + 3) & ~3, (C + 3) & ~3, rows.in_base, rows.in_off,
                                    rows.out_base, rows.out_off, rows.tau, g->coef_tau, g->means_p ? g->means_p : g->means,

@@ -82,6 +82,7 @@ struct GmmState {
   int32_t* cert_cnt = nullptr;     // [row tiles]: rows of the tile that have finished / passed (zero between calls)
   int32_t* live_tiles = nullptr;   // [1 + row tiles]: number of row tiles that are not certified, then their indices
   size_t rowwise_lds = 0;
+  bool few_on = true;              // asd_use_few_rows
 };
 
 }  // namespace asd

@@ -5,13 +5,14 @@ import torch
 
 import gpu_helpers as H
 from oracle_helpers import oracle_setup
-from paper_2505_03983_amd import runtime
+from paper_2505_03983_amd import binding, runtime
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def _denoise(cfg, n, seed=3, keep=None):
+def _denoise(cfg, n, seed=3, keep=None, tiled=False):
+    """tiled: on the tiled kernels, whichever the call would take by itself; else it is expected not to take them."""
     T, p, model = oracle_setup(cfg)
     rng = np.random.default_rng(seed)
     if cfg["kind"] == "gmm":     # unequal weights
@@ -19,6 +20,8 @@ def _denoise(cfg, n, seed=3, keep=None):
         from oracle_helpers import gmm_model
         model = gmm_model(T, p)
     ctx = runtime.open_ctx(cfg, p, seed=0, chains=-(-n // cfg["L"]))
+    ctx.use_few_rows(not tiled)
+    ctx.profile_enable(True)
     tau = rng.integers(1, cfg["K"] + 1, n).astype(np.int32)
     ab = T["abar"][tau]
     x0 = p["means"][rng.integers(0, cfg["C"], n)] + 0.5 * rng.standard_normal((n, cfg["d"]))
@@ -28,6 +31,7 @@ def _denoise(cfg, n, seed=3, keep=None):
     out = torch.full((n, cfg["d"]), float("nan"), dtype=torch.float32, device=DEV)
     ctx.denoise(torch.from_numpy(x).to(DEV), torch.from_numpy(tau).to(DEV), out)
     torch.cuda.synchronize()
+    assert ctx.profile_read(binding.PROF["GMM_LOGITS" if tiled else "GMM_ROWWISE"], 1)[0] == 1
     ctx.close()
     if keep is not None:
         return out.cpu().numpy(), None
@@ -35,14 +39,14 @@ def _denoise(cfg, n, seed=3, keep=None):
 
 
 @pytest.mark.parametrize("d, C, n", [
-    (1, 1, 1), (2, 64, 5), (15, 17, 1030), (64, 4, 16383),      # the row-wise kernel
-    (4, 1, 1), (16, 16, 17), (4, 150, 77), (512, 16, 1024),     # the one with the mixture in LDS: a row per wavefront
-    (16, 16, 16384), (256, 16, 8195), (1000, 8, 32771),         # four rows per wavefront, the last ones missing
-    (8, 32, 16384), (516, 4, 1000), (4, 16, 131072),            # just past them
+    (1, 1, 1), (2, 64, 5), (3, 80, 1024), (15, 17, 1030), (64, 4, 16383), (3, 21, 32768),   # the row-wise kernel
+    (4, 1, 1), (16, 16, 17), (4, 128, 77), (512, 20, 1024),     # the one with the mixture in LDS: a row per wavefront
+    (16, 16, 16384), (256, 16, 8195), (1000, 7, 32771),         # four rows per wavefront, the last ones missing
+    (8, 32, 16384), (516, 4, 512), (4, 129, 77), (4, 16, 131072), (3, 22, 16384),       # just past them
     (1, 257, 1), (257, 1, 3), (15, 18, 15), (17, 16, 16),       # one partial tile in every direction
     (100, 64, 33), (97, 65, 16), (256, 1024, 1), (260, 1028, 47), (301, 1003, 40),   # k shared by 1, 2, 4 wavefronts
     (5, 33, 8200), (64, 1024, 1025), (130, 1027, 993),    # 32 x 32 tiles: last row, column and k step partial
-    (2000, 3000, 9),                                      # a mixture that no LDS holds, neither size a tile's multiple
+    (2000, 3000, 9), (1093, 3003, 9), (1093, 3003, 700),  # mixtures that no LDS holds, and the largest of odd sizes
 ])
 def test_mixture_calls_of_few_rows(d, C, n):
     """fp32 products and sums: logits of up to ~2^9 in fp32 move a weight by at most 2^9 2^-24 = 3e-5 of itself, and
@@ -79,26 +83,25 @@ def test_mixture_scratch_is_bounded(d, C):
 @pytest.mark.parametrize("d, C, n", [(96, 1056, 15000), (80, 1040, 19000), (500, 1000, 8100),
                                      (96, 1056, 16400), (160, 640, 16400)])
 def test_mixture_calls_on_the_tiled_kernels(d, C, n):
-    """The least products that go to the tiles: two fp16 terms, three bf16 terms, fp32; then the least rows that go to
-    256-wide tiles, C ending inside one (same bound)."""
-    got, want = _denoise(dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25), n)
+    """Two fp16 terms, three bf16 terms, fp32; then the least rows that go to 256-wide tiles, C ending inside one (same
+    bound)."""
+    got, want = _denoise(dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25), n, tiled=True)
     assert H.rel_err(got, want) <= 3e-5
 
 
-@pytest.mark.parametrize("d, C, n", [
-    (1000, 4000, 1001),     # 256 tiles of the first product, 64 of the second (64 x 64 instead)
-    (500, 1000, 9000),      # both products on smaller tiles, none full at the edges; 8127 of the rows: neither
-    (512, 2052, 8100),      # neither
+@pytest.mark.parametrize("d, C, n, part", [
+    (1000, 4000, 1001, 500),      # 256 tiles of the first product, 64 of the second (64 x 64 instead); 128 (64 x 128) and 32
+    (500, 1000, 9000, 8127),      # both products on smaller tiles, none full at the edges; neither
+    (512, 2052, 8100, 4100),      # neither; both
 ])
-def test_fp32_tiles_do_not_depend_on_their_size(d, C, n):
+def test_fp32_tiles_do_not_depend_on_their_size(d, C, n, part):
     """Calls of the fp32 kernels on either side of the rule that picks smaller tiles, and parts of them, which go to others:
     the sums of an element are the same in every tile, so shared rows are equal bit for bit; against the oracle as above."""
-    got, want = _denoise(dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25), n)
+    cfg = dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25)
+    got, want = _denoise(cfg, n, tiled=True)
     assert H.rel_err(got, want) <= 3e-5
-    m = n - 70 - (n - 70) * 9 // 100
-    if m * C * d >= 4e9:
-        part, _ = _denoise(dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25), n, keep=m)
-        assert np.array_equal(part, got[:m])
+    first, _ = _denoise(cfg, n, keep=part, tiled=True)
+    assert np.array_equal(first, got[:part])
 
 
 @pytest.mark.parametrize("terms", [1, 2])
@@ -199,7 +202,6 @@ def test_mlp_draft_call_of_few_rows_with_a_large_matrix(terms, width, chains):
 
 def test_mlp_weights_may_start_anywhere():
     """Weight matrices that are parts of a larger array, at an odd element: the same bits as from arrays of their own."""
-    from paper_2505_03983_amd import binding
     cfg = dict(kind="mlp", d=24, E=8, width=72, n_blocks=2, K=20, L=4, act_terms=2)
     T, p, _ = oracle_setup(cfg)
     x = torch.randn(37, 24, generator=torch.Generator(device=DEV).manual_seed(3), device=DEV)
@@ -224,7 +226,6 @@ def test_mlp_weights_may_start_anywhere():
 @pytest.mark.parametrize("d, C", [(64, 60), (128, 130), (96, 1056)])     # mixture in LDS; few rows; operands packed once
 def test_mixture_means_may_start_anywhere(d, C):
     """Means that are part of a larger array, at an odd element: the same bits as from an array of their own."""
-    from paper_2505_03983_amd import binding
     cfg = dict(kind="gmm", d=d, C=C, K=20, L=64, var=0.25)
     T, p, _ = oracle_setup(cfg)
     n = 15000 if C == 1056 else 200
@@ -244,3 +245,27 @@ def test_mixture_means_may_start_anywhere(d, C):
         ctx.close()
         outs.append(out)
     assert bool(torch.isfinite(outs[0]).all()) and torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("terms", [1, 2])
+def test_split_sums_do_not_depend_on_the_kernel(terms):
+    """Draft calls whose sums over K are added in parts: 24 rows take the kernel for few rows, which adds its parts in
+    registers, 64 rows the 64 x 64 tiles and a second launch that adds them from memory, in the same four parts.  The rows
+    they share are equal bit for bit."""
+    cfg = dict(kind="mlp", d=64, E=16, width=4096, n_blocks=2, K=20, L=2, act_terms=terms)
+    T, p, _ = oracle_setup(cfg)
+    p["out_clip"] = 0.0
+    y0 = torch.randn(64, 64, generator=torch.Generator(device=DEV).manual_seed(2), device=DEV)
+    values = []
+    for B in (24, 64):
+        ctx = runtime.open_ctx(cfg, p, seed=0, chains=B)
+        traj = torch.zeros(B, cfg["K"] + 1, 64, device=DEV)
+        traj[:, 0] = y0[:B]
+        a = torch.zeros(B, dtype=torch.int32, device=DEV)
+        x0hat = torch.zeros(B, 2, 64, device=DEV)
+        ctx.draft(traj, a)
+        ctx.verify(traj, a, x0hat)
+        torch.cuda.synchronize()
+        ctx.close()
+        values.append(x0hat[:24, 0].clone())
+    assert bool(torch.isfinite(values[0]).all()) and torch.equal(values[0], values[1])

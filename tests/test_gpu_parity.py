@@ -60,7 +60,8 @@ def test_normals_and_uniforms_match_oracle():
 # ---------------------------------------------------------------------------
 # denoisers
 # ---------------------------------------------------------------------------
-def _denoise_case(cfg, n_rows, seed=0, chains=None, L=None, out_clip=None, split=None):
+def _denoise_case(cfg, n_rows, seed=0, chains=None, L=None, out_clip=None, split=None, tiled=False):
+    """tiled: on the tiled mixture kernels, whose least calls these are too small for."""
     T, p, model = oracle_setup(cfg)
     if out_clip is not None:
         p["out_clip"] = out_clip
@@ -69,6 +70,9 @@ def _denoise_case(cfg, n_rows, seed=0, chains=None, L=None, out_clip=None, split
     if split is not None:
         ctx.use_split_gemm(split)
         assert ctx.split_gemm_active() == bool(split and cfg["d"] % 16 == 0 and cfg["C"] % 16 == 0)
+    if tiled:
+        ctx.use_few_rows(False)
+        ctx.profile_enable(True)
     rng = np.random.default_rng(seed)
     tau = rng.integers(1, cfg["K"] + 1, n_rows).astype(np.int32)
     ab = T["abar"][tau]
@@ -82,6 +86,8 @@ def _denoise_case(cfg, n_rows, seed=0, chains=None, L=None, out_clip=None, split
     ctx.denoise(xd, torch.from_numpy(tau).to(DEV), out)
     torch.cuda.synchronize()
     want = model(K_minus(tau, cfg["K"]), x.astype(np.float64))
+    if tiled:
+        assert ctx.profile_read(binding.PROF["GMM_LOGITS"], 1)[0] == 1
     ctx.close()
     return out.cpu().numpy(), want
 
@@ -113,7 +119,7 @@ def test_gmm_matrix_core_denoiser(shape, split):
     # enough rows*C*d to select the matrix-core path
     chains = max(8, -(-rows // 16), int(np.ceil((1 << 26) / (shape["C"] * shape["d"] * 16))) + 1)
     cfg = dict(kind="gmm", K=50, chains=chains, L=16, var=0.25, **shape)
-    got, want = _denoise_case(cfg, rows, split=split)
+    got, want = _denoise_case(cfg, rows, split=split, tiled=True)
     e = H.rel_err(got, want)
     _log("gmm mfma", shape, "split", split, "rows", rows, "rel err", e)
     assert e <= 1e-4
@@ -157,10 +163,13 @@ def test_one_term_activations_at_full_size():
 # ---------------------------------------------------------------------------
 # one round, teacher-forced from oracle states
 # ---------------------------------------------------------------------------
-def _teacher_forced(cfg, seed, chains_checked, rounds_per_chain=4, model_seed=1):
+def _teacher_forced(cfg, seed, chains_checked, rounds_per_chain=4, model_seed=1, tiled=False):
     T, p, model = oracle_setup(cfg, model_seed)
     tol = H.TOL[cfg["kind"]]
     ctx = runtime.open_ctx(cfg, p, seed=seed)
+    if tiled:                    # both model calls on the tiled mixture kernels (see _denoise_case)
+        ctx.use_few_rows(False)
+        ctx.profile_enable(True)
     B, K = cfg["chains"], cfg["K"]
     recs = {}
     for c in chains_checked:
@@ -190,6 +199,8 @@ def _teacher_forced(cfg, seed, chains_checked, rounds_per_chain=4, model_seed=1)
             if c not in recs:
                 assert out["a_next"][c] == K and out["accepted"][c] == -1
                 assert not out["traj"][c].any()
+    if tiled:
+        assert [ctx.profile_read(binding.PROF["GMM_LOGITS"], call)[0] for call in (0, 1)] == [rounds_per_chain] * 2
     ctx.close()
     _log("teacher-forced", cfg["kind"], "d", cfg["d"], "rounds compared", n_own + n_other,
          "of them on the other branch of a flagged near-tie", n_other, "worst errors",
@@ -238,6 +249,7 @@ def test_matrix_core_denoiser_is_deterministic():
     cfg = dict(kind="gmm", d=48, C=1024, K=30, chains=70, L=24, var=0.25)
     T, p, _ = oracle_setup(cfg)
     ctx = runtime.open_ctx(cfg, p, seed=1)
+    ctx.use_few_rows(False)      # (calls of this size take other kernels by themselves)
     rng = np.random.default_rng(4)
     x = torch.from_numpy(rng.standard_normal((900, cfg["d"])).astype(np.float32)).to(DEV)
     tau = torch.from_numpy(rng.integers(1, cfg["K"] + 1, 900).astype(np.int32)).to(DEV)
@@ -253,6 +265,7 @@ def test_matrix_core_denoiser_is_deterministic():
     # one round from the same states, twice: draft call (K split), draft, verify call, accept
     B, K, L, d = cfg["chains"], cfg["K"], cfg["L"], cfg["d"]
     results = []
+    ctx.profile_enable(True)
     for _ in range(2):
         traj = torch.zeros((B, K + 1, d), dtype=torch.float32, device=DEV)
         traj[:, 0] = torch.arange(B, device=DEV, dtype=torch.float32)[:, None] * 0.01 + 0.3
@@ -265,6 +278,7 @@ def test_matrix_core_denoiser_is_deterministic():
         results.append((traj.clone(), a.clone(), x0hat.clone()))
     for u, v in zip(results[0], results[1]):
         assert torch.equal(u, v)
+    assert [ctx.profile_read(binding.PROF["GMM_LOGITS"], call)[0] for call in (0, 1)] == [2, 2]
     ctx.close()
 
 
@@ -277,6 +291,8 @@ def test_sparse_combine_is_bit_identical_to_the_dense_loop():
         T, p, model = oracle_setup(cfg)
         ctx = runtime.open_ctx(cfg, p, seed=0)
         assert ctx.split_gemm_active()
+        ctx.use_few_rows(False)      # (the first case's calls take other kernels by themselves)
+        ctx.profile_enable(True)
         rng = np.random.default_rng(7)
         tau = np.sort(rng.integers(1, cfg["K"] + 1, n_rows)).astype(np.int32)      # tiles of similar noise level
         ab = T["abar"][tau]
@@ -291,6 +307,7 @@ def test_sparse_combine_is_bit_identical_to_the_dense_loop():
             torch.cuda.synchronize()
             outs.append(out)
         assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+        assert ctx.profile_read(binding.PROF["GMM_COMBINE"], 1)[0] == 3
         want = model(K_minus(tau, cfg["K"]), x.astype(np.float64))
         e = H.rel_err(outs[0].cpu().numpy(), want)
         _log("sparse combine", cfg["C"], "components: bit-identical to dense, rel err vs oracle", e)
@@ -457,7 +474,7 @@ def test_round_midsize_matrix_core_shapes():
                 # (no K split), then a ragged row tile with the second GEMM's K split two ways
                 dict(kind="gmm", d=96, C=1056, K=20, chains=90, L=8, var=0.25),
                 dict(kind="gmm", d=64, C=1024, K=20, chains=70, L=16, var=0.25)):
-        _teacher_forced(cfg, seed=2, chains_checked=[0, 33, cfg["chains"] - 1], rounds_per_chain=2)
+        _teacher_forced(cfg, seed=2, chains_checked=[0, 33, cfg["chains"] - 1], rounds_per_chain=2, tiled=True)
 
 
 # ---------------------------------------------------------------------------
