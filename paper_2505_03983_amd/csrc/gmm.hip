@@ -1636,8 +1636,6 @@ void gmm_destroy(asd_ctx* ctx) {
   (void)hipFree(g->means_p);
   (void)hipFree(g->means_img);
   (void)hipFree(g->means_t_img);
-  (void)hipFree(g->means_img_s);
-  (void)hipFree(g->means_t_img_s);
   (void)hipFree(g->means_img2);
   (void)hipFree(g->means_t_img2);
   (void)hipFree(g->means_img_big);

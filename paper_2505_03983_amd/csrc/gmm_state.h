@@ -29,8 +29,6 @@ struct GmmState {
   // split-bf16 verify GEMMs (gemm_split3.h): the means, split and laid out as LDS images, for both GEMMs
   uint8_t* means_img = nullptr;    // B of the logits GEMM  ([C, d])
   uint8_t* means_t_img = nullptr;  // B of the combine GEMM ([d, C])
-  uint8_t* means_img_s = nullptr;  // the same two for the draft call's tiling (K slabs of 32)
-  uint8_t* means_t_img_s = nullptr;
   // Both GEMMs on two fp16 terms per operand (d and C multiples of 32; then the images above do not exist): the means
   // times b_scale as one image per GEMM for both tilings, the scale of every row of a call's first GEMM, and the
   // means as two fp16 terms carry them (what the closed form of a one-hot row must use)
