@@ -179,7 +179,7 @@ ASD_API asd_status asd_verify(asd_ctx* ctx, const float* traj, const int32_t* a,
  *   (-1 for finished chains).
  *   stats (DEV fp32 [chains, L, 4], may be NULL) receives per examined slot
  *   (<d,xi>, |d|^2, log u, rho) with d = x0a - x0hat[s]  (slot 0: zeros).
- *   The window is examined in order, eight slots at a time, up to the group
+ *   The window is examined in order, in groups of eight slots, up to the group
  *   that holds the first rejection; entries of later slots are left as they
  *   were. */
 ASD_API asd_status asd_accept(asd_ctx* ctx, float* traj, int32_t* a, const float* x0hat,

@@ -121,7 +121,7 @@ typedef enum {
   ASD_PROF_GMM_LOGITS = 3,   /* GMM logits GEMM  X M^T (+ the rows' fp16 scales) */
   ASD_PROF_GMM_SOFTMAX = 4,  /* GMM, between the two GEMMs: row maxima, one-hot rows */
   ASD_PROF_GMM_COMBINE = 5,  /* GMM  P M  GEMM + affine combination           */
-  ASD_PROF_MLP_PACK = 6,     /* MLP input packing (bf16 x ; time embedding)   */
+  ASD_PROF_MLP_PACK = 6,     /* MLP input packing, of rows the round kernels have not packed where they listed them */
   ASD_PROF_MLP_GEMM_IN = 7,  /* MLP first layer                               */
   ASD_PROF_MLP_GEMM_BLK = 8, /* MLP residual blocks (one launch per block)    */
   ASD_PROF_MLP_GEMM_OUT = 9, /* MLP output layer                              */
@@ -142,7 +142,8 @@ ASD_API asd_status asd_profile_select(asd_ctx* ctx, uint32_t slots);
 ASD_API asd_status asd_profile_read(asd_ctx* ctx, int32_t kernel, int32_t call, int64_t* launches, double* total_ms);
 ASD_API asd_status asd_profile_rows(asd_ctx* ctx, int64_t* draft_rows, int64_t* verify_rows);
 /* What the accept kernel touched since then: x0hat rows it read for the accept test (it examines a window eight
- * slots at a time and stops at the group that holds the first rejection) and rows it resampled (one per
+ * slots at a time, sixteen where sixteen groups of wavefronts share a chain, and stops at those that hold the first
+ * rejection) and rows it resampled (one per
  * chain-round that ended in a rejection). */
 ASD_API asd_status asd_profile_accept_rows(asd_ctx* ctx, int64_t* examined_rows, int64_t* resampled_rows);
 /* Matrix work the mixture denoiser's verify calls left out since then (split-operand kernels only; all zero

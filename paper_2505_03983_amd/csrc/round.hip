@@ -659,16 +659,17 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
           bit = (logu <= rho) ? 1 : 0;
         }
       }
-      if (stats && valid) {
+      // Alg. 2: accepted prefix = trailing ones of the ballot
+      const unsigned long long inv = ~__ballot(bit);
+      const int first = inv ? (__ffsll((long long)inv) - 1) : 64;
+      // (statistics end with the group of eight slots that holds the first rejection, also where a chunk is two of them)
+      if (stats && valid && lane < first / 8 * 8 + 8) {
         float* sp = stats + ((int64_t)c * L + k) * 4;
         sp[0] = sd;
         sp[1] = sv;
         sp[2] = (k == 0 || !(sg_t > 0.f)) ? 0.f : logu;
         sp[3] = (k == 0) ? 0.f : rho;
       }
-      // Alg. 2: accepted prefix = trailing ones of the ballot
-      const unsigned long long inv = ~__ballot(bit);
-      const int first = inv ? (__ffsll((long long)inv) - 1) : 64;
       if (lane == first) {
         s_rej[0] = sd;
         s_rej[1] = sv;

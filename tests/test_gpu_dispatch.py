@@ -176,6 +176,37 @@ def test_round_kernels_do_not_depend_on_how_many_wavefronts_share_a_chain(d, L, 
             assert torch.equal(t1[i, :int(a1[i]) + 1], t2[i, :int(a2[i]) + 1])
 
 
+@pytest.mark.parametrize("chains", [3, 300, 700, 1200, 5000])      # 16, 8, 4, 2 and 1 groups of wavefronts a chain
+def test_accept_statistics_end_with_the_group_of_the_first_rejection(chains):
+    """asd_accept leaves the entries behind the group of eight slots that holds the first rejection as they were, however
+    many slots it looks at together."""
+    cfg = dict(kind="gmm", d=12, C=3, K=60, L=32, var=0.25)
+    T, p, _ = oracle_setup(cfg)
+    ctx = runtime.open_ctx(cfg, p, seed=6, chains=chains)
+    K, L, d = cfg["K"], cfg["L"], cfg["d"]
+    traj = torch.zeros(chains, K + 1, d, device=DEV)
+    traj[:, 0] = torch.randn(chains, d, generator=torch.Generator(device=DEV).manual_seed(1), device=DEV)
+    a = torch.zeros(chains, dtype=torch.int32, device=DEV)
+    x0hat = torch.zeros(chains, L, d, device=DEV)
+    acc = torch.zeros(chains, dtype=torch.int32, device=DEV)
+    ends = set()
+    for _ in range(5):
+        before = a.cpu().numpy()
+        stats = torch.full((chains, L, 4), -7.0, device=DEV)
+        ctx.draft(traj, a)
+        ctx.verify(traj, a, x0hat)
+        ctx.accept(traj, a, x0hat, acc, stats)
+        torch.cuda.synchronize()
+        written = (stats.cpu().numpy() != -7.0).any(axis=2)
+        for c in range(chains):
+            w, n = min(L, K - before[c]), int(acc[c]) if before[c] < K else 0
+            end = 0 if before[c] == K else w if n == w else min(w, n // 8 * 8 + 8)
+            assert written[c, :end].all() and not written[c, end:].any(), (c, before[c], n)
+            ends.add(end)
+    ctx.close()
+    assert 8 in ends and len(ends) > 2
+
+
 @pytest.mark.parametrize("terms, width, chains", [(1, 2304, 5), (2, 2304, 5), (2, 2304, 33), (2, 2560, 24), (1, 2560, 64)])
 def test_mlp_draft_call_of_few_rows_with_a_large_matrix(terms, width, chains):
     """The draft call of a few chains adds its sums over K in parts where the weights are large (parts of 18 and of 10
