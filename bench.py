@@ -197,12 +197,14 @@ def roofline(res, w=None, kernel=None):
         cand = [n for n in ("GMM_LOGITS/verify", "GMM_COMBINE/verify", "GMM_ROWWISE/verify") if n in k]
         name = kernel or max(cand, key=lambda n: k[n]["total_ms"])      # the one the sample spends most time in
         launches = k[name]["launches"]
-        # 2*C*d flops per row for either GEMM (the row-wise kernel does both: 4*C*d)
-        per_row = (4.0 if name.startswith("GMM_ROWWISE") else 2.0) * cfg["C"] * cfg["d"]
+        # 2*C*d flops per row for either GEMM (a call outside the tiled kernels is timed as a whole: 4*C*d)
+        tiled = not name.startswith("GMM_ROWWISE")
+        per_row = (2.0 if tiled else 4.0) * cfg["C"] * cfg["d"]
         dtype = "f32"
-        # the row-wise kernel runs on the vector ALUs; its bound is the fp32 vector peak (same figure)
-        bound = "mfma" if not name.startswith("GMM_ROWWISE") else "alu"
-        if bound == "mfma" and res.get("split"):
+        # Outside the tiled kernels, mixtures of up to 10240 numbers take a row-wise kernel on the vector ALUs (their fp32
+        # peak is the same figure), larger ones two kernels on the fp32 matrix cores.
+        bound = "mfma" if tiled or cfg["C"] * cfg["d"] > 10240 else "alu"
+        if tiled and res.get("split"):
             executed_per_method = float(res.get("split_products") or 6)
             dtype = "f16" if executed_per_method == 3.0 else "bf16"
             slab = 32 if executed_per_method == 3.0 else 16                      # components per K slab of the second GEMM
@@ -274,8 +276,8 @@ def hbm_kernels(res):
     their noise (Philox4x32-10 + Box-Muller per four coordinates) and are bound by that arithmetic, not by HBM;
     the figures say how far from the HBM roof that leaves them.
     draft: reads y_a and x0a (2 rows per live chain), writes the w drafted rows.
-    accept: reads x0a and the x0hat rows of the slots it examines -- it walks the window eight slots at a time
-    and stops at the group holding the first rejection, so it reads far fewer than the w - 1 rows of the window
+    accept: reads x0a and the x0hat rows of the slots it examines -- it walks the window eight slots (with few chains
+    sixteen) at a time and stops at those holding the first rejection, so it reads far fewer than the w - 1 rows of the window
     (the count comes from the device) -- and, on a rejection, reads and rewrites one trajectory row.
     `whole_window` is the same figure had it read every slot: an upper bound, kept for comparison."""
     cfg, k = res["cfg"], res["kernels"]
