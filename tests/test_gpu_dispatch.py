@@ -72,6 +72,7 @@ def test_mixture_scratch_is_bounded(d, C):
     had its own)."""
     cfg = dict(kind="gmm", d=d, C=C, K=4, L=64, var=0.25)
     T, p, _ = oracle_setup(cfg)
+    runtime.open_ctx(cfg, p, chains=1).close()     # (the first context of a process also loads the kernels)
     torch.cuda.synchronize()
     free = torch.cuda.mem_get_info()[0]
     ctx = runtime.open_ctx(cfg, p, chains=16384)
