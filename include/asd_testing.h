@@ -94,6 +94,14 @@ ASD_API int32_t asd_early_accept_active(const asd_ctx* ctx);
 ASD_API asd_status asd_profile_early_accept(asd_ctx* ctx, int64_t* model_rows, int64_t* chain_rounds, int64_t* window_rows,
                                             int64_t* resampled_rows);
 
+/* Windows in pieces (inside asd_sample and asd_sample_noalloc; networks, at most 16384 model rows per call, neither window
+ * control nor model-call reuse, where a model call on fewer rows is enough faster): a window's slots are drafted, verified
+ * and tested a piece at a time -- about as many as the chain has lately accepted in a row -- and the next piece only if
+ * every slot before it was accepted, since what lies behind the first rejection is thrown away.  Samples and round counts
+ * are the same, bit for bit; the model evaluates fewer rows, which is what asd_profile_rows then counts.  on = 0: windows
+ * are taken whole (for tests and timing comparisons).  Default: on. */
+ASD_API asd_status asd_use_window_pieces(asd_ctx* ctx, int32_t on);
+
 /* Raw generator output: out DEV uint32 [nblk, 4] = Philox4x32-10 words for
  * counters (blk, step, chain, stream_id), blk = 0..nblk-1, key = seed. */
 ASD_API asd_status asd_debug_philox(uint64_t seed, uint32_t chain, uint32_t step, uint32_t stream_id,

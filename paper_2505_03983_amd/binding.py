@@ -75,6 +75,7 @@ def lib():
             "asd_profile_model_work": (i32, [vp, vp, vp, vp, vp, vp, vp, vp]),
             "asd_use_tall_tiles": (i32, [vp, i32]),
             "asd_use_few_rows": (i32, [vp, i32]),
+            "asd_use_window_pieces": (i32, [vp, i32]),
             "asd_tall_tiles_active": (i32, [vp]),
             "asd_use_early_accept": (i32, [vp, i32]),
             "asd_early_accept_active": (i32, [vp]),
@@ -273,6 +274,9 @@ class Ctx:
 
     def tall_tiles_active(self):
         return bool(lib().asd_tall_tiles_active(self.h))
+
+    def use_window_pieces(self, on=True):
+        _check(lib().asd_use_window_pieces(self.h, int(bool(on))))
 
     def use_early_accept(self, on=True):
         _check(lib().asd_use_early_accept(self.h, int(bool(on))))

@@ -154,14 +154,15 @@ static asd_status build(asd_ctx* ctx, const asd_config* cfg) {
   ASD_HIP(hipMemset(ctx->row_counts, 0, sizeof(int64_t) * 8));
   ASD_HIP(hipMalloc(&ctx->pending, sizeof(int32_t) * (size_t)ctx->B));
   ASD_HIP(hipMemset(ctx->pending, 0, sizeof(int32_t) * (size_t)ctx->B));
-  ASD_HIP(hipMalloc(&ctx->live, sizeof(int32_t) * (1 + 2 * kLiveRing)));
-  ASD_HIP(hipMemset(ctx->live, 0, sizeof(int32_t) * (1 + 2 * kLiveRing)));
+  ASD_HIP(hipMalloc(&ctx->live, sizeof(int32_t) * kLiveInts));
+  ASD_HIP(hipMemset(ctx->live, 0, sizeof(int32_t) * kLiveInts));
   ASD_HIP(hipMalloc(&ctx->win, sizeof(int32_t) * 2 * (size_t)ctx->B));
+  ASD_HIP(hipMalloc(&ctx->piece_state, sizeof(int32_t) * 3 * (size_t)ctx->B));
   ASD_HIP(hipMalloc(&ctx->chain_max, sizeof(unsigned long long)));
   ASD_HIP(hipMemset(ctx->chain_max, 0, sizeof(unsigned long long)));
   ASD_HIP(hipMalloc(&ctx->key_dev, sizeof(Key)));
   ASD_HIP(hipMemcpy(ctx->key_dev, &ctx->key, sizeof(Key), hipMemcpyHostToDevice));
-  ASD_HIP(hipHostMalloc((void**)&ctx->live_host, sizeof(int32_t) * 2 * kLiveRing, hipHostMallocDefault));
+  ASD_HIP(hipHostMalloc((void**)&ctx->live_host, sizeof(int32_t) * (kLiveInts - 1), hipHostMallocDefault));
   ctx->live_ev = new (std::nothrow) hipEvent_t[kLiveRing]();
   if (!ctx->live_ev) return ASD_ENOMEM;
   for (int i = 0; i < kLiveRing; ++i) ASD_HIP(hipEventCreateWithFlags(&ctx->live_ev[i], hipEventDisableTiming));
@@ -175,6 +176,10 @@ static void drop_round_graphs(asd_ctx* ctx) {
   if (ctx->gexec_light) (void)hipGraphExecDestroy(ctx->gexec_light);
   ctx->gexec = nullptr;
   ctx->gexec_light = nullptr;
+  for (hipGraphExec_t& g : ctx->gexec_rows) {
+    if (g) (void)hipGraphExecDestroy(g);
+    g = nullptr;
+  }
 }
 
 static void teardown(asd_ctx* ctx) {
@@ -197,6 +202,7 @@ static void teardown(asd_ctx* ctx) {
   (void)hipFree(ctx->live);
   (void)hipFree(ctx->chain_max);
   (void)hipFree(ctx->win);
+  (void)hipFree(ctx->piece_state);
   (void)hipFree(ctx->key_dev);
   drop_round_graphs(ctx);
   if (ctx->own_stream) (void)hipStreamDestroy(ctx->own_stream);
@@ -217,12 +223,12 @@ static RowPlan draft_rows(asd_ctx* ctx, const float* traj) {
                  ctx->fold_plans && ctx->kind == ASD_DEN_MLP};
 }
 
-static RowPlan verify_rows(asd_ctx* ctx, const float* traj, float* x0hat) {
+static RowPlan verify_rows(asd_ctx* ctx, const float* traj, float* x0hat, int likely = 0) {
   int per_chain = ctx->L - 1 + (ctx->reuse_now ? 1 : 0);   // tested slots, plus yhat_b with model-call reuse
   const int block = ctx->cur_win ? 0 : model_row_block(ctx);    // the planner's filling of each chain's block (launch_plan_verify)
   if (block > 0) per_chain = (per_chain + block - 1) / block * block;
   return RowPlan{ctx->B * per_chain, ctx->n_rows_dev + 1, traj, x0hat, ctx->in_off, ctx->out_off, ctx->row_tau, 1,
-                 ctx->row_chain, ctx->fold_plans && draft_packs_rows(ctx)};
+                 ctx->row_chain, ctx->fold_plans && draft_packs_rows(ctx), likely};
 }
 
 __global__ void set_key_kernel(Key* dst, Key key) { *dst = key; }
@@ -330,8 +336,9 @@ asd_status asd_accept(asd_ctx* ctx, float* traj, int32_t* a, const float* x0hat,
 // All launches of one round of Alg. 1 on `st`, plus the copy of the live-chain ring to the host.
 // light (early accept only): the early accept kernel alone (behind the planning kernel, which starts the round) --
 // for rounds in which, as far as the host knows, that kernel takes every chain.  A chain it does not take stays where
-// it is until the next full round.
-static asd_status enqueue_round(asd_ctx* ctx, float* traj, int32_t* rounds, float* x0hat, hipStream_t st, bool light) {
+// it is until the next full round.  likely: rows to expect in the verify call (0: as many as there can be).
+static asd_status enqueue_round(asd_ctx* ctx, float* traj, int32_t* rounds, float* x0hat, hipStream_t st, bool light,
+                                int likely) {
   // No planning kernels here: the rows of the draft call were listed by the previous round's accept
   // kernel (by init_state before round 0), those of the verify call are listed by the draft kernel.
   // (or, for large batches, by the planning kernels: see fold_plans)
@@ -346,29 +353,57 @@ static asd_status enqueue_round(asd_ctx* ctx, float* traj, int32_t* rounds, floa
     ASD_TRY(launch_draft(ctx, traj, ctx->a, st, ctx->live, pending));
     if (ctx->L > 1 || ctx->reuse_now) {
       if (!ctx->fold_plans) ASD_TRY(launch_plan_verify(ctx, ctx->a, st, pending));
-      ASD_TRY(model_eval(ctx, verify_rows(ctx, traj, x0hat), st));
+      ASD_TRY(model_eval(ctx, verify_rows(ctx, traj, x0hat, likely), st));
     }
     ASD_TRY(launch_accept(ctx, traj, ctx->a, x0hat, ctx->L + (ctx->reuse_now ? 1 : 0), nullptr, nullptr, rounds,
                           ctx->live, st, pending));
   }
   // The whole ring is copied: slot r % kLiveRing keeps its value until round r + kLiveRing overwrites it,
   // long after the host has read it.
-  ASD_HIP(hipMemcpyAsync(ctx->live_host, ctx->live + 1, sizeof(int32_t) * 2 * kLiveRing, hipMemcpyDeviceToHost, st));
+  ASD_HIP(hipMemcpyAsync(ctx->live_host, ctx->live + 1, sizeof(int32_t) * (kLiveInts - 1), hipMemcpyDeviceToHost, st));
   return ASD_OK;
+}
+
+// Windows in pieces (device_util.h): the least slots of a piece, 0 where windows are taken whole.  A pass over the batch then
+// costs the draft call, about 24 us of round kernels, and a model call on `least` rows a chain instead of L - 1, and there are
+// a sixth to a quarter more passes than rounds.  Four slots, or as many more as the tiles that four take have room for.
+// Measured, whole / in pieces, milliseconds a sample: 64 chains, 4096 wide, 6 blocks, d 3072, L 32 (a run of 4.3 slots on
+// average) 211.5 / 113.5, from 358 k verified rows to 89 k; 256 chains, 1024 wide, 4 blocks, d 112, L 16 (2.0 slots) 7.61 /
+// 5.78.  (One chain of it: rows cost nothing there, windows are taken whole.)
+static int piece_least(const asd_ctx* ctx) {
+  if (ctx->kind != ASD_DEN_MLP || ctx->L <= 4 || !ctx->fold_plans || ctx->reuse_now || ctx->cur_win || !ctx->pieces_on) return 0;
+  const double at_four = mlp_call_cost(ctx, 1, 4 * ctx->B), fixed = mlp_call_cost(ctx, 0, ctx->B) + 24.0;
+  int least = 4;
+  while (least + 1 < ctx->L && mlp_call_cost(ctx, 1, (least + 1) * ctx->B) <= 1.05 * at_four) ++least;
+  const double piece = mlp_call_cost(ctx, 1, least * ctx->B), whole = mlp_call_cost(ctx, 1, (ctx->L - 1) * ctx->B);
+  return 1.25 * (fixed + piece) < fixed + whole ? least : 0;
+}
+
+// How many rows a pass in pieces will bring varies by a factor of L / least over a sample, and what tiles a model call should
+// take varies with it.  Which forms there are: least rows a chain, twice that, four times, ... (hint 0, 1, ...), and the most
+// there can be (-1).  The grid covers all rows in every form.
+static int hinted_rows(const asd_ctx* ctx, int hint) { return hint < 0 ? 0 : (ctx->B * ctx->cur_pieces.least) << hint; }
+static int row_hint(const asd_ctx* ctx, int rows_seen) {
+  for (int h = 0; h < asd_ctx::kRowHints && hinted_rows(ctx, h) < ctx->B * (ctx->L - 1); ++h)
+    if (rows_seen <= hinted_rows(ctx, h)) return h;
+  return -1;
 }
 
 // Capture one round into a graph (launch-bound workloads: one graph launch instead of ~8 kernel launches).
 // Every launch argument of a round is the same in every round: the round index and the live ring are
 // advanced on the device, the seed is read from device memory.
-static asd_status ensure_round_graph(asd_ctx* ctx, float* traj, int32_t* rounds, hipStream_t st, bool light) {
+static asd_status ensure_round_graph(asd_ctx* ctx, float* traj, int32_t* rounds, hipStream_t st, bool light, int hint,
+                                     hipGraphExec_t* out) {
   const bool valid = ctx->g_traj == traj && ctx->g_rounds == rounds && ctx->g_stream == st &&
-                     ctx->g_win == ctx->cur_win && ctx->g_reuse == ctx->reuse_now && ctx->g_early == ctx->early_now;
+                     ctx->g_win == ctx->cur_win && ctx->g_reuse == ctx->reuse_now && ctx->g_early == ctx->early_now &&
+                     ctx->g_pieces == (ctx->cur_pieces.state != nullptr);
   if (!valid) drop_round_graphs(ctx);   // both forms were captured for other arguments
-  hipGraphExec_t& exec = light ? ctx->gexec_light : ctx->gexec;
+  hipGraphExec_t& exec = light ? ctx->gexec_light : hint >= 0 ? ctx->gexec_rows[hint] : ctx->gexec;
+  *out = exec;
   if (exec) return ASD_OK;
   hipGraph_t graph = nullptr;
   ASD_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-  asd_status s = enqueue_round(ctx, traj, rounds, ctx->x0hat, st, light);
+  asd_status s = enqueue_round(ctx, traj, rounds, ctx->x0hat, st, light, hinted_rows(ctx, hint));
   hipError_t e = hipStreamEndCapture(st, &graph);
   if (s != ASD_OK) {
     if (graph) (void)hipGraphDestroy(graph);
@@ -384,6 +419,8 @@ static asd_status ensure_round_graph(asd_ctx* ctx, float* traj, int32_t* rounds,
   ctx->g_win = ctx->cur_win;
   ctx->g_reuse = ctx->reuse_now;
   ctx->g_early = ctx->early_now;
+  ctx->g_pieces = ctx->cur_pieces.state != nullptr;
+  *out = exec;
   return ASD_OK;
 }
 
@@ -408,8 +445,11 @@ static asd_status sample_rounds(asd_ctx* ctx, const float* y0, float* traj, int3
       c->fold_plans = c->n_rows_max <= 16384;
       c->reuse_now = c->reuse;
       c->early_now = early_accept_possible(c) && !c->fold_plans && !c->reuse_now;
+      const int least = piece_least(c);
+      if (least > 0) c->cur_pieces = Pieces{c->piece_state, least};
     }
     ~WinScope() {
+      c->cur_pieces = Pieces{};
       c->cur_win = nullptr;
       c->fold_plans = false;
       c->reuse_now = false;
@@ -434,16 +474,18 @@ static asd_status sample_rounds(asd_ctx* ctx, const float* y0, float* traj, int3
   int r = 0;
   int done_at = -1;
   bool light = false;
+  int hint = -1;   // windows in pieces: by the rows of pass r - lag
   // Alg. 1 ends within K iterations (correctness theorem); a light round may leave a chain waiting, at most `lag`
-  // rounds in a row before a full one comes
+  // rounds in a row before a full one comes; every pass in pieces moves every chain by a slot at least
   const int r_cap = (ctx->early_now ? (lag + 2) : 1) * ctx->K + lag + 1;
   for (; r < r_cap; ++r) {
     const int slot = r % kLiveRing;
     if (use_graph && r > 0) {
-      ASD_TRY(ensure_round_graph(ctx, traj, rounds, st, light));  // round 0 ran eagerly (first-use set-up)
-      ASD_HIP(hipGraphLaunch(light ? ctx->gexec_light : ctx->gexec, st));
+      hipGraphExec_t exec = nullptr;
+      ASD_TRY(ensure_round_graph(ctx, traj, rounds, st, light, hint, &exec));  // round 0 ran eagerly (first-use set-up)
+      ASD_HIP(hipGraphLaunch(exec, st));
     } else {
-      ASD_TRY(enqueue_round(ctx, traj, rounds, x0hat, st, light));
+      ASD_TRY(enqueue_round(ctx, traj, rounds, x0hat, st, light, hinted_rows(ctx, hint)));
     }
     ASD_HIP(hipEventRecord(ctx->live_ev[slot], st));
     if (r >= lag) {
@@ -456,11 +498,12 @@ static asd_status sample_rounds(asd_ctx* ctx, const float* y0, float* traj, int3
       // the early accept kernel took every chain of round r - lag: the rounds to come are launched without the
       // kernels behind it, until one of them reports a chain it could not take (which has waited since)
       light = ctx->early_now && ctx->live_host[kLiveRing + q] == 0;
+      if (ctx->cur_pieces.state) hint = row_hint(ctx, ctx->live_host[kLiveRing + q]);
     }
   }
   ASD_HIP(hipStreamSynchronize(st));
   if (done_at < 0) return fail(ASD_EDEVICE, "asd_sample: chains did not finish within %d rounds", r_cap);
-  ctx->last_rounds = done_at + 1;
+  ctx->last_rounds = ctx->cur_pieces.state ? ctx->live_host[kLiveMaxRounds - 1] : done_at + 1;
   return ASD_OK;
 }
 
@@ -532,6 +575,12 @@ asd_status asd_use_adaptive_window(asd_ctx* ctx, int32_t on) {
 asd_status asd_use_call_reuse(asd_ctx* ctx, int32_t on) {
   if (!ctx) return fail(ASD_EINVAL, "ctx is NULL");
   ctx->reuse = on != 0;
+  return ASD_OK;
+}
+
+asd_status asd_use_window_pieces(asd_ctx* ctx, int32_t on) {
+  if (!ctx) return fail(ASD_EINVAL, "ctx is NULL");
+  ctx->pieces_on = on != 0;
   return ASD_OK;
 }
 

@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "../../include/asd_testing.h"
+#include "device_util.h"
 #include "gmm_cert.h"
 #include "rng.h"
 
@@ -78,6 +79,7 @@ struct RowPlan {
   // about a chain's earlier rows to guess -- never to decide -- something about this one.
   const int32_t* chain = nullptr;
   bool packed = false;    // the kernels that listed the rows have packed them (PackOut)
+  int likely = 0;         // rows to expect, where the host knows better than n (0: n): which tiles suit, nothing else
 };
 
 struct GmmState;
@@ -119,6 +121,7 @@ struct Profiler {
 
 // The context behind the opaque handle.
 struct asd_ctx {
+  static constexpr int kRowHints = 4;
   int device = 0;
   int32_t K = 0, L = 0, B = 0, d = 0, n_tau = 0;
   int64_t n_rows_max = 0;  // B * L
@@ -142,14 +145,16 @@ struct asd_ctx {
   // owned by asd_sample
   float* x0hat = nullptr;  // [B, L, d]
   int32_t* a = nullptr;    // [B]
-  int32_t* live = nullptr;       // DEV [1 + 2 kLiveRing]: round index, the ring of live-chain counters, the ring of
-                                 // chains a round's early accept kernel left pending
+  int32_t* live = nullptr;       // DEV [kLiveInts]: round index, the ring of live-chain counters, the ring of chains a round's
+                                 // early accept kernel left pending (or, in pieces, of a pass's verify rows), and in
+                                 // pieces the largest round count of a finished chain
   int32_t* live_host = nullptr;  // pinned mirror
   hipEvent_t* live_ev = nullptr;
   int32_t last_rounds = 0;
   // one round of the cheap-round path as an instantiated HIP graph, valid for (g_traj, g_rounds, g_stream)
   hipGraphExec_t gexec = nullptr;
   hipGraphExec_t gexec_light = nullptr;   // the light round (draft call + early accept kernel only), same validity
+  hipGraphExec_t gexec_rows[kRowHints] = {};   // rounds in pieces with tiles for ever fewer rows (row_hint), same validity
   const void* g_traj = nullptr;
   const void* g_rounds = nullptr;
   hipStream_t g_stream = nullptr;
@@ -160,8 +165,12 @@ struct asd_ctx {
   int32_t* win = nullptr;      // DEV [2 B]: window of each chain, then the controller's state (asd_sample, adaptive)
   int32_t* cur_win = nullptr;  // what the round kernels are given: win while an adaptive sample runs, else NULL (= L)
   bool adaptive = false;
+  bool pieces_on = true;       // the switch of windows in pieces (asd_use_window_pieces)
+  int32_t* piece_state = nullptr;  // DEV [3 B]: see Pieces (device_util.h)
+  asd::Pieces cur_pieces;      // what the round kernels are given: in pieces while a sample that pays for them runs
   const void* g_win = nullptr; // cur_win the round graph was captured with
   bool g_reuse = false;        // reuse_now the round graph was captured with
+  bool g_pieces = false;       // whether the round graph was captured with windows in pieces
   bool fold_plans = false;     // set while asd_sample's rounds run: see PlanOut
   // Model-call reuse across rounds (asd_use_call_reuse): the verify call also evaluates the last proposal sample
   // yhat_b of every window (slot w of x0hat, hence L + 1 slots per chain there); a chain whose whole window was
@@ -189,6 +198,7 @@ struct asd_ctx {
 namespace asd {
 
 constexpr int kLiveRing = 8;
+constexpr int kLiveMaxRounds = 1 + 2 * kLiveRing, kLiveInts = kLiveMaxRounds + 1;   // ctx->live: the last word, and all of them
 
 // Whether kernels get the device-side counters of rows and executed work (asd_profile_rows, asd_profile_model_work).
 inline bool prof_counting(const asd_ctx* ctx) { return ctx->prof.on; }
@@ -228,6 +238,7 @@ asd_status mlp_create(asd_ctx* ctx, const asd_denoiser& den);
 void mlp_destroy(asd_ctx* ctx);
 PackOut mlp_pack_out(const asd_ctx* ctx);
 asd_status mlp_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st);
+double mlp_call_cost(const asd_ctx* ctx, int call, int rows);   // microseconds, roughly: for choices between ways to batch
 
 // What a kernel outside the mixture denoiser needs to certify rows one-hot and form their model values (gmm_cert.h);
 // false when the denoiser's own verify call would not do the same, bit for bit.

@@ -71,4 +71,28 @@ __device__ __forceinline__ int window_next(int state, int w_used, int n_acc) {
   return state - (state >> 2) + (n_acc == w_used ? 2 * w_used : n_acc);
 }
 
+// ----------------------------------------------------------------------------
+// Windows taken in pieces (asd_sample against a network).  What lies behind the first rejection of a window is thrown away
+// -- 26 of 31 verified rows, in the image-shaped workload -- so a window's slots are drafted, verified and tested a piece at
+// a time, and the next piece only if every slot before it was accepted.  Every row that is evaluated is the row the whole
+// window would have held there, from the same x0a and the same noise: samples and round counts are the same, bit for bit.
+// Chains don't wait for each other: in one pass over the batch some begin a window (draft call and first piece), others go
+// on with theirs.  A piece is 5/4 of a running mean of the chain's accepted run length (kept as the window controller keeps
+// its own), at least `least` slots: between one and two of the mean cost the same within 3% over the measured runs, and
+// fewer slots than fill the model call's tiles save nothing.
+// state[c] = slots of the current window already accepted, state[B + c] = the mean's integer state, state[2 B + c] = rounds.
+// ----------------------------------------------------------------------------
+struct Pieces {
+  int32_t* state = nullptr;   // NULL: windows are taken whole
+  int least = 0;
+};
+struct PieceRange {
+  int lo, hi;   // slots lo .. hi - 1 of the window
+};
+__device__ __forceinline__ PieceRange piece_range(const Pieces& p, int c, int B, int L, int w) {
+  if (!p.state) return PieceRange{0, w};
+  const int lo = p.state[c];
+  return PieceRange{lo, min(w, lo + max(p.least, min(L, (5 * p.state[B + c]) >> 4)))};
+}
+
 }  // namespace asd

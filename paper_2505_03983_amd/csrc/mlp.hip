@@ -49,7 +49,7 @@ struct TileCost {
 constexpr TileCost kTileCost[2][5] = {
     {{128, 256, 1.f, 1.05f, 9.f}, {128, 128, 3.f, 0.75f, 0.f}, {64, 128, 3.f, 0.45f, 0.f}, {64, 64, 3.5f, 0.33f, 0.f}, {32, 64, 4.f, 0.2f, 0.f}},
     {{128, 256, 0.f, 2.0f, 10.5f}, {128, 128, 3.f, 1.1f, 0.f}, {64, 128, 3.5f, 0.6f, 0.f}, {64, 64, 4.7f, 0.365f, 0.f}, {32, 64, 4.5f, 0.26f, 0.f}}};
-static int pick_tile(int planes, int n, int N, int K) {
+static int pick_tile(int planes, int n, int N, int K, float* time = nullptr) {
   int best = 0;
   float best_t = INFINITY;
   for (int i = 0; i < 5; ++i) {
@@ -63,6 +63,7 @@ static int pick_tile(int planes, int n, int N, int K) {
       best = i;
     }
   }
+  if (time) *time = best_t;
   return best;
 }
 
@@ -107,21 +108,27 @@ static hipError_t mlp_gemm_few(int tile, const int* n_dev, int n, int N, int K, 
                    : launch_gemm_bf16_few<FewRowsCfg<2, 2, 8, PL>>(n_dev, n, N, K, A, Wt, e, st, splits);
 }
 
+static bool large_matrix(int N, int Kp) { return (int64_t)N * Kp * 2 >= (8 << 20); }   // takes several microseconds to stream
+// Workgroups that share the K of a draft call's tile: see mlp_gemm_planes.
+static int draft_splits(int n, int N, int Kp) {
+  const int64_t tiles = ceil_div(n, 64) * ceil_div(N, 64);
+  int splits = 1;
+  while (large_matrix(N, Kp) && splits < kMaxSplits && tiles * splits < 256 && (Kp / 64) % (2 * splits) == 0) splits *= 2;
+  return splits;
+}
+
+// likely: rows to expect (n is the most there can be)
 template <int PL, class Epi>
-static hipError_t mlp_gemm_planes(int call, const int* n_dev, int n, int N, int K, SlabMat A, SlabMat Wt, Epi e,
+static hipError_t mlp_gemm_planes(int call, const int* n_dev, int n, int likely, int N, int K, SlabMat A, SlabMat Wt, Epi e,
                                   hipStream_t st, const SplitScratch& sc) {
   const int Kp = slab_count(K) * 32;
-  const bool large = (int64_t)N * Kp * 2 >= (8 << 20);   // a weight matrix that takes several microseconds to stream
+  const bool large = large_matrix(N, Kp);
   // One row per chain against a large matrix: a stream of the weights, K split over workgroups.  64 x 64 tiles and a K split
   // that gives every CU a workgroup keep ~14 MB of it in flight, which is what HBM latency asks for; only a large matrix
   // repays the second launch.  (The split is a matter of the sizes alone, and the kernel for few rows adds its parts up
   // the same way: the bits do not depend on which of them runs.)
   typedef typename MlpTiles<PL>::T64x64 T;
-  int splits = 1;
-  if (call == 0 && large && n <= sc.rows) {
-    const int64_t tiles = ceil_div(n, T::BM) * ceil_div(N, T::BN);
-    while (splits < kMaxSplits && tiles * splits < 256 && (Kp / 64) % (2 * splits) == 0) splits *= 2;
-  }
+  const int splits = call == 0 && n <= sc.rows ? draft_splits(n, N, Kp) : 1;
   const int few = pick_few_tile(n, N, splits);
   if (few >= 0) return mlp_gemm_few<PL>(few, n_dev, n, N, K, A, Wt, e, st, splits);
   if (call == 0) {
@@ -135,14 +142,27 @@ static hipError_t mlp_gemm_planes(int call, const int* n_dev, int n, int N, int 
     if (e0 != hipSuccess) return e0;
     m_lo = kSmallVerifyRows;
   }
-  return mlp_gemm_tile<PL, 1>(pick_tile(PL, n, N, Kp), n_dev, n, N, K, A, Wt, e, st, m_lo, 0x7fffffff);
+  return mlp_gemm_tile<PL, 1>(pick_tile(PL, likely, N, Kp), n_dev, n, N, K, A, Wt, e, st, m_lo, 0x7fffffff);
 }
 
 template <class Epi>
-static hipError_t mlp_gemm(int call, const int* n_dev, int n, int N, int K, SlabMat A, SlabMat Wt, Epi e, hipStream_t st,
+static hipError_t mlp_gemm(const RowPlan& rows, int N, int K, SlabMat A, SlabMat Wt, Epi e, hipStream_t st,
                            const SplitScratch& sc) {
-  return A.plane > 0 ? mlp_gemm_planes<2>(call, n_dev, n, N, K, A, Wt, e, st, sc)
-                     : mlp_gemm_planes<1>(call, n_dev, n, N, K, A, Wt, e, st, sc);
+  const int likely = rows.likely > 0 ? std::min(rows.likely, rows.n) : rows.n;
+  return A.plane > 0 ? mlp_gemm_planes<2>(rows.call, rows.n_dev, rows.n, likely, N, K, A, Wt, e, st, sc)
+                     : mlp_gemm_planes<1>(rows.call, rows.n_dev, rows.n, likely, N, K, A, Wt, e, st, sc);
+}
+
+// A product of `rows` rows in microseconds, by the figures at pick_tile and pick_few_tile; one that is split over K streams
+// its weights at 2.4 TB/s and adds its parts in 5 us.
+static double product_cost(int planes, int call, int rows, int N, int K) {
+  const int Kp = slab_count(K) * 32, splits = call == 0 ? draft_splits(rows, N, Kp) : 1;
+  const int few = pick_few_tile(rows, N, splits);
+  if (few >= 0) return (few == 0 ? 1.5 : 2.0) + (planes == 2 ? 3.6 : 2.5) * (few == 0 ? 1.0 : 1.6) * Kp / 1024.0;
+  if (splits > 1) return 2e-6 * N * Kp / 2.4 + 5.0;
+  float t;
+  (void)pick_tile(planes, rows, N, Kp, &t);
+  return t;
 }
 
 struct MlpState {
@@ -397,6 +417,13 @@ PackOut mlp_pack_out(const asd_ctx* ctx) {
   return PackOut{s->in_bf, s->rows_pad * 32, s->in_plane, s->temb, s->E, ctx->d};
 }
 
+double mlp_call_cost(const asd_ctx* ctx, int call, int rows) {
+  const MlpState* s = ctx->mlp;
+  const int p = s->act_terms, W = s->width;
+  return product_cost(p, call, rows, W, s->in_dim) + s->n_blocks * product_cost(p, call, rows, W, W) +
+         product_cost(p, call, rows, ctx->d, W);
+}
+
 asd_status mlp_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
   MlpState* s = ctx->mlp;
   const int n = rows.n, d = ctx->d, W = s->width;
@@ -415,7 +442,7 @@ asd_status mlp_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
   SlabMat h[2] = {{s->hb[0], s->rows_pad, s->h_plane}, {s->hb[1], s->rows_pad, s->h_plane}};
   {
     ProfScope ps(ctx, ASD_PROF_MLP_GEMM_IN, rows.call, st);
-    ASD_HIP(mlp_gemm(rows.call, rows.n_dev, n, W, s->in_dim, in, SlabMat{s->wp_in, w_rows, 0},
+    ASD_HIP(mlp_gemm(rows, W, s->in_dim, in, SlabMat{s->wp_in, w_rows, 0},
                      InEpi{s->h, s->hb[0], s->b_in, W, slab, s->h_plane}, st, s->split));
   }
   int cur = 0;
@@ -423,13 +450,13 @@ asd_status mlp_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
   for (int l = 0; l < s->n_blocks; ++l) {
     ProfScope ps(ctx, ASD_PROF_MLP_GEMM_BLK, rows.call, st);
     const BlockEpi e{s->h, s->hb[cur ^ 1], s->b_blk ? s->b_blk + (size_t)l * W : nullptr, W, slab, s->h_plane};
-    ASD_HIP(mlp_gemm(rows.call, rows.n_dev, n, W, W, h[cur], SlabMat{s->wp_blk + l * blk, w_rows, 0}, e, st, s->split));
+    ASD_HIP(mlp_gemm(rows, W, W, h[cur], SlabMat{s->wp_blk + l * blk, w_rows, 0}, e, st, s->split));
     cur ^= 1;
   }
   {
     ProfScope ps(ctx, ASD_PROF_MLP_GEMM_OUT, rows.call, st);
     const OutEpi e{rows.out_base, rows.out_off, s->b_out, s->out_clip, s->eps_coef, rows.tau, rows.in_base, rows.in_off};
-    ASD_HIP(mlp_gemm(rows.call, rows.n_dev, n, d, W, h[cur], SlabMat{s->wp_out, slab_rows(d), 0}, e, st, s->split));
+    ASD_HIP(mlp_gemm(rows, d, W, h[cur], SlabMat{s->wp_out, slab_rows(d), 0}, e, st, s->split));
   }
   return ASD_OK;
 }

@@ -26,10 +26,13 @@ __device__ __forceinline__ void pack_temb(const PackOut& p, int64_t row, int tau
 __global__ void init_state_kernel(int B, int K, int d, const Key* __restrict__ key_p, const float* __restrict__ y0,
                                   float* __restrict__ traj, int32_t* __restrict__ a,
                                   int32_t* __restrict__ rounds, int32_t* __restrict__ round_idx, int L,
-                                  int32_t* __restrict__ win, int32_t* __restrict__ carry, PlanOut plan) {
+                                  int32_t* __restrict__ win, int32_t* __restrict__ carry, Pieces pieces, PlanOut plan) {
   const int c = blockIdx.x;
   const Key key = *key_p;
-  if (c == 0 && threadIdx.x == 0 && round_idx) *round_idx = 0;
+  if (c == 0 && threadIdx.x == 0 && round_idx) {
+    round_idx[0] = 0;
+    round_idx[kLiveMaxRounds] = 0;
+  }
   if (plan.in_off && threadIdx.x == 0) {  // the draft call of round 0: y_0 of every chain
     plan.in_off[c] = (int64_t)c * (K + 1) * d;
     plan.out_off[c] = (int64_t)c * d;
@@ -58,6 +61,11 @@ __global__ void init_state_kernel(int B, int K, int d, const Key* __restrict__ k
       win[B + c] = 4 * L;
       win[c] = window_of(4 * L, L);
     }
+    if (pieces.state) {
+      pieces.state[c] = 0;
+      pieces.state[B + c] = 4 * L;
+      pieces.state[2 * B + c] = 0;
+    }
   }
 }
 
@@ -79,7 +87,7 @@ static PlanOut plan_out(asd_ctx* ctx, int32_t* ring) {
 asd_status launch_init_state(asd_ctx* ctx, const float* y0, float* traj, int32_t* a, int32_t* rounds,
                              hipStream_t st) {
   hipLaunchKernelGGL(init_state_kernel, dim3(ctx->B), dim3(256), 0, st, ctx->B, ctx->K, ctx->d, ctx->key_dev, y0,
-                     traj, a, rounds, ctx->live, ctx->L, ctx->cur_win, ctx->carry, plan_out(ctx, nullptr));
+                     traj, a, rounds, ctx->live, ctx->L, ctx->cur_win, ctx->carry, ctx->cur_pieces, plan_out(ctx, nullptr));
   ASD_HIP(hipGetLastError());
   return ASD_OK;
 }
@@ -242,7 +250,8 @@ asd_status launch_plan_verify(asd_ctx* ctx, const int32_t* a, hipStream_t st, co
 // ----------------------------------------------------------------------------
 // What the draft kernel does for the rest of the round when the plans are folded in (PlanOut), by one wavefront per chain.
 // Returns the place of the chain's first row in the list.
-__device__ __forceinline__ int draft_books(int c, int lane, int K, int Lwin, int d, int ac, int w, bool live,
+// lo, hi: the slots of the window this launch drafts (0 and the window's length, or a piece of it).
+__device__ __forceinline__ int draft_books(int c, int lane, int K, int Lwin, int d, int ac, int lo, int hi, bool live,
                                             const PlanOut& plan, int extra) {
   // Bookkeeping of the round, once: the draft call has consumed its row count; the round index
   // advances and this round's slot of the live-chain ring starts at zero (the accept kernel adds to it).
@@ -255,9 +264,11 @@ __device__ __forceinline__ int draft_books(int c, int lane, int K, int Lwin, int
       plan.ring[1 + kLiveRing + (r % kLiveRing)] = 0;
     }
   }
-  // This chain's rows of the verify call: the drafted samples of slots 1..w-1, read in place from the
-  // trajectory, results to x0hat[c][slot].  One atomic add reserves the range; the wavefront fills it.
-  const int cnt = w - 1 + ((extra && live && ac + w < K) ? 1 : 0);
+  // This chain's rows of the verify call: the drafted samples of slots 1..w-1 (of a piece: lo..hi-1, slot lo having been
+  // drafted with the piece before it), read in place from the trajectory, results to x0hat[c][slot].  One atomic add
+  // reserves the range; the wavefront fills it.
+  const int first = max(lo, 1);
+  const int cnt = hi - first + ((extra && live && ac + hi < K) ? 1 : 0);
   int base = 0;
   if (cnt > 0) {
     if (lane == 0) {
@@ -265,12 +276,12 @@ __device__ __forceinline__ int draft_books(int c, int lane, int K, int Lwin, int
       if (plan.row_counts) atomicAdd((unsigned long long*)&plan.row_counts[1], (unsigned long long)cnt);
     }
     base = __shfl(base, 0, 64);
-    for (int s = 1 + lane; s <= cnt; s += 64) {
-      const int i = ac + s;
-      plan.in_off[base + s - 1] = ((int64_t)c * (K + 1) + i) * d;
-      plan.out_off[base + s - 1] = ((int64_t)c * (Lwin + extra) + s) * d;
-      plan.row_tau[base + s - 1] = plan.tau[i];
-      plan.row_chain[base + s - 1] = c;
+    for (int r = lane; r < cnt; r += 64) {
+      const int s = first + r, i = ac + s;
+      plan.in_off[base + r] = ((int64_t)c * (K + 1) + i) * d;
+      plan.out_off[base + r] = ((int64_t)c * (Lwin + extra) + s) * d;
+      plan.row_tau[base + r] = plan.tau[i];
+      plan.row_chain[base + r] = c;
     }
   }
   return base;
@@ -284,7 +295,7 @@ __global__ __launch_bounds__(256) void draft_kernel(int K, int Lwin, int d, cons
                                                     const float* __restrict__ sigma,
                                                     const float* __restrict__ x0a, float* __restrict__ traj,
                                                     const int32_t* __restrict__ win, PlanOut plan, int extra,
-                                                    const int32_t* __restrict__ pending) {
+                                                    const int32_t* __restrict__ pending, Pieces pieces) {
   // extra (FOLD only): 1 = the verify call also evaluates yhat_b of a window that ends before K (slot w of
   // x0hat, which then has Lwin + 1 slots per chain).  pending (or NULL; not with FOLD): chains with pending[c] == 0
   // have had their round already (accept_early_kernel).
@@ -294,14 +305,16 @@ __global__ __launch_bounds__(256) void draft_kernel(int K, int Lwin, int d, cons
   const int ac = a[c];
   const bool live = ac < K && ac >= 0 && !(pending && !pending[c]);
   const int w = live ? min(win ? win[c] : Lwin, K - ac) : 0;
-  if (FOLD && blockIdx.x == 0 && threadIdx.x < 64) (void)draft_books(c, threadIdx.x, K, Lwin, d, ac, w, live, plan, extra);
+  const PieceRange pr = live ? piece_range(pieces, c, gridDim.y, Lwin, w) : PieceRange{0, 0};
+  if (FOLD && blockIdx.x == 0 && threadIdx.x < 64)
+    (void)draft_books(c, threadIdx.x, K, Lwin, d, ac, pr.lo, pr.hi, live, plan, extra);
   if (blk >= nblk || !live) return;
   const Key key = *key_p;
   const bool vec = (d & 3) == 0;
-  float* row = traj + ((int64_t)c * (K + 1) + ac) * d;
+  float* row = traj + ((int64_t)c * (K + 1) + ac + pr.lo) * d;
   float4 y = load4(row, blk, d, vec);
   const float4 g = load4(x0a + (int64_t)c * d, blk, d, vec);
-  for (int k = 0; k < w; ++k) {
+  for (int k = pr.lo; k < pr.hi; ++k) {
     const int i = ac + k;
     const float cx = c_x[i], c0 = c_0[i], sg = sigma[i];
     const float4 xi = normal4(key, (uint32_t)c, (uint32_t)(i + 1), (uint32_t)blk);
@@ -329,7 +342,7 @@ __global__ __launch_bounds__(1024) void draft_split_kernel(int K, int Lwin, int 
                                                            const float* __restrict__ sigma,
                                                            const float* __restrict__ x0a, float* __restrict__ traj,
                                                            const int32_t* __restrict__ win, PlanOut plan, int extra,
-                                                           const int32_t* __restrict__ pending) {
+                                                           const int32_t* __restrict__ pending, Pieces pieces) {
   // (packs the rows it lists if the row is one wavefront wide: draft_packs_rows)
   __shared__ float4 s_xi[kDraftChunk][64];
   __shared__ int s_base;
@@ -339,19 +352,23 @@ __global__ __launch_bounds__(1024) void draft_split_kernel(int K, int Lwin, int 
   const int nblk = (d + 3) >> 2;
   const int ac = a[c];
   const bool live = ac < K && ac >= 0 && !(pending && !pending[c]);
-  const int w = live ? min(win ? win[c] : Lwin, K - ac) : 0;
+  const int w_all = live ? min(win ? win[c] : Lwin, K - ac) : 0;
+  const PieceRange pr = live ? piece_range(pieces, c, gridDim.y, Lwin, w_all) : PieceRange{0, 0};
   // (the last wavefront: the first has the walk to do)
   if (FOLD && blockIdx.x == 0 && wave == nw - 1) {
-    const int b = draft_books(c, lane, K, Lwin, d, ac, w, live, plan, extra);
+    const int b = draft_books(c, lane, K, Lwin, d, ac, pr.lo, pr.hi, live, plan, extra);
     if (lane == 0) s_base = b;
   }
   if (!live) return;
   const bool pack = FOLD && plan.pack.in_bf && gridDim.x == 1;
-  const int listed = w - 1 + ((extra && ac + w < K) ? 1 : 0);
+  // a0: the step the walk starts at; its k-th row (slot lo + k + 1) is number k + skip of the rows listed, of which there
+  // are `listed` -- a piece that is not a window's first also lists the row it starts from
+  const int w = pr.hi - pr.lo, a0 = ac + pr.lo, skip = pr.lo > 0 ? 1 : 0;
+  const int listed = pr.hi - max(pr.lo, 1) + ((extra && ac + pr.hi < K) ? 1 : 0);
   const Key key = *key_p;
   const bool vec = (d & 3) == 0;
   const bool mine = blk < nblk;
-  float* row = traj + ((int64_t)c * (K + 1) + ac) * d;
+  float* row = traj + ((int64_t)c * (K + 1) + a0) * d;
   float4 y = make_float4(0.f, 0.f, 0.f, 0.f), g = y;
   if (wave == 0 && mine) {
     y = load4(row, blk, d, vec);
@@ -362,16 +379,20 @@ __global__ __launch_bounds__(1024) void draft_split_kernel(int K, int Lwin, int 
     // lane k holds the coefficients of the chunk's slot k
     float cxv = 0.f, c0v = 0.f, sgv = 0.f;
     if (wave == 0 && lane < n) {
-      cxv = c_x[ac + base + lane];
-      c0v = c_0[ac + base + lane];
-      sgv = sigma[ac + base + lane];
+      cxv = c_x[a0 + base + lane];
+      c0v = c_0[a0 + base + lane];
+      sgv = sigma[a0 + base + lane];
     }
     if (base > 0) __syncthreads();   // the walk is done with the last chunk
-    for (int k = wave; k < n; k += nw) s_xi[k][lane] = normal4(key, (uint32_t)c, (uint32_t)(ac + base + k + 1), (uint32_t)blk);
+    for (int k = wave; k < n; k += nw) s_xi[k][lane] = normal4(key, (uint32_t)c, (uint32_t)(a0 + base + k + 1), (uint32_t)blk);
     __syncthreads();
     if (pack && wave > 0)
       for (int k = wave - 1; k < n; k += nw - 1)
-        if (base + k < listed) pack_temb(plan.pack, s_base + base + k, plan.tau[ac + base + k + 1], lane, 64);
+        if (base + k + skip < listed) pack_temb(plan.pack, s_base + base + k + skip, plan.tau[a0 + base + k + 1], lane, 64);
+    if (pack && skip && base == 0 && wave == 0) {
+      if (mine) pack_row4(plan.pack, s_base, blk, y);
+      pack_temb(plan.pack, s_base, plan.tau[a0], lane, 64);
+    }
     if (wave == 0 && mine) {
       for (int k0 = 0; k0 < n; k0 += 4) {
         float4 xi[4];
@@ -389,7 +410,7 @@ __global__ __launch_bounds__(1024) void draft_split_kernel(int K, int Lwin, int 
           y.w = fmaf(sg, xi[u].w, fmaf(cx, y.w, c0 * g.w));
           row += d;
           store4(row, blk, d, vec, y);
-          if (pack && base + k0 + u < listed) pack_row4(plan.pack, s_base + base + k0 + u, blk, y);
+          if (pack && base + k0 + u + skip < listed) pack_row4(plan.pack, s_base + base + k0 + u + skip, blk, y);
         }
       }
     }
@@ -422,13 +443,14 @@ asd_status launch_draft(asd_ctx* ctx, float* traj, const int32_t* a, hipStream_t
     const dim3 sgrid((unsigned)ceil_div(nblk, 64), (unsigned)ctx->B);
     hipLaunchKernelGGL(plan.in_off ? draft_split_kernel<true> : draft_split_kernel<false>, sgrid, dim3(64 * share), 0, st,
                        ctx->K, ctx->L, ctx->d, ctx->key_dev, a, ctx->c_x, ctx->c_0, ctx->sigma, ctx->x0a, traj, ctx->cur_win,
-                       plan, plan.in_off && ctx->reuse_now ? 1 : 0, plan.in_off ? (const int32_t*)nullptr : pending);
+                       plan, plan.in_off && ctx->reuse_now ? 1 : 0, plan.in_off ? (const int32_t*)nullptr : pending, ctx->cur_pieces);
   } else if (plan.in_off)
     hipLaunchKernelGGL(draft_kernel<true>, grid, dim3(threads), 0, st, ctx->K, ctx->L, ctx->d, ctx->key_dev, a, ctx->c_x,
-                       ctx->c_0, ctx->sigma, ctx->x0a, traj, ctx->cur_win, plan, ctx->reuse_now ? 1 : 0, (const int32_t*)nullptr);
+                       ctx->c_0, ctx->sigma, ctx->x0a, traj, ctx->cur_win, plan, ctx->reuse_now ? 1 : 0, (const int32_t*)nullptr,
+                       ctx->cur_pieces);
   else
     hipLaunchKernelGGL(draft_kernel<false>, grid, dim3(threads), 0, st, ctx->K, ctx->L, ctx->d, ctx->key_dev, a, ctx->c_x,
-                       ctx->c_0, ctx->sigma, ctx->x0a, traj, ctx->cur_win, plan, 0, pending);
+                       ctx->c_0, ctx->sigma, ctx->x0a, traj, ctx->cur_win, plan, 0, pending, Pieces{});
   ASD_HIP(hipGetLastError());
   return ASD_OK;
 }
@@ -535,7 +557,7 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
                                                       int32_t* __restrict__ rounds, int32_t* __restrict__ live,
                                                       int32_t* __restrict__ win, PlanOut plan,
                                                       int64_t* __restrict__ prof_counts,
-                                                      const int32_t* __restrict__ pending) {
+                                                      const int32_t* __restrict__ pending, Pieces pieces) {
   // pending (or NULL): chains with pending[c] == 0 have had their round already (accept_early_kernel)
   __shared__ float s_part[kAcceptChunkMax][16][2];  // per slot of the chunk, per wavefront: partial <D,xi>, |D|^2
   __shared__ float s_rej[2];                     // <D,xi>, |D|^2 of the first rejected slot
@@ -550,7 +572,11 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
   const int ac = a[c];
   // the verify call has consumed its row count: the draft kernel of the next round starts from zero
   if constexpr (FOLD) {
-    if (c == 0 && tid == 0) plan.n_rows[1] = 0;
+    if (c == 0 && tid == 0) {
+      // (how many there were tells the host which tiles suit the next ones)
+      if (pieces.state && live) live[1 + kLiveRing + ((live[0] - 1) % kLiveRing)] = plan.n_rows[1];
+      plan.n_rows[1] = 0;
+    }
   }
   if (ac >= K || ac < 0) {
     if (tid == 0 && accepted) accepted[c] = -1;
@@ -558,7 +584,10 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
   }
   if (pending && !pending[c]) return;
   const Key key = *key_p;
-  const int w = min(win ? win[c] : L, K - ac);
+  // (of a window taken in pieces, slots lo .. w - 1 of the w_all there are; else lo is 0 and w all of it)
+  const int w_all = min(win ? win[c] : L, K - ac);
+  const PieceRange pr = piece_range(pieces, c, gridDim.x, L, w_all);
+  const int lo = pr.lo, w = pr.hi;
   const int nblk = (d + 3) >> 2;
   const bool vec = (d & 3) == 0;
   const float* g_a = x0a + (int64_t)c * d;
@@ -585,8 +614,8 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
 
   int n_acc = w;
   int examined = 0;   // slots whose x0hat row was read for the test
-  for (int base = 0; base < w; base += chunk) {
-    examined = min(w, base + chunk) - 1;
+  for (int base = lo; base < w; base += chunk) {
+    examined = min(w, base + chunk) - max(lo, 1);
     // one lane per slot of the chunk, for the test below: what does not depend on the sums (where a slot's latency is what
     // counts, ahead of them)
     float logu = 0.f, sg_t = 0.f, c0_t = 0.f;
@@ -683,11 +712,13 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
     }
   }
 
-  const int a_next = n_acc < w ? ac + n_acc + 1 : ac + w;
+  // a piece whose slots were all accepted, and not the window's last: the chain's window goes on with the next one
+  const bool goes_on = n_acc == w && w < w_all;
+  const int a_next = goes_on ? ac : n_acc < w ? ac + n_acc + 1 : ac + w;
   // whole window accepted, and the model value at yhat_b is there (see below)
-  const bool carried = carry && n_acc == w && a_next < K;
+  const bool carried = carry && n_acc == w && !goes_on && a_next < K;
   // this chain's row of the next round's draft call
-  [[maybe_unused]] const bool lists = FOLD && a_next < K && !carried;
+  [[maybe_unused]] const bool lists = FOLD && a_next < K && !carried && !goes_on;
   // its place in the list (thread 0).  A row that is packed needs it behind the resampling, so it is asked for now; else
   // last: all chains add to one word, and thousands of them that end together queue there while holding their CU (2048
   // chains, d 64, L 4: accept 72 us asked for here, 65 below).
@@ -742,12 +773,22 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
       if (n_acc < w) atomicAdd((unsigned long long*)&prof_counts[3], 1ull);
     }
     if (accepted) accepted[c] = n_acc;
-    if (rounds) rounds[c] += 1;
+    if (rounds && !goes_on) rounds[c] += 1;
     if (win) {
       const int B = gridDim.x;
       const int st = window_next(win[B + c], w, n_acc);
       win[B + c] = st;
       win[c] = window_of(st, L);
+    }
+    if (pieces.state) {
+      const int B = gridDim.x;
+      pieces.state[c] = goes_on ? w : 0;
+      if (!goes_on) {
+        pieces.state[B + c] = window_next(pieces.state[B + c], w_all, n_acc);
+        const int r = pieces.state[2 * B + c] + 1;
+        pieces.state[2 * B + c] = r;
+        if (live && a_next >= K) atomicMax(&live[kLiveMaxRounds], r);
+      }
     }
     // the round index was advanced at the start of this round
     if (live && a_next < K) atomicAdd(&live[1 + ((live[0] - 1) % kLiveRing)], 1);
@@ -1084,7 +1125,7 @@ asd_status launch_accept(asd_ctx* ctx, float* traj, int32_t* a, const float* x0h
   const auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(ctx->B), dim3(64 * waves * groups), 0, st, ctx->K, ctx->L, ctx->d, ctx->key_dev, a, ctx->c_0,
                        ctx->sigma, ctx->x0a, carry, x0hat, x0_slots, traj, accepted, stats, rounds, live, ctx->cur_win, plan,
-                       prof_counts, pending);
+                       prof_counts, pending, ctx->cur_pieces);
   };
   if (plan.in_off) {
     if (groups >= 8) go(accept_kernel<true, 1>);

@@ -301,3 +301,35 @@ def test_split_sums_do_not_depend_on_the_kernel(terms):
         ctx.close()
         values.append(x0hat[:24, 0].clone())
     assert bool(torch.isfinite(values[0]).all()) and torch.equal(values[0], values[1])
+
+
+@pytest.mark.parametrize("d, E, width, blocks, K, L, chains, terms", [
+    (112, 16, 1024, 2, 60, 16, 256, 2),      # the draft kernel packs what it lists; accept chunks as long as a window
+    (264, 24, 1024, 1, 90, 37, 200, 1),      # rows of two wavefronts, packed by a kernel of its own; chunks of eight slots
+    (1032, 16, 2056, 1, 50, 24, 64, 2),      # a draft call that is split over K
+    (16, 8, 2048, 2, 40, 7, 2200, 2),        # a wavefront a chain throughout
+])
+def test_windows_in_pieces_change_no_bit(d, E, width, blocks, K, L, chains, terms):
+    """Whole samples with windows taken in pieces and whole, as graphs and plain launches: the same trajectories, round
+    counts and number of rounds, from fewer model rows."""
+    cfg = dict(kind="mlp", d=d, E=E, width=width, n_blocks=blocks, K=K, L=L, act_terms=terms)
+    _, p, _ = oracle_setup(cfg)
+    ctx = runtime.open_ctx(cfg, p, seed=0, chains=chains)
+    runs = []
+    for pieces, graphs, profile in ((False, True, False), (True, True, False), (True, False, False), (False, True, True), (True, True, True)):
+        ctx.use_window_pieces(pieces)
+        ctx.use_graphs(graphs)
+        ctx.profile_enable(profile)
+        ctx.set_seed(6)
+        traj = torch.full((chains, K + 1, d), float("nan"), device=DEV)
+        rounds = torch.zeros(chains, dtype=torch.int32, device=DEV)
+        n = ctx.sample(traj, rounds)
+        torch.cuda.synchronize()
+        runs.append((traj, rounds, n, ctx.profile_rows()))
+    ctx.close()
+    traj, rounds, n, _ = runs[0]
+    assert bool(torch.isfinite(traj).all()) and n == int(rounds.max())
+    for t, r, m, _ in runs[1:]:
+        assert m == n and torch.equal(r, rounds) and torch.equal(t, traj)
+    (starts, whole), (starts_p, pieces) = runs[3][3], runs[4][3]
+    assert starts == starts_p == int(rounds.sum()) and pieces < 0.8 * whole
