@@ -158,8 +158,8 @@ static asd_status build(asd_ctx* ctx, const asd_config* cfg) {
   ASD_HIP(hipMemset(ctx->live, 0, sizeof(int32_t) * kLiveInts));
   ASD_HIP(hipMalloc(&ctx->win, sizeof(int32_t) * 2 * (size_t)ctx->B));
   ASD_HIP(hipMalloc(&ctx->piece_state, sizeof(int32_t) * 3 * (size_t)ctx->B));
-  ASD_HIP(hipMalloc(&ctx->chain_max, sizeof(unsigned long long)));
-  ASD_HIP(hipMemset(ctx->chain_max, 0, sizeof(unsigned long long)));
+  ASD_HIP(hipMalloc(&ctx->chain_max, 2 * sizeof(unsigned long long)));
+  ASD_HIP(hipMemset(ctx->chain_max, 0, 2 * sizeof(unsigned long long)));
   ASD_HIP(hipMalloc(&ctx->key_dev, sizeof(Key)));
   ASD_HIP(hipMemcpy(ctx->key_dev, &ctx->key, sizeof(Key), hipMemcpyHostToDevice));
   ASD_HIP(hipHostMalloc((void**)&ctx->live_host, sizeof(int32_t) * (kLiveInts - 1), hipHostMallocDefault));
@@ -515,10 +515,9 @@ asd_status asd_sample(asd_ctx* ctx, const float* y0, float* traj, int32_t* round
   hipStream_t st = (hipStream_t)stream;
   // Small mixtures: the whole sample is one launch, a workgroup per chain (profiling wants the
   // stand-alone kernels, whose times it reports).
-  if (ctx->resident_enabled && !ctx->prof.on && gmm_chain_supported(ctx)) {
-    ASD_TRY(flush_key(ctx, st));
+  // (The key travels as an argument there: no launch for it.)
+  if (ctx->resident_enabled && !ctx->prof.on && gmm_chain_supported(ctx))
     return gmm_chain_sample(ctx, y0, traj, rounds, st);
-  }
   return sample_rounds(ctx, y0, traj, rounds, ctx->x0hat, true, st);
 }
 

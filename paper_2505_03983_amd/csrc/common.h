@@ -160,7 +160,7 @@ struct asd_ctx {
   hipStream_t g_stream = nullptr;
   hipStream_t own_stream = nullptr;  // used instead of the legacy default stream, which cannot be captured
   bool graphs_enabled = true;
-  unsigned long long* chain_max = nullptr;  // DEV: (launch id << 32 | largest round count) of the chain-resident sampler
+  unsigned long long* chain_max = nullptr;  // DEV [2]: RoundsOut of the chain-resident sampler (gmm_chain.hip)
   uint32_t chain_launches = 0;
   int32_t* win = nullptr;      // DEV [2 B]: window of each chain, then the controller's state (asd_sample, adaptive)
   int32_t* cur_win = nullptr;  // what the round kernels are given: win while an adaptive sample runs, else NULL (= L)

@@ -21,11 +21,31 @@
 // from LDS.  The formulas and the counters are those of the stand-alone kernels,
 // so the same parity bars apply.  Every wavefront leaves the loop when its chain
 // reaches K, which takes at most K rounds.
+//
+// Mixtures of a few numbers have a kernel of their own, a wavefront per chain (gmm_wave_sample_kernel, below).
 #include "common.h"
 #include "device_util.h"
 #include "gmm_state.h"
 
 namespace asd {
+
+// Where a launch leaves its largest round count: (launch id, rounds) packed, so that the maximum needs no reset between
+// samples, and a count of the chains that have reported; the last of them hands the result to the host (a copy behind the
+// kernel was 4 us of the sample).
+struct RoundsOut {
+  unsigned long long* state;   // DEV [2]: the maximum; chains reported, over all launches of the context
+  uint32_t* host;              // the result, in pinned host memory
+  uint32_t launch_id;
+  __device__ __forceinline__ void report(int R, int chains) const {
+    atomicMax(state, ((unsigned long long)launch_id << 32) | (unsigned)R);
+    __threadfence();
+    if ((atomicAdd(state + 1, 1ull) + 1ull) % (unsigned)chains == 0) {
+      __threadfence();
+      const unsigned long long m = __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(host, (uint32_t)m, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  }
+};
 
 namespace {
 
@@ -255,12 +275,11 @@ __device__ __forceinline__ void gmm_eval_row(int slot, int a, const ChainLayout&
 }  // namespace
 
 __global__ __launch_bounds__(1024) void gmm_chain_sample_kernel(
-    int K, int L, int d, int C, const Key* __restrict__ key_p, const float* __restrict__ c_x,
+    int K, int L, int d, int C, Key key, const float* __restrict__ c_x,
     const float* __restrict__ c_0, const float* __restrict__ sigma, const int32_t* __restrict__ tau,
     const float4* __restrict__ coef_tau, const float* __restrict__ means, const float* __restrict__ musq,
     const float* __restrict__ log_w, const float* __restrict__ y0, float* __restrict__ traj,
-    int32_t* __restrict__ rounds, unsigned long long* __restrict__ max_rounds, uint32_t launch_id,
-    int adaptive) {
+    int32_t* __restrict__ rounds, RoundsOut out, int adaptive) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
   __shared__ float s_logu[64], s_dot[64], s_vv[64], s_sc[64];
   __shared__ int s_bit[64];
@@ -280,7 +299,6 @@ __global__ __launch_bounds__(1024) void gmm_chain_sample_kernel(
   float* yh = lds + l.yh;
   float* x0 = lds + l.x0;
   float* xi_l = lds + l.xi;
-  const Key key = *key_p;
   // The schedule and the denoiser's per-step coefficients: a round would otherwise start with a chain
   // of dependent global loads (tau_a, then its coefficients) and reload the tables step by step.
   const float4* sch = reinterpret_cast<const float4*>(lds + l.sch);
@@ -436,8 +454,291 @@ __global__ __launch_bounds__(1024) void gmm_chain_sample_kernel(
   }
   if (tid == 0) {
     if (rounds) rounds[c] = R;
-    // (launch id, rounds) packed so that the maximum needs no reset between samples
-    atomicMax(max_rounds, ((unsigned long long)launch_id << 32) | (unsigned)R);
+    out.report(R, gridDim.x);
+  }
+}
+
+// ----------------------------------------------------------------------------
+// Mixtures of a few numbers: a chain is one wavefront, and nothing in its loop is shared.
+//
+// What bounds the kernel above on such a shape is its thirteen stages a round, each an LDS round trip and a barrier of
+// mostly idle wavefronts (9 us a round at d 2, C 4, L 8, of which the arithmetic is a few hundred cycles).  Here a slot of
+// the window is a lane -- G = 64 / (slots, rounded up to a power of two) lanes, which share its components -- so the model
+// value of every slot, its accept test and the scan over the slots are register arithmetic, and the only barrier is the
+// one behind the set-up.  The noise of a chain depends on its steps only: the set-up generates it, and log u, for all K
+// steps with every thread of the workgroup (four wavefronts at least; those without a chain then leave).  A round is
+//   x0a by every slot's lanes alike; the draft by a lane per coordinate; the verify call, a slot per lane; the test; one
+//   ballot; the reflection by the lanes of the coordinates, which keep y_a in a register; the rows the chain keeps go to
+//   the trajectory (those behind the first rejection would be written again by the next round).
+// Measured, microseconds a sample with its launch and the wait for it, a workgroup / a wavefront a chain, (d, C, L, K, chains):
+// (2, 4, 8, 100, 8) 138 / 55, K = 1000 922 / 269; (4, 16, 16, 200, 64) 217 / 96; (12, 16, 10, 200, 8) 237 / 160; (2, 4, 8, 100, 20000)
+// 1878 / 785.
+// LDS operations of a wavefront complete in order; wave_lds_fence keeps the compiler to it.
+// ----------------------------------------------------------------------------
+namespace {
+
+constexpr int kWaveBlocks = 4;   // d <= 16
+
+struct WaveLayout {
+  int dq, lanes, per_lane;     // floats of a padded row; lanes a slot's components are shared by; components a lane has
+  size_t m, ql, sch, chain;    // offsets in floats; first chain's part
+  size_t xi, logu, yh, ps, chain_floats;   // offsets within a chain's part; its size
+};
+
+__host__ __device__ inline WaveLayout wave_layout(int C, int d, int L, int K) {
+  WaveLayout l;
+  l.dq = (d + 3) & ~3;
+  int slots = 4;
+  while (slots < L) slots *= 2;
+  l.lanes = 64 / slots;
+  l.per_lane = (C + l.lanes - 1) / l.lanes;
+  l.m = 0;                                  // [C][dq] means, columns past d zero
+  l.sch = l.m + (size_t)C * l.dq;           // [K][8] (c_x, c_0, sigma, -, kappa, gamma, cx, cm) of step i
+  l.ql = l.sch + (size_t)K * 8;             // [C][2] |mu|^2, log w
+  l.chain = l.ql + (((size_t)C * 2 + 3) & ~(size_t)3);
+  l.xi = 0;                                 // [K][dq] xi_{i+1}, columns past d zero
+  l.yh = l.xi + (size_t)K * l.dq;           // [L+1][dq] yhat_a (= y_a) .. yhat_b
+  l.ps = l.yh + (size_t)(L + 1) * l.dq;     // [per_lane][64] logits
+  l.logu = l.ps + (size_t)l.per_lane * 64;  // [K] log u_{i+1}
+  l.chain_floats = l.logu + (((size_t)K + 3) & ~(size_t)3);
+  return l;
+}
+
+__device__ __forceinline__ void wave_lds_fence() { asm volatile("" ::: "memory"); }
+
+template <int MASK>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), MASK, 0xf, 0xf, true));
+}
+// Sum and maximum over groups of n (1, 2, 4, 8, 16) neighbouring lanes, in every lane (the steps of wave_sum).
+__device__ __forceinline__ float group_sum(float v, int n) {
+  if (n > 1) v += dpp<0xB1>(v);
+  if (n > 2) v += dpp<0x4E>(v);
+  if (n > 4) v += dpp<0x141>(v);
+  if (n > 8) v += dpp<0x140>(v);
+  return v;
+}
+__device__ __forceinline__ float group_max(float v, int n) {
+  if (n > 1) v = fmaxf(v, dpp<0xB1>(v));
+  if (n > 2) v = fmaxf(v, dpp<0x4E>(v));
+  if (n > 4) v = fmaxf(v, dpp<0x141>(v));
+  if (n > 8) v = fmaxf(v, dpp<0x140>(v));
+  return v;
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+// component e (0 .. 4 DB - 1, a lane's own) of a row in registers
+template <int DB>
+__device__ __forceinline__ float pick(const float (&v)[4 * DB], int e) {
+  float r = v[0];
+#pragma unroll
+  for (int j = 1; j < 4 * DB; ++j) r = e == j ? v[j] : r;
+  return r;
+}
+
+}  // namespace
+
+// DB: blocks of four coordinates in a row.  Chains blockIdx.x cpw .. + cpw - 1, a wavefront each; blockDim.x is a multiple of
+// 64 and at least 64 cpw.
+template <int DB>
+__global__ __launch_bounds__(512) void gmm_wave_sample_kernel(
+    int B, int K, int L, int d, int C, int cpw, Key key, const float* __restrict__ c_x, const float* __restrict__ c_0,
+    const float* __restrict__ sigma, const int32_t* __restrict__ tau, const float4* __restrict__ coef_tau,
+    const float* __restrict__ means, const float* __restrict__ musq, const float* __restrict__ log_w,
+    const float* __restrict__ y0, float* __restrict__ traj, int32_t* __restrict__ rounds, RoundsOut rout, int adaptive) {
+  constexpr int DQ = 4 * DB;
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const WaveLayout l = wave_layout(C, d, L, K);
+  const int tid = threadIdx.x, nthreads = blockDim.x;
+  const int c0 = blockIdx.x * cpw, chains = min(cpw, B - c0);
+  for (int i = tid; i < K; i += nthreads) {
+    float4* e = reinterpret_cast<float4*>(lds + l.sch) + 2 * i;
+    e[0] = make_float4(c_x[i], c_0[i], sigma[i], 0.f);
+    e[1] = coef_tau[tau[i]];
+  }
+  for (int t = tid; t < C * DQ; t += nthreads) {
+    const int k = t / DQ, j = t % DQ;
+    lds[l.m + t] = j < d ? means[(int64_t)k * d + j] : 0.f;
+  }
+  for (int k = tid; k < C; k += nthreads) {
+    lds[l.ql + 2 * k] = musq[k];
+    lds[l.ql + 2 * k + 1] = log_w[k];
+  }
+  for (int cc = 0; cc < chains; ++cc) {
+    float* mine = lds + l.chain + cc * l.chain_floats;
+    for (int t = tid; t < K * DB; t += nthreads) {
+      const int i = t / DB, blk = t % DB;
+      float4 v = normal4(key, (uint32_t)(c0 + cc), (uint32_t)(i + 1), (uint32_t)blk);
+      if (4 * blk + 1 >= d) v.y = 0.f;
+      if (4 * blk + 2 >= d) v.z = 0.f;
+      if (4 * blk + 3 >= d) v.w = 0.f;
+      *reinterpret_cast<float4*>(mine + l.xi + 4 * t) = v;
+    }
+    for (int i = tid; i < K; i += nthreads) mine[l.logu + i] = logf(uniform1(key, (uint32_t)(c0 + cc), (uint32_t)(i + 1)));
+  }
+  __syncthreads();
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  if (wave >= chains) return;
+
+  const int c = c0 + wave;
+  float* mine = lds + l.chain + wave * l.chain_floats;
+  const float* m_l = lds + l.m;
+  const float* xi_l = mine + l.xi;
+  const float* logu = mine + l.logu;
+  float* yh = mine + l.yh;
+  float* ps = mine + l.ps + lane;
+  const float2* ql = reinterpret_cast<const float2*>(lds + l.ql);
+  const float4* sch = reinterpret_cast<const float4*>(lds + l.sch);
+  const int G = l.lanes, slot = lane / G, part = lane % G;
+  constexpr float kLog2e = 1.4426950408889634f;   // logits in base-2 units for the hardware exp2
+
+  // D(x, .) with the step's coefficients cf, in every lane of the slot
+  auto model = [&](const float (&x)[DQ], float4 cf, float (&out)[DQ]) {
+    float mx = -INFINITY;
+    int j = 0;
+    for (int k = part; k < C; k += G, ++j) {
+      float dot = 0.f;
+#pragma unroll
+      for (int b = 0; b < DB; ++b) {
+        const float4 mv = *reinterpret_cast<const float4*>(m_l + k * DQ + 4 * b);
+        dot = fmaf(x[4 * b], mv.x, fmaf(x[4 * b + 1], mv.y, fmaf(x[4 * b + 2], mv.z, fmaf(x[4 * b + 3], mv.w, dot))));
+      }
+      const float2 q = ql[k];
+      const float lg = kLog2e * fmaf(cf.x, dot, fmaf(-cf.y, q.x, q.y));
+      ps[64 * j] = lg;
+      mx = fmaxf(mx, lg);
+    }
+    mx = group_max(mx, G);
+    float sum = 0.f, acc[DQ];
+#pragma unroll
+    for (int e = 0; e < DQ; ++e) acc[e] = 0.f;
+    j = 0;
+    for (int k = part; k < C; k += G, ++j) {
+      const float lg = ps[64 * j];
+      const float p = !(lg - mx < -kCertZeroGap) ? __builtin_amdgcn_exp2f(lg - mx) : 0.f;   // (gmm_cert.h)
+      sum += p;
+#pragma unroll
+      for (int b = 0; b < DB; ++b) {
+        const float4 mv = *reinterpret_cast<const float4*>(m_l + k * DQ + 4 * b);
+        acc[4 * b] = fmaf(p, mv.x, acc[4 * b]);
+        acc[4 * b + 1] = fmaf(p, mv.y, acc[4 * b + 1]);
+        acc[4 * b + 2] = fmaf(p, mv.z, acc[4 * b + 2]);
+        acc[4 * b + 3] = fmaf(p, mv.w, acc[4 * b + 3]);
+      }
+    }
+    const float sc = cf.w / group_sum(sum, G);
+#pragma unroll
+    for (int e = 0; e < DQ; ++e) out[e] = e < d ? fmaf(cf.z, x[e], sc * group_sum(acc[e], G)) : 0.f;
+  };
+  auto row = [&](const float* p, float (&v)[DQ]) {
+#pragma unroll
+    for (int b = 0; b < DB; ++b) {
+      const float4 t = *reinterpret_cast<const float4*>(p + 4 * b);
+      v[4 * b] = t.x;
+      v[4 * b + 1] = t.y;
+      v[4 * b + 2] = t.z;
+      v[4 * b + 3] = t.w;
+    }
+  };
+
+  float* out_row = traj + (int64_t)c * (K + 1) * d;
+  // lane e < DQ: coordinate e of y_a (0 past d)
+  float y = 0.f;
+  if (lane < d) {
+    if (y0) {
+      y = y0[(int64_t)c * d + lane];
+    } else {
+      const float4 v = normal4(key, (uint32_t)c, 0u, (uint32_t)(lane >> 2));
+      y = (lane & 3) == 0 ? v.x : (lane & 3) == 1 ? v.y : (lane & 3) == 2 ? v.z : v.w;
+    }
+    out_row[lane] = y;
+  }
+  const int e = min(lane, DQ - 1);
+  int a = 0, R = 0;
+  int wstate = 4 * L;
+  while (a < K) {
+    const int w = min(adaptive ? window_of(wstate, L) : L, K - a);
+    if (lane < DQ) yh[lane] = y;
+    wave_lds_fence();
+    float x[DQ], ga[DQ], gk[DQ];
+    row(yh, x);
+    model(x, sch[2 * a + 1], ga);
+    // draft: the lanes of the coordinates walk the window, operands of four steps at a time
+    float v = y;
+    const float g = pick<DB>(ga, e);
+    for (int k0 = 0; k0 < w; k0 += 4) {
+      float4 sc[4];
+      float xi[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = min(k0 + u, w - 1);
+        sc[u] = sch[2 * (a + k)];
+        xi[u] = xi_l[(a + k) * DQ + e];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (k0 + u >= w) break;
+        v = fmaf(sc[u].z, xi[u], fmaf(sc[u].x, v, sc[u].y * g));
+        if (lane < DQ) yh[(k0 + u + 1) * DQ + lane] = v;
+      }
+    }
+    wave_lds_fence();
+    // verify and test: slot 0 is accepted by construction, sigma == 0 rejects
+    const int s = min(slot, w - 1), i = a + s;
+    float dot = 0.f, vv = 0.f;
+    bool bit = true;
+    if (w > 1) {
+      row(yh + s * DQ, x);
+      model(x, sch[2 * i + 1], gk);
+      float xi[DQ];
+      row(xi_l + i * DQ, xi);
+#pragma unroll
+      for (int j = 0; j < DQ; ++j) {
+        const float D = ga[j] - gk[j];
+        dot = fmaf(D, xi[j], dot);
+        vv = fmaf(D, D, vv);
+      }
+      const float4 sc = sch[2 * i];
+      if (slot >= 1 && slot < w) {
+        bit = false;
+        if (sc.z > 0.f) {
+          const float vxi = sc.y * dot, v2 = sc.y * sc.y * vv;
+          bit = logu[i] <= -(vxi / sc.z + v2 / (2.0f * sc.z * sc.z));
+        }
+      }
+    }
+    const unsigned long long rejected = __ballot(!bit);
+    const int lr = rejected ? __ffsll((long long)rejected) - 1 : 64;   // first lane of the first rejected slot
+    const int n_acc = rejected ? lr / G : w;
+    int keep = w;   // rows y_{a+1} .. y_{a+keep} are final
+    if (n_acc < w) {
+      const float4 sc = sch[2 * (a + n_acc)];
+      const float dr = lane_value(dot, lr), vr = lane_value(vv, lr);
+      const float coef = (vr > 0.f) ? (sc.y + 2.0f * sc.z * dr / vr) : 0.f;
+      float gr[DQ];
+#pragma unroll
+      for (int j = 0; j < DQ; ++j) gr[j] = lane_value(gk[j], lr);
+      keep = n_acc + 1;
+      y = fmaf(-(g - pick<DB>(gr, e)), coef, yh[keep * DQ + e]);
+      if (lane < DQ) yh[keep * DQ + lane] = y;
+    } else {
+      y = v;
+    }
+    wave_lds_fence();
+    float* dst = out_row + (int64_t)(a + 1) * d;
+    for (int t = lane; t < keep * DQ; t += 64) {
+      const int r = t / DQ, j = t % DQ;
+      if (j < d) dst[(int64_t)r * d + j] = yh[DQ + t];
+    }
+    wave_lds_fence();
+    wstate = window_next(wstate, w, n_acc);
+    a += keep;
+    ++R;
+  }
+  if (lane == 0) {
+    if (rounds) rounds[c] = R;
+    rout.report(R, B);
   }
 }
 
@@ -455,9 +756,49 @@ inline size_t chain_lds_bytes(const asd_ctx* ctx) {
 
 }  // namespace
 
+// How many chains share a workgroup as a wavefront each (0: a chain takes a workgroup).  A lane walks its components by
+// itself, so the line lies at the instructions a model value costs it, by (d, C, L), microseconds a sample of K 200, workgroup /
+// wavefront: 208 (8, 32, 16) 222 / 138, 288 (2, 64, 16) 219 / 136, 336 (16, 64, 8) 257 / 251, 416 (8, 64, 16) 249 / 208 but (8, 128,
+// 8) 237 / 247, 672 (16, 64, 16) 251 / 274, 1152 (2, 256, 16) 229 / 362.
+constexpr int kWaveWork = 340;
+static int wave_chains(const asd_ctx* ctx) {
+  const int C = ctx->gmm->C, d = ctx->d;
+  if (d > 4 * kWaveBlocks || ctx->L > 64) return 0;
+  const WaveLayout l = wave_layout(C, d, ctx->L, ctx->K);
+  if ((int64_t)l.per_lane * (2 * l.dq + 10) > kWaveWork) return 0;
+  const size_t room = 158 * 1024 / sizeof(float);
+  if (l.chain + l.chain_floats > room) return 0;
+  // one a workgroup while there are CUs for all; else as many as a SIMD has places for, if LDS has
+  int n = (int)std::min<int64_t>(8, ceil_div(ctx->B, 256));
+  while (l.chain + n * l.chain_floats > room) --n;
+  return n;
+}
+
 bool gmm_chain_supported(const asd_ctx* ctx) {
   if (ctx->kind != ASD_DEN_GMM || !ctx->gmm || ctx->L > 64 || ctx->d > 4096) return false;
   return chain_lds_bytes(ctx) + 2048 <= 160 * 1024;
+}
+
+// Dynamic LDS above the default limit needs the attribute, once per kernel and size.
+static hipError_t allow_lds(const void* kernel, size_t bytes, size_t* allowed) {
+  if (bytes <= *allowed) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess) *allowed = bytes;
+  return e;
+}
+
+template <int DB>
+static asd_status launch_wave(asd_ctx* ctx, int cpw, const float* y0, float* traj, int32_t* rounds, RoundsOut out, hipStream_t st) {
+  const GmmState* g = ctx->gmm;
+  const WaveLayout l = wave_layout(g->C, ctx->d, ctx->L, ctx->K);
+  const size_t bytes = sizeof(float) * (l.chain + cpw * l.chain_floats);
+  static size_t allowed = 0;
+  ASD_HIP(allow_lds((const void*)gmm_wave_sample_kernel<DB>, bytes, &allowed));
+  hipLaunchKernelGGL(gmm_wave_sample_kernel<DB>, dim3((unsigned)ceil_div(ctx->B, cpw)), dim3(64 * std::max(4, cpw)), bytes, st,
+                     ctx->B, ctx->K, ctx->L, ctx->d, g->C, cpw, ctx->key, ctx->c_x, ctx->c_0, ctx->sigma, ctx->tau, g->coef_tau,
+                     g->means, g->musq, g->log_w, y0, traj, rounds, out, ctx->adaptive ? 1 : 0);
+  ASD_HIP(hipGetLastError());
+  return ASD_OK;
 }
 
 asd_status gmm_chain_sample(asd_ctx* ctx, const float* y0, float* traj, int32_t* rounds, hipStream_t st) {
@@ -466,21 +807,27 @@ asd_status gmm_chain_sample(asd_ctx* ctx, const float* y0, float* traj, int32_t*
     set_error("chain-resident sampler: the mixture, the window and the schedule do not fit in LDS");
     return ASD_EUNSUPPORTED;
   }
-  const size_t lds_bytes = chain_lds_bytes(ctx);
-  const int nw = chain_waves(ctx);
-  static size_t attr_bytes = 0;  // dynamic LDS above the default limit needs the attribute
-  if (lds_bytes > attr_bytes) {
-    ASD_HIP(hipFuncSetAttribute((const void*)gmm_chain_sample_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds_bytes));
-    attr_bytes = lds_bytes;
+  const RoundsOut out{ctx->chain_max, (uint32_t*)ctx->live_host, ++ctx->chain_launches};
+  const int cpw = wave_chains(ctx);
+  if (cpw > 0) {
+    switch ((ctx->d + 3) / 4) {
+      case 1: ASD_TRY(launch_wave<1>(ctx, cpw, y0, traj, rounds, out, st)); break;
+      case 2: ASD_TRY(launch_wave<2>(ctx, cpw, y0, traj, rounds, out, st)); break;
+      case 3: ASD_TRY(launch_wave<3>(ctx, cpw, y0, traj, rounds, out, st)); break;
+      default: ASD_TRY(launch_wave<4>(ctx, cpw, y0, traj, rounds, out, st)); break;
+    }
+  } else {
+    const size_t lds_bytes = chain_lds_bytes(ctx);
+    const int nw = chain_waves(ctx);
+    static size_t allowed = 0;
+    ASD_HIP(allow_lds((const void*)gmm_chain_sample_kernel, lds_bytes, &allowed));
+    hipLaunchKernelGGL(gmm_chain_sample_kernel, dim3(ctx->B), dim3(64 * nw), lds_bytes, st, ctx->K, ctx->L, ctx->d,
+                       g->C, ctx->key, ctx->c_x, ctx->c_0, ctx->sigma, ctx->tau, g->coef_tau, g->means, g->musq,
+                       g->log_w, y0, traj, rounds, out, ctx->adaptive ? 1 : 0);
+    ASD_HIP(hipGetLastError());
   }
-  hipLaunchKernelGGL(gmm_chain_sample_kernel, dim3(ctx->B), dim3(64 * nw), lds_bytes, st, ctx->K, ctx->L, ctx->d,
-                     g->C, ctx->key_dev, ctx->c_x, ctx->c_0, ctx->sigma, ctx->tau, g->coef_tau, g->means, g->musq,
-                     g->log_w, y0, traj, rounds, ctx->chain_max, ++ctx->chain_launches, ctx->adaptive ? 1 : 0);
-  ASD_HIP(hipGetLastError());
-  ASD_HIP(hipMemcpyAsync(ctx->live_host, ctx->chain_max, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
   ASD_HIP(hipStreamSynchronize(st));
-  ctx->last_rounds = ctx->live_host[0];  // low word: the largest round count of this launch
+  ctx->last_rounds = ctx->live_host[0];
   return ASD_OK;
 }
 

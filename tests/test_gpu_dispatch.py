@@ -333,3 +333,34 @@ def test_windows_in_pieces_change_no_bit(d, E, width, blocks, K, L, chains, term
         assert m == n and torch.equal(r, rounds) and torch.equal(t, traj)
     (starts, whole), (starts_p, pieces) = runs[3][3], runs[4][3]
     assert starts == starts_p == int(rounds.sum()) and pieces < 0.8 * whole
+
+
+@pytest.mark.parametrize("d, C, L, K, chains, adaptive", [
+    (1, 1, 1, 3, 2, False),           # nothing but a step
+    (2, 4, 8, 40, 5, False),
+    (3, 7, 5, 30, 300, True),         # lanes without a component; two chains a workgroup
+    (5, 40, 16, 40, 4, False),        # two blocks of coordinates, the second mostly padding
+    (9, 16, 3, 25, 600, False),       # three; windows shorter than the lanes' slots; three chains a workgroup
+    (16, 8, 17, 50, 3, True),         # two lanes a slot
+    (13, 5, 64, 70, 3, False),        # a lane a slot; windows nearly as long as the chain
+    (4, 6, 12, 1000, 2100, False),    # as many chains a workgroup as LDS holds
+])
+def test_samples_of_a_wavefront_per_chain(d, C, L, K, chains, adaptive):
+    """Whole samples of mixtures of a few numbers against the oracle, chain by chain (1e-4, the bar of fp32 denoisers)."""
+    cfg = dict(kind="gmm", d=d, C=C, K=K, L=L, var=0.25)
+    T, p, model = oracle_setup(cfg)
+    ctx = runtime.open_ctx(cfg, p, seed=8, chains=chains)
+    assert ctx.resident_active()
+    ctx.use_adaptive_window(adaptive)
+    traj = torch.full((chains, K + 1, d), float("nan"), device=DEV)
+    rounds = torch.zeros(chains, dtype=torch.int32, device=DEV)
+    n = ctx.sample(traj, rounds)
+    y0 = traj[:, 0].clone()
+    given = torch.full_like(traj, float("nan"))
+    assert ctx.sample(given, None, y0) == n == int(rounds.max())
+    ctx.close()
+    assert bool(torch.isfinite(traj).all()) and torch.equal(traj, given)
+    for c in sorted({0, 1, chains // 2, chains - 1}):
+        f = H.follow_chain(cfg, T, model, 8, c, traj[c].cpu().numpy(), 1e-4, adaptive=adaptive)
+        assert H.rel_err(traj[c].cpu().numpy(), f["y"]) <= 1e-4
+        assert int(rounds[c]) == f["R"]
