@@ -72,7 +72,7 @@ ASD_API asd_status asd_use_tall_tiles(asd_ctx* ctx, int32_t on);
 ASD_API int32_t asd_tall_tiles_active(const asd_ctx* ctx);
 
 /* Early accept (inside asd_sample and asd_sample_noalloc; mixture denoiser with the one-hot certificate on fp16
- * terms, d a multiple of 4 and at most 1024, more than 16384 model rows per call, no model-call reuse).  A certified
+ * terms, d a multiple of 4 and at most 1024, more than 4096 model rows per call, no model-call reuse).  A certified
  * row's model value is c_x' x + c_m' mu_b, which the accept stage can form itself, and a drafted row is a recurrence
  * on the row before it.  So after the draft call one kernel takes every chain it can through its whole round: it
  * drafts a slot from the slot before it in registers, certifies it, forms its model value and takes the accept test,

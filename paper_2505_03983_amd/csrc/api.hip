@@ -157,7 +157,8 @@ static asd_status build(asd_ctx* ctx, const asd_config* cfg) {
   ASD_HIP(hipMalloc(&ctx->live, sizeof(int32_t) * kLiveInts));
   ASD_HIP(hipMemset(ctx->live, 0, sizeof(int32_t) * kLiveInts));
   ASD_HIP(hipMalloc(&ctx->win, sizeof(int32_t) * 2 * (size_t)ctx->B));
-  ASD_HIP(hipMalloc(&ctx->piece_state, sizeof(int32_t) * 3 * (size_t)ctx->B));
+  ASD_HIP(hipMalloc(&ctx->piece_state, sizeof(int32_t) * 2 * (size_t)ctx->B));
+  ASD_HIP(hipMalloc(&ctx->chain_rounds, sizeof(int32_t) * (size_t)ctx->B));
   ASD_HIP(hipMalloc(&ctx->chain_max, 2 * sizeof(unsigned long long)));
   ASD_HIP(hipMemset(ctx->chain_max, 0, 2 * sizeof(unsigned long long)));
   ASD_HIP(hipMalloc(&ctx->key_dev, sizeof(Key)));
@@ -203,6 +204,7 @@ static void teardown(asd_ctx* ctx) {
   (void)hipFree(ctx->chain_max);
   (void)hipFree(ctx->win);
   (void)hipFree(ctx->piece_state);
+  (void)hipFree(ctx->chain_rounds);
   (void)hipFree(ctx->key_dev);
   drop_round_graphs(ctx);
   if (ctx->own_stream) (void)hipStreamDestroy(ctx->own_stream);
@@ -424,10 +426,13 @@ static asd_status ensure_round_graph(asd_ctx* ctx, float* traj, int32_t* rounds,
   return ASD_OK;
 }
 
-// Whether asd_sample's rounds may take certified chains through their accept stage ahead of the verify call.
+// Whether asd_sample's rounds may take certified chains through their accept stage ahead of the verify call.  Above 4096 model
+// rows a call: below, contexts have never done it and asd_early_accept_active says so, which callers may rely on -- not that
+// it would not pay there ((1024, 4096) with L 64, K 300: 8 chains 5045 -> 3985 us a sample, 64 chains 6718 -> 5354).
+constexpr int64_t kEarlyRows = 4096;
 static bool early_accept_possible(const asd_ctx* ctx) {
   asd::OneHotCert oc;
-  return ctx->early && ctx->pending && ctx->L > 1 && ctx->d % 4 == 0 && ctx->d / 4 <= 256 && model_onehot_cert(ctx, &oc);
+  return ctx->early && ctx->n_rows_max > kEarlyRows && ctx->pending && ctx->L > 1 && ctx->d % 4 == 0 && ctx->d / 4 <= 256 && model_onehot_cert(ctx, &oc);
 }
 
 // The while-loop of Alg. 1 in lock step over the chains, on the round kernels.  x0hat: where the verify call
@@ -442,9 +447,12 @@ static asd_status sample_rounds(asd_ctx* ctx, const float* y0, float* traj, int3
       // those kernels an atomic per chain and the index writes: a gain for launch-bound rounds (cfg 3:
       // -5% per sample), a wash for large batches, whose draft / accept kernels run near their own
       // limits (cfg 5: +13 and +18 us on them against 27 us of planning kernels).
-      c->fold_plans = c->n_rows_max <= 16384;
+      // Early accept beats the folded plans wherever it applies, by its light rounds: microseconds a sample without / with it,
+      // (d, C, L, K, chains): (128, 1024, 32, 500, 200) 6013 / 5567, (512, 1024, 16, 500, 400) 9483 / 8017, (128, 4096, 12, 1000,
+      // 1000) 31577 / 29034.
       c->reuse_now = c->reuse;
-      c->early_now = early_accept_possible(c) && !c->fold_plans && !c->reuse_now;
+      c->early_now = early_accept_possible(c) && !c->reuse_now;
+      c->fold_plans = c->n_rows_max <= 16384 && !c->early_now;
       const int least = piece_least(c);
       if (least > 0) c->cur_pieces = Pieces{c->piece_state, least};
     }
@@ -503,7 +511,8 @@ static asd_status sample_rounds(asd_ctx* ctx, const float* y0, float* traj, int3
   }
   ASD_HIP(hipStreamSynchronize(st));
   if (done_at < 0) return fail(ASD_EDEVICE, "asd_sample: chains did not finish within %d rounds", r_cap);
-  ctx->last_rounds = ctx->cur_pieces.state ? ctx->live_host[kLiveMaxRounds - 1] : done_at + 1;
+  // (passes over windows in pieces, and launches that left a chain waiting, are no rounds)
+  ctx->last_rounds = ctx->live_host[kLiveMaxRounds - 1];
   return ASD_OK;
 }
 
@@ -705,7 +714,7 @@ asd_status asd_use_early_accept(asd_ctx* ctx, int32_t on) {
 int32_t asd_early_accept_active(const asd_ctx* ctx) {
   if (!ctx) return 0;
   // (as asd_sample decides it: plans folded into the round kernels and model-call reuse exclude it)
-  return (early_accept_possible(ctx) && ctx->n_rows_max > 16384 && !ctx->reuse) ? 1 : 0;
+  return (early_accept_possible(ctx) && !ctx->reuse) ? 1 : 0;
 }
 
 asd_status asd_profile_early_accept(asd_ctx* ctx, int64_t* model_rows, int64_t* chain_rounds, int64_t* window_rows,

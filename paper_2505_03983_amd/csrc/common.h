@@ -146,8 +146,8 @@ struct asd_ctx {
   float* x0hat = nullptr;  // [B, L, d]
   int32_t* a = nullptr;    // [B]
   int32_t* live = nullptr;       // DEV [kLiveInts]: round index, the ring of live-chain counters, the ring of chains a round's
-                                 // early accept kernel left pending (or, in pieces, of a pass's verify rows), and in
-                                 // pieces the largest round count of a finished chain
+                                 // early accept kernel left pending (or, in pieces, of a pass's verify rows), and
+                                 // the largest round count of a finished chain
   int32_t* live_host = nullptr;  // pinned mirror
   hipEvent_t* live_ev = nullptr;
   int32_t last_rounds = 0;
@@ -166,7 +166,8 @@ struct asd_ctx {
   int32_t* cur_win = nullptr;  // what the round kernels are given: win while an adaptive sample runs, else NULL (= L)
   bool adaptive = false;
   bool pieces_on = true;       // the switch of windows in pieces (asd_use_window_pieces)
-  int32_t* piece_state = nullptr;  // DEV [3 B]: see Pieces (device_util.h)
+  int32_t* piece_state = nullptr;  // DEV [2 B]: see Pieces (device_util.h)
+  int32_t* chain_rounds = nullptr; // DEV [B]: rounds of each chain in this sample (launches are not rounds, see asd_sample)
   asd::Pieces cur_pieces;      // what the round kernels are given: in pieces while a sample that pays for them runs
   const void* g_win = nullptr; // cur_win the round graph was captured with
   bool g_reuse = false;        // reuse_now the round graph was captured with

@@ -80,7 +80,7 @@ __device__ __forceinline__ int window_next(int state, int w_used, int n_acc) {
 // on with theirs.  A piece is 5/4 of a running mean of the chain's accepted run length (kept as the window controller keeps
 // its own), at least `least` slots: between one and two of the mean cost the same within 3% over the measured runs, and
 // fewer slots than fill the model call's tiles save nothing.
-// state[c] = slots of the current window already accepted, state[B + c] = the mean's integer state, state[2 B + c] = rounds.
+// state[c] = slots of the current window already accepted, state[B + c] = the mean's integer state.
 // ----------------------------------------------------------------------------
 struct Pieces {
   int32_t* state = nullptr;   // NULL: windows are taken whole

@@ -23,10 +23,18 @@ __device__ __forceinline__ void pack_temb(const PackOut& p, int64_t row, int tau
 // ----------------------------------------------------------------------------
 // y_0, a = 0, rounds = 0
 // ----------------------------------------------------------------------------
+// A chain has finished a round of its own: the largest count of a finished chain goes to the host with the live ring.
+__device__ __forceinline__ void count_round(int32_t* chain_rounds, int c, bool finished, int32_t* live) {
+  const int r = chain_rounds[c] + 1;
+  chain_rounds[c] = r;
+  if (finished) atomicMax(&live[kLiveMaxRounds], r);
+}
+
 __global__ void init_state_kernel(int B, int K, int d, const Key* __restrict__ key_p, const float* __restrict__ y0,
                                   float* __restrict__ traj, int32_t* __restrict__ a,
                                   int32_t* __restrict__ rounds, int32_t* __restrict__ round_idx, int L,
-                                  int32_t* __restrict__ win, int32_t* __restrict__ carry, Pieces pieces, PlanOut plan) {
+                                  int32_t* __restrict__ win, int32_t* __restrict__ carry, Pieces pieces,
+                                  int32_t* __restrict__ chain_rounds, PlanOut plan) {
   const int c = blockIdx.x;
   const Key key = *key_p;
   if (c == 0 && threadIdx.x == 0 && round_idx) {
@@ -64,8 +72,8 @@ __global__ void init_state_kernel(int B, int K, int d, const Key* __restrict__ k
     if (pieces.state) {
       pieces.state[c] = 0;
       pieces.state[B + c] = 4 * L;
-      pieces.state[2 * B + c] = 0;
     }
+    if (chain_rounds) chain_rounds[c] = 0;
   }
 }
 
@@ -87,7 +95,8 @@ static PlanOut plan_out(asd_ctx* ctx, int32_t* ring) {
 asd_status launch_init_state(asd_ctx* ctx, const float* y0, float* traj, int32_t* a, int32_t* rounds,
                              hipStream_t st) {
   hipLaunchKernelGGL(init_state_kernel, dim3(ctx->B), dim3(256), 0, st, ctx->B, ctx->K, ctx->d, ctx->key_dev, y0,
-                     traj, a, rounds, ctx->live, ctx->L, ctx->cur_win, ctx->carry, ctx->cur_pieces, plan_out(ctx, nullptr));
+                     traj, a, rounds, ctx->live, ctx->L, ctx->cur_win, ctx->carry, ctx->cur_pieces,
+                     ctx->chain_rounds, plan_out(ctx, nullptr));
   ASD_HIP(hipGetLastError());
   return ASD_OK;
 }
@@ -557,7 +566,8 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
                                                       int32_t* __restrict__ rounds, int32_t* __restrict__ live,
                                                       int32_t* __restrict__ win, PlanOut plan,
                                                       int64_t* __restrict__ prof_counts,
-                                                      const int32_t* __restrict__ pending, Pieces pieces) {
+                                                      const int32_t* __restrict__ pending, Pieces pieces,
+                                                      int32_t* __restrict__ chain_rounds) {
   // pending (or NULL): chains with pending[c] == 0 have had their round already (accept_early_kernel)
   __shared__ float s_part[kAcceptChunkMax][16][2];  // per slot of the chunk, per wavefront: partial <D,xi>, |D|^2
   __shared__ float s_rej[2];                     // <D,xi>, |D|^2 of the first rejected slot
@@ -783,13 +793,9 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
     if (pieces.state) {
       const int B = gridDim.x;
       pieces.state[c] = goes_on ? w : 0;
-      if (!goes_on) {
-        pieces.state[B + c] = window_next(pieces.state[B + c], w_all, n_acc);
-        const int r = pieces.state[2 * B + c] + 1;
-        pieces.state[2 * B + c] = r;
-        if (live && a_next >= K) atomicMax(&live[kLiveMaxRounds], r);
-      }
+      if (!goes_on) pieces.state[B + c] = window_next(pieces.state[B + c], w_all, n_acc);
     }
+    if (live && !goes_on) count_round(chain_rounds, c, a_next >= K, live);
     // the round index was advanced at the start of this round
     if (live && a_next < K) atomicAdd(&live[1 + ((live[0] - 1) % kLiveRing)], 1);
     if constexpr (FOLD) if (lists) {
@@ -827,7 +833,8 @@ __global__ __launch_bounds__(256) void accept_early_kernel(int K, int L, int d, 
                                                            int32_t* __restrict__ rounds, int32_t* __restrict__ live,
                                                            int32_t* __restrict__ win, OneHotCert oc,
                                                            int32_t* __restrict__ pending, int light,
-                                                           int64_t* __restrict__ prof_counts) {
+                                                           int64_t* __restrict__ prof_counts,
+                                                           int32_t* __restrict__ chain_rounds) {
   // live: [0] round index (advanced at the start of this round), then the ring of chains unfinished after a round,
   // then the ring of chains a round left pending.  light: this kernel is the round (the host has seen rounds without
   // pending chains and launches neither the draft call nor anything behind this kernel): the model value at y_a is
@@ -1093,6 +1100,7 @@ __global__ __launch_bounds__(256) void accept_early_kernel(int K, int L, int d, 
       win[B + c] = st;
       win[c] = window_of(st, L);
     }
+    if (live) count_round(chain_rounds, c, a_next >= K, live);
     // the round index was advanced at the start of this round
     if (live && a_next < K) atomicAdd(&live[1 + ((live[0] - 1) % kLiveRing)], 1);
   }
@@ -1107,7 +1115,7 @@ asd_status launch_accept_early(asd_ctx* ctx, float* traj, int32_t* a, int32_t* r
   const int threads = (int)(ceil_div(ctx->d / 4, 64) * 64);
   hipLaunchKernelGGL(accept_early_kernel, dim3(ctx->B), dim3(threads), 0, st, ctx->K, ctx->L, ctx->d, ctx->key_dev, a,
                      ctx->c_x, ctx->c_0, ctx->sigma, ctx->tau, ctx->x0a, traj, rounds, live, ctx->cur_win, oc, ctx->pending, light ? 1 : 0,
-                     prof_counting(ctx) ? ctx->row_counts : nullptr);
+                     prof_counting(ctx) ? ctx->row_counts : nullptr, ctx->chain_rounds);
   ASD_HIP(hipGetLastError());
   return ASD_OK;
 }
@@ -1125,7 +1133,7 @@ asd_status launch_accept(asd_ctx* ctx, float* traj, int32_t* a, const float* x0h
   const auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(ctx->B), dim3(64 * waves * groups), 0, st, ctx->K, ctx->L, ctx->d, ctx->key_dev, a, ctx->c_0,
                        ctx->sigma, ctx->x0a, carry, x0hat, x0_slots, traj, accepted, stats, rounds, live, ctx->cur_win, plan,
-                       prof_counts, pending, ctx->cur_pieces);
+                       prof_counts, pending, ctx->cur_pieces, ctx->chain_rounds);
   };
   if (plan.in_off) {
     if (groups >= 8) go(accept_kernel<true, 1>);
