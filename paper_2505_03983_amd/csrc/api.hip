@@ -142,31 +142,42 @@ static asd_status build(asd_ctx* ctx, const asd_config* cfg) {
   ASD_HIP(hipMalloc(&ctx->out_off, sizeof(int64_t) * rows));
   ASD_HIP(hipMalloc(&ctx->row_tau, sizeof(int32_t) * rows));
   ASD_HIP(hipMalloc(&ctx->row_chain, sizeof(int32_t) * rows));
-  ASD_HIP(hipMalloc(&ctx->n_rows_dev, sizeof(int32_t) * 2));
-  ASD_HIP(hipMemset(ctx->n_rows_dev, 0, sizeof(int32_t) * 2));
+  {
+    // the arrays of an entry or two per chain, and the counters: one allocation, all zero (sixteen of their own took most of
+    // a small context's set-up)
+    const size_t B = (size_t)ctx->B;
+    size_t used = 0;
+    const auto take = [&](size_t bytes) {
+      const size_t at = used;
+      used += (bytes + 255) & ~(size_t)255;
+      return at;
+    };
+    const size_t n_rows = take(2 * sizeof(int32_t)), live = take(sizeof(int32_t) * kLiveInts), counts = take(8 * sizeof(int64_t)),
+                 chain_max = take(2 * sizeof(unsigned long long)), key = take(sizeof(Key)), a = take(sizeof(int32_t) * B),
+                 carry = take(sizeof(int32_t) * B), pending = take(sizeof(int32_t) * B), chain_rounds = take(sizeof(int32_t) * B),
+                 win = take(2 * sizeof(int32_t) * B), pieces = take(2 * sizeof(int32_t) * B);
+    ASD_HIP(hipMalloc(&ctx->small, used));
+    ASD_HIP(hipMemset(ctx->small, 0, used));
+    ctx->n_rows_dev = reinterpret_cast<int32_t*>(ctx->small + n_rows);
+    ctx->live = reinterpret_cast<int32_t*>(ctx->small + live);
+    ctx->row_counts = reinterpret_cast<int64_t*>(ctx->small + counts);
+    ctx->chain_max = reinterpret_cast<unsigned long long*>(ctx->small + chain_max);
+    ctx->key_dev = reinterpret_cast<Key*>(ctx->small + key);
+    ctx->a = reinterpret_cast<int32_t*>(ctx->small + a);
+    ctx->carry = reinterpret_cast<int32_t*>(ctx->small + carry);
+    ctx->pending = reinterpret_cast<int32_t*>(ctx->small + pending);
+    ctx->chain_rounds = reinterpret_cast<int32_t*>(ctx->small + chain_rounds);
+    ctx->win = reinterpret_cast<int32_t*>(ctx->small + win);
+    ctx->piece_state = reinterpret_cast<int32_t*>(ctx->small + pieces);
+  }
   ASD_HIP(hipMalloc(&ctx->x0a, sizeof(float) * (size_t)ctx->B * ctx->d));
   // one more slot per chain than the window: with model-call reuse slot w holds the model value at yhat_b
   ASD_HIP(hipMalloc(&ctx->x0hat, sizeof(float) * (size_t)ctx->B * ((size_t)ctx->L + 1) * (size_t)ctx->d));
-  ASD_HIP(hipMalloc(&ctx->carry, sizeof(int32_t) * (size_t)ctx->B));
-  ASD_HIP(hipMemset(ctx->carry, 0, sizeof(int32_t) * (size_t)ctx->B));
-  ASD_HIP(hipMalloc(&ctx->a, sizeof(int32_t) * (size_t)ctx->B));
-  ASD_HIP(hipMalloc(&ctx->row_counts, sizeof(int64_t) * 8));
-  ASD_HIP(hipMemset(ctx->row_counts, 0, sizeof(int64_t) * 8));
-  ASD_HIP(hipMalloc(&ctx->pending, sizeof(int32_t) * (size_t)ctx->B));
-  ASD_HIP(hipMemset(ctx->pending, 0, sizeof(int32_t) * (size_t)ctx->B));
-  ASD_HIP(hipMalloc(&ctx->live, sizeof(int32_t) * kLiveInts));
-  ASD_HIP(hipMemset(ctx->live, 0, sizeof(int32_t) * kLiveInts));
-  ASD_HIP(hipMalloc(&ctx->win, sizeof(int32_t) * 2 * (size_t)ctx->B));
-  ASD_HIP(hipMalloc(&ctx->piece_state, sizeof(int32_t) * 2 * (size_t)ctx->B));
-  ASD_HIP(hipMalloc(&ctx->chain_rounds, sizeof(int32_t) * (size_t)ctx->B));
-  ASD_HIP(hipMalloc(&ctx->chain_max, 2 * sizeof(unsigned long long)));
-  ASD_HIP(hipMemset(ctx->chain_max, 0, 2 * sizeof(unsigned long long)));
-  ASD_HIP(hipMalloc(&ctx->key_dev, sizeof(Key)));
   ASD_HIP(hipMemcpy(ctx->key_dev, &ctx->key, sizeof(Key), hipMemcpyHostToDevice));
-  ASD_HIP(hipHostMalloc((void**)&ctx->live_host, sizeof(int32_t) * (kLiveInts - 1), hipHostMallocDefault));
-  ctx->live_ev = new (std::nothrow) hipEvent_t[kLiveRing]();
-  if (!ctx->live_ev) return ASD_ENOMEM;
-  for (int i = 0; i < kLiveRing; ++i) ASD_HIP(hipEventCreateWithFlags(&ctx->live_ev[i], hipEventDisableTiming));
+  ASD_HIP(hipHostMalloc((void**)&ctx->report, sizeof(HostReport), hipHostMallocMapped | hipHostMallocCoherent));
+  memset(ctx->report, 0, sizeof(HostReport));
+  ASD_HIP(hipHostGetDevicePointer((void**)&ctx->report_dev, ctx->report, 0));
+  ASD_HIP(hipEventCreateWithFlags(&ctx->order_ev, hipEventDisableTiming));
   if (ctx->kind == ASD_DEN_GMM) return gmm_create(ctx, cfg->den);
   return mlp_create(ctx, cfg->den);
 }
@@ -195,28 +206,14 @@ static void teardown(asd_ctx* ctx) {
   (void)hipFree(ctx->out_off);
   (void)hipFree(ctx->row_tau);
   (void)hipFree(ctx->row_chain);
-  (void)hipFree(ctx->n_rows_dev);
   (void)hipFree(ctx->x0a);
+  (void)hipFree(ctx->small);
   (void)hipFree(ctx->x0hat);
-  (void)hipFree(ctx->carry);
-  (void)hipFree(ctx->a);
-  (void)hipFree(ctx->live);
-  (void)hipFree(ctx->chain_max);
-  (void)hipFree(ctx->win);
-  (void)hipFree(ctx->piece_state);
-  (void)hipFree(ctx->chain_rounds);
-  (void)hipFree(ctx->key_dev);
   drop_round_graphs(ctx);
   if (ctx->own_stream) (void)hipStreamDestroy(ctx->own_stream);
-  (void)hipFree(ctx->row_counts);
-  (void)hipFree(ctx->pending);
   ctx->prof.destroy();
-  if (ctx->live_host) (void)hipHostFree(ctx->live_host);
-  if (ctx->live_ev) {
-    for (int i = 0; i < kLiveRing; ++i)
-      if (ctx->live_ev[i]) (void)hipEventDestroy(ctx->live_ev[i]);
-    delete[] ctx->live_ev;
-  }
+  if (ctx->report) (void)hipHostFree(ctx->report);
+  if (ctx->order_ev) (void)hipEventDestroy(ctx->order_ev);
   delete ctx;
 }
 
@@ -335,7 +332,7 @@ asd_status asd_accept(asd_ctx* ctx, float* traj, int32_t* a, const float* x0hat,
   return ASD_OK;
 }
 
-// All launches of one round of Alg. 1 on `st`, plus the copy of the live-chain ring to the host.
+// All launches of one round of Alg. 1 on `st`.
 // light (early accept only): the early accept kernel alone (behind the planning kernel, which starts the round) --
 // for rounds in which, as far as the host knows, that kernel takes every chain.  A chain it does not take stays where
 // it is until the next full round.  likely: rows to expect in the verify call (0: as many as there can be).
@@ -360,10 +357,34 @@ static asd_status enqueue_round(asd_ctx* ctx, float* traj, int32_t* rounds, floa
     ASD_TRY(launch_accept(ctx, traj, ctx->a, x0hat, ctx->L + (ctx->reuse_now ? 1 : 0), nullptr, nullptr, rounds,
                           ctx->live, st, pending));
   }
-  // The whole ring is copied: slot r % kLiveRing keeps its value until round r + kLiveRing overwrites it,
-  // long after the host has read it.
-  ASD_HIP(hipMemcpyAsync(ctx->live_host, ctx->live + 1, sizeof(int32_t) * (kLiveInts - 1), hipMemcpyDeviceToHost, st));
   return ASD_OK;
+}
+
+// Waits for what the kernels have to say of round r (start_round of round r + 1, which has been queued): the chains it left
+// unfinished, the second ring's entry, the largest round count so far.  Reads memory rather than waiting for an event, and
+// asks the stream now and then: if it has run dry without the report, or failed, so has the sample.
+static asd_status wait_report(asd_ctx* ctx, int r, hipStream_t st, int32_t (&v)[3]) {
+  const volatile uint64_t* w = ctx->report->word[r % kLiveRing];
+  const auto there = [&]() {
+    bool ok = true;
+    for (int i = 0; i < 3; ++i) {
+      const uint64_t x = w[i];
+      v[i] = (int32_t)(uint32_t)x;
+      ok = ok && (uint32_t)(x >> 32) == (uint32_t)r + 1u;
+    }
+    return ok;
+  };
+  for (;;) {
+    for (int spin = 0; spin < 2000; ++spin) {
+      if (there()) return ASD_OK;
+      __builtin_ia32_pause();
+    }
+    const hipError_t e = hipStreamQuery(st);
+    if (e == hipErrorNotReady) continue;
+    ASD_HIP(e);
+    if (there()) return ASD_OK;
+    return fail(ASD_EDEVICE, "asd_sample: round %d ended without a report", r);
+  }
 }
 
 // Windows in pieces (device_util.h): the least slots of a piece, 0 where windows are taken whole.  A pass over the batch then
@@ -473,12 +494,14 @@ static asd_status sample_rounds(asd_ctx* ctx, const float* y0, float* traj, int3
   if (use_graph && st == nullptr) {
     // the legacy default stream cannot be captured: run on a stream of our own, ordered after the caller's work
     if (!ctx->own_stream) ASD_HIP(hipStreamCreateWithFlags(&ctx->own_stream, hipStreamNonBlocking));
-    ASD_HIP(hipEventRecord(ctx->live_ev[0], caller));
-    ASD_HIP(hipStreamWaitEvent(ctx->own_stream, ctx->live_ev[0], 0));
+    ASD_HIP(hipEventRecord(ctx->order_ev, caller));
+    ASD_HIP(hipStreamWaitEvent(ctx->own_stream, ctx->order_ev, 0));
     st = ctx->own_stream;
   }
   ASD_TRY(flush_key(ctx, st));
+  memset(ctx->report->word, 0, sizeof(ctx->report->word));   // (the last sample's kernels have ended)
   ASD_TRY(launch_init_state(ctx, y0, traj, ctx->a, rounds, st));
+  int32_t seen[3] = {0, 0, 0};
   int r = 0;
   int done_at = -1;
   bool light = false;
@@ -487,7 +510,6 @@ static asd_status sample_rounds(asd_ctx* ctx, const float* y0, float* traj, int3
   // rounds in a row before a full one comes; every pass in pieces moves every chain by a slot at least
   const int r_cap = (ctx->early_now ? (lag + 2) : 1) * ctx->K + lag + 1;
   for (; r < r_cap; ++r) {
-    const int slot = r % kLiveRing;
     if (use_graph && r > 0) {
       hipGraphExec_t exec = nullptr;
       ASD_TRY(ensure_round_graph(ctx, traj, rounds, st, light, hint, &exec));  // round 0 ran eagerly (first-use set-up)
@@ -495,24 +517,22 @@ static asd_status sample_rounds(asd_ctx* ctx, const float* y0, float* traj, int3
     } else {
       ASD_TRY(enqueue_round(ctx, traj, rounds, x0hat, st, light, hinted_rows(ctx, hint)));
     }
-    ASD_HIP(hipEventRecord(ctx->live_ev[slot], st));
     if (r >= lag) {
-      const int q = (r - lag) % kLiveRing;
-      ASD_HIP(hipEventSynchronize(ctx->live_ev[q]));
-      if (ctx->live_host[q] == 0) {
+      ASD_TRY(wait_report(ctx, r - lag, st, seen));
+      if (seen[0] == 0) {
         done_at = r - lag;
         break;
       }
       // the early accept kernel took every chain of round r - lag: the rounds to come are launched without the
       // kernels behind it, until one of them reports a chain it could not take (which has waited since)
-      light = ctx->early_now && ctx->live_host[kLiveRing + q] == 0;
-      if (ctx->cur_pieces.state) hint = row_hint(ctx, ctx->live_host[kLiveRing + q]);
+      light = ctx->early_now && seen[1] == 0;
+      if (ctx->cur_pieces.state) hint = row_hint(ctx, seen[1]);
     }
   }
   ASD_HIP(hipStreamSynchronize(st));
   if (done_at < 0) return fail(ASD_EDEVICE, "asd_sample: chains did not finish within %d rounds", r_cap);
   // (passes over windows in pieces, and launches that left a chain waiting, are no rounds)
-  ctx->last_rounds = ctx->live_host[kLiveMaxRounds - 1];
+  ctx->last_rounds = seen[2];
   return ASD_OK;
 }
 

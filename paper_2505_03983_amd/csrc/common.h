@@ -48,6 +48,7 @@ struct PackOut {
   const uint16_t* temb = nullptr;
   int E = 0, d = 0;
 };
+struct HostReport;
 struct PlanOut {
   int64_t* in_off = nullptr;    // NULL: the kernel writes no plan
   int64_t* out_off = nullptr;
@@ -57,6 +58,7 @@ struct PlanOut {
   const int32_t* tau = nullptr; // step -> time index
   int64_t* row_counts = nullptr;  // [2] running totals for the profiler, or NULL
   int32_t* ring = nullptr;      // round index + live-chain ring, advanced once per round
+  HostReport* host = nullptr;   // where that tells the host of the round before (report_round)
   PackOut pack;
 };
 
@@ -134,6 +136,7 @@ struct asd_ctx {
   float* c_0 = nullptr;
   float* sigma = nullptr;
   int32_t* tau = nullptr;
+  uint8_t* small = nullptr;       // what the counters and the arrays by chain below are parts of
   // row plan scratch
   int64_t* in_off = nullptr;
   int64_t* out_off = nullptr;
@@ -148,8 +151,9 @@ struct asd_ctx {
   int32_t* live = nullptr;       // DEV [kLiveInts]: round index, the ring of live-chain counters, the ring of chains a round's
                                  // early accept kernel left pending (or, in pieces, of a pass's verify rows), and
                                  // the largest round count of a finished chain
-  int32_t* live_host = nullptr;  // pinned mirror
-  hipEvent_t* live_ev = nullptr;
+  asd::HostReport* report = nullptr;      // pinned host memory the kernels write to, ...
+  asd::HostReport* report_dev = nullptr;  // ... as the device sees it
+  hipEvent_t order_ev = nullptr;          // orders own_stream behind the caller's
   int32_t last_rounds = 0;
   // one round of the cheap-round path as an instantiated HIP graph, valid for (g_traj, g_rounds, g_stream)
   hipGraphExec_t gexec = nullptr;
@@ -200,6 +204,14 @@ namespace asd {
 
 constexpr int kLiveRing = 8;
 constexpr int kLiveMaxRounds = 1 + 2 * kLiveRing, kLiveInts = kLiveMaxRounds + 1;   // ctx->live: the last word, and all of them
+
+// What the host reads of a running sample.  A word holds the number of rounds started when it was written in its upper half,
+// so a word says itself whether it is the one waited for.  Slot r % kLiveRing: round r's entries of ctx->live's rings (how many
+// chains it left unfinished; the second ring) and the largest round count so far.
+struct HostReport {
+  uint64_t word[kLiveRing][3];
+  uint32_t chain_rounds;   // the chain-resident sampler's result
+};
 
 // Whether kernels get the device-side counters of rows and executed work (asd_profile_rows, asd_profile_model_work).
 inline bool prof_counting(const asd_ctx* ctx) { return ctx->prof.on; }

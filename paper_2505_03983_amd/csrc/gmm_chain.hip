@@ -807,7 +807,7 @@ asd_status gmm_chain_sample(asd_ctx* ctx, const float* y0, float* traj, int32_t*
     set_error("chain-resident sampler: the mixture, the window and the schedule do not fit in LDS");
     return ASD_EUNSUPPORTED;
   }
-  const RoundsOut out{ctx->chain_max, (uint32_t*)ctx->live_host, ++ctx->chain_launches};
+  const RoundsOut out{ctx->chain_max, &ctx->report_dev->chain_rounds, ++ctx->chain_launches};
   const int cpw = wave_chains(ctx);
   if (cpw > 0) {
     switch ((ctx->d + 3) / 4) {
@@ -827,7 +827,7 @@ asd_status gmm_chain_sample(asd_ctx* ctx, const float* y0, float* traj, int32_t*
     ASD_HIP(hipGetLastError());
   }
   ASD_HIP(hipStreamSynchronize(st));
-  ctx->last_rounds = ctx->live_host[0];
+  ctx->last_rounds = (int32_t) * (const volatile uint32_t*)&ctx->report->chain_rounds;
   return ASD_OK;
 }
 

@@ -23,6 +23,24 @@ __device__ __forceinline__ void pack_temb(const PackOut& p, int64_t row, int tau
 // ----------------------------------------------------------------------------
 // y_0, a = 0, rounds = 0
 // ----------------------------------------------------------------------------
+// A round starts: tell the host how the one before ended (a copy of the rings behind every round cost it 3 us and a gap, and
+// the event the host waited for another), advance the round index and clear this round's slot of the rings
+// (ring[0] = index of the next round, ring[1 + r % kLiveRing] = chains still unfinished after round r).  One thread.
+__device__ __forceinline__ void start_round(int32_t* ring, HostReport* host) {
+  const int r = ring[0], slot = r % kLiveRing;
+  if (host && r > 0) {
+    const int prev = (r - 1) % kLiveRing;
+    const uint64_t tag = (uint64_t)(uint32_t)r << 32;
+    const int32_t v[3] = {ring[1 + prev], ring[1 + kLiveRing + prev], ring[kLiveMaxRounds]};
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      __hip_atomic_store(&host->word[prev][i], tag | (uint32_t)v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  ring[0] = r + 1;
+  ring[1 + slot] = 0;
+  ring[1 + kLiveRing + slot] = 0;
+}
+
 // A chain has finished a round of its own: the largest count of a finished chain goes to the host with the live ring.
 __device__ __forceinline__ void count_round(int32_t* chain_rounds, int c, bool finished, int32_t* live) {
   const int r = chain_rounds[c] + 1;
@@ -88,6 +106,7 @@ static PlanOut plan_out(asd_ctx* ctx, int32_t* ring) {
   p.tau = ctx->tau;
   p.row_counts = prof_counting(ctx) ? ctx->row_counts : nullptr;
   p.ring = ring;
+  p.host = ctx->report_dev;
   if (ctx->kind == ASD_DEN_MLP) p.pack = mlp_pack_out(ctx);
   return p;
 }
@@ -142,7 +161,7 @@ __global__ __launch_bounds__(1024) void plan_rows_kernel(int B, int K, int L, in
                                                          int64_t* __restrict__ in_off, int64_t* __restrict__ out_off,
                                                          int32_t* __restrict__ row_tau,
                                                          int32_t* __restrict__ row_chain, int32_t* __restrict__ n_rows,
-                                                         int32_t* __restrict__ ring,
+                                                         int32_t* __restrict__ ring, HostReport* __restrict__ host,
                                                          int64_t* __restrict__ row_counts,
                                                          const int32_t* __restrict__ win,
                                                          const int32_t* __restrict__ carry, int extra, int slots,
@@ -157,14 +176,7 @@ __global__ __launch_bounds__(1024) void plan_rows_kernel(int B, int K, int L, in
   __shared__ int s_wave[16];
   __shared__ int s_total;
   __shared__ int s_off[1024], s_cnt[1024], s_ac[1024];
-  // A round starts here: advance the round index and clear this round's slot of the live-chain ring
-  // (ring[0] = index of the next round, ring[1 + r % kLiveRing] = chains still unfinished after round r).
-  if (threadIdx.x == 0 && blockIdx.x == 0 && ring) {
-    const int r = ring[0];
-    ring[0] = r + 1;
-    ring[1 + (r % kLiveRing)] = 0;
-    ring[1 + kLiveRing + (r % kLiveRing)] = 0;
-  }
+  if (threadIdx.x == 0 && blockIdx.x == 0 && ring) start_round(ring, host);
   __shared__ int s_pc[1024];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int base = 0, real = 0;
@@ -228,7 +240,7 @@ __global__ __launch_bounds__(1024) void plan_rows_kernel(int B, int K, int L, in
 asd_status launch_plan_draft(asd_ctx* ctx, const int32_t* a, hipStream_t st, int32_t* ring) {
   ProfScope ps(ctx, ASD_PROF_PLAN, 0, st);
   hipLaunchKernelGGL(plan_rows_kernel<0>, dim3(1), dim3(1024), 0, st, ctx->B, ctx->K, ctx->L, ctx->d, a, ctx->tau,
-                     ctx->in_off, ctx->out_off, ctx->row_tau, ctx->row_chain, ctx->n_rows_dev + 0, ring,
+                     ctx->in_off, ctx->out_off, ctx->row_tau, ctx->row_chain, ctx->n_rows_dev + 0, ring, ctx->report_dev,
                      prof_counting(ctx) ? ctx->row_counts : nullptr, ctx->cur_win,
                      ctx->reuse_now ? ctx->carry : (const int32_t*)nullptr, 0, ctx->L, 0, (const int32_t*)nullptr);
   ASD_HIP(hipGetLastError());
@@ -241,7 +253,7 @@ asd_status launch_plan_verify(asd_ctx* ctx, const int32_t* a, hipStream_t st, co
   // up to 64 workgroups share the filling of a large plan (a chain per wavefront at a time, see the kernel)
   const unsigned wgs = (unsigned)std::min<int64_t>(64, std::max<int64_t>(1, ctx->n_rows_max / 1024));
   hipLaunchKernelGGL(plan_rows_kernel<1>, dim3(wgs), dim3(1024), 0, st, ctx->B, ctx->K, ctx->L, ctx->d, a, ctx->tau,
-                     ctx->in_off, ctx->out_off, ctx->row_tau, ctx->row_chain, ctx->n_rows_dev + 1, (int32_t*)nullptr,
+                     ctx->in_off, ctx->out_off, ctx->row_tau, ctx->row_chain, ctx->n_rows_dev + 1, (int32_t*)nullptr, (HostReport*)nullptr,
                      prof_counting(ctx) ? ctx->row_counts : nullptr, ctx->cur_win, (const int32_t*)nullptr,
                      ctx->reuse_now ? 1 : 0, ctx->L + (ctx->reuse_now ? 1 : 0), ctx->cur_win ? 0 : model_row_block(ctx),
                      pending);
@@ -266,12 +278,7 @@ __device__ __forceinline__ int draft_books(int c, int lane, int K, int Lwin, int
   // advances and this round's slot of the live-chain ring starts at zero (the accept kernel adds to it).
   if (c == 0 && lane == 0) {
     plan.n_rows[0] = 0;
-    if (plan.ring) {
-      const int r = plan.ring[0];
-      plan.ring[0] = r + 1;
-      plan.ring[1 + (r % kLiveRing)] = 0;
-      plan.ring[1 + kLiveRing + (r % kLiveRing)] = 0;
-    }
+    if (plan.ring) start_round(plan.ring, plan.host);
   }
   // This chain's rows of the verify call: the drafted samples of slots 1..w-1 (of a piece: lo..hi-1, slot lo having been
   // drafted with the piece before it), read in place from the trajectory, results to x0hat[c][slot].  One atomic add
