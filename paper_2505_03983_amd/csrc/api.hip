@@ -227,7 +227,7 @@ static RowPlan verify_rows(asd_ctx* ctx, const float* traj, float* x0hat, int li
   const int block = ctx->cur_win ? 0 : model_row_block(ctx);    // the planner's filling of each chain's block (launch_plan_verify)
   if (block > 0) per_chain = (per_chain + block - 1) / block * block;
   return RowPlan{ctx->B * per_chain, ctx->n_rows_dev + 1, traj, x0hat, ctx->in_off, ctx->out_off, ctx->row_tau, 1,
-                 ctx->row_chain, ctx->fold_plans && draft_packs_rows(ctx), likely};
+                 ctx->row_chain, ctx->fold_plans && draft_packs_rows(ctx), -1, likely};
 }
 
 __global__ void set_key_kernel(Key* dst, Key key) { *dst = key; }
@@ -581,8 +581,10 @@ asd_status asd_sample_sequential(asd_ctx* ctx, const float* y0, float* traj, voi
   } fold_scope(ctx);
   ASD_TRY(launch_init_state(ctx, y0, traj, ctx->a, nullptr, st));
   for (int i = 0; i < ctx->K; ++i) {
-    ASD_TRY(model_eval(ctx, draft_rows(ctx, traj), st));
-    ASD_TRY(launch_seq_step(ctx, traj, i, st));
+    RowPlan rows = draft_rows(ctx, traj);
+    if (ctx->kind == ASD_DEN_MLP) rows.seq_step = i;
+    ASD_TRY(model_eval(ctx, rows, st));
+    if (ctx->kind != ASD_DEN_MLP) ASD_TRY(launch_seq_step(ctx, traj, i, st));
   }
   ASD_HIP(hipStreamSynchronize(st));
   return ASD_OK;

@@ -81,6 +81,7 @@ struct RowPlan {
   // about a chain's earlier rows to guess -- never to decide -- something about this one.
   const int32_t* chain = nullptr;
   bool packed = false;    // the kernels that listed the rows have packed them (PackOut)
+  int seq_step = -1;      // >= 0 (networks only): the rows are all chains at this step, and the call takes the step (SeqEpi)
   int likely = 0;         // rows to expect, where the host knows better than n (0: n): which tiles suit, nothing else
 };
 

@@ -81,6 +81,10 @@ __global__ __launch_bounds__(64 * Cfg::NW) void gemm_bf16_few_kernel(const int* 
 #pragma unroll
   for (int s = 0; s < STAGES; ++s)
     if (s < nst) issue(s);
+  float4 aux = make_float4(0.f, 0.f, 0.f, 0.f);   // what an epilogue can make ready while the loads are on their way
+  if constexpr (Epi::kAux) {
+    if (fin && nok) aux = epi.aux4(m, n);
+  }
   // (the row count is itself a load from memory: asked for behind the others, it costs a live workgroup nothing)
   const int M = M_dev ? min(*M_dev, M_max) : M_max;
   if (m0 >= M) {
@@ -157,7 +161,11 @@ __global__ __launch_bounds__(64 * Cfg::NW) void gemm_bf16_few_kernel(const int* 
     }
   }
   if (nslabs > part_slabs) acc = sum + acc;
-  if (fin && m < M && nok) epi.store4(m, n, make_float4(acc[0], acc[1], acc[2], acc[3]), prev, col);
+  if (fin && m < M && nok) {
+    const float4 v = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    if constexpr (Epi::kAux) epi.store4(m, n, v, prev, col, aux);
+    else epi.store4(m, n, v, prev, col);
+  }
 }
 
 template <class Cfg, class Epi>

@@ -263,7 +263,7 @@ struct InEpi {  // h = acc + b; hb = bf16 terms of h
   const float* bias;
   int64_t ld, slab;  // pitch of h (fp32), elements of a slab of hb (bf16)
   int64_t lo_plane; // > 0: offset of hb's second plane (two-term activations)
-  static constexpr bool kLoads = false;
+  static constexpr bool kLoads = false, kAux = false;
   // four consecutive columns n..n+3 (n % 4 == 0) of row m
   __device__ __forceinline__ float4 load4(int, int) const { return make_float4(0.f, 0.f, 0.f, 0.f); }
   __device__ __forceinline__ float4 column4(int n) const { return load_bias4(bias, n); }
@@ -280,7 +280,7 @@ struct BlockEpi {  // h += SiLU(acc + b); hb_next = bf16 terms of h
   const float* bias;
   int64_t ld, slab;
   int64_t lo_plane;
-  static constexpr bool kLoads = true;
+  static constexpr bool kLoads = true, kAux = false;
   __device__ __forceinline__ float4 load4(int m, int n) const {
     return *reinterpret_cast<const float4*>(h + (int64_t)m * ld + n);
   }
@@ -294,6 +294,23 @@ struct BlockEpi {  // h += SiLU(acc + b); hb_next = bf16 terms of h
   }
 };
 
+// x_0 from the output layer's acc + b: converted where the network estimates the noise (ec; x the row evaluated), clipped
+__device__ __forceinline__ float4 out_value(float4 v, bool eps, float2 ec, float4 x, float clip) {
+  if (eps) {
+    v.x = fmaf(x.x, ec.x, -v.x * ec.y);
+    v.y = fmaf(x.y, ec.x, -v.y * ec.y);
+    v.z = fmaf(x.z, ec.x, -v.z * ec.y);
+    v.w = fmaf(x.w, ec.x, -v.w * ec.y);
+  }
+  if (clip > 0.f) {
+    v.x = fminf(fmaxf(v.x, -clip), clip);
+    v.y = fminf(fmaxf(v.y, -clip), clip);
+    v.z = fminf(fmaxf(v.z, -clip), clip);
+    v.w = fminf(fmaxf(v.w, -clip), clip);
+  }
+  return v;
+}
+
 struct OutEpi {  // out[out_off[m] + n] = acc + b, as x_0 (or converted from a noise estimate), clipped
   float* out_base;
   const int64_t* out_off;
@@ -304,26 +321,64 @@ struct OutEpi {  // out[out_off[m] + n] = acc + b, as x_0 (or converted from a n
   const int32_t* tau;
   const float* in_base;
   const int64_t* in_off;
-  static constexpr bool kLoads = false;
+  static constexpr bool kLoads = false, kAux = false;
   __device__ __forceinline__ float4 load4(int, int) const { return make_float4(0.f, 0.f, 0.f, 0.f); }
   __device__ __forceinline__ float4 column4(int n) const { return load_bias4(bias, n); }
   __device__ __forceinline__ void store4(int m, int n, float4 a, float4, float4 b) const {
-    float4 v = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+    float2 ec = make_float2(0.f, 0.f);
+    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
     if (eps_coef) {
-      const float2 ec = eps_coef[tau[m]];
-      const float4 x = *reinterpret_cast<const float4*>(in_base + in_off[m] + n);
-      v.x = fmaf(x.x, ec.x, -v.x * ec.y);
-      v.y = fmaf(x.y, ec.x, -v.y * ec.y);
-      v.z = fmaf(x.z, ec.x, -v.z * ec.y);
-      v.w = fmaf(x.w, ec.x, -v.w * ec.y);
+      ec = eps_coef[tau[m]];
+      x = *reinterpret_cast<const float4*>(in_base + in_off[m] + n);
     }
-    if (clip > 0.f) {
-      v.x = fminf(fmaxf(v.x, -clip), clip);
-      v.y = fminf(fmaxf(v.y, -clip), clip);
-      v.z = fminf(fmaxf(v.z, -clip), clip);
-      v.w = fminf(fmaxf(v.w, -clip), clip);
+    *reinterpret_cast<float4*>(out_base + out_off[m] + n) =
+        out_value(make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w), eps_coef != nullptr, ec, x, clip);
+  }
+};
+
+// The output layer of a sequential step (row m: chain m, at step i): takes the step with the value it has just formed, and
+// packs the row for the next one.  As a kernel of its own the step was 4 us of a policy step's 38.  Same expressions as
+// seq_step_kernel's, same bits.
+struct SeqEpi {
+  float* traj;   // the chains' row i, (K + 1) d apart; row i + 1 behind it
+  int64_t chain_stride;
+  const float* bias;
+  float clip;
+  const float2* eps_coef;   // NULL: the network predicts x_0
+  const int32_t* tau;       // step -> time index
+  const float* c_x;
+  const float* c_0;
+  const float* sigma;
+  const Key* key;
+  int i, d;
+  PackOut pack;             // in_bf NULL: the last step
+  int64_t* row_counts;      // row total for the profiler, or NULL
+  static constexpr bool kLoads = true, kAux = true;
+  __device__ __forceinline__ float4 load4(int m, int n) const {
+    return *reinterpret_cast<const float4*>(traj + m * chain_stride + n);
+  }
+  __device__ __forceinline__ float4 column4(int n) const { return load_bias4(bias, n); }
+  __device__ __forceinline__ float4 aux4(int m, int n) const { return normal4(*key, (uint32_t)m, (uint32_t)(i + 1), (uint32_t)n >> 2); }
+  __device__ __forceinline__ void store4(int m, int n, float4 a, float4 y, float4 b) const { store4(m, n, a, y, b, aux4(m, n)); }
+  __device__ __forceinline__ void store4(int m, int n, float4 a, float4 y, float4 b, float4 xi) const {
+    const float2 ec = eps_coef ? eps_coef[tau[i]] : make_float2(0.f, 0.f);
+    const float4 g = out_value(make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w), eps_coef != nullptr, ec, y, clip);
+    const float cx = c_x[i], c0 = c_0[i], sg = sigma[i];
+    y.x = fmaf(sg, xi.x, fmaf(cx, y.x, c0 * g.x));
+    y.y = fmaf(sg, xi.y, fmaf(cx, y.y, c0 * g.y));
+    y.z = fmaf(sg, xi.z, fmaf(cx, y.z, c0 * g.z));
+    y.w = fmaf(sg, xi.w, fmaf(cx, y.w, c0 * g.w));
+    *reinterpret_cast<float4*>(traj + m * chain_stride + d + n) = y;
+    if (!pack.in_bf) return;
+    store_act4(pack.in_bf + (n >> 5) * pack.slab + (int64_t)m * 32 + (n & 31), pack.plane, y);
+    const uint16_t* te = pack.temb + (int64_t)tau[i + 1] * pack.E;
+    for (int e = n; e < pack.E; e += d) {   // four numbers of the embedding to four columns of the row
+      const int k = d + e;
+      uint16_t* dst = pack.in_bf + (k >> 5) * pack.slab + (int64_t)m * 32 + (k & 31);
+      *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(te + e);
+      if (pack.plane) *reinterpret_cast<uint2*>(dst + pack.plane) = make_uint2(0u, 0u);
     }
-    *reinterpret_cast<float4*>(out_base + out_off[m] + n) = v;
+    if (row_counts && n == 0) atomicAdd((unsigned long long*)row_counts, 1ull);
   }
 };
 
@@ -455,6 +510,14 @@ asd_status mlp_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
   }
   {
     ProfScope ps(ctx, ASD_PROF_MLP_GEMM_OUT, rows.call, st);
+    if (rows.seq_step >= 0) {
+      const bool more = rows.seq_step + 1 < ctx->K;
+      const SeqEpi e{const_cast<float*>(rows.in_base) + (int64_t)rows.seq_step * d, (int64_t)(ctx->K + 1) * d, s->b_out, s->out_clip,
+                     s->eps_coef, ctx->tau, ctx->c_x, ctx->c_0, ctx->sigma, ctx->key_dev, rows.seq_step, d,
+                     more ? mlp_pack_out(ctx) : PackOut{}, more && prof_counting(ctx) ? ctx->row_counts : nullptr};
+      ASD_HIP(mlp_gemm(rows, d, W, h[cur], SlabMat{s->wp_out, slab_rows(d), 0}, e, st, s->split));
+      return ASD_OK;
+    }
     const OutEpi e{rows.out_base, rows.out_off, s->b_out, s->out_clip, s->eps_coef, rows.tau, rows.in_base, rows.in_off};
     ASD_HIP(mlp_gemm(rows, d, W, h[cur], SlabMat{s->wp_out, slab_rows(d), 0}, e, st, s->split));
   }

@@ -471,9 +471,8 @@ asd_status launch_draft(asd_ctx* ctx, float* traj, const int32_t* a, hipStream_t
   return ASD_OK;
 }
 
-// Sequential baseline: every chain takes step i, and the next step's model row (row c: chain c) is listed, and packed, with
-// it.  (With a kernel each for the step index, the plan and the packing a step of 64 chains of d 112 was ten launches, and
-// the host's pace.)
+// Sequential baseline, mixtures: every chain takes step i, and the next step's model row (row c: chain c) is listed with it.
+// (A network's output layer takes the step itself: SeqEpi in mlp.hip.)
 __global__ __launch_bounds__(256) void seq_step_kernel(int K, int d, int i, const Key* __restrict__ key_p,
                                                        const float* __restrict__ c_x, const float* __restrict__ c_0,
                                                        const float* __restrict__ sigma, const float* __restrict__ x0a,
@@ -487,7 +486,6 @@ __global__ __launch_bounds__(256) void seq_step_kernel(int K, int d, int i, cons
       plan.row_tau[c] = plan.tau[i + 1];
       if (c == 0 && plan.row_counts) atomicAdd((unsigned long long*)&plan.row_counts[0], (unsigned long long)gridDim.y);
     }
-    if (plan.pack.in_bf) pack_temb(plan.pack, c, plan.tau[i + 1], threadIdx.x, blockDim.x);
   }
   if (blk >= (d + 3) >> 2) return;
   const Key key = *key_p;
@@ -502,7 +500,6 @@ __global__ __launch_bounds__(256) void seq_step_kernel(int K, int d, int i, cons
   y.z = fmaf(sg, xi.z, fmaf(cx, y.z, c0 * g.z));
   y.w = fmaf(sg, xi.w, fmaf(cx, y.w, c0 * g.w));
   store4(row + d, blk, d, vec, y);
-  if (more && plan.pack.in_bf) pack_row4(plan.pack, c, blk, y);
 }
 
 asd_status launch_seq_step(asd_ctx* ctx, float* traj, int32_t step, hipStream_t st) {

@@ -364,3 +364,25 @@ def test_samples_of_a_wavefront_per_chain(d, C, L, K, chains, adaptive):
         f = H.follow_chain(cfg, T, model, 8, c, traj[c].cpu().numpy(), 1e-4, adaptive=adaptive)
         assert H.rel_err(traj[c].cpu().numpy(), f["y"]) <= 1e-4
         assert int(rounds[c]) == f["R"]
+
+
+@pytest.mark.parametrize("d, E, width, blocks, chains, terms, eps", [
+    (8, 24, 64, 1, 3, 2, False),         # an embedding longer than the row; one tile of 16 rows
+    (40, 8, 512, 2, 100, 1, True),       # ragged columns, tiles of 32 rows, a noise-predicting network
+    (104, 16, 520, 1, 1100, 2, False),   # the tiles of many rows
+    (64, 16, 2304, 1, 5, 2, True),       # sums in parts, added in registers
+    (72, 16, 2560, 1, 64, 1, False),     # ... and in a launch of their own (few rows of the output layer)
+    (2560, 8, 2560, 1, 64, 2, False),    # ... the output layer's too
+])
+def test_sequential_steps_of_a_network(d, E, width, blocks, chains, terms, eps):
+    """The step taken by the output layer against windows of one slot, whose draft call and draft kernel take it on their
+    own: the same chains bit for bit."""
+    cfg = dict(kind="mlp", d=d, E=E, width=width, n_blocks=blocks, K=7, L=1, act_terms=terms)
+    _, p, _ = oracle_setup(cfg)
+    p["predict_eps"] = eps
+    ctx = runtime.open_ctx(cfg, p, seed=5, chains=chains)
+    one, seq = (torch.full((chains, cfg["K"] + 1, d), float("nan"), device=DEV) for _ in range(2))
+    ctx.sample(one)
+    ctx.sample_sequential(seq)
+    ctx.close()
+    assert bool(torch.isfinite(one).all()) and torch.equal(one, seq)
