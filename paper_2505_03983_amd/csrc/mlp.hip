@@ -294,14 +294,12 @@ struct BlockEpi {  // h += SiLU(acc + b); hb_next = bf16 terms of h
   }
 };
 
-// x_0 from the output layer's acc + b: converted where the network estimates the noise (ec; x the row evaluated), clipped
-__device__ __forceinline__ float4 out_value(float4 v, bool eps, float2 ec, float4 x, float clip) {
-  if (eps) {
-    v.x = fmaf(x.x, ec.x, -v.x * ec.y);
-    v.y = fmaf(x.y, ec.x, -v.y * ec.y);
-    v.z = fmaf(x.z, ec.x, -v.z * ec.y);
-    v.w = fmaf(x.w, ec.x, -v.w * ec.y);
-  }
+// The output layer's acc + b as x_0: converted where the network estimates the noise (x the row evaluated), and clipped.
+__device__ __forceinline__ float4 from_noise(float4 v, float2 ec, float4 x) {
+  return make_float4(fmaf(x.x, ec.x, -v.x * ec.y), fmaf(x.y, ec.x, -v.y * ec.y), fmaf(x.z, ec.x, -v.z * ec.y),
+                     fmaf(x.w, ec.x, -v.w * ec.y));
+}
+__device__ __forceinline__ float4 clipped(float4 v, float clip) {
   if (clip > 0.f) {
     v.x = fminf(fmaxf(v.x, -clip), clip);
     v.y = fminf(fmaxf(v.y, -clip), clip);
@@ -325,14 +323,9 @@ struct OutEpi {  // out[out_off[m] + n] = acc + b, as x_0 (or converted from a n
   __device__ __forceinline__ float4 load4(int, int) const { return make_float4(0.f, 0.f, 0.f, 0.f); }
   __device__ __forceinline__ float4 column4(int n) const { return load_bias4(bias, n); }
   __device__ __forceinline__ void store4(int m, int n, float4 a, float4, float4 b) const {
-    float2 ec = make_float2(0.f, 0.f);
-    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (eps_coef) {
-      ec = eps_coef[tau[m]];
-      x = *reinterpret_cast<const float4*>(in_base + in_off[m] + n);
-    }
-    *reinterpret_cast<float4*>(out_base + out_off[m] + n) =
-        out_value(make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w), eps_coef != nullptr, ec, x, clip);
+    float4 v = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+    if (eps_coef) v = from_noise(v, eps_coef[tau[m]], *reinterpret_cast<const float4*>(in_base + in_off[m] + n));
+    *reinterpret_cast<float4*>(out_base + out_off[m] + n) = clipped(v, clip);
   }
 };
 
@@ -361,8 +354,9 @@ struct SeqEpi {
   __device__ __forceinline__ float4 aux4(int m, int n) const { return normal4(*key, (uint32_t)m, (uint32_t)(i + 1), (uint32_t)n >> 2); }
   __device__ __forceinline__ void store4(int m, int n, float4 a, float4 y, float4 b) const { store4(m, n, a, y, b, aux4(m, n)); }
   __device__ __forceinline__ void store4(int m, int n, float4 a, float4 y, float4 b, float4 xi) const {
-    const float2 ec = eps_coef ? eps_coef[tau[i]] : make_float2(0.f, 0.f);
-    const float4 g = out_value(make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w), eps_coef != nullptr, ec, y, clip);
+    float4 g = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+    if (eps_coef) g = from_noise(g, eps_coef[tau[i]], y);
+    g = clipped(g, clip);
     const float cx = c_x[i], c0 = c_0[i], sg = sigma[i];
     y.x = fmaf(sg, xi.x, fmaf(cx, y.x, c0 * g.x));
     y.y = fmaf(sg, xi.y, fmaf(cx, y.y, c0 * g.y));
