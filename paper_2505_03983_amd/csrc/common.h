@@ -150,7 +150,7 @@ struct asd_ctx {
   float* x0hat = nullptr;  // [B, L, d]
   int32_t* a = nullptr;    // [B]
   int32_t* live = nullptr;       // DEV [kLiveInts]: round index, the ring of live-chain counters, the ring of chains a round's
-                                 // early accept kernel left pending (or, in pieces, of a pass's verify rows), and
+                                 // early accept kernel left pending (or, without it, of a round's verify rows), and
                                  // the largest round count of a finished chain
   asd::HostReport* report = nullptr;      // pinned host memory the kernels write to, ...
   asd::HostReport* report_dev = nullptr;  // ... as the device sees it
@@ -159,7 +159,7 @@ struct asd_ctx {
   // one round of the cheap-round path as an instantiated HIP graph, valid for (g_traj, g_rounds, g_stream)
   hipGraphExec_t gexec = nullptr;
   hipGraphExec_t gexec_light = nullptr;   // the light round (draft call + early accept kernel only), same validity
-  hipGraphExec_t gexec_rows[kRowHints] = {};   // rounds in pieces with tiles for ever fewer rows (row_hint), same validity
+  hipGraphExec_t gexec_rows[kRowHints] = {};   // rounds with tiles for ever more rows (row_hint), same validity
   const void* g_traj = nullptr;
   const void* g_rounds = nullptr;
   hipStream_t g_stream = nullptr;
@@ -174,6 +174,7 @@ struct asd_ctx {
   int32_t* piece_state = nullptr;  // DEV [2 B]: see Pieces (device_util.h)
   int32_t* chain_rounds = nullptr; // DEV [B]: rounds of each chain in this sample (launches are not rounds, see asd_sample)
   asd::Pieces cur_pieces;      // what the round kernels are given: in pieces while a sample that pays for them runs
+  int hint_rows = 0;           // rows of hint 0 while a sample runs whose rows vary (row_hint), else 0
   const void* g_win = nullptr; // cur_win the round graph was captured with
   bool g_reuse = false;        // reuse_now the round graph was captured with
   bool g_pieces = false;       // whether the round graph was captured with windows in pieces

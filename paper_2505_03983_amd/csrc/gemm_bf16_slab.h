@@ -90,20 +90,16 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_bf16_slab_kernel(const int*
                                                                       int nslabs, const uint16_t* __restrict__ A,
                                                                       int64_t a_slab, int64_t a_plane,
                                                                       const uint16_t* __restrict__ W, int64_t w_slab,
-                                                                      Epi epi, float* __restrict__ part, int m_lo,
-                                                                      int m_hi) {
+                                                                      Epi epi, float* __restrict__ part) {
   constexpr int BM = Cfg::BM, BN = Cfg::BN, SPS = Cfg::SPS, STAGES = Cfg::STAGES, MI = Cfg::MI, NJ = Cfg::NJ, NW = Cfg::NW;
   constexpr int AR = Cfg::AR, PL = Cfg::PL, AI = PL * MI;   // AI: A fragments per k group (all planes)
   constexpr int WM = Cfg::WM, WN = Cfg::WN, NG = Cfg::NG;
   constexpr int A_LOADS = Cfg::A_LOADS, LPSL = Cfg::LPSL, LPS = Cfg::LPS;
   extern __shared__ __attribute__((aligned(16))) uint8_t ldsb[];
 
-  const int M_all = M_dev ? *M_dev : M_max;   // the gate below looks at the true row count
-  const int M = min(M_all, M_max);
+  const int M = M_dev ? min(*M_dev, M_max) : M_max;
   const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  // (m_lo, m_hi]: the row counts this launch serves -- the caller may queue several tile shapes for one
-  // product and let the row count, known on the device only, pick the one that runs
-  if (m0 >= M || M_all <= m_lo || M_all > m_hi) return;
+  if (m0 >= M) return;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -346,13 +342,11 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_bf16_slab_kernel(const int*
 // One thread per four columns of a row: partials added in z order, then the epilogue.
 template <class Epi>
 __global__ __launch_bounds__(256) void splitk_finish_kernel(const int* __restrict__ M_dev, int M_max, int N, int splits,
-                                                            const float* __restrict__ part, Epi epi, int m_lo,
-                                                            int m_hi) {
-  const int M_all = M_dev ? *M_dev : M_max;
-  const int M = min(M_all, M_max);
+                                                            const float* __restrict__ part, Epi epi) {
+  const int M = M_dev ? min(*M_dev, M_max) : M_max;
   const int m = blockIdx.y;
   const int n = (blockIdx.x * 256 + threadIdx.x) * 4;
-  if (m >= M || n >= N || M_all <= m_lo || M_all > m_hi) return;
+  if (m >= M || n >= N) return;
   const float4 prev = Epi::kLoads ? epi.load4(m, n) : make_float4(0.f, 0.f, 0.f, 0.f);
   float4 v = *reinterpret_cast<const float4*>(part + (int64_t)m * N + n);
   for (int z = 1; z < splits; ++z) {
@@ -372,7 +366,7 @@ struct SlabMat {
 // splits > 1 needs (number of 64-wide slab pairs) % splits == 0 and `part` of splits * M * N floats.
 template <class Cfg, int CALL, class Epi>
 inline hipError_t launch_gemm_bf16_slab(const int* M_dev, int M, int N, int K, SlabMat A, SlabMat W, Epi epi, hipStream_t st,
-                                        int splits = 1, float* part = nullptr, int m_lo = -1, int m_hi = 0x7fffffff) {
+                                        int splits = 1, float* part = nullptr) {
   const int nslabs = slab_count(K);
   if (splits < 1 || (nslabs / 2) % splits != 0 || (splits > 1 && !part)) return hipErrorInvalidValue;
   if (M > A.rows || N > W.rows || A.rows % kSlabRows || W.rows % kSlabRows) return hipErrorInvalidValue;
@@ -386,10 +380,10 @@ inline hipError_t launch_gemm_bf16_slab(const int* M_dev, int M, int N, int K, S
     attr_set = true;
   }
   hipLaunchKernelGGL(kern, grid, dim3(Cfg::THREADS), Cfg::LDS_BYTES, st, M_dev, M, N, nslabs, A.p, A.rows * 32, A.plane,
-                     W.p, W.rows * 32, epi, part, m_lo, m_hi);
+                     W.p, W.rows * 32, epi, part);
   if (splits > 1)
     hipLaunchKernelGGL(splitk_finish_kernel<Epi>, dim3((unsigned)((N / 4 + 255) / 256), (unsigned)M), dim3(256), 0, st,
-                       M_dev, M, N, splits, part, epi, m_lo, m_hi);
+                       M_dev, M, N, splits, part, epi);
   return hipGetLastError();
 }
 

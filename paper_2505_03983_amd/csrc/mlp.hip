@@ -72,22 +72,17 @@ constexpr int kMaxSplits = 8;
 struct SplitScratch {
   float* part = nullptr;   // [kMaxSplits][rows][max N] fp32 partial tiles
   int rows = 0;            // rows the scratch was sized for (one per chain)
-  bool small_verify = false;  // verify calls may be far below their row bound (windows from the controller)
 };
-// Verify calls of at most this many rows against a large weight matrix have a launch of their own when the controller
-// chooses the windows: both are queued, and the row count in device memory decides which one does the work.
-constexpr int kSmallVerifyRows = 256;
 
 template <int PL, int CALL, class Epi>
-static hipError_t mlp_gemm_tile(int tile, const int* n_dev, int n, int N, int K, SlabMat A, SlabMat Wt, Epi e, hipStream_t st,
-                                int m_lo, int m_hi) {
+static hipError_t mlp_gemm_tile(int tile, const int* n_dev, int n, int N, int K, SlabMat A, SlabMat Wt, Epi e, hipStream_t st) {
   typedef MlpTiles<PL> T;
   switch (tile) {
-    case 0: return launch_gemm_bf16_slab<typename T::T128x256, CALL>(n_dev, n, N, K, A, Wt, e, st, 1, nullptr, m_lo, m_hi);
-    case 1: return launch_gemm_bf16_slab<typename T::T128x128, CALL>(n_dev, n, N, K, A, Wt, e, st, 1, nullptr, m_lo, m_hi);
-    case 2: return launch_gemm_bf16_slab<typename T::T64x128, CALL>(n_dev, n, N, K, A, Wt, e, st, 1, nullptr, m_lo, m_hi);
-    case 3: return launch_gemm_bf16_slab<typename T::T64x64, CALL>(n_dev, n, N, K, A, Wt, e, st, 1, nullptr, m_lo, m_hi);
-    default: return launch_gemm_bf16_slab<typename T::T32x64, CALL>(n_dev, n, N, K, A, Wt, e, st, 1, nullptr, m_lo, m_hi);
+    case 0: return launch_gemm_bf16_slab<typename T::T128x256, CALL>(n_dev, n, N, K, A, Wt, e, st);
+    case 1: return launch_gemm_bf16_slab<typename T::T128x128, CALL>(n_dev, n, N, K, A, Wt, e, st);
+    case 2: return launch_gemm_bf16_slab<typename T::T64x128, CALL>(n_dev, n, N, K, A, Wt, e, st);
+    case 3: return launch_gemm_bf16_slab<typename T::T64x64, CALL>(n_dev, n, N, K, A, Wt, e, st);
+    default: return launch_gemm_bf16_slab<typename T::T32x64, CALL>(n_dev, n, N, K, A, Wt, e, st);
   }
 }
 
@@ -122,7 +117,6 @@ template <int PL, class Epi>
 static hipError_t mlp_gemm_planes(int call, const int* n_dev, int n, int likely, int N, int K, SlabMat A, SlabMat Wt, Epi e,
                                   hipStream_t st, const SplitScratch& sc) {
   const int Kp = slab_count(K) * 32;
-  const bool large = large_matrix(N, Kp);
   // One row per chain against a large matrix: a stream of the weights, K split over workgroups.  64 x 64 tiles and a K split
   // that gives every CU a workgroup keep ~14 MB of it in flight, which is what HBM latency asks for; only a large matrix
   // repays the second launch.  (The split is a matter of the sizes alone, and the kernel for few rows adds its parts up
@@ -133,16 +127,9 @@ static hipError_t mlp_gemm_planes(int call, const int* n_dev, int n, int likely,
   if (few >= 0) return mlp_gemm_few<PL>(few, n_dev, n, N, K, A, Wt, e, st, splits);
   if (call == 0) {
     if (splits > 1) return launch_gemm_bf16_slab<T, 0>(n_dev, n, N, K, A, Wt, e, st, splits, sc.part);
-    return mlp_gemm_tile<PL, 0>(pick_tile(PL, n, N, Kp), n_dev, n, N, K, A, Wt, e, st, -1, 0x7fffffff);
+    return mlp_gemm_tile<PL, 0>(pick_tile(PL, n, N, Kp), n_dev, n, N, K, A, Wt, e, st);
   }
-  int m_lo = -1;
-  if (sc.small_verify && n > kSmallVerifyRows && large) {
-    const hipError_t e0 = mlp_gemm_tile<PL, 1>(pick_tile(PL, kSmallVerifyRows, N, Kp), n_dev, kSmallVerifyRows, N, K, A, Wt, e,
-                                               st, -1, kSmallVerifyRows);
-    if (e0 != hipSuccess) return e0;
-    m_lo = kSmallVerifyRows;
-  }
-  return mlp_gemm_tile<PL, 1>(pick_tile(PL, likely, N, Kp), n_dev, n, N, K, A, Wt, e, st, m_lo, 0x7fffffff);
+  return mlp_gemm_tile<PL, 1>(pick_tile(PL, likely, N, Kp), n_dev, n, N, K, A, Wt, e, st);
 }
 
 template <class Epi>
@@ -476,7 +463,6 @@ double mlp_call_cost(const asd_ctx* ctx, int call, int rows) {
 asd_status mlp_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
   MlpState* s = ctx->mlp;
   const int n = rows.n, d = ctx->d, W = s->width;
-  s->split.small_verify = ctx->cur_win != nullptr;
   if (!rows.packed) {
     ProfScope ps(ctx, ASD_PROF_MLP_PACK, rows.call, st);
     const int groups = s->in_dim / 8;

@@ -571,7 +571,8 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
                                                       int32_t* __restrict__ win, PlanOut plan,
                                                       int64_t* __restrict__ prof_counts,
                                                       const int32_t* __restrict__ pending, Pieces pieces,
-                                                      int32_t* __restrict__ chain_rounds) {
+                                                      int32_t* __restrict__ chain_rounds,
+                                                      const int32_t* rows_seen) {
   // pending (or NULL): chains with pending[c] == 0 have had their round already (accept_early_kernel)
   __shared__ float s_part[kAcceptChunkMax][16][2];  // per slot of the chunk, per wavefront: partial <D,xi>, |D|^2
   __shared__ float s_rej[2];                     // <D,xi>, |D|^2 of the first rejected slot
@@ -584,13 +585,11 @@ __global__ __launch_bounds__(1024) void accept_kernel(int K, int L, int d, const
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int ac = a[c];
-  // the verify call has consumed its row count: the draft kernel of the next round starts from zero
+  // the verify call has consumed its row count, which tells the host what tiles suit the next ones: the draft kernel of the
+  // next round starts from zero
+  if (rows_seen && live && c == 0 && tid == 0) live[1 + kLiveRing + ((live[0] - 1) % kLiveRing)] = *rows_seen;
   if constexpr (FOLD) {
-    if (c == 0 && tid == 0) {
-      // (how many there were tells the host which tiles suit the next ones)
-      if (pieces.state && live) live[1 + kLiveRing + ((live[0] - 1) % kLiveRing)] = plan.n_rows[1];
-      plan.n_rows[1] = 0;
-    }
+    if (c == 0 && tid == 0) plan.n_rows[1] = 0;
   }
   if (ac >= K || ac < 0) {
     if (tid == 0 && accepted) accepted[c] = -1;
@@ -1137,7 +1136,8 @@ asd_status launch_accept(asd_ctx* ctx, float* traj, int32_t* a, const float* x0h
   const auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(ctx->B), dim3(64 * waves * groups), 0, st, ctx->K, ctx->L, ctx->d, ctx->key_dev, a, ctx->c_0,
                        ctx->sigma, ctx->x0a, carry, x0hat, x0_slots, traj, accepted, stats, rounds, live, ctx->cur_win, plan,
-                       prof_counts, pending, ctx->cur_pieces, ctx->chain_rounds);
+                       prof_counts, pending, ctx->cur_pieces, ctx->chain_rounds,
+                       pending ? (const int32_t*)nullptr : ctx->n_rows_dev + 1);
   };
   if (plan.in_off) {
     if (groups >= 8) go(accept_kernel<true, 1>);
