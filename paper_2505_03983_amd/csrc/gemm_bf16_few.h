@@ -9,6 +9,14 @@
 // same layers take 4.2 us instead of 5.1, but a sample's accept tests would then see other roundings than a larger
 // batch's.  Accumulators passed from wavefront to wavefront instead: 0.15 us a pass, 7 us in all.)
 //
+// Of the 9000 cycles of 16 x 1024 x 1024, two planes, 3500 passed until half of the operands had landed and 4200 in the
+// products, two thirds of that waiting for LDS: the loads were global ones, behind which the compiler waits for every read
+// of LDS outstanding (load_to_lds), and it moved the reads up against their products.  As buffer loads, with the reads a batch ahead held
+// in place, the products take 2900, the 64 dependent instructions' own latency: 4.8 -> 4.3 us a layer, 1536 x 1536 6.5 -> 5.8, 2048 x
+// 2048 7.9 -> 7.1; one plane 3.8 -> 3.5, 5.2 -> 4.8, 6.0 -> 5.7.  (Stages of 8 slabs, whose first lands sooner: 4.9, a hand-over
+// costs 400 cycles.  A wavefront that loads its operands into registers, with no hand-over at all: 6.5, sixty loads of it on
+// their way are too few.)
+//
 // v_mfma_f32_16x16x32_bf16 adds its products in the order of two 32x32x16 (k 0..15, then 16..31), bit for bit.  One plane
 // of A: an instruction takes a slab.  Two planes: an instruction takes 16 k, the hi terms in its lower k half, the lo terms
 // in its upper one, the weights in both -- the order of the tiled kernel, at one instruction instead of two.  The weights
@@ -65,8 +73,8 @@ __global__ __launch_bounds__(64 * Cfg::NW) void gemm_bf16_few_kernel(const int* 
   }
   const int nst = (nslabs + SS - 1) / SS;
   const uint32_t lane_off = (lane >> 2) * 64 + (((lane & 3) ^ ((lane >> 4) & 3)) * 16);
-  const uint8_t* abase = reinterpret_cast<const uint8_t*>(A) + (int64_t)m0 * 64 + lane_off;
-  const uint8_t* wbase = reinterpret_cast<const uint8_t*>(W) + (int64_t)n0 * 64 + lane_off;
+  const uint8_t* abase = reinterpret_cast<const uint8_t*>(A) + (int64_t)m0 * 64;
+  const uint8_t* wbase = reinterpret_cast<const uint8_t*>(W) + (int64_t)n0 * 64;
   auto issue = [&](int st) {   // (blocks past the last slab repeat it; nobody reads them)
     uint8_t* dst = ldsb + ((st % STAGES) * SS + wave % SS) * (BPS * 1024);
     const int s = min(st * SS + wave % SS, nslabs - 1);
@@ -75,7 +83,7 @@ __global__ __launch_bounds__(64 * Cfg::NW) void gemm_bf16_few_kernel(const int* 
       const int j = Cfg::WPS == 1 ? i : (wave / SS) * LPW + i;   // block of the slab
       const uint8_t* g = j < PL * MI ? abase + ((int64_t)s * a_slab + (int64_t)(j / MI) * a_plane + (j % MI) * 16 * 32) * 2
                                      : wbase + ((int64_t)s * w_slab + (j - PL * MI) * 16 * 32) * 2;
-      __builtin_amdgcn_global_load_lds((glb_ptr_t)g, (lds_ptr_t)(dst + j * 1024), 16, 0, 0);
+      load_to_lds(g, lane_off, dst + j * 1024);
     }
   };
 #pragma unroll
@@ -116,14 +124,15 @@ __global__ __launch_bounds__(64 * Cfg::NW) void gemm_bf16_few_kernel(const int* 
       const uint8_t* sb = ldsb + (st % STAGES) * (Cfg::STAGE_BLOCKS * 1024);
       const int ns = min(SS, nslabs - st * SS);   // even
       v8bf af[2][U][H], wf[2][U][H];
+      auto read_one = [&](int buf, int s0, int u, int g) {
+        af[buf][u][g] = *reinterpret_cast<const v8bf*>(sb + (s0 + u) * (BPS * 1024) + a_off + cp[g]);
+        wf[buf][u][g] = *reinterpret_cast<const v8bf*>(sb + (s0 + u) * (BPS * 1024) + w_off + cp[g]);
+      };
       auto read = [&](int buf, int s0) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-          for (int g = 0; g < H; ++g) {
-            af[buf][u][g] = *reinterpret_cast<const v8bf*>(sb + (s0 + u) * (BPS * 1024) + a_off + cp[g]);
-            wf[buf][u][g] = *reinterpret_cast<const v8bf*>(sb + (s0 + u) * (BPS * 1024) + w_off + cp[g]);
-          }
+          for (int g = 0; g < H; ++g) read_one(buf, s0, u, g);
       };
       auto mma = [&](int buf, int s0) {
 #pragma unroll
@@ -136,17 +145,21 @@ __global__ __launch_bounds__(64 * Cfg::NW) void gemm_bf16_few_kernel(const int* 
           }
       };
       if (ns == SS && (next <= st * SS ? part_slabs >= SS : next >= st * SS + SS)) {
-        // a full stage of one part: straight-line code, reads a batch ahead
+        // a full stage of one part: straight-line code, reads a batch ahead.  (Left to itself the compiler moves every read
+        // up against the product that needs it, and the loop pays the latency of LDS for each.)
         close_part(st * SS);
         read(0, 0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s0 = 0; s0 < SS; s0 += U) {
-          if (s0 + U < SS) read((s0 / U + 1) & 1, s0 + U);
 #pragma unroll
           for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int g = 0; g < H; ++g)
+            for (int g = 0; g < H; ++g) {
+              if (s0 + U < SS) read_one((s0 / U + 1) & 1, s0 + U, u, g);
               acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[(s0 / U) & 1][u][g], af[(s0 / U) & 1][u][g], acc, 0, 0, 0);
+              __builtin_amdgcn_sched_barrier(0);
+            }
         }
       } else {
         for (int s0 = 0; s0 < ns; s0 += U) {   // (reads past ns stay inside the stage: SS is a multiple of U)

@@ -73,3 +73,22 @@ def test_no_lds_read_is_outstanding_at_a_barrier(source, least, tmp_path):
     assert len(ks) >= least
     bad = {k: b for k, b in ((k, reads_at_barriers(v)) for k, v in ks.items()) if any(b)}
     assert not bad, bad
+
+
+def test_kernels_that_load_through_buffers_hand_over_cleanly(tmp_path):
+    """The same for the kernels all of whose direct loads are buffer loads (the products of few rows), and those loads do
+    not make the compiler wait for every read of LDS at once: waits in their loops leave some outstanding."""
+    out = tmp_path / "k.s"
+    flags = [f for f in build.FLAGS if f != "-shared"]
+    r = subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + flags +
+                       ["--cuda-device-only", "-S", os.path.join(build.CSRC, "mlp.hip"), "-o", str(out)],
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
+    asm = re.sub(r"\bbuffer_load_dwordx4 (?=.* lds\b)", "global_load_lds_dwordx4 ", out.read_text())
+    ks = {k: v for k, v in kernels(asm).items() if "gemm_bf16_few" in k}
+    assert len(ks) >= 16
+    bad = {k: b for k, b in ((k, reads_at_barriers(v)) for k, v in ks.items()) if any(b)}
+    assert not bad, bad
+    for k, body in ks.items():
+        waits = [int(m.group(1)) for m in (re.search(r"lgkmcnt\((\d+)\)", x) for x in body if x.startswith("s_waitcnt")) if m]
+        assert sum(n >= 2 for n in waits) >= 6, (k, waits)
