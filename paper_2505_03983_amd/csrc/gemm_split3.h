@@ -48,8 +48,10 @@
 //    alike, so the pairing of elements is exact; per slab a wavefront reads 3 (MI + NJ) fragments
 //    and issues 6 MI NJ MFMAs -- twice the MFMAs per fragment of a plain bf16 GEMM.
 //
-// Requirements (checked by the host): K % 16 == 0, rows of A 16-byte aligned.  Rows of the image past
-// N are zero.  M is read from device memory; workgroups past it exit at once.
+// Requirements (checked by the host): K a multiple of the slab -- or of 4, with KTAIL: the image's last slab is then padded
+// with zeros, and the loader puts the Op's kPadA, which load_a maps to 0, in place of A's columns past K (a row ends
+// there).  Rows of A 16-byte aligned.  Rows of the image past N are zero.  M is read from device memory; workgroups past it
+// exit at once.
 //
 // Sparse K (Ops with kSparseK, no K split).  When load_a maps whole stretches of A to exactly 0.0f -- the
 // second GEMM of the mixture denoiser, whose A operand is 2^(logit - row maximum): once a posterior has
@@ -103,7 +105,7 @@ struct Split3Cfg {
 // Bytes of the B image for an [N, K] operand.
 template <class Cfg>
 inline size_t split3_image_bytes(int N, int K) {
-  return (size_t)((N + Cfg::BN - 1) / Cfg::BN) * (size_t)(K / Cfg::BK) * Cfg::B_STAGE;
+  return (size_t)((N + Cfg::BN - 1) / Cfg::BN) * (size_t)((K + Cfg::BK - 1) / Cfg::BK) * Cfg::B_STAGE;
 }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -151,23 +153,23 @@ __device__ __forceinline__ void split_pack(const float (&x)[8], u32x4 (&p)[3]) {
   else split2_pack(x, p[0], p[1]);
 }
 
-// B [N, K] fp32 (row stride ldb), times `scale` (a power of two; 1 for three bf16 terms) -> image.  One thread per
-// (row of the padded tile grid, chunk of 8 k).
+// B [N, K] fp32 (row stride ldb), times `scale` (a power of two; 1 for three bf16 terms) -> image, zeros in the padding of K to
+// whole slabs.  One thread per (row of the padded tile grid, chunk of 8 k).
 template <class Cfg>
 __global__ __launch_bounds__(256) void split3_pack_b_kernel(const float* __restrict__ B, int64_t ldb, int N, int K,
                                                             uint8_t* __restrict__ img, float scale) {
-  const int kc = K / 8;
+  const int nslabs = (K + Cfg::BK - 1) / Cfg::BK, kc = nslabs * Cfg::KQ;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t n_pad = (int64_t)((N + Cfg::BN - 1) / Cfg::BN) * Cfg::BN;
   if (idx >= n_pad * kc) return;
   const int n = (int)(idx / kc), c8 = (int)(idx % kc);
   float x[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) x[e] = n < N ? scale * B[(int64_t)n * ldb + c8 * 8 + e] : 0.f;
+  for (int e = 0; e < 8; ++e) x[e] = n < N && c8 * 8 + e < K ? scale * B[(int64_t)n * ldb + c8 * 8 + e] : 0.f;
   u32x4 p[3];
   split_pack<Cfg::PLANES>(x, p);
   const int tn = n / Cfg::BN, r = n % Cfg::BN, ks = c8 / Cfg::KQ, c = c8 % Cfg::KQ;
-  uint8_t* dst = img + ((int64_t)tn * (K / Cfg::BK) + ks) * Cfg::B_STAGE + r * Cfg::RB + Cfg::slot(r, c) * 16;
+  uint8_t* dst = img + ((int64_t)tn * nslabs + ks) * Cfg::B_STAGE + r * Cfg::RB + Cfg::slot(r, c) * 16;
 #pragma unroll
   for (int pl = 0; pl < Cfg::PLANES; ++pl) *reinterpret_cast<u32x4*>(dst + pl * Cfg::B_PLANE) = p[pl];
 }
@@ -176,7 +178,7 @@ template <class Cfg>
 inline hipError_t launch_split3_pack_b(const float* B, int64_t ldb, int N, int K, uint8_t* img, hipStream_t st,
                                        float scale = 1.f) {
   const int64_t n_pad = (int64_t)((N + Cfg::BN - 1) / Cfg::BN) * Cfg::BN;
-  const int64_t threads = n_pad * (K / 8);
+  const int64_t threads = n_pad * ((K + Cfg::BK - 1) / Cfg::BK * Cfg::KQ);
   hipLaunchKernelGGL(split3_pack_b_kernel<Cfg>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, B, ldb, N, K,
                      img, scale);
   return hipGetLastError();
@@ -193,7 +195,7 @@ inline hipError_t launch_split3_pack_b(const float* B, int64_t ldb, int N, int K
 // GEMM of the mixture denoiser: A = 1 GB of logits, 8 column tiles): all column tiles of a row tile run on one
 // XCD, back to back, so a tile of A crosses the fabric once instead of once per XCD.
 // One output tile (tile_m, tile_n) by the calling workgroup.
-template <class Cfg, class Op>
+template <class Cfg, class Op, bool KTAIL = false>
 __device__ __forceinline__ void split3_tile(int M, int M_max, int N, int K, const RowSrc& A,
                                             const uint8_t* __restrict__ Bimg, Op& op, float* __restrict__ part,
                                             int sparse, int tile_m, int tile_n) {
@@ -221,7 +223,7 @@ __device__ __forceinline__ void split3_tile(int M, int M_max, int N, int K, cons
   const int wave = tid >> 6;
   const Frag<Cfg> fr{wave / Cfg::WGN, wave % Cfg::WGN, lane & 31, lane >> 5, tile_n};
   const int splits = gridDim.z;                  // K split: this workgroup contracts slabs kb .. kb + nk - 1
-  const int nk_all = K / BK, kb = blockIdx.z * (nk_all / splits);
+  const int nk_all = KTAIL ? (K + BK - 1) / BK : K / BK, kb = blockIdx.z * (nk_all / splits);
   int nk = nk_all / splits;
 
   // ---- loaders.  A: thread = (row lrow + RPP p, chunk lkq of 8 k).  B: thread t copies bytes 16 t + 16 THREADS q
@@ -281,8 +283,19 @@ __device__ __forceinline__ void split3_tile(int M, int M_max, int N, int K, cons
     const int64_t sl = slab_of(kt);
 #pragma unroll
     for (int p = 0; p < RA; ++p) {
-      ra[slot][p][0] = *reinterpret_cast<const float4*>(ap[p] + sl * BK);
-      ra[slot][p][1] = *reinterpret_cast<const float4*>(ap[p] + sl * BK + 4);
+      if constexpr (KTAIL) {   // (no K split: kb is 0)
+        const int k = (int)sl * BK + lkq * 8;
+        const float* row = ap[p] - lkq * 8;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const bool in = k + 4 * h < K;
+          const float4 v = *reinterpret_cast<const float4*>(row + (in ? k + 4 * h : 0));
+          ra[slot][p][h] = in ? v : make_float4(Op::kPadA, Op::kPadA, Op::kPadA, Op::kPadA);
+        }
+      } else {
+        ra[slot][p][0] = *reinterpret_cast<const float4*>(ap[p] + sl * BK);
+        ra[slot][p][1] = *reinterpret_cast<const float4*>(ap[p] + sl * BK + 4);
+      }
     }
 #pragma unroll
     for (int q = 0; q < B_LOADS; ++q)
@@ -413,7 +426,7 @@ __device__ __forceinline__ void split3_tile(int M, int M_max, int N, int K, cons
 }
 
 // Grid: (column tiles, row tiles, K splits), one tile per workgroup.
-template <class Cfg, class Op, int CALL, bool ROWS_PER_XCD>
+template <class Cfg, class Op, int CALL, bool ROWS_PER_XCD, bool KTAIL>
 __global__ __launch_bounds__(Cfg::THREADS, 2) void gemm_split3_nt_kernel(const int* __restrict__ M_dev, int M_max,
                                                                          int N, int K, RowSrc A,
                                                                          const uint8_t* __restrict__ Bimg, Op op,
@@ -431,7 +444,7 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void gemm_split3_nt_kernel(const i
     tile_m = (int)(8 * G + r % 8);
     tile_n = (int)(r / 8);
   }
-  split3_tile<Cfg, Op>(M, M_max, N, K, A, Bimg, op, part, sparse, tile_m, tile_n);
+  split3_tile<Cfg, Op, KTAIL>(M, M_max, N, K, A, Bimg, op, part, sparse, tile_m, tile_n);
 }
 
 // The list form, for an Op with kTileList that carries lists of the wanted tiles: tile_list = 8 lists of list_cap
@@ -504,11 +517,11 @@ inline bool split3_sparse_fits(int K, int groups, int group_cols) {
 // splits > 1 (Ops with kSplitK, not with ROWS_PER_XCD): `part` = gemm_f32_splitk_floats(splits, M_max, N) floats.
 // sparse: let an Op with kSparseK skip the slabs of K it marks dead (needs K / BK <= 65535, the Op's column groups a
 // multiple of BK wide and K a multiple of them; otherwise the loop stays dense).
-template <class Cfg, int CALL, bool ROWS_PER_XCD, class Op>
+template <class Cfg, int CALL, bool ROWS_PER_XCD, bool KTAIL = false, class Op>
 inline hipError_t launch_gemm_split3_nt(const int* M_dev, int M_max, int N, int K, RowSrc A, const uint8_t* Bimg,
                                         Op op, hipStream_t st, int splits = 1, float* part = nullptr, bool sparse = false,
                                         const int32_t* run_if = nullptr, int run_val = 0) {
-  if (K % Cfg::BK != 0 || K <= 0 || splits < 1) return hipErrorInvalidValue;
+  if (K % (KTAIL ? 4 : Cfg::BK) != 0 || K <= 0 || splits < 1 || (KTAIL && splits > 1)) return hipErrorInvalidValue;
   size_t lds = Cfg::LDS_BYTES;
   if constexpr (Op::kSparseK) {
     sparse = sparse && splits == 1 && split3_sparse_fits<Cfg>(K, op.groups(), op.group_cols());
@@ -521,7 +534,7 @@ inline hipError_t launch_gemm_split3_nt(const int* M_dev, int M_max, int N, int 
   unsigned mt = (unsigned)((M_max + Cfg::BM - 1) / Cfg::BM);
   if (ROWS_PER_XCD) mt = (mt + 7) / 8 * 8;
   dim3 grid((unsigned)((N + Cfg::BN - 1) / Cfg::BN), mt, (unsigned)splits);
-  auto kern = gemm_split3_nt_kernel<Cfg, Op, CALL, ROWS_PER_XCD>;
+  auto kern = gemm_split3_nt_kernel<Cfg, Op, CALL, ROWS_PER_XCD, KTAIL>;
   static bool attr_set = false;   // dynamic LDS above the default limit needs the attribute once per kernel
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);

@@ -336,6 +336,7 @@ __global__ __launch_bounds__(256) void gmm_rowwise_lds_kernel(const int* __restr
 // (pmax[row][WGN*column_tile + wn]); the softmax normalisation is finished
 // inside GEMM 2, so the logits are written once and read once.
 struct LogitOp {
+  static constexpr float kPadA = 0.f;
   static constexpr bool kSplitK = false;
   static constexpr bool kSparseK = false;
   static constexpr bool kTileList = true;
@@ -445,6 +446,7 @@ struct LogitOp {
 // into exp(logit - rowmax) on its way into LDS; the row sums are accumulated on
 // the side and divided out in the epilogue.
 struct CombineOp {
+  static constexpr float kPadA = -INFINITY;   // a logit of weight 0
   static constexpr bool kSplitK = true;
   static constexpr bool kSparseK = true;
   static constexpr bool kTileList = false;
@@ -1388,17 +1390,24 @@ struct TiledCost {
 constexpr TiledCost kTiledF32 = {128, 128, 256, 0., .078, 6.5, .055, 7.8}, kTiledBf16 = {128, 128, 256, 36., .0365, 7.3, .048, 11.5},
                     kTiledFp16 = {128, 128, 256, 34., .0151, 13.8, .0259, 18.3}, kDraftF32 = {64, 64, 512, 0., .0395, 3.3, .0438, 8.5},
                     kDraftFp16 = {64, 128, 256, 2., .0109, 6.3, .003, 9.9};
+static double tiled_cost(const TiledCost& k, int splits, int64_t n, int64_t d, int64_t C) {
+  const double r1 = (double)(ceil_div(n, k.bm) * ceil_div(C, k.bn)) / k.slots;
+  const double r2 = (double)(ceil_div(n, k.bm) * ceil_div(d, k.bn) * splits) / k.slots;
+  return k.launch + (k.d1 * d + k.o1) * std::max(1., r1) + (k.c2 * C / splits + k.o2) * std::max(1., r2);
+}
 static bool few_rows_pays(const TiledCost& k, int splits, int64_t n, int64_t d, int64_t C) {
   const bool large = few_large_tiles(n, (int)C);
   const int b = large ? 32 : 16, group = large ? 128 : 64;
   const double f1 = (double)(ceil_div(n, b) * ceil_div(C, group)) / 256., f2 = (double)(ceil_div(n, b) * ceil_div(d, b)) / 256.;
   const double few = large ? 5. + .0127 * d + .0057 * C + (.0241 * d + 1.06) * f1 + (.009 * C + 1.06) * f2
                            : .0085 * d + .0031 * C + .49 * f1 + (.0066 * C + .49) * f2;
-  const double r1 = (double)(ceil_div(n, k.bm) * ceil_div(C, k.bn)) / k.slots;
-  const double r2 = (double)(ceil_div(n, k.bm) * ceil_div(d, k.bn) * splits) / k.slots;
-  const double tiled = k.launch + (k.d1 * d + k.o1) * std::max(1., r1) + (k.c2 * C / splits + k.o2) * std::max(1., r2);
-  return few < tiled;
+  return few < tiled_cost(k, splits, n, d, C);
 }
+// Whether a verify call of a size that is no multiple of 16 is faster padded to whole slabs of fp16 terms, five launches, than
+// on fp32 tiles, two: by the figures above.  Microseconds a call, fp32 / padded, (d, C) x rows: (1000, 4000) x 5000 789 / 409,
+// (500, 2000) x 8000 408 / 199, (1020, 3000) x 3000 426 / 255, (300, 1000) x 8000 143 / 119; and where it is not, (100, 400) x
+// 12000 59 / 88, (900, 100) x 12000 120 / 137, (60, 516) x 20000 89 / 109, (36, 2052) x 8000 163 / 171.
+static bool padding_pays(int64_t n, int64_t d, int64_t C) { return tiled_cost(kTiledFp16, 1, n, d, C) < tiled_cost(kTiledF32, 1, n, d, C); }
 
 asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
   GmmState* g = new (std::nothrow) GmmState();
@@ -1454,8 +1463,13 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
   g->rowwise_lds = sizeof(float) * 4 * (size_t)(d + C);
   const bool aligned = (d % 4 == 0) && (C % 4 == 0);
   g->use_mfma = aligned && (double)ctx->n_rows_max * C * d >= (double)(1 << 26);
-  if (g->use_mfma && d % 16 == 0 && C % 16 == 0) {
-    if (d % GmmTile2::BK == 0 && C % GmmTile2::BK == 0) {
+  // d or C no multiple of 16: the verify call on fp16 terms too, the sums over d and C padded to whole slabs (KTAIL).  Against 64
+  // bits its error is that of the whole-slab form, below the fp32 kernels' -- a slab's products are added with fewer roundings:
+  // relative (2-norm) error against double precision, fp32 / this, 5000 rows of (1000, 4000) 5.3e-7 / 3.6e-7, 8000 of (300, 1000)
+  // 3.5e-7 / 2.2e-7, of (36, 2052) 3.0e-7 / 2.3e-7, largest error over the results' rms 2.4e-5 / 2.4e-5, 2.4e-5 / 1.5e-5, 9.0e-6 / 4.7e-6.
+  const bool multiple = d % 16 == 0 && C % 16 == 0;
+  if (g->use_mfma) {
+    if (!multiple || (d % GmmTile2::BK == 0 && C % GmmTile2::BK == 0)) {
       // fp16 terms for both calls: the means times b_scale (a power of two that brings the largest |mu| into fp16's
       // upper range), one image per GEMM for both tilings, and the means as their two fp16 terms carry them
       uint32_t* mx_dev = nullptr;
@@ -1478,8 +1492,9 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
       hipLaunchKernelGGL(gmm_means22_kernel, dim3((unsigned)ceil_div((int64_t)C * d, 256)), dim3(256), 0, 0, g->means,
                          (int64_t)C * d, g->b_scale, g->means22);
       ASD_HIP(hipGetLastError());
-      g->two_ok = g->split_draft_ok = true;
-      if (ctx->n_rows_max >= kBigRows) {   // enough rows for 256 x 256 tiles to fill the chip
+      (multiple ? g->two_ok : g->pad_ok) = true;
+      g->split_draft_ok = multiple;
+      if (multiple && ctx->n_rows_max >= kBigRows) {   // enough rows for 256 x 256 tiles to fill the chip
         ASD_HIP(hipMalloc(&g->means_img_big, split3_image_bytes<Split2BigCfg>(C, d)));
         ASD_HIP(hipMalloc(&g->means_t_img_big, split3_image_bytes<Split2BigCfg>(d, C)));
         ASD_HIP(launch_split3_pack_b<Split2BigCfg>(g->means, d, C, d, g->means_img_big, 0, g->b_scale));
@@ -1493,7 +1508,7 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
       ASD_HIP(launch_split3_pack_b<GmmTileSplit>(g->means_t, C, d, C, g->means_t_img, 0));
     }
     ASD_HIP(hipDeviceSynchronize());
-    g->split_ok = g->use_split = true;
+    g->split_ok = g->use_split = multiple;
     const int np_v = GmmTileSplit::WGN * (int)ceil_div(C, GmmTileSplit::BN);   // partial maxima per row, verify call
     ASD_HIP(hipMalloc(&g->rmax, sizeof(float) * (size_t)ctx->n_rows_max));
     ASD_HIP(hipMalloc(&g->glive, (size_t)ceil_div(ctx->n_rows_max, CombineOp::kRowmaxTile) * np_v));
@@ -1691,13 +1706,15 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
     ASD_HIP(hipGetLastError());
     return ASD_OK;
   }
-  const bool split = g->use_split && (rows.call == 1 || g->split_draft_ok);
+  const bool padded = g->pad_ok && rows.call == 1 && padding_pays(n, d, C);
+  const bool split = padded || (g->use_split && (rows.call == 1 || g->split_draft_ok));
   // K split of the draft call's second GEMM (few output tiles, long K); both of its tilings use slabs of 32
   static_assert(GmmTileSplitSkinny::BK == GmmTileSkinny::BK, "one split plan for both");
   const int splits = (!rows.call && g->draft_splits > 1 && n <= ctx->B) ? g->draft_splits : 1;
   // (A screened context keeps its own kernels at every size: the draft call's verdict and the certificate's candidates
   // pass from call to call there.)
-  const TiledCost& tiled = rows.call ? (!split ? kTiledF32 : g->two_ok ? kTiledFp16 : kTiledBf16) : (split ? kDraftFp16 : kDraftF32);
+  const bool two = split && (g->two_ok || padded);   // fp16 terms (both calls), else three bf16 terms (verify call only)
+  const TiledCost& tiled = rows.call ? (!split ? kTiledF32 : two ? kTiledFp16 : kTiledBf16) : (split ? kDraftFp16 : kDraftF32);
   if (!g->use_mfma || (g->few_on && !g->screen_ok && few_rows_pays(tiled, splits, n, d, C))) {
     ProfScope ps(ctx, ASD_PROF_GMM_ROWWISE, rows.call, st);
     ASD_HIP(launch_gmm_few(FewArgs{rows.n_dev, 0, n, d, C, (d + 3) & ~3, (C + 3) & ~3, rows.in_base, rows.in_off,
@@ -1761,7 +1778,6 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
     op1.tile_count = g->tile_count;
     op1.list_cap = g->list_cap;
   }
-  const bool two = split && g->two_ok;   // fp16 terms (both calls), else three bf16 terms (verify call only)
   {
     ProfScope ps(ctx, ASD_PROF_GMM_LOGITS, rows.call, st);
     if (two) {   // every row has its scale first: from the screening pass's quantiser, the draft call's certificate, else a kernel of its own
@@ -1781,6 +1797,9 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
       if (big) ASD_HIP(launch_gemm_split2_big<false>(rows.n_dev, n, C, d, X, g->means_img_big, op1, st, false, on, 0));
     } else if (big) {
       ASD_HIP(launch_gemm_split2_big<false>(rows.n_dev, n, C, d, X, g->means_img_big, op1, st, false, nullptr, 0));
+    } else if (padded) {
+      ASD_HIP((d % GmmTile2::BK ? launch_gemm_split3_nt<GmmTile2, 1, false, true>(rows.n_dev, n, C, d, X, g->means_img2, op1, st)
+                                : launch_gemm_split3_nt<GmmTile2, 1, false>(rows.n_dev, n, C, d, X, g->means_img2, op1, st)));
     } else if (two) {
       ASD_HIP(rows.call ? launch_gemm_split3_nt<GmmTile2, 1, false>(rows.n_dev, n, C, d, X, g->means_img2, op1, st)
                         : launch_gemm_split3_nt<GmmTile2Skinny, 0, false>(rows.n_dev, n, C, d, X, g->means_img2, op1, st));
@@ -1832,7 +1851,9 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
     if (two) {
       op2.a_scale = 32768.f;   // the weights are at most 1: 2^15 is the largest power of two fp16 can take them at
       op2.b_scale = g->b_scale;
-      if (rows.call == 0) {
+      if (padded && C % GmmTile2::BK) {
+        ASD_HIP((launch_gemm_split3_nt<GmmTile2, 1, true, true>(rows.n_dev, n, d, C, P, g->means_t_img2, op2, st)));
+      } else if (rows.call == 0) {
         ASD_HIP(launch_gemm_split3_nt<GmmTile2Skinny, 0, false>(rows.n_dev, n, d, C, P, g->means_t_img2, op2, st, splits,
                                                                  g->part));
       } else {

@@ -38,6 +38,7 @@ struct GmmState {
   float* a_scale = nullptr;        // [rows_max]
   float* means22 = nullptr;        // [C, d]
   bool two_ok = false;
+  bool pad_ok = false;             // d or C no multiple of 16: the verify call on fp16 terms, the operands' K padded
   // ... and for verify calls of many rows the same two images for 256 x 256 tiles (gemm_split2_big.h): launches in
   // which every tile is wanted take those
   uint8_t* means_img_big = nullptr;

@@ -386,3 +386,22 @@ def test_sequential_steps_of_a_network(d, E, width, blocks, chains, terms, eps):
     ctx.sample_sequential(seq)
     ctx.close()
     assert bool(torch.isfinite(one).all()) and torch.equal(one, seq)
+
+
+@pytest.mark.parametrize("d, C, n", [
+    (1000, 4000, 1001),     # a quarter of the last slab of d; whole slabs of C
+    (516, 1060, 5000),      # an eighth of the last slab of d and of C; a row, column and component tile with four in it
+    (512, 2052, 4100),      # whole slabs of d
+    (2052, 516, 2000),
+])
+def test_mixture_sums_padded_to_whole_slabs(d, C, n):
+    """d or C no multiple of 16: fp16 terms, their sums padded to whole slabs, against the oracle (the bound of the tiled kernels
+    above) and against its 64 bits summed over the call: an fp32 sum of K products in K / 16 steps or more, each rounded by 2^-24
+    of a partial sum, errs by 2^-24 sqrt(K / 16) of it or so, twice as the two sums meet, and the logits' errors reach the
+    weights times their size, a few tens here.  A call does not depend on the rows behind it."""
+    cfg = dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25)
+    got, want = _denoise(cfg, n, tiled=True)
+    assert H.rel_err(got, want) <= 3e-5
+    assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 2.0 ** -24 * np.sqrt(max(d, C) / 16) * 4
+    first, _ = _denoise(cfg, n, keep=n - 130, tiled=True)
+    assert np.array_equal(first, got[:n - 130])
