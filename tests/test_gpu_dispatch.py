@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import gpu_helpers as H
-from oracle_helpers import oracle_setup
+from oracle_helpers import gmm_model, oracle_setup
 from paper_2505_03983_amd import binding, runtime
 
 pytestmark = pytest.mark.gpu
@@ -361,6 +361,35 @@ def test_samples_of_a_wavefront_per_chain(d, C, L, K, chains, adaptive):
     ctx.close()
     assert bool(torch.isfinite(traj).all()) and torch.equal(traj, given)
     for c in sorted({0, 1, chains // 2, chains - 1}):
+        f = H.follow_chain(cfg, T, model, 8, c, traj[c].cpu().numpy(), 1e-4, adaptive=adaptive)
+        assert H.rel_err(traj[c].cpu().numpy(), f["y"]) <= 1e-4
+        assert int(rounds[c]) == f["R"]
+
+
+@pytest.mark.parametrize("d, C, L, K, chains, adaptive, empty", [
+    (3, 300, 2, 9, 2, False, 0),      # more tiles of components than wavefronts
+    (20, 66, 9, 25, 2, False, 16),    # a tile of components that weigh nothing
+    (64, 128, 17, 40, 3, True, 0),    # one tile of rows, full
+    (70, 129, 18, 60, 3, False, 33),  # two, the second of one row; a thread has no coordinate, one component alone in a tile
+    (33, 97, 64, 90, 2, False, 0),    # logits through LDS, a ring of one window's noise
+    (128, 20, 33, 150, 2, False, 0),  # ... and logits that stay in registers
+    (260, 8, 5, 21, 2, False, 0),     # more coordinates than threads
+])
+def test_samples_of_a_workgroup_per_chain(d, C, L, K, chains, adaptive, empty):
+    """The same for mixtures a workgroup holds; the first components may weigh nothing (the oracle leaves them out)."""
+    cfg = dict(kind="gmm", d=d, C=C, K=K, L=L, var=0.25)
+    T, p, _ = oracle_setup(cfg)
+    model = gmm_model(T, dict(p, means=p["means"][empty:], log_w=p["log_w"][empty:]))
+    p["log_w"][:empty] = -np.inf
+    ctx = runtime.open_ctx(cfg, p, seed=8, chains=chains)
+    assert ctx.resident_active()
+    ctx.use_adaptive_window(adaptive)
+    traj = torch.full((chains, K + 1, d), float("nan"), device=DEV)
+    rounds = torch.zeros(chains, dtype=torch.int32, device=DEV)
+    n = ctx.sample(traj, rounds)
+    ctx.close()
+    assert bool(torch.isfinite(traj).all()) and n == int(rounds.max())
+    for c in range(chains):
         f = H.follow_chain(cfg, T, model, 8, c, traj[c].cpu().numpy(), 1e-4, adaptive=adaptive)
         assert H.rel_err(traj[c].cpu().numpy(), f["y"]) <= 1e-4
         assert int(rounds[c]) == f["R"]
