@@ -229,7 +229,7 @@ ASD_API asd_status asd_use_adaptive_window(asd_ctx* ctx, int32_t on);
 ASD_API asd_status asd_use_call_reuse(asd_ctx* ctx, int32_t on);
 
 /* For a Gaussian-mixture denoiser small enough to sit in one CU's LDS (with the window of a chain),
- * asd_sample runs Alg. 1 for each chain inside one workgroup: one launch per sample instead of
+ * asd_sample runs Alg. 1 for each chain inside one workgroup (one wavefront, for a few numbers): one launch per sample instead of
  * several per round (chains do not interact, so no step of the method changes; rounds[c] keeps its
  * meaning and asd_last_round_count returns the largest of them).  on = 0 forces the lock-step
  * round kernels; the two paths agree to rounding.  Default: on.  Other shapes ignore the switch. */
