@@ -655,8 +655,8 @@ __global__ __launch_bounds__(64 * NW) void gmm_chain_sample_kernel(
 // ----------------------------------------------------------------------------
 // Mixtures of a few numbers: a chain is one wavefront, and nothing in its loop is shared.
 //
-// What bounds the kernel above on such a shape is its thirteen stages a round, each an LDS round trip and a barrier of
-// mostly idle wavefronts (9 us a round at d 2, C 4, L 8, of which the arithmetic is a few hundred cycles).  Here a slot of
+// What bounds the kernel above on such a shape is its stages, each an LDS round trip and a barrier of mostly idle
+// wavefronts (9 us a round at d 2, C 4, L 8, of which the arithmetic is a few hundred cycles).  Here a slot of
 // the window is a lane -- G = 64 / (slots, rounded up to a power of two) lanes, which share its components -- so the model
 // value of every slot, its accept test and the scan over the slots are register arithmetic, and the only barrier is the
 // one behind the set-up.  The noise of a chain depends on its steps only: the set-up generates it, and log u, for all K
@@ -664,9 +664,11 @@ __global__ __launch_bounds__(64 * NW) void gmm_chain_sample_kernel(
 //   x0a by every slot's lanes alike; the draft by a lane per coordinate; the verify call, a slot per lane; the test; one
 //   ballot; the reflection by the lanes of the coordinates, which keep y_a in a register; the rows the chain keeps go to
 //   the trajectory (those behind the first rejection would be written again by the next round).
-// Measured, microseconds a sample with its launch and the wait for it, a workgroup / a wavefront a chain, (d, C, L, K, chains):
-// (2, 4, 8, 100, 8) 138 / 55, K = 1000 922 / 269; (4, 16, 16, 200, 64) 217 / 96; (12, 16, 10, 200, 8) 237 / 160; (2, 4, 8, 100, 20000)
-// 1878 / 785.
+// A lane's first component, and often its only one, stays in registers, the walk's operands are asked for ahead of x0a, and no
+// value is picked from a row by an index (which the compiler makes a trip through scratch memory of).
+// Measured, microseconds a sample with its launch and the wait for it, a workgroup (as it was then) / a wavefront a chain / without
+// those trips, (d, C, L, K, chains): (2, 4, 8, 100, 8) 138 / 53 / 47, K = 1000 922 / 269 / 230; (4, 16, 16, 200, 64) 217 / 96 / 88;
+// (12, 16, 10, 200, 8) 237 / 160 / 149; (2, 4, 8, 100, 20000) 1878 / 785 / 624.
 // LDS operations of a wavefront complete in order; wave_lds_fence keeps the compiler to it.
 // ----------------------------------------------------------------------------
 namespace {
@@ -700,12 +702,16 @@ __host__ __device__ inline WaveLayout wave_layout(int C, int d, int L, int K) {
 
 __device__ __forceinline__ void wave_lds_fence() { asm volatile("" ::: "memory"); }
 
-// component e (0 .. 4 DB - 1, a lane's own) of a row in registers
+// component e (0 .. 4 DB - 1, a lane's own) of a row in registers.  (The compiler makes an indexed read of scratch memory of these
+// selections unless each is a value of its own: a store and a load through the caches, a few hundred cycles.)
 template <int DB>
 __device__ __forceinline__ float pick(const float (&v)[4 * DB], int e) {
   float r = v[0];
 #pragma unroll
-  for (int j = 1; j < 4 * DB; ++j) r = e == j ? v[j] : r;
+  for (int j = 1; j < 4 * DB; ++j) {
+    r = e == j ? v[j] : r;
+    asm("" : "+v"(r));
+  }
   return r;
 }
 
@@ -762,14 +768,30 @@ __global__ __launch_bounds__(512) void gmm_wave_sample_kernel(
   float* ps = mine + l.ps + lane;
   const float2* ql = reinterpret_cast<const float2*>(lds + l.ql);
   const float4* sch = reinterpret_cast<const float4*>(lds + l.sch);
-  const int G = l.lanes, slot = lane / G, part = lane % G;
-  constexpr float kLog2e = 1.4426950408889634f;   // logits in base-2 units for the hardware exp2
+  const int gshift = __builtin_ctz((unsigned)l.lanes), G = 1 << gshift, slot = lane >> gshift, part = lane & (G - 1);
+
+  // the lane's first component, and often its only one, stays in registers
+  float m0[DQ];
+#pragma unroll
+  for (int b = 0; b < DB; ++b) {
+    const float4 t = *reinterpret_cast<const float4*>(m_l + min(part, C - 1) * DQ + 4 * b);
+    m0[4 * b] = t.x;
+    m0[4 * b + 1] = t.y;
+    m0[4 * b + 2] = t.z;
+    m0[4 * b + 3] = t.w;
+  }
+  const float2 ql0 = ql[min(part, C - 1)];
 
   // D(x, .) with the step's coefficients cf, in every lane of the slot
   auto model = [&](const float (&x)[DQ], float4 cf, float (&out)[DQ]) {
-    float mx = -INFINITY;
-    int j = 0;
-    for (int k = part; k < C; k += G, ++j) {
+    float dot0 = 0.f;
+#pragma unroll
+    for (int b = 0; b < DB; ++b)
+      dot0 = fmaf(x[4 * b], m0[4 * b], fmaf(x[4 * b + 1], m0[4 * b + 1], fmaf(x[4 * b + 2], m0[4 * b + 2], fmaf(x[4 * b + 3], m0[4 * b + 3], dot0))));
+    const float lg0 = part < C ? logit2(cf.x, dot0, cf.y, ql0.x, ql0.y) : -INFINITY;
+    float mx = lg0;
+    int j = 1;
+    for (int k = part + G; k < C; k += G, ++j) {
       float dot = 0.f;
 #pragma unroll
       for (int b = 0; b < DB; ++b) {
@@ -777,18 +799,18 @@ __global__ __launch_bounds__(512) void gmm_wave_sample_kernel(
         dot = fmaf(x[4 * b], mv.x, fmaf(x[4 * b + 1], mv.y, fmaf(x[4 * b + 2], mv.z, fmaf(x[4 * b + 3], mv.w, dot))));
       }
       const float2 q = ql[k];
-      const float lg = kLog2e * fmaf(cf.x, dot, fmaf(-cf.y, q.x, q.y));
+      const float lg = logit2(cf.x, dot, cf.y, q.x, q.y);
       ps[64 * j] = lg;
       mx = fmaxf(mx, lg);
     }
     mx = group_max(mx, G);
-    float sum = 0.f, acc[DQ];
+    const float p0 = zero_cut_exp2(lg0 - mx);
+    float sum = p0, acc[DQ];
 #pragma unroll
-    for (int e = 0; e < DQ; ++e) acc[e] = 0.f;
-    j = 0;
-    for (int k = part; k < C; k += G, ++j) {
-      const float lg = ps[64 * j];
-      const float p = !(lg - mx < -kCertZeroGap) ? __builtin_amdgcn_exp2f(lg - mx) : 0.f;   // (gmm_cert.h)
+    for (int e = 0; e < DQ; ++e) acc[e] = p0 * m0[e];
+    j = 1;
+    for (int k = part + G; k < C; k += G, ++j) {
+      const float p = zero_cut_exp2(ps[64 * j] - mx);
       sum += p;
 #pragma unroll
       for (int b = 0; b < DB; ++b) {
@@ -834,27 +856,39 @@ __global__ __launch_bounds__(512) void gmm_wave_sample_kernel(
     if (lane < DQ) yh[lane] = y;
     wave_lds_fence();
     float x[DQ], ga[DQ], gk[DQ];
+    struct Step {
+      float4 sc;
+      float xi;
+    };
+    auto fetch = [&](int k) {
+      const int i = a + min(k, w - 1);
+      return Step{sch[2 * i], xi_l[i * DQ + e]};
+    };
+    Step now[4];   // (asked for ahead of the model value)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) now[u] = fetch(u);
     row(yh, x);
     model(x, sch[2 * a + 1], ga);
     // draft: the lanes of the coordinates walk the window, operands of four steps at a time
     float v = y;
     const float g = pick<DB>(ga, e);
-    for (int k0 = 0; k0 < w; k0 += 4) {
-      float4 sc[4];
-      float xi[4];
+    auto step = [&](int k, const Step& q) {
+      v = fmaf(q.sc.z, q.xi, fmaf(q.sc.x, v, q.sc.y * g));
+      if (lane < DQ) yh[(k + 1) * DQ + lane] = v;
+    };
+    int k0 = 0;
+    for (; k0 + 4 <= w; k0 += 4) {   // the next four are on their way
+      Step nx[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k = min(k0 + u, w - 1);
-        sc[u] = sch[2 * (a + k)];
-        xi[u] = xi_l[(a + k) * DQ + e];
-      }
+      for (int u = 0; u < 4; ++u) nx[u] = fetch(k0 + 4 + u);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (k0 + u >= w) break;
-        v = fmaf(sc[u].z, xi[u], fmaf(sc[u].x, v, sc[u].y * g));
-        if (lane < DQ) yh[(k0 + u + 1) * DQ + lane] = v;
-      }
+      for (int u = 0; u < 4; ++u) step(k0 + u, now[u]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) now[u] = nx[u];
     }
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+      if (k0 + u < w) step(k0 + u, now[u]);
     wave_lds_fence();
     // verify and test: slot 0 is accepted by construction, sigma == 0 rejects
     const int s = min(slot, w - 1), i = a + s;
@@ -882,7 +916,7 @@ __global__ __launch_bounds__(512) void gmm_wave_sample_kernel(
     }
     const unsigned long long rejected = __ballot(!bit);
     const int lr = rejected ? __ffsll((long long)rejected) - 1 : 64;   // first lane of the first rejected slot
-    const int n_acc = rejected ? lr / G : w;
+    const int n_acc = rejected ? lr >> gshift : w;
     int keep = w;   // rows y_{a+1} .. y_{a+keep} are final
     if (n_acc < w) {
       const float4 sc = sch[2 * (a + n_acc)];
@@ -934,8 +968,8 @@ inline bool chain_fits(const asd_ctx* ctx, int ring) { return chain_lds_bytes(ct
 
 // How many chains share a workgroup as a wavefront each (0: a chain takes a workgroup).  A lane walks its components by
 // itself, so the line lies at the instructions a model value costs it.  Microseconds a sample of K 200, a workgroup / a
-// wavefront a chain, by those instructions and (d, C, L): 208 (8, 32, 16) 195 / 139; 288 (2, 64, 16) 177 / 136,
-// (16, 16, 16) 204 / 164, (12, 16, 10) 202 / 160; 336 (16, 64, 8) 216 / 250; 416 (8, 64, 16) 198 / 190.
+// wavefront a chain, by those instructions and (d, C, L): 208 (8, 32, 16) 195 / 127; 288 (2, 64, 16) 177 / 128,
+// (16, 16, 16) 204 / 156, (12, 16, 10) 202 / 148; 336 (16, 64, 8) 216 / 240; 416 (8, 64, 16) 198 / 176.
 constexpr int kWaveWork = 300;
 static int wave_chains(const asd_ctx* ctx) {
   const int C = ctx->gmm->C, d = ctx->d;
