@@ -952,13 +952,17 @@ namespace {
 
 // Wavefronts per workgroup: enough for the tiles of the logits pass, within 4..16, and eight where the draft, a thread per coordinate,
 // would leave no more than two of four to make the noise (microseconds a sample of K 200, 4 / 8 wavefronts: (300, 4, 8) 561 / 441,
-// (240, 16, 8) 443 / 359, (200, 8, 4) 503 / 432, (128, 16, 16) 304 / 250, (128, 60, 4) 401 / 370); and the parts that sums over components are cut
+// (240, 16, 8) 443 / 359, (200, 8, 4) 503 / 432, (128, 16, 16) 304 / 250, (128, 60, 4) 401 / 370).  Chains that share a CU take
+// each other's slots instead: with more than 256 of them eight only where a row has more coordinates than four have threads ((100, 20,
+// 12), 600 chains: 570 / 676; (300, 30, 4) at K 100, 300 chains: 766 / 659).  And the parts that sums over components are cut
 // into, which are a wavefront's each but keep to fewer where the tiles are few (results do not depend on the wavefronts).
 inline int chain_items(const asd_ctx* ctx) {
   const ChainLayout l = chain_layout(ctx->gmm->C, ctx->d, ctx->L, ctx->K, ctx->L);
   return (l.C16 / 16) * (l.tr / 16);
 }
-inline int chain_waves(int items, int d) { return items > 8 ? 16 : (items > 4 || d > 100 ? 8 : 4); }
+inline int chain_waves(int items, int d, int chains) {
+  return items > 8 ? 16 : (items > 4 || d > (chains > 256 ? 240 : 100) ? 8 : 4);
+}
 inline int chain_parts(int items) { return items >= 16 ? 16 : (items >= 8 ? 8 : 4); }
 // ring: steps the noise ring holds (L, or 2 L where that fits too: then the noise of later steps is made aside)
 inline size_t chain_lds_bytes(const asd_ctx* ctx, int ring) {
@@ -1043,7 +1047,7 @@ asd_status gmm_chain_sample(asd_ctx* ctx, const float* y0, float* traj, int32_t*
   } else {
     const int ring = chain_fits(ctx, 2 * ctx->L) ? 2 * ctx->L : ctx->L;
     const size_t lds_bytes = chain_lds_bytes(ctx, ring);
-    const int items = chain_items(ctx), nw = chain_waves(items, ctx->d), parts = chain_parts(items);
+    const int items = chain_items(ctx), nw = chain_waves(items, ctx->d, ctx->B), parts = chain_parts(items);
     if (nw == 4) ASD_TRY((launch_chain<4, 4>(ctx, ring, lds_bytes, y0, traj, rounds, out, st)));
     else if (nw == 8 && parts == 4) ASD_TRY((launch_chain<8, 4>(ctx, ring, lds_bytes, y0, traj, rounds, out, st)));
     else if (nw == 8) ASD_TRY((launch_chain<8, 8>(ctx, ring, lds_bytes, y0, traj, rounds, out, st)));
