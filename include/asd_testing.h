@@ -18,8 +18,9 @@ extern "C" {
 ASD_API int32_t asd_resident_active(const asd_ctx* ctx);
 /* Non-zero if the tiled kernels of this context's mixture verify calls work on split operands: the number of 16-bit
  * matrix-core products they spend on one fp32 product -- 3 (two fp16 terms per operand: d and C multiples of 32, both
- * model calls) or 6 (three bf16 terms: multiples of 16, the verify call only).  Calls that take the kernels for few rows
- * (asd_use_few_rows) are fp32 throughout. */
+ * model calls; other multiples of 4, verify and asd_denoise calls with the rows for it: see asd_use_split_gemm) or 6 (three
+ * bf16 terms: multiples of 16, the verify call only).  Calls that take the kernels for few rows (asd_use_few_rows) are fp32
+ * throughout.  Which kernels a call took: ASD_PROF_GMM_SOFTMAX is timed on split operands only. */
 ASD_API int32_t asd_split_gemm_active(const asd_ctx* ctx);
 
 /* Mixture contexts large enough for the tiled kernels (d and C multiples of 4, chains * L * C * d >= 2^26) still send a

@@ -1463,13 +1463,15 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
   g->rowwise_lds = sizeof(float) * 4 * (size_t)(d + C);
   const bool aligned = (d % 4 == 0) && (C % 4 == 0);
   g->use_mfma = aligned && (double)ctx->n_rows_max * C * d >= (double)(1 << 26);
-  // d or C no multiple of 16: the verify call on fp16 terms too, the sums over d and C padded to whole slabs (KTAIL).  Against 64
+  // d or C no multiple of 16: the verify calls that padding_pays for take fp16 terms too, the sums over d and C padded to whole
+  // slabs (KTAIL).  Against 64
   // bits its error is that of the whole-slab form, below the fp32 kernels' -- a slab's products are added with fewer roundings:
   // relative (2-norm) error against double precision, fp32 / this, 5000 rows of (1000, 4000) 5.3e-7 / 3.6e-7, 8000 of (300, 1000)
   // 3.5e-7 / 2.2e-7, of (36, 2052) 3.0e-7 / 2.3e-7, largest error over the results' rms 2.4e-5 / 2.4e-5, 2.4e-5 / 1.5e-5, 9.0e-6 / 4.7e-6.
   const bool multiple = d % 16 == 0 && C % 16 == 0;
+  g->ragged = g->use_mfma && !multiple;
   if (g->use_mfma) {
-    if (!multiple || (d % GmmTile2::BK == 0 && C % GmmTile2::BK == 0)) {
+    if (g->ragged || (d % GmmTile2::BK == 0 && C % GmmTile2::BK == 0)) {
       // fp16 terms for both calls: the means times b_scale (a power of two that brings the largest |mu| into fp16's
       // upper range), one image per GEMM for both tilings, and the means as their two fp16 terms carry them
       uint32_t* mx_dev = nullptr;
@@ -1492,7 +1494,7 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
       hipLaunchKernelGGL(gmm_means22_kernel, dim3((unsigned)ceil_div((int64_t)C * d, 256)), dim3(256), 0, 0, g->means,
                          (int64_t)C * d, g->b_scale, g->means22);
       ASD_HIP(hipGetLastError());
-      (multiple ? g->two_ok : g->pad_ok) = true;
+      g->two_ok = true;
       g->split_draft_ok = multiple;
       if (multiple && ctx->n_rows_max >= kBigRows) {   // enough rows for 256 x 256 tiles to fill the chip
         ASD_HIP(hipMalloc(&g->means_img_big, split3_image_bytes<Split2BigCfg>(C, d)));
@@ -1508,7 +1510,7 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
       ASD_HIP(launch_split3_pack_b<GmmTileSplit>(g->means_t, C, d, C, g->means_t_img, 0));
     }
     ASD_HIP(hipDeviceSynchronize());
-    g->split_ok = g->use_split = multiple;
+    g->split_ok = g->use_split = true;
     const int np_v = GmmTileSplit::WGN * (int)ceil_div(C, GmmTileSplit::BN);   // partial maxima per row, verify call
     ASD_HIP(hipMalloc(&g->rmax, sizeof(float) * (size_t)ctx->n_rows_max));
     ASD_HIP(hipMalloc(&g->glive, (size_t)ceil_div(ctx->n_rows_max, CombineOp::kRowmaxTile) * np_v));
@@ -1706,14 +1708,13 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
     ASD_HIP(hipGetLastError());
     return ASD_OK;
   }
-  const bool padded = g->pad_ok && rows.call == 1 && padding_pays(n, d, C);
-  const bool split = padded || (g->use_split && (rows.call == 1 || g->split_draft_ok));
+  const bool split = g->use_split && (g->ragged ? rows.call == 1 && padding_pays(n, d, C) : rows.call == 1 || g->split_draft_ok);
   // K split of the draft call's second GEMM (few output tiles, long K); both of its tilings use slabs of 32
   static_assert(GmmTileSplitSkinny::BK == GmmTileSkinny::BK, "one split plan for both");
   const int splits = (!rows.call && g->draft_splits > 1 && n <= ctx->B) ? g->draft_splits : 1;
   // (A screened context keeps its own kernels at every size: the draft call's verdict and the certificate's candidates
   // pass from call to call there.)
-  const bool two = split && (g->two_ok || padded);   // fp16 terms (both calls), else three bf16 terms (verify call only)
+  const bool two = split && g->two_ok;   // fp16 terms (both calls), else three bf16 terms (verify call only)
   const TiledCost& tiled = rows.call ? (!split ? kTiledF32 : two ? kTiledFp16 : kTiledBf16) : (split ? kDraftFp16 : kDraftF32);
   if (!g->use_mfma || (g->few_on && !g->screen_ok && few_rows_pays(tiled, splits, n, d, C))) {
     ProfScope ps(ctx, ASD_PROF_GMM_ROWWISE, rows.call, st);
@@ -1797,7 +1798,7 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
       if (big) ASD_HIP(launch_gemm_split2_big<false>(rows.n_dev, n, C, d, X, g->means_img_big, op1, st, false, on, 0));
     } else if (big) {
       ASD_HIP(launch_gemm_split2_big<false>(rows.n_dev, n, C, d, X, g->means_img_big, op1, st, false, nullptr, 0));
-    } else if (padded) {
+    } else if (two && g->ragged) {
       ASD_HIP((d % GmmTile2::BK ? launch_gemm_split3_nt<GmmTile2, 1, false, true>(rows.n_dev, n, C, d, X, g->means_img2, op1, st)
                                 : launch_gemm_split3_nt<GmmTile2, 1, false>(rows.n_dev, n, C, d, X, g->means_img2, op1, st)));
     } else if (two) {
@@ -1851,7 +1852,7 @@ asd_status gmm_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
     if (two) {
       op2.a_scale = 32768.f;   // the weights are at most 1: 2^15 is the largest power of two fp16 can take them at
       op2.b_scale = g->b_scale;
-      if (padded && C % GmmTile2::BK) {
+      if (g->ragged && C % GmmTile2::BK) {
         ASD_HIP((launch_gemm_split3_nt<GmmTile2, 1, true, true>(rows.n_dev, n, d, C, P, g->means_t_img2, op2, st)));
       } else if (rows.call == 0) {
         ASD_HIP(launch_gemm_split3_nt<GmmTile2Skinny, 0, false>(rows.n_dev, n, d, C, P, g->means_t_img2, op2, st, splits,

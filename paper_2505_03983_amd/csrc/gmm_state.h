@@ -29,7 +29,7 @@ struct GmmState {
   // split-bf16 verify GEMMs (gemm_split3.h): the means, split and laid out as LDS images, for both GEMMs
   uint8_t* means_img = nullptr;    // B of the logits GEMM  ([C, d])
   uint8_t* means_t_img = nullptr;  // B of the combine GEMM ([d, C])
-  // Both GEMMs on two fp16 terms per operand (d and C multiples of 32; then the images above do not exist): the means
+  // Both GEMMs on two fp16 terms per operand (d and C multiples of 32, or ragged; then the images above do not exist): the means
   // times b_scale as one image per GEMM for both tilings, the scale of every row of a call's first GEMM, and the
   // means as two fp16 terms carry them (what the closed form of a one-hot row must use)
   uint8_t* means_img2 = nullptr;
@@ -38,7 +38,6 @@ struct GmmState {
   float* a_scale = nullptr;        // [rows_max]
   float* means22 = nullptr;        // [C, d]
   bool two_ok = false;
-  bool pad_ok = false;             // d or C no multiple of 16: the verify call on fp16 terms, the operands' K padded
   // ... and for verify calls of many rows the same two images for 256 x 256 tiles (gemm_split2_big.h): launches in
   // which every tile is wanted take those
   uint8_t* means_img_big = nullptr;
@@ -46,6 +45,7 @@ struct GmmState {
   bool big_ok = false;
   bool big_on = true;              // the switch (asd_use_tall_tiles)
   bool split_draft_ok = false;     // d and C are multiples of 32: the draft call can take the split kernels too
+  bool ragged = false;             // d or C no multiple of 16: fp16 terms, padded, in the verify calls they are faster for; no others
   bool split_ok = false;           // the shape allows them
   bool use_split = false;          // ... and they are switched on (asd_use_split_gemm)
   // DEV [8], summed over the verify calls while profiling: tiles of logits computed / there were (calls that went

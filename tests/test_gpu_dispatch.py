@@ -11,16 +11,22 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def _denoise(cfg, n, seed=3, keep=None, tiled=False):
-    """tiled: on the tiled kernels, whichever the call would take by itself; else it is expected not to take them."""
+def _denoise(cfg, n, seed=3, keep=None, tiled=False, split=None, change=None):
+    """tiled: on the tiled kernels, whichever the call would take by itself; else it is expected not to take them.  split
+    (not None): the switch of the split operands, and whether the call is expected to have taken them.  change: of the means."""
     T, p, model = oracle_setup(cfg)
     rng = np.random.default_rng(seed)
+    if change is not None:
+        p["means"] = change(p["means"])
     if cfg["kind"] == "gmm":     # unequal weights
         p["log_w"] = np.log(rng.dirichlet(np.ones(cfg["C"]))).astype(np.float32)
         from oracle_helpers import gmm_model
         model = gmm_model(T, p)
     ctx = runtime.open_ctx(cfg, p, seed=0, chains=-(-n // cfg["L"]))
     ctx.use_few_rows(not tiled)
+    if split is not None:
+        ctx.use_split_gemm(split)
+        assert ctx.split_gemm_active() == split
     ctx.profile_enable(True)
     tau = rng.integers(1, cfg["K"] + 1, n).astype(np.int32)
     ab = T["abar"][tau]
@@ -32,6 +38,8 @@ def _denoise(cfg, n, seed=3, keep=None, tiled=False):
     ctx.denoise(torch.from_numpy(x).to(DEV), torch.from_numpy(tau).to(DEV), out)
     torch.cuda.synchronize()
     assert ctx.profile_read(binding.PROF["GMM_LOGITS" if tiled else "GMM_ROWWISE"], 1)[0] == 1
+    if split is not None:
+        assert ctx.profile_read(binding.PROF["GMM_SOFTMAX"], 1)[0] == int(split)
     ctx.close()
     if keep is not None:
         return out.cpu().numpy(), None
@@ -99,9 +107,9 @@ def test_fp32_tiles_do_not_depend_on_their_size(d, C, n, part):
     """Calls of the fp32 kernels on either side of the rule that picks smaller tiles, and parts of them, which go to others:
     the sums of an element are the same in every tile, so shared rows are equal bit for bit; against the oracle as above."""
     cfg = dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25)
-    got, want = _denoise(cfg, n, tiled=True)
+    got, want = _denoise(cfg, n, tiled=True, split=False)
     assert H.rel_err(got, want) <= 3e-5
-    first, _ = _denoise(cfg, n, keep=part, tiled=True)
+    first, _ = _denoise(cfg, n, keep=part, tiled=True, split=False)
     assert np.array_equal(first, got[:part])
 
 
@@ -429,8 +437,30 @@ def test_mixture_sums_padded_to_whole_slabs(d, C, n):
     of a partial sum, errs by 2^-24 sqrt(K / 16) of it or so, twice as the two sums meet, and the logits' errors reach the
     weights times their size, a few tens here.  A call does not depend on the rows behind it."""
     cfg = dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25)
-    got, want = _denoise(cfg, n, tiled=True)
-    assert H.rel_err(got, want) <= 3e-5
-    assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 2.0 ** -24 * np.sqrt(max(d, C) / 16) * 4
-    first, _ = _denoise(cfg, n, keep=n - 130, tiled=True)
-    assert np.array_equal(first, got[:n - 130])
+    on, want = _denoise(cfg, n, tiled=True, split=True)
+    off, _ = _denoise(cfg, n, keep=n, tiled=True, split=False)
+    for got in (on, off):
+        assert H.rel_err(got, want) <= 3e-5
+        assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 2.0 ** -24 * np.sqrt(max(d, C) / 16) * 4
+    assert not np.array_equal(on, off)
+    first, _ = _denoise(cfg, n, keep=n - 130, tiled=True, split=True)
+    assert np.array_equal(first, on[:n - 130])
+
+
+def test_samples_of_a_ragged_mixture_on_split_operands():
+    """Whole samples whose verify calls take padded fp16 terms, on fewer rows than there may be once windows are cut and chains
+    end, against the oracle chain by chain (1e-4, the bar of fp32 denoisers)."""
+    cfg = dict(kind="gmm", d=300, C=1000, K=70, L=32, var=0.25)
+    T, p, model = oracle_setup(cfg)
+    chains = 256
+    ctx = runtime.open_ctx(cfg, p, seed=9, chains=chains)
+    traj, rounds = torch.full((chains, 71, 300), float("nan"), device=DEV), torch.zeros(chains, dtype=torch.int32, device=DEV)
+    ctx.profile_enable(True)
+    n = ctx.sample(traj, rounds)
+    taken = ctx.profile_read(binding.PROF["GMM_SOFTMAX"], 1)[0]
+    ctx.close()
+    assert taken >= n and bool(torch.isfinite(traj).all())
+    for c in (0, 100, chains - 1):
+        f = H.follow_chain(cfg, T, model, 9, c, traj[c].cpu().numpy(), 1e-4)
+        assert H.rel_err(traj[c].cpu().numpy(), f["y"]) <= 1e-4
+        assert int(rounds[c]) == f["R"]
