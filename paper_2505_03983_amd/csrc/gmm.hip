@@ -1470,7 +1470,9 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
   // 3.5e-7 / 2.2e-7, of (36, 2052) 3.0e-7 / 2.3e-7, largest error over the results' rms 2.4e-5 / 2.4e-5, 2.4e-5 / 1.5e-5, 9.0e-6 / 4.7e-6.
   const bool multiple = d % 16 == 0 && C % 16 == 0;
   g->ragged = g->use_mfma && !multiple;
-  if (g->use_mfma) {
+  bool wanted = g->use_mfma && multiple;
+  for (int64_t n = ctx->n_rows_max; g->ragged && !wanted && n > 0; n /= 2) wanted = padding_pays(n, d, C);
+  if (wanted) {
     if (g->ragged || (d % GmmTile2::BK == 0 && C % GmmTile2::BK == 0)) {
       // fp16 terms for both calls: the means times b_scale (a power of two that brings the largest |mu| into fp16's
       // upper range), one image per GEMM for both tilings, and the means as their two fp16 terms carry them

@@ -447,6 +447,17 @@ def test_mixture_sums_padded_to_whole_slabs(d, C, n):
     assert np.array_equal(first, on[:n - 130])
 
 
+@pytest.mark.parametrize("d, C", [(100, 400), (900, 100), (36, 2052)])
+def test_mixtures_no_call_of_which_is_padded_hold_no_terms(d, C):
+    """Ragged sizes whose sums are faster on fp32 tiles at any number of rows: nothing to switch on."""
+    cfg = dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25)
+    _, p, _ = oracle_setup(cfg)
+    ctx = runtime.open_ctx(cfg, p, chains=750)
+    ctx.use_split_gemm(True)
+    assert not ctx.split_gemm_active()
+    ctx.close()
+
+
 def test_samples_of_a_ragged_mixture_on_split_operands():
     """Whole samples whose verify calls take padded fp16 terms, on fewer rows than there may be once windows are cut and chains
     end, against the oracle chain by chain (1e-4, the bar of fp32 denoisers)."""
