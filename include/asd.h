@@ -243,8 +243,8 @@ ASD_API asd_status asd_use_resident(asd_ctx* ctx, int32_t on);
  * six products (2^-23 on average, never above 2^-21), in the verify call.  Nothing in the method changes: it is
  * another way to evaluate the same fp32 contraction, about 2.3x (1.5x) faster on this chip than its fp32 matrix
  * pipe.  Other multiples of 4: two fp16 terms in verify and asd_denoise calls with enough rows for the sums, padded to
- * multiples of 32, to be the faster way (an element below 2^-10 of the largest one of its row of x, or of all
- * means, keeps fewer than 22 bits of its own).
+ * multiples of 32, to be the faster way, if every component and every coordinate of the means has an element above 2^-10
+ * of the largest of all (an element below that keeps fewer than 22 bits of its own; the same holds within a row of x).
  * on = 0 selects the fp32 MFMA kernels.  Default: on.  Other shapes ignore the switch, and so do calls too small to fill
  * the chip with these kernels' tiles: they take fp32 MFMA kernels of their own either way. */
 ASD_API asd_status asd_use_split_gemm(asd_ctx* ctx, int32_t on);

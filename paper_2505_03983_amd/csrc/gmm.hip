@@ -112,12 +112,18 @@ __global__ void gmm_prep_kernel(int C, int d, int cp, int dp, const float* __res
   if (threadIdx.x == 0) musq[k] = red[0];
 }
 
-// Largest |v[i]| as the bits of a float (non-negative floats order like their bit patterns); *out = 0 on entry.
-__global__ __launch_bounds__(256) void gmm_absmax_kernel(const float* __restrict__ v, int64_t n, uint32_t* __restrict__ out) {
+// The largest magnitude of a row of v [rows][cols]: the most and, rows of zeros aside, the least there is, as the bits of floats
+// (non-negative floats order like their bit patterns) and the complement of such bits; both 0 on entry.  A wavefront per row.
+__global__ __launch_bounds__(256) void gmm_spread_kernel(const float* __restrict__ v, int rows, int cols, uint32_t* __restrict__ out) {
+  const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= rows) return;
   float mx = 0.f;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) mx = fmaxf(mx, fabsf(v[i]));
+#pragma unroll 8
+  for (int j = lane; j < cols; j += 64) mx = fmaxf(mx, fabsf(v[(int64_t)r * cols + j]));
   mx = wave_max(mx);
-  if ((threadIdx.x & 63) == 0) atomicMax(out, __float_as_uint(mx));
+  if (lane != 0 || mx == 0.f) return;
+  atomicMax(out, __float_as_uint(mx));
+  atomicMax(out + 1, ~__float_as_uint(mx));
 }
 
 // The power of two that brings a largest magnitude mx into [2^14, 2^15): fp16's largest finite number is 65504, and
@@ -1408,6 +1414,10 @@ static bool few_rows_pays(const TiledCost& k, int splits, int64_t n, int64_t d, 
 // (500, 2000) x 8000 408 / 199, (1020, 3000) x 3000 426 / 255, (300, 1000) x 8000 143 / 119; and where it is not, (100, 400) x
 // 12000 59 / 88, (900, 100) x 12000 120 / 137, (60, 516) x 20000 89 / 109, (36, 2052) x 8000 163 / 171.
 static bool padding_pays(int64_t n, int64_t d, int64_t C) { return tiled_cost(kTiledFp16, 1, n, d, C) < tiled_cost(kTiledF32, 1, n, d, C); }
+// ... and whether it may: an element below 2^-10 of the largest one of the means keeps fewer than 22 bits, so every component
+// and every coordinate has to have one above it.  (One mean 1e5 times the others, which fp32 carries as well as any: 3.7e-8
+// fp32, 5.2e-8 as fp16 terms, and 1.3e-7 / 2.3e-7 in the worst coordinate of (1020, 3000).)
+static bool split_spread(float most, float least) { return most < INFINITY && least >= 0x1p-10f * most; }
 
 asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
   GmmState* g = new (std::nothrow) GmmState();
@@ -1464,29 +1474,37 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
   const bool aligned = (d % 4 == 0) && (C % 4 == 0);
   g->use_mfma = aligned && (double)ctx->n_rows_max * C * d >= (double)(1 << 26);
   // d or C no multiple of 16: the verify calls that padding_pays for take fp16 terms too, the sums over d and C padded to whole
-  // slabs (KTAIL).  Against 64
-  // bits its error is that of the whole-slab form, below the fp32 kernels' -- a slab's products are added with fewer roundings:
-  // relative (2-norm) error against double precision, fp32 / this, 5000 rows of (1000, 4000) 5.3e-7 / 3.6e-7, 8000 of (300, 1000)
-  // 3.5e-7 / 2.2e-7, of (36, 2052) 3.0e-7 / 2.3e-7, largest error over the results' rms 2.4e-5 / 2.4e-5, 2.4e-5 / 1.5e-5, 9.0e-6 / 4.7e-6.
+  // slabs (KTAIL).  For means of like sizes (split_spread) the error against 64 bits is below that of the fp32 kernels, a slab's
+  // products being added with fewer roundings: relative (2-norm) error, fp32 / this, 5000 rows of (1000, 4000) 5.3e-7 / 3.5e-7, all
+  // means positive 3.4e-7 / 2.0e-7, all near 100 2.3e-5 / 1.5e-5, rows on one component 2.83e-8 / 2.83e-8; 8000 of (300, 1000)
+  // 3.4e-7 / 2.3e-7, 4100 of (512, 2052) 4.6e-7 / 3.2e-7.  (Three bf16 terms, which have fp32's range: 2.5e-6 with all means
+  // positive, and 614 us a call of (1000, 4000) where these take 432 and fp32 850.)
   const bool multiple = d % 16 == 0 && C % 16 == 0;
   g->ragged = g->use_mfma && !multiple;
   bool wanted = g->use_mfma && multiple;
   for (int64_t n = ctx->n_rows_max; g->ragged && !wanted && n > 0; n /= 2) wanted = padding_pays(n, d, C);
+  if (wanted && (g->ragged || (d % GmmTile2::BK == 0 && C % GmmTile2::BK == 0))) {
+    uint32_t bits[2] = {0, 0};   // the largest magnitude of a component's mean (ragged: and of a coordinate's): most, least
+    uint32_t* bits_dev = nullptr;
+    ASD_HIP(hipMalloc(&bits_dev, sizeof(bits)));
+    hipError_t e1 = hipMemset(bits_dev, 0, sizeof(bits));
+    hipLaunchKernelGGL(gmm_spread_kernel, dim3((unsigned)ceil_div(C, 4)), dim3(256), 0, 0, g->means, C, d, bits_dev);
+    if (g->ragged)
+      hipLaunchKernelGGL(gmm_spread_kernel, dim3((unsigned)ceil_div(d, 4)), dim3(256), 0, 0, g->means_t, d, C, bits_dev);
+    hipError_t e2 = hipGetLastError();
+    hipError_t e3 = hipMemcpy(bits, bits_dev, sizeof(bits), hipMemcpyDeviceToHost);
+    (void)hipFree(bits_dev);
+    ASD_HIP(e1);
+    ASD_HIP(e2);
+    ASD_HIP(e3);
+    const float most = __builtin_bit_cast(float, bits[0]), least = __builtin_bit_cast(float, ~bits[1]);
+    g->b_scale = fp16_scale(most);
+    if (g->ragged) wanted = most == 0.f || split_spread(most, least);
+  }
   if (wanted) {
     if (g->ragged || (d % GmmTile2::BK == 0 && C % GmmTile2::BK == 0)) {
       // fp16 terms for both calls: the means times b_scale (a power of two that brings the largest |mu| into fp16's
       // upper range), one image per GEMM for both tilings, and the means as their two fp16 terms carry them
-      uint32_t* mx_dev = nullptr;
-      uint32_t mx_bits = 0;
-      ASD_HIP(hipMalloc(&mx_dev, sizeof(uint32_t)));
-      ASD_HIP(hipMemset(mx_dev, 0, sizeof(uint32_t)));
-      hipLaunchKernelGGL(gmm_absmax_kernel, dim3(256), dim3(256), 0, 0, g->means, (int64_t)C * d, mx_dev);
-      hipError_t e1 = hipGetLastError();
-      hipError_t e2 = hipMemcpy(&mx_bits, mx_dev, sizeof(uint32_t), hipMemcpyDeviceToHost);
-      (void)hipFree(mx_dev);
-      ASD_HIP(e1);
-      ASD_HIP(e2);
-      g->b_scale = fp16_scale(__builtin_bit_cast(float, mx_bits));
       ASD_HIP(hipMalloc(&g->means_img2, split3_image_bytes<GmmTile2>(C, d)));
       ASD_HIP(hipMalloc(&g->means_t_img2, split3_image_bytes<GmmTile2>(d, C)));
       ASD_HIP(launch_split3_pack_b<GmmTile2>(g->means, d, C, d, g->means_img2, 0, g->b_scale));

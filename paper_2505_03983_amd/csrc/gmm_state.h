@@ -46,7 +46,7 @@ struct GmmState {
   bool big_on = true;              // the switch (asd_use_tall_tiles)
   bool split_draft_ok = false;     // d and C are multiples of 32: the draft call can take the split kernels too
   bool ragged = false;             // d or C no multiple of 16: fp16 terms, padded, in the verify calls they are faster for; no others
-  bool split_ok = false;           // the shape allows them
+  bool split_ok = false;           // the shape (and, ragged, the means) allow them
   bool use_split = false;          // ... and they are switched on (asd_use_split_gemm)
   // DEV [8], summed over the verify calls while profiling: tiles of logits computed / there were (calls that went
   // through the screening launches), K slabs the second GEMM's workgroups visited / there were, tiles of the calls

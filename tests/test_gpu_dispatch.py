@@ -458,6 +458,25 @@ def test_mixtures_no_call_of_which_is_padded_hold_no_terms(d, C):
     ctx.close()
 
 
+@pytest.mark.parametrize("change", ["component", "coordinate"])
+def test_mixtures_of_mixed_size_stay_on_fp32(change):
+    """One component, or one coordinate, a millionth of the others: fp16 terms that share a scale would keep a few of its bits
+    only.  The context has none to switch on, and the call is the one with the switch off, bit for bit."""
+    def shrink(m):
+        m = m.copy()
+        m[(17 if change == "component" else slice(None)), (slice(None) if change == "component" else 5)] *= 1e-6
+        return m
+    cfg = dict(kind="gmm", d=516, C=1060, K=50, L=16, var=0.25)
+    _, p, _ = oracle_setup(cfg)
+    ctx = runtime.open_ctx(cfg, dict(p, means=shrink(p["means"])), chains=-(-5000 // 16))
+    ctx.use_split_gemm(True)
+    assert not ctx.split_gemm_active()
+    ctx.close()
+    got, want = _denoise(cfg, 5000, tiled=True, change=shrink)
+    off, _ = _denoise(cfg, 5000, keep=5000, tiled=True, split=False, change=shrink)
+    assert H.rel_err(got, want) <= 3e-5 and np.array_equal(got, off)
+
+
 def test_samples_of_a_ragged_mixture_on_split_operands():
     """Whole samples whose verify calls take padded fp16 terms, on fewer rows than there may be once windows are cut and chains
     end, against the oracle chain by chain (1e-4, the bar of fp32 denoisers)."""
