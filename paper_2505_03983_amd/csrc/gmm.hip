@@ -129,10 +129,10 @@ __global__ __launch_bounds__(256) void gmm_spread_kernel(const float* __restrict
 // The power of two that brings a largest magnitude mx into [2^14, 2^15): fp16's largest finite number is 65504, and
 // the larger the scaled values, the less of their second terms falls below fp16's normal range.  1 for 0, inf, NaN.
 __host__ __device__ __forceinline__ float fp16_scale(float mx) {
-  if (!(mx > 0.f) || !(mx < 3.0e38f)) return 1.f;
+  if (!(mx > 0.f) || !(mx < INFINITY)) return 1.f;
   int e;
   (void)frexpf(mx, &e);   // mx = f 2^e, f in [0.5, 1)
-  return ldexpf(1.f, max(-100, min(100, 15 - e)));
+  return ldexpf(1.f, min(100, 15 - e));   // (2^-113 at least)
 }
 
 // The means as the two fp16 terms of the split carry them: out = (m1 + m2) / scale with m1 = the nearest fp16 of
@@ -1416,8 +1416,9 @@ static bool few_rows_pays(const TiledCost& k, int splits, int64_t n, int64_t d, 
 static bool padding_pays(int64_t n, int64_t d, int64_t C) { return tiled_cost(kTiledFp16, 1, n, d, C) < tiled_cost(kTiledF32, 1, n, d, C); }
 // ... and whether it may: an element below 2^-10 of the largest one of the means keeps fewer than 22 bits, so every component
 // and every coordinate has to have one above it.  (One mean 1e5 times the others, which fp32 carries as well as any: 3.7e-8
-// fp32, 5.2e-8 as fp16 terms, and 1.3e-7 / 2.3e-7 in the worst coordinate of (1020, 3000).)
-static bool split_spread(float most, float least) { return most < INFINITY && least >= 0x1p-10f * most; }
+// fp32, 5.2e-8 as fp16 terms, and 1.3e-7 / 2.3e-7 in the worst coordinate of (1020, 3000).)  The largest stays where the
+// product of its scale and the smallest a row can have, 2^-113, is a normal number.
+static bool split_spread(float most, float least) { return most < 0x1p28f && least >= 0x1p-10f * most; }
 
 asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
   GmmState* g = new (std::nothrow) GmmState();

@@ -477,6 +477,34 @@ def test_mixtures_of_mixed_size_stay_on_fp32(change):
     assert H.rel_err(got, want) <= 3e-5 and np.array_equal(got, off)
 
 
+@pytest.mark.parametrize("d, C", [(516, 1060), (96, 1056)])
+def test_rows_near_the_largest_float_on_split_operands(d, C):
+    """Points of up to 1e36 among ordinary ones: their terms are scaled into fp16's range like any other's, and what the model
+    adds to c_x' x is lost in its rounding."""
+    cfg = dict(kind="gmm", d=d, C=C, K=50, L=16, var=0.25)
+    T, p, _ = oracle_setup(cfg)
+    n, far = 4100, [0, 1, 130, 4099]
+    ctx = runtime.open_ctx(cfg, p, chains=-(-n // 16))
+    ctx.use_few_rows(False)
+    assert ctx.split_gemm_active()
+    x = np.random.default_rng(4).standard_normal((n, d)).astype(np.float32)
+    near = x.copy()
+    x[far] *= np.array([1e34, 6e34, 1e35, 2e35], dtype=np.float32)[:, None]
+    tau = np.full(n, 25, dtype=np.int32)
+    outs = []
+    for rows in (x, near):
+        out = torch.full((n, d), float("nan"), dtype=torch.float32, device=DEV)
+        ctx.denoise(torch.from_numpy(rows).to(DEV), torch.from_numpy(tau).to(DEV), out)
+        outs.append(out.cpu().numpy())
+    ctx.close()
+    ab = T["abar"][25]
+    cx = np.sqrt(ab) * p["var"] / (ab * p["var"] + 1 - ab)
+    want = cx * x[far].astype(np.float64)
+    assert np.abs(outs[0][far] - want).max() <= 1e-6 * np.abs(want).max() and np.isfinite(outs[0]).all()
+    keep = np.setdiff1d(np.arange(n), far)
+    assert np.array_equal(outs[0][keep], outs[1][keep])
+
+
 def test_samples_of_a_ragged_mixture_on_split_operands():
     """Whole samples whose verify calls take padded fp16 terms, on fewer rows than there may be once windows are cut and chains
     end, against the oracle chain by chain (1e-4, the bar of fp32 denoisers)."""
