@@ -503,8 +503,17 @@ static asd_status sample_rounds(asd_ctx* ctx, const float* y0, float* traj, int3
     ASD_HIP(hipStreamWaitEvent(ctx->own_stream, ctx->order_ev, 0));
     st = ctx->own_stream;
   }
+  // Rounds write to the caller's trajectory and to the host report (whose words tell samples apart only by there being none
+  // left of another), so none is on the stream when this returns, with an error either.
+  struct Drain {
+    hipStream_t st;
+    bool on;
+    ~Drain() {
+      if (on) (void)hipStreamSynchronize(st);
+    }
+  } drain{st, true};
   ASD_TRY(flush_key(ctx, st));
-  memset(ctx->report->word, 0, sizeof(ctx->report->word));   // (the last sample's kernels have ended)
+  memset(ctx->report->word, 0, sizeof(ctx->report->word));
   ASD_TRY(launch_init_state(ctx, y0, traj, ctx->a, rounds, st));
   int32_t seen[3] = {0, 0, 0};
   int r = 0;
@@ -534,6 +543,7 @@ static asd_status sample_rounds(asd_ctx* ctx, const float* y0, float* traj, int3
       if (ctx->hint_rows) hint = row_hint(ctx, seen[1]);
     }
   }
+  drain.on = false;
   ASD_HIP(hipStreamSynchronize(st));
   if (done_at < 0) return fail(ASD_EDEVICE, "asd_sample: chains did not finish within %d rounds", r_cap);
   // (passes over windows in pieces, and launches that left a chain waiting, are no rounds)
