@@ -1483,7 +1483,8 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
   const bool multiple = d % 16 == 0 && C % 16 == 0;
   g->ragged = g->use_mfma && !multiple;
   bool wanted = g->use_mfma && multiple;
-  for (int64_t n = ctx->n_rows_max; g->ragged && !wanted && n > 0; n /= 2) wanted = padding_pays(n, d, C);
+  for (int64_t n = ctx->n_rows_max; g->ragged && !wanted && n > 0; n /= 2)
+    wanted = padding_pays(n, d, C) && !few_rows_pays(kTiledFp16, 1, n, d, C);
   if (wanted && (g->ragged || (d % GmmTile2::BK == 0 && C % GmmTile2::BK == 0))) {
     uint32_t bits[2] = {0, 0};   // the largest magnitude of a component's mean (ragged: and of a coordinate's): most, least
     uint32_t* bits_dev = nullptr;
