@@ -388,18 +388,27 @@ static asd_status wait_report(asd_ctx* ctx, int r, hipStream_t st, int32_t (&v)[
 }
 
 // Windows in pieces (device_util.h): the least slots of a piece, 0 where windows are taken whole.  A pass over the batch then
-// costs the draft call, about 24 us of round kernels, and a model call on `least` rows a chain instead of L - 1, and there are
-// a sixth to a quarter more passes than rounds.  Four slots, or as many more as the tiles that four take have room for.
+// costs the draft call, about 24 us of round kernels, and a model call on `least` rows a chain instead of L - 1, which are also
+// drafted, written and tested (5 us a million numbers), and there are a sixth to a quarter more passes than rounds.  Four slots, or
+// as many more as the tiles that four take have room for.
 // Measured, whole / in pieces, milliseconds a sample: 64 chains, 4096 wide, 6 blocks, d 3072, L 32 (a run of 4.3 slots on
 // average) 211.5 / 113.5, from 358 k verified rows to 89 k; 256 chains, 1024 wide, 4 blocks, d 112, L 16 (2.0 slots) 7.61 /
 // 5.78.  (One chain of it: rows cost nothing there, windows are taken whole.)
+//
+// A piece's products run on tiles for its own rows, but on the kernel for few rows only where that suits the most the call can
+// bring (picked by the rows of the round but one before, it made pieces up to 1.4 times slower).  Short runs make up for it, with
+// fewer passes than said; runs grow as the schedule gets finer, from 2.0 slots at K 20 to 3.1 at 200, 4.4 at 400 and 6.3 at 800.
+// Measured, 305 samples of 1..256 chains, widths of 64..4096, L 5..32, in pieces by the cost of a piece on the kernels for its own
+// rows and whole by that on those it takes: in pieces / whole 0.76..1.05 at K up to 200 (16 of 208 above 1), 0.74..1.12 at 300..800
+// (55 of 97 above 1).
 static int piece_least(const asd_ctx* ctx) {
   if (ctx->kind != ASD_DEN_MLP || ctx->L <= 4 || !ctx->fold_plans || ctx->reuse_now || ctx->cur_win || !ctx->pieces_on) return 0;
-  const double at_four = mlp_call_cost(ctx, 1, 4 * ctx->B), fixed = mlp_call_cost(ctx, 0, ctx->B) + 24.0;
+  const int B = ctx->B, most = (ctx->L - 1) * B;
+  const auto verify = [&](int rows) { return mlp_call_cost(ctx, 1, rows, ctx->K > 256 ? most : rows) + 5e-6 * rows * ctx->d; };
+  const double at_four = verify(4 * B), fixed = mlp_call_cost(ctx, 0, B, B) + 24.0;
   int least = 4;
-  while (least + 1 < ctx->L && mlp_call_cost(ctx, 1, (least + 1) * ctx->B) <= 1.05 * at_four) ++least;
-  const double piece = mlp_call_cost(ctx, 1, least * ctx->B), whole = mlp_call_cost(ctx, 1, (ctx->L - 1) * ctx->B);
-  return 1.25 * (fixed + piece) < fixed + whole ? least : 0;
+  while (least + 1 < ctx->L && verify((least + 1) * B) <= 1.05 * at_four) ++least;
+  return 1.25 * (fixed + verify(least * B)) < fixed + verify(most) ? least : 0;
 }
 
 // How many rows a verify call will bring varies by a factor of ten and more over a sample where the controller chooses the

@@ -253,7 +253,8 @@ asd_status mlp_create(asd_ctx* ctx, const asd_denoiser& den);
 void mlp_destroy(asd_ctx* ctx);
 PackOut mlp_pack_out(const asd_ctx* ctx);
 asd_status mlp_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st);
-double mlp_call_cost(const asd_ctx* ctx, int call, int rows);   // microseconds, roughly: for choices between ways to batch
+// microseconds of a call of `rows` rows on the kernels for `most`, roughly: for choices between ways to batch
+double mlp_call_cost(const asd_ctx* ctx, int call, int rows, int most);
 
 // What a kernel outside the mixture denoiser needs to certify rows one-hot and form their model values (gmm_cert.h);
 // false when the denoiser's own verify call would not do the same, bit for bit.

@@ -140,11 +140,11 @@ static hipError_t mlp_gemm(const RowPlan& rows, int N, int K, SlabMat A, SlabMat
                      : mlp_gemm_planes<1>(rows.call, rows.n_dev, rows.n, likely, N, K, A, Wt, e, st, sc);
 }
 
-// A product of `rows` rows in microseconds, by the figures at pick_tile and pick_few_tile; one that is split over K streams
-// its weights at 2.4 TB/s and adds its parts in 5 us.
-static double product_cost(int planes, int call, int rows, int N, int K) {
+// A product of `rows` rows, where the call could bring `most`, in microseconds, by the figures at pick_tile and pick_few_tile; one
+// that is split over K streams its weights at 2.4 TB/s and adds its parts in 5 us.
+static double product_cost(int planes, int call, int rows, int most, int N, int K) {
   const int Kp = slab_count(K) * 32, splits = call == 0 ? draft_splits(rows, N, Kp) : 1;
-  const int few = pick_few_tile(rows, N, splits);
+  const int few = pick_few_tile(most, N, splits);
   if (few >= 0) return (few == 0 ? 1.5 : 2.0) + (planes == 2 ? 3.6 : 2.5) * (few == 0 ? 1.0 : 1.6) * Kp / 1024.0;
   if (splits > 1) return 2e-6 * N * Kp / 2.4 + 5.0;
   float t;
@@ -453,11 +453,11 @@ PackOut mlp_pack_out(const asd_ctx* ctx) {
   return PackOut{s->in_bf, s->rows_pad * 32, s->in_plane, s->temb, s->E, ctx->d};
 }
 
-double mlp_call_cost(const asd_ctx* ctx, int call, int rows) {
+double mlp_call_cost(const asd_ctx* ctx, int call, int rows, int most) {
   const MlpState* s = ctx->mlp;
   const int p = s->act_terms, W = s->width;
-  return product_cost(p, call, rows, W, s->in_dim) + s->n_blocks * product_cost(p, call, rows, W, W) +
-         product_cost(p, call, rows, ctx->d, W);
+  return product_cost(p, call, rows, most, W, s->in_dim) + s->n_blocks * product_cost(p, call, rows, most, W, W) +
+         product_cost(p, call, rows, most, ctx->d, W);
 }
 
 asd_status mlp_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {

@@ -343,6 +343,25 @@ def test_windows_in_pieces_change_no_bit(d, E, width, blocks, K, L, chains, term
     assert starts == starts_p == int(rounds.sum()) and pieces < 0.8 * whole
 
 
+@pytest.mark.parametrize("K, taken", [(80, True), (300, False)])
+def test_windows_are_whole_where_pieces_would_cost_more(K, taken):
+    """A piece's products are on the kernel for whole windows' rows: it pays on a coarse schedule, whose windows end after two
+    slots, and not on a fine one (measured 1.08 times slower)."""
+    cfg = dict(kind="mlp", d=48, E=16, width=648, n_blocks=5, K=K, L=14, act_terms=2)
+    _, p, _ = oracle_setup(cfg)
+    ctx = runtime.open_ctx(cfg, p, seed=0, chains=48)
+    rows = []
+    for pieces in (True, False):
+        ctx.use_window_pieces(pieces)
+        ctx.profile_enable(True)
+        ctx.set_seed(6)
+        ctx.sample(torch.empty((48, K + 1, 48), device=DEV))
+        torch.cuda.synchronize()
+        rows.append(ctx.profile_rows()[1])
+    ctx.close()
+    assert (rows[0] < rows[1]) == taken and rows[0] <= rows[1]
+
+
 @pytest.mark.parametrize("d, C, L, K, chains, adaptive", [
     (1, 1, 1, 3, 2, False),           # nothing but a step
     (2, 4, 8, 40, 5, False),
