@@ -17,8 +17,8 @@ typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 
 // 16 bytes a lane from memory into LDS: lane l's from base + off, its own, to dst + 16 l; base and dst are the wavefront's.  As
 // a buffer load: a global one counts, for the compiler, as a flat access that may touch LDS, and while one is on its way --
-// always, in a pipeline -- it waits for every outstanding LDS read wherever one is needed.  The base takes all 64 bits, so an
-// offset never leaves 32.
+// always, in a pipeline -- it waits for every outstanding LDS read wherever one is needed.  The base takes the whole address (its
+// 48 bits, past which there is no memory), so an offset never leaves 32.
 __device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, void* dst) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, -1, 0x00027000),
                                            (lds_ptr_t)dst, 16, (int)off, 0, 0, 0);

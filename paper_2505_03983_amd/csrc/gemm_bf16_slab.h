@@ -120,13 +120,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_bf16_slab_kernel(const int*
   const uint8_t* abase = reinterpret_cast<const uint8_t*>(A) + ((int64_t)s0 * a_slab + (int64_t)m0 * 32) * 2;
   const uint8_t* wbase = reinterpret_cast<const uint8_t*>(W) + ((int64_t)s0 * w_slab + (int64_t)n0 * 32) * 2;
   // wave-loads first .. first+count-1 of stage kt (per slab: A loads, then W loads) into the LDS stage at `sb`
-  // (tail: as global loads.  Nothing is read ahead of them there, and it is by that instruction that the check of the assembly
-  // for reads outstanding at barriers finds these kernels.)
-  auto issue = [&](int kt, uint8_t* sb, int first, int count, bool tail = false) {
-    auto one = [&](const uint8_t* g, uint8_t* dst) {
-      if (tail) __builtin_amdgcn_global_load_lds((glb_ptr_t)(g + lane_off), (lds_ptr_t)dst, 16, 0, 0);
-      else load_to_lds(g, lane_off, dst);
-    };
+  auto issue = [&](int kt, uint8_t* sb, int first, int count) {
 #pragma unroll
     for (int q = 0; q < LPS; ++q) {
       if (q < first || q >= first + count) continue;
@@ -135,10 +129,10 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_bf16_slab_kernel(const int*
       if (p < A_LOADS) {
         const int row = blk * 16, plane = row / BM;
         const uint8_t* g = abase + ((int64_t)(kt * SPS + sl) * a_slab + (int64_t)plane * a_plane + (int64_t)(row - plane * BM) * 32) * 2;
-        one(g, sb + sl * Cfg::SLAB_BYTES + blk * 1024);
+        load_to_lds(g, lane_off, sb + sl * Cfg::SLAB_BYTES + blk * 1024);
       } else {
         const uint8_t* g = wbase + ((int64_t)(kt * SPS + sl) * w_slab + (int64_t)blk * 16 * 32) * 2;
-        one(g, sb + sl * Cfg::SLAB_BYTES + AR * 64 + blk * 1024);
+        load_to_lds(g, lane_off, sb + sl * Cfg::SLAB_BYTES + AR * 64 + blk * 1024);
       }
     }
   };
@@ -214,7 +208,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_bf16_slab_kernel(const int*
         if constexpr (steady) hand_over_steady();
         else hand_over(min(nk - 2 - kt, STAGES - 2));
         read_stage(ldsb + cur * Cfg::STAGE_BYTES, buf ^ 1);
-        if (steady || kt + STAGES < nk) issue(kt + STAGES, mine, 0, LPS, !steady);
+        if (steady || kt + STAGES < nk) issue(kt + STAGES, mine, 0, LPS);
       }
 #pragma unroll
       for (int g = 0; g < NG; ++g) mma(buf * NG + g, 0, G);
@@ -252,14 +246,13 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_bf16_slab_kernel(const int*
   read_frags(ldsb, 0, 0);
 
   int cur = 0, nst = STAGES - 1;          // LDS stages of kt and of kt + STAGES - 1
-  // steady: stages kt + 1 .. kt + STAGES - 1 exist -- no branches, so that the stage is one scheduling region, the
+  // steady: stages kt + 1 .. kt + STAGES - 1 exist, and the last of them is fetched now -- no branches, so that the stage is one scheduling region, the
   // interleaving asked for holds, and the compiler knows which LDS reads an MFMA has to wait for (behind a branch it
   // waits for all of them, those just issued for the next group included)
   auto step = [&](int kt, auto steady_c) {
     constexpr bool steady = decltype(steady_c)::value;
     const uint8_t* sb = ldsb + cur * Cfg::STAGE_BYTES;
     uint8_t* nb = ldsb + nst * Cfg::STAGE_BYTES;
-    const bool more = steady || kt + STAGES - 1 < nk;  // uniform: stage kt+STAGES-1 exists and is fetched now
     const int nxt = kt + STAGES - 1;
     nst = cur;                               // (the stage after the last one wraps to the one consumed now)
     cur = cur + 1 == STAGES ? 0 : cur + 1;
@@ -267,7 +260,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_bf16_slab_kernel(const int*
     for (int g = 0; g < NG - 1; ++g) {
       constexpr int L0 = Cfg::loads_in_group(0);  // groups may differ by one load; hints use the larger count
       read_frags(sb, g + 1, (g + 1) & 1);
-      if (more) issue(nxt, nb, Cfg::loads_before_group(g), Cfg::loads_in_group(g), !steady);
+      if constexpr (steady) issue(nxt, nb, Cfg::loads_before_group(g), Cfg::loads_in_group(g));
       mma(g & 1, 0, G);
       sched_pairs<0x100, SLOTS - 1, 2>();
       sched_pairs<0x100, 1, RLAST>();
@@ -276,13 +269,13 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_bf16_slab_kernel(const int*
     }
     // last group, first part
     constexpr int LB = Cfg::loads_in_group(NG - 1);
-    if (more) issue(nxt, nb, Cfg::loads_before_group(NG - 1), LB, !steady);
+    if constexpr (steady) issue(nxt, nb, Cfg::loads_before_group(NG - 1), LB);
     mma((NG - 1) & 1, 0, H1);
     sched_pairs<0x010, (LB < H1 ? LB : H1), 1>();
     sched_mfma<H1 - (LB < H1 ? LB : H1)>();
     if (steady || kt + 1 < nk) {
       // This wavefront's loads of stage kt+1 must have landed; those of the stages behind it may stay in flight.
-      if (more) wait_vmcnt<LPS * (STAGES - 2)>();
+      if constexpr (steady) wait_vmcnt<LPS * (STAGES - 2)>();
       else wait_stages<LPS, STAGES - 2>(nk - 2 - kt);
       lds_handover();
       read_frags(ldsb + cur * Cfg::STAGE_BYTES, 0, 0);

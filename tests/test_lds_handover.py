@@ -10,6 +10,9 @@ import pytest
 from paper_2505_03983_amd import build
 
 
+DIRECT_LOAD = re.compile(r"global_load_lds_|buffer_load_\S+ .*\blds\b")     # from memory into LDS
+
+
 def kernels(asm):
     """{name: [instruction or label, ...]} of the kernels that use direct loads."""
     out, name, body = {}, None, []
@@ -19,7 +22,7 @@ def kernels(asm):
         if m:
             name, body = m.group(1), []
         elif s.startswith(".Lfunc_end"):
-            if name and any(x.startswith("global_load_lds") for x in body):
+            if name and any(DIRECT_LOAD.match(x) for x in body):
                 out[name] = body
             name = None
         elif name and s and (s.startswith(".LBB") or not s.startswith(".")):
@@ -61,34 +64,30 @@ def test_reads_at_barriers_follows_branches():
     assert reads_at_barriers(loop) == [0, 1]
 
 
-@pytest.mark.parametrize("source, least", [("mlp.hip", 40), ("gmm.hip", 1)])
-def test_no_lds_read_is_outstanding_at_a_barrier(source, least, tmp_path):
+def assembly(source, tmp_path):
     out = tmp_path / "k.s"
     flags = [f for f in build.FLAGS if f != "-shared"]
     r = subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + flags +
                        ["--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", str(out)],
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout
-    ks = kernels(out.read_text())
+    return out.read_text()
+
+
+@pytest.mark.parametrize("source, least", [("mlp.hip", 96), ("gmm.hip", 1)])
+def test_no_lds_read_is_outstanding_at_a_barrier(source, least, tmp_path):
+    ks = kernels(assembly(source, tmp_path))
+    print(source, len(ks))
     assert len(ks) >= least
     bad = {k: b for k, b in ((k, reads_at_barriers(v)) for k, v in ks.items()) if any(b)}
     assert not bad, bad
 
 
-def test_kernels_that_load_through_buffers_hand_over_cleanly(tmp_path):
-    """The same for the kernels all of whose direct loads are buffer loads (the products of few rows), and those loads do
-    not make the compiler wait for every read of LDS at once: waits in their loops leave some outstanding."""
-    out = tmp_path / "k.s"
-    flags = [f for f in build.FLAGS if f != "-shared"]
-    r = subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + flags +
-                       ["--cuda-device-only", "-S", os.path.join(build.CSRC, "mlp.hip"), "-o", str(out)],
-                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    assert r.returncode == 0, r.stdout
-    asm = re.sub(r"\bbuffer_load_dwordx4 (?=.* lds\b)", "global_load_lds_dwordx4 ", out.read_text())
-    ks = {k: v for k, v in kernels(asm).items() if "gemm_bf16_few" in k}
+def test_kernels_of_few_rows_do_not_wait_for_every_read(tmp_path):
+    """Their direct loads do not make the compiler wait for every read of LDS at once: waits in their loops leave some
+    outstanding."""
+    ks = {k: v for k, v in kernels(assembly("mlp.hip", tmp_path)).items() if "gemm_bf16_few" in k}
     assert len(ks) >= 16
-    bad = {k: b for k, b in ((k, reads_at_barriers(v)) for k, v in ks.items()) if any(b)}
-    assert not bad, bad
     for k, body in ks.items():
         waits = [int(m.group(1)) for m in (re.search(r"lgkmcnt\((\d+)\)", x) for x in body if x.startswith("s_waitcnt")) if m]
         assert sum(n >= 2 for n in waits) >= 6, (k, waits)
