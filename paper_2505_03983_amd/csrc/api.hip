@@ -459,9 +459,13 @@ static asd_status ensure_round_graph(asd_ctx* ctx, float* traj, int32_t* rounds,
   return ASD_OK;
 }
 
-// Whether asd_sample's rounds may take certified chains through their accept stage ahead of the verify call.  Above 4096 model
-// rows a call: below, contexts have never done it and asd_early_accept_active says so, which callers may rely on -- not that
-// it would not pay there ((1024, 4096) with L 64, K 300: 8 chains 5045 -> 3985 us a sample, 64 chains 6718 -> 5354).
+// Whether asd_sample's rounds may take certified chains through their accept stage ahead of the verify call.  It pays where the
+// posteriors collapse on one component, and costs the kernel, and the planning kernels of rounds whose plans could be folded,
+// where they never do.  Measured over 8 mixtures of d 128..1024, C 256..4096, 4800..6144 model rows a call and K 60 and 400, with /
+// without it: well separated components 0.77..0.98 (0.89..1.00 with windows by the controller), overlapping ones 0.96..1.03 (once,
+// 96 chains of (1024, 4096) with L 64 at K 60, 1.08).  The line at 4096 rows a call is where the measurements over sizes end, not
+// where it stops paying: of (1024, 4096) with L 64, K 300, 8 chains take 5045 us a sample without and 3985 with it, 64 chains
+// 6718 and 5354.
 constexpr int64_t kEarlyRows = 4096;
 static bool early_accept_possible(const asd_ctx* ctx) {
   asd::OneHotCert oc;
@@ -759,7 +763,7 @@ asd_status asd_use_early_accept(asd_ctx* ctx, int32_t on) {
 
 int32_t asd_early_accept_active(const asd_ctx* ctx) {
   if (!ctx) return 0;
-  // (as asd_sample decides it: plans folded into the round kernels and model-call reuse exclude it)
+  // (as asd_sample decides it: model-call reuse excludes it)
   return (early_accept_possible(ctx) && !ctx->reuse) ? 1 : 0;
 }
 

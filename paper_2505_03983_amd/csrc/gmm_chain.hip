@@ -973,9 +973,11 @@ inline bool chain_fits(const asd_ctx* ctx, int ring) { return chain_lds_bytes(ct
 }  // namespace
 
 // How many chains share a workgroup as a wavefront each (0: a chain takes a workgroup).  A lane walks its components by
-// itself, so the line lies at the instructions a model value costs it.  Microseconds a sample of K 200, a workgroup / a
-// wavefront a chain, by those instructions and (d, C, L): 208 (8, 32, 16) 195 / 127; 288 (2, 64, 16) 177 / 128,
-// (16, 16, 16) 204 / 156, (12, 16, 10) 202 / 148; 336 (16, 64, 8) 216 / 240; 416 (8, 64, 16) 198 / 176.
+// itself, and the instructions a model value costs it say up to where that is the faster way whatever else the call is: of 350
+// random calls (d 1..16, C 1..600, L 2..64, 1..6000 chains), a wavefront / a workgroup a chain, 282 of at most 300 instructions
+// 0.09..1.00.  Above them it depends on what the workgroup's form costs, its stages and, where chains share CUs, their number:
+// 68 calls of 300..900 0.11..1.77, 14 of them above 1.02 (few chains); of (16, 64, 8) at 336, K 200, 8 chains, 240 / 216 us, of (8,
+// 64, 16) at 416 176 / 198.  Those keep the workgroup.
 constexpr int kWaveWork = 300;
 static int wave_chains(const asd_ctx* ctx) {
   const int C = ctx->gmm->C, d = ctx->d;

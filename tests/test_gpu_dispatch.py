@@ -311,17 +311,19 @@ def test_split_sums_do_not_depend_on_the_kernel(terms):
     assert bool(torch.isfinite(values[0]).all()) and torch.equal(values[0], values[1])
 
 
-@pytest.mark.parametrize("d, E, width, blocks, K, L, chains, terms", [
-    (112, 16, 1024, 2, 60, 16, 256, 2),      # the draft kernel packs what it lists; accept chunks as long as a window
-    (264, 24, 1024, 1, 90, 37, 200, 1),      # rows of two wavefronts, packed by a kernel of its own; chunks of eight slots
-    (1032, 16, 2056, 1, 50, 24, 64, 2),      # a draft call that is split over K
-    (16, 8, 2048, 2, 40, 7, 2200, 2),        # a wavefront a chain throughout
+@pytest.mark.parametrize("d, E, width, blocks, K, L, chains, terms, eps", [
+    (112, 16, 1024, 2, 60, 16, 256, 2, False),      # the draft kernel packs what it lists; accept chunks as long as a window
+    (264, 24, 1024, 1, 90, 37, 200, 1, False),      # rows of two wavefronts, packed by a kernel of its own; chunks of eight slots
+    (1032, 16, 2056, 1, 50, 24, 64, 2, False),      # a draft call that is split over K
+    (16, 8, 2048, 2, 40, 7, 2200, 2, False),        # a wavefront a chain throughout
+    (112, 16, 1024, 2, 60, 16, 256, 2, True),       # a network that estimates the noise: its values also take the rows evaluated
 ])
-def test_windows_in_pieces_change_no_bit(d, E, width, blocks, K, L, chains, terms):
+def test_windows_in_pieces_change_no_bit(d, E, width, blocks, K, L, chains, terms, eps):
     """Whole samples with windows taken in pieces and whole, as graphs and plain launches: the same trajectories, round
     counts and number of rounds, from fewer model rows."""
     cfg = dict(kind="mlp", d=d, E=E, width=width, n_blocks=blocks, K=K, L=L, act_terms=terms)
     _, p, _ = oracle_setup(cfg)
+    p["predict_eps"] = eps
     ctx = runtime.open_ctx(cfg, p, seed=0, chains=chains)
     runs = []
     for pieces, graphs, profile in ((False, True, False), (True, True, False), (True, False, False), (False, True, True), (True, True, True)):
@@ -341,6 +343,26 @@ def test_windows_in_pieces_change_no_bit(d, E, width, blocks, K, L, chains, term
         assert m == n and torch.equal(r, rounds) and torch.equal(t, traj)
     (starts, whole), (starts_p, pieces) = runs[3][3], runs[4][3]
     assert starts == starts_p == int(rounds.sum()) and pieces < 0.8 * whole
+
+
+@pytest.mark.parametrize("graphs", [True, False])
+def test_controlled_windows_do_not_depend_on_the_rows_a_round_is_launched_for(graphs):
+    """Rounds are launched in forms for the rows the round but one before brought, 4, 8, 16, 32 a chain or the most there can
+    be, each with its own tiles.  A batch goes through them in its own time: the chains two batches share are equal bit for
+    bit, trajectory and rounds."""
+    cfg = dict(kind="mlp", d=264, E=24, width=1032, n_blocks=2, K=120, L=48, act_terms=1, predict_eps=True)
+    _, p, _ = oracle_setup(cfg)
+    runs = []
+    for chains in (150, 3):
+        ctx = runtime.open_ctx(cfg, p, seed=3, chains=chains)
+        ctx.use_adaptive_window(True)
+        ctx.use_graphs(graphs)
+        traj, rounds = torch.full((chains, 121, 264), float("nan"), device=DEV), torch.zeros(chains, dtype=torch.int32, device=DEV)
+        assert ctx.sample(traj, rounds) == int(rounds.max())
+        ctx.close()
+        runs.append((traj[:3].clone(), rounds[:3].clone()))
+    assert bool(torch.isfinite(runs[0][0]).all())
+    assert torch.equal(runs[0][0], runs[1][0]) and torch.equal(runs[0][1], runs[1][1])
 
 
 @pytest.mark.parametrize("K, taken", [(80, True), (300, False)])

@@ -667,7 +667,7 @@ def test_early_accept_is_bit_identical_and_takes_chains():
     assert not ctx.early_accept_active()
     ctx.close()
     small = runtime.open_ctx(dict(W.CONFIGS[5], chains=48), W.make_params(dict(W.CONFIGS[5], chains=48), 1), seed=0)
-    assert not small.early_accept_active()      # plans folded into the round kernels
+    assert not small.early_accept_active()      # 3072 model rows a call: not more than 4096
     small.close()
 
 

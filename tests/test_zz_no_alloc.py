@@ -49,6 +49,10 @@ def test_noalloc_sample_equals_sample_twice_in_a_row_second_smaller():
     small_mlp = dict(kind="mlp", d=16, E=8, width=64, n_blocks=2, K=30, chains=6, L=12)
     _, pm, _ = oracle_setup(small_mlp)
     _pair(small_mlp, pm, seed=10)
+    # windows in pieces
+    pieces = dict(kind="mlp", d=112, E=16, width=1024, n_blocks=2, K=40, chains=256, L=16)
+    _, pp, _ = oracle_setup(pieces)
+    _pair(pieces, pp, seed=13)
     # a shape on which the early accept kernel and the rounds launched without the kernels behind it are at work
     # (17 k model rows per call; 8.5 MiB of scratch, which the chains left to the verify call use)
     early = dict(kind="gmm", d=128, C=256, K=200, chains=272, L=64, var=0.25)
