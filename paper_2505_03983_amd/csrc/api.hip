@@ -420,8 +420,21 @@ static int piece_least(const asd_ctx* ctx) {
 static int hinted_rows(const asd_ctx* ctx, int hint) { return hint < 0 ? 0 : ctx->hint_rows << hint; }
 static int row_hint(const asd_ctx* ctx, int rows_seen) {
   for (int h = 0; h < asd_ctx::kRowHints && hinted_rows(ctx, h) < ctx->B * (ctx->L - 1); ++h)
-    if (rows_seen <= hinted_rows(ctx, h)) return h;
+    if (rows_seen <= hinted_rows(ctx, h)) return ctx->hint_form[h];
   return -1;
+}
+// Hints that pick the same tiles share a form: a round's graph is made for each, 20 us of the host that few chains show where
+// every sample has a trajectory buffer of its own (one chain, 512 wide, windows by the controller, K 60: such a sample took 117 us
+// longer than one into the same buffer, now 41; without hints 9..60 over the sizes tried).
+static void set_hint_forms(asd_ctx* ctx) {
+  const int most = ctx->B * (ctx->L - 1 + (ctx->reuse_now ? 1 : 0));
+  uint32_t tiles[asd_ctx::kRowHints];
+  for (int h = 0; h < asd_ctx::kRowHints; ++h) {
+    tiles[h] = mlp_verify_tiles(ctx, std::min(hinted_rows(ctx, h), most), most);
+    int form = 0;
+    while (tiles[form] != tiles[h]) ++form;
+    ctx->hint_form[h] = tiles[h] == mlp_verify_tiles(ctx, most, most) ? -1 : form;
+  }
 }
 
 // Capture one round into a graph (launch-bound workloads: one graph launch instead of ~8 kernel launches).
@@ -493,6 +506,7 @@ static asd_status sample_rounds(asd_ctx* ctx, const float* y0, float* traj, int3
       const int least = piece_least(c);
       if (least > 0) c->cur_pieces = Pieces{c->piece_state, least};
       c->hint_rows = c->kind == ASD_DEN_MLP && (least > 0 || c->cur_win) ? std::max(4, least) * c->B : 0;
+      if (c->hint_rows) set_hint_forms(c);
     }
     ~WinScope() {
       c->cur_pieces = Pieces{};

@@ -175,6 +175,7 @@ struct asd_ctx {
   int32_t* chain_rounds = nullptr; // DEV [B]: rounds of each chain in this sample (launches are not rounds, see asd_sample)
   asd::Pieces cur_pieces;      // what the round kernels are given: in pieces while a sample that pays for them runs
   int hint_rows = 0;           // rows of hint 0 while a sample runs whose rows vary (row_hint), else 0
+  int hint_form[kRowHints];    // the first of the hints whose rounds are launched alike, -1 if as for the most rows
   const void* g_win = nullptr; // cur_win the round graph was captured with
   bool g_reuse = false;        // reuse_now the round graph was captured with
   bool g_pieces = false;       // whether the round graph was captured with windows in pieces
@@ -255,6 +256,8 @@ PackOut mlp_pack_out(const asd_ctx* ctx);
 asd_status mlp_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st);
 // microseconds of a call of `rows` rows on the kernels for `most`, roughly: for choices between ways to batch
 double mlp_call_cost(const asd_ctx* ctx, int call, int rows, int most);
+// the tiles a verify call takes where `likely` rows are expected of the `most` it can bring: equal words, equal launches
+uint32_t mlp_verify_tiles(const asd_ctx* ctx, int likely, int most);
 
 // What a kernel outside the mixture denoiser needs to certify rows one-hot and form their model values (gmm_cert.h);
 // false when the denoiser's own verify call would not do the same, bit for bit.

@@ -460,6 +460,17 @@ double mlp_call_cost(const asd_ctx* ctx, int call, int rows, int most) {
          product_cost(p, call, rows, most, ctx->d, W);
 }
 
+uint32_t mlp_verify_tiles(const asd_ctx* ctx, int likely, int most) {
+  const MlpState* s = ctx->mlp;
+  const int shapes[3][2] = {{s->width, s->in_dim}, {s->width, s->width}, {ctx->d, s->width}};
+  uint32_t tiles = 0;
+  for (const auto& p : shapes) {   // (as mlp_gemm_planes picks them)
+    const int few = pick_few_tile(most, p[0], 1);
+    tiles = 8 * tiles + (few >= 0 ? 5 + few : pick_tile(s->act_terms, likely, p[0], slab_count(p[1]) * 32));
+  }
+  return tiles;
+}
+
 asd_status mlp_eval(asd_ctx* ctx, const RowPlan& rows, hipStream_t st) {
   MlpState* s = ctx->mlp;
   const int n = rows.n, d = ctx->d, W = s->width;

@@ -1,12 +1,17 @@
 // A stand-in for the HIP runtime library in host-only tests of the library's control flow: memory is the host's, kernels do
-// nothing, and every call on a stream or graph is noted.  A call named to host_runtime_fail returns an error once.
+// nothing, and every call on a stream or graph is noted.  A call named to host_runtime_fail returns an error once.  Asked about a
+// stream, it first reports the next round as the kernels would (HostReport in common.h), while host_runtime_rounds lasts.
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <string>
+#include <vector>
 
 namespace {
 std::string notes, failing;
+uint64_t (*report)[3];          // the last pinned allocation
+std::vector<int> seen;          // of every round to report: the second ring's entry
+uint32_t reported;
 char symbol[1 << 16];
 int call(const char* name) {
   notes += name;
@@ -25,9 +30,14 @@ extern "C" {
 const char* host_runtime_notes() { return notes.c_str(); }
 void host_runtime_clear() { notes.clear(); }
 void host_runtime_fail(const char* name) { failing = name; }
+void host_runtime_rounds(const int* values, int n) { seen.assign(values, values + n), reported = 0; }
 
 int hipMalloc(void** p, size_t n) { return *p = std::calloc(1, n ? n : 1), 0; }
-int hipHostMalloc(void** p, size_t n, unsigned) { return hipMalloc(p, n); }
+int hipHostMalloc(void** p, size_t n, unsigned) {
+  hipMalloc(p, n);
+  report = static_cast<uint64_t(*)[3]>(*p);
+  return 0;
+}
 int hipHostGetDevicePointer(void** d, void* h, unsigned) { return *d = h, 0; }
 int hipFree(void* p) { return std::free(p), 0; }
 int hipHostFree(void* p) { return std::free(p), 0; }
@@ -48,7 +58,13 @@ int hipEventRecord(void*, void*) { return 0; }
 int hipStreamCreateWithFlags(void** s, unsigned) { return handle(s); }
 int hipStreamDestroy(void* s) { return std::free(s), 0; }
 int hipStreamWaitEvent(void*, void*, unsigned) { return 0; }
-int hipStreamQuery(void*) { return call("query"); }
+int hipStreamQuery(void*) {
+  if (reported < seen.size()) {
+    const uint32_t r = reported++, v[3] = {reported < seen.size(), (uint32_t)seen[r], reported};
+    for (int i = 0; i < 3; ++i) report[r % 8][i] = (uint64_t)(r + 1) << 32 | v[i];
+  }
+  return call("query");
+}
 int hipStreamSynchronize(void*) { return call("synchronize"); }
 int hipStreamBeginCapture(void*, int) { return call("begin"); }
 int hipStreamEndCapture(void*, void** g) { return handle(g), call("end"); }
