@@ -113,17 +113,30 @@ __global__ void gmm_prep_kernel(int C, int d, int cp, int dp, const float* __res
 }
 
 // The largest magnitude of a row of v [rows][cols]: the most and, rows of zeros aside, the least there is, as the bits of floats
-// (non-negative floats order like their bit patterns) and the complement of such bits; both 0 on entry.  A wavefront per row.
+// (non-negative floats order like their bit patterns) and the complement of such bits; both 0 on entry.  A wavefront per row at
+// a time, two atomics a workgroup (two a row, all on one line, took 80 us of 4000 rows).
 __global__ __launch_bounds__(256) void gmm_spread_kernel(const float* __restrict__ v, int rows, int cols, uint32_t* __restrict__ out) {
-  const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  float mx = 0.f;
+  __shared__ uint32_t s_best[2][4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t most = 0, least = 0;
+  for (int r = blockIdx.x * 4 + wave; r < rows; r += gridDim.x * 4) {
+    float mx = 0.f;
 #pragma unroll 8
-  for (int j = lane; j < cols; j += 64) mx = fmaxf(mx, fabsf(v[(int64_t)r * cols + j]));
-  mx = wave_max(mx);
-  if (lane != 0 || mx == 0.f) return;
-  atomicMax(out, __float_as_uint(mx));
-  atomicMax(out + 1, ~__float_as_uint(mx));
+    for (int j = lane; j < cols; j += 64) mx = fmaxf(mx, fabsf(v[(int64_t)r * cols + j]));
+    mx = wave_max(mx);
+    if (mx == 0.f) continue;
+    most = max(most, __float_as_uint(mx));
+    least = max(least, ~__float_as_uint(mx));
+  }
+  if (lane == 0) {
+    s_best[0][wave] = most;
+    s_best[1][wave] = least;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    const uint32_t* b = s_best[threadIdx.x];
+    atomicMax(out + threadIdx.x, max(max(b[0], b[1]), max(b[2], b[3])));
+  }
 }
 
 // The power of two that brings a largest magnitude mx into [2^14, 2^15): fp16's largest finite number is 65504, and
@@ -1490,9 +1503,9 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
     uint32_t* bits_dev = nullptr;
     ASD_HIP(hipMalloc(&bits_dev, sizeof(bits)));
     hipError_t e1 = hipMemset(bits_dev, 0, sizeof(bits));
-    hipLaunchKernelGGL(gmm_spread_kernel, dim3((unsigned)ceil_div(C, 4)), dim3(256), 0, 0, g->means, C, d, bits_dev);
+    hipLaunchKernelGGL(gmm_spread_kernel, dim3((unsigned)std::min<int64_t>(256, ceil_div(C, 4))), dim3(256), 0, 0, g->means, C, d, bits_dev);
     if (g->ragged)
-      hipLaunchKernelGGL(gmm_spread_kernel, dim3((unsigned)ceil_div(d, 4)), dim3(256), 0, 0, g->means_t, d, C, bits_dev);
+      hipLaunchKernelGGL(gmm_spread_kernel, dim3((unsigned)std::min<int64_t>(256, ceil_div(d, 4))), dim3(256), 0, 0, g->means_t, d, C, bits_dev);
     hipError_t e2 = hipGetLastError();
     hipError_t e3 = hipMemcpy(bits, bits_dev, sizeof(bits), hipMemcpyDeviceToHost);
     (void)hipFree(bits_dev);
@@ -1504,15 +1517,41 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
     if (g->ragged) wanted = most == 0.f || split_spread(most, least);
   }
   if (wanted) {
-    if (g->ragged || (d % GmmTile2::BK == 0 && C % GmmTile2::BK == 0)) {
+    const bool two = g->ragged || (d % GmmTile2::BK == 0 && C % GmmTile2::BK == 0);
+    const int np_v = GmmTileSplit::WGN * (int)ceil_div(C, GmmTileSplit::BN);   // partial maxima per row, verify call
+    const size_t rows = (size_t)ctx->n_rows_max, row_tiles_v = (size_t)ceil_div(ctx->n_rows_max, CombineOp::kRowmaxTile);
+    {
+      // one allocation (each took some 10 us to make and 70 to give back)
+      size_t used = 0;
+      const auto take = [&](size_t bytes) {
+        const size_t at = used;
+        used += (bytes + 255) & ~(size_t)255;
+        return at;
+      };
+      const size_t img = take(two ? split3_image_bytes<GmmTile2>(C, d) : split3_image_bytes<GmmTileSplit>(C, d)),
+                   t_img = take(two ? split3_image_bytes<GmmTile2>(d, C) : split3_image_bytes<GmmTileSplit>(d, C)),
+                   a_scale = take(two ? sizeof(float) * rows : 0), means22 = take(two ? sizeof(float) * (size_t)C * d : 0),
+                   rmax = take(sizeof(float) * rows), glive = take(row_tiles_v * np_v), onehot = take(sizeof(int32_t) * rows),
+                   onehot_tile = take(row_tiles_v), work = take(8 * sizeof(unsigned long long));
+      ASD_HIP(hipMalloc(&g->split_mem, used));
+      (two ? g->means_img2 : g->means_img) = g->split_mem + img;
+      (two ? g->means_t_img2 : g->means_t_img) = g->split_mem + t_img;
+      if (two) {
+        g->a_scale = reinterpret_cast<float*>(g->split_mem + a_scale);
+        g->means22 = reinterpret_cast<float*>(g->split_mem + means22);
+      }
+      g->rmax = reinterpret_cast<float*>(g->split_mem + rmax);
+      g->glive = g->split_mem + glive;
+      g->onehot = reinterpret_cast<int32_t*>(g->split_mem + onehot);
+      g->onehot_tile = g->split_mem + onehot_tile;
+      g->work_counts = reinterpret_cast<unsigned long long*>(g->split_mem + work);
+      ASD_HIP(hipMemset(g->work_counts, 0, 8 * sizeof(unsigned long long)));
+    }
+    if (two) {
       // fp16 terms for both calls: the means times b_scale (a power of two that brings the largest |mu| into fp16's
       // upper range), one image per GEMM for both tilings, and the means as their two fp16 terms carry them
-      ASD_HIP(hipMalloc(&g->means_img2, split3_image_bytes<GmmTile2>(C, d)));
-      ASD_HIP(hipMalloc(&g->means_t_img2, split3_image_bytes<GmmTile2>(d, C)));
       ASD_HIP(launch_split3_pack_b<GmmTile2>(g->means, d, C, d, g->means_img2, 0, g->b_scale));
       ASD_HIP(launch_split3_pack_b<GmmTile2>(g->means_t, C, d, C, g->means_t_img2, 0, g->b_scale));
-      ASD_HIP(hipMalloc(&g->a_scale, sizeof(float) * (size_t)ctx->n_rows_max));
-      ASD_HIP(hipMalloc(&g->means22, sizeof(float) * (size_t)C * d));
       hipLaunchKernelGGL(gmm_means22_kernel, dim3((unsigned)ceil_div((int64_t)C * d, 256)), dim3(256), 0, 0, g->means,
                          (int64_t)C * d, g->b_scale, g->means22);
       ASD_HIP(hipGetLastError());
@@ -1526,20 +1565,11 @@ asd_status gmm_create(asd_ctx* ctx, const asd_denoiser& den) {
         g->big_ok = true;
       }
     } else {   // the verify call only, on three bf16 terms
-      ASD_HIP(hipMalloc(&g->means_img, split3_image_bytes<GmmTileSplit>(C, d)));
-      ASD_HIP(hipMalloc(&g->means_t_img, split3_image_bytes<GmmTileSplit>(d, C)));
       ASD_HIP(launch_split3_pack_b<GmmTileSplit>(g->means, d, C, d, g->means_img, 0));
       ASD_HIP(launch_split3_pack_b<GmmTileSplit>(g->means_t, C, d, C, g->means_t_img, 0));
     }
     ASD_HIP(hipDeviceSynchronize());
     g->split_ok = g->use_split = true;
-    const int np_v = GmmTileSplit::WGN * (int)ceil_div(C, GmmTileSplit::BN);   // partial maxima per row, verify call
-    ASD_HIP(hipMalloc(&g->rmax, sizeof(float) * (size_t)ctx->n_rows_max));
-    ASD_HIP(hipMalloc(&g->glive, (size_t)ceil_div(ctx->n_rows_max, CombineOp::kRowmaxTile) * np_v));
-    ASD_HIP(hipMalloc(&g->onehot, sizeof(int32_t) * (size_t)ctx->n_rows_max));
-    ASD_HIP(hipMalloc(&g->onehot_tile, (size_t)ceil_div(ctx->n_rows_max, CombineOp::kRowmaxTile)));
-    ASD_HIP(hipMalloc(&g->work_counts, 8 * sizeof(unsigned long long)));
-    ASD_HIP(hipMemset(g->work_counts, 0, 8 * sizeof(unsigned long long)));
     // screening pass of the verify call: full tiles only, and the second GEMM must be able to skip what it leaves out
     if (d % 128 == 0 && C % ScreenTile::BM == 0 && C % GmmTileSplit::BN == 0 && d <= 2048 && g->two_ok &&
         split3_sparse_fits<GmmTile2>(C, np_v, GmmTile2::WN)) {
@@ -1673,14 +1703,9 @@ void gmm_destroy(asd_ctx* ctx) {
   if (!g) return;
   (void)hipFree(g->means_t);
   (void)hipFree(g->means_p);
-  (void)hipFree(g->means_img);
-  (void)hipFree(g->means_t_img);
-  (void)hipFree(g->means_img2);
-  (void)hipFree(g->means_t_img2);
+  (void)hipFree(g->split_mem);
   (void)hipFree(g->means_img_big);
   (void)hipFree(g->means_t_img_big);
-  (void)hipFree(g->means22);
-  (void)hipFree(g->a_scale);
   (void)hipFree(g->musq);
   (void)hipFree(g->coef_tau);
   (void)hipFree(g->part);
@@ -1694,11 +1719,6 @@ void gmm_destroy(asd_ctx* ctx) {
   (void)hipFree(g->tile_list);
   (void)hipFree(g->tile_count);
   (void)hipFree(g->screen_on);
-  (void)hipFree(g->work_counts);
-  (void)hipFree(g->rmax);
-  (void)hipFree(g->glive);
-  (void)hipFree(g->onehot);
-  (void)hipFree(g->onehot_tile);
   (void)hipFree(g->cert_amin);
   (void)hipFree(g->chain_comp);
   (void)hipFree(g->cert_tile);

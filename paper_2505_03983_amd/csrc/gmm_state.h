@@ -26,6 +26,7 @@ struct GmmState {
   float* part = nullptr;         // split-K scratch of the draft call's second GEMM: [splits][chains][d] tiles, [splits][chains] sums
   int draft_splits = 1;
   bool use_mfma = false;
+  uint8_t* split_mem = nullptr;    // what the images below, a_scale, means22 and the arrays by row of the split GEMMs are parts of
   // split-bf16 verify GEMMs (gemm_split3.h): the means, split and laid out as LDS images, for both GEMMs
   uint8_t* means_img = nullptr;    // B of the logits GEMM  ([C, d])
   uint8_t* means_t_img = nullptr;  // B of the combine GEMM ([d, C])
